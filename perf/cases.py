@@ -183,19 +183,32 @@ def _pools(case, seed, dev):
     return layers, table, lens.to(torch.int32), g
 
 
+def _list_room(case):
+    """Entries of a page list: what the plan keeps of the longest sequence the configuration admits, and some."""
+    pages = _max_pages(case)
+    return min(SINK + WINDOW + _keep_counts(case, pages)[0][2] + LIST_ROOM, pages)
+
+
+def _tokens(case, n_layers, g, dev):
+    """The token a reuse step appends, per layer, and the step's logits."""
+    batch, H = case["batch"], case["n_kv_heads"]
+    rows = [[torch.randn((batch, H, HEAD_DIM), generator=g, device=dev).to(torch.bfloat16) for _ in range(2)] for _ in range(n_layers)]
+    stride = -(-case["vocab"] // 8) * 8
+    return rows, (3 * torch.randn((batch, stride), generator=g, device=dev)).to(torch.bfloat16)
+
+
 def prepare(case, seed):
     dev = torch.device("cuda")
     kind, batch, H = case["kind"], case["batch"], case["n_kv_heads"]
     layers, table, lens, g = _pools(case, seed, dev)
-    longest = -(-case["ctx_hi"] // case["page_size"])
     pages = _max_pages(case)
-    # (a list has room for what the plan keeps of the longest sequence the configuration admits)
-    room = SINK + WINDOW + _keep_counts(case, max(longest, pages))[0][2] + LIST_ROOM
-    lib = pk.Chess(pk.Config(case["n_q_heads"], H, case["page_size"], batch, pages, min(room, pages), case["fan_c"], case["fan_g"],
+    lib = pk.Chess(pk.Config(case["n_q_heads"], H, case["page_size"], batch, pages, _list_room(case), case["fan_c"], case["fan_g"],
                              summary_dtype=pk.SUMMARY_BF16 if case["summaries"] == "bf16" else pk.SUMMARY_F32))
     s = {"case": dict(case), "lib": lib, "plan": _plan(case), "table": table, "lens": lens, "layers": layers,
          "ws": lib.new_workspace(dev)}
-    for y in layers:
+    if kind == "reuse":
+        tokens, s["logits"] = _tokens(case, len(layers), g, dev)
+    for i, y in enumerate(layers):
         y["out"] = torch.empty((batch, case["n_q_heads"], HEAD_DIM), dtype=torch.float32, device=dev)
         y["ids"] = torch.full((batch, H, lib.cfg.max_selected_pages), -1, dtype=torch.int32, device=dev)
         y["n"] = torch.zeros((batch, H), dtype=torch.int32, device=dev)
@@ -205,14 +218,11 @@ def prepare(case, seed):
             lib.summarize(y["k"], table, lens, y["summ"])
         if kind == "reuse":
             lib.select(y["q"], y["summ"], lens, s["plan"], y["ids"], y["n"], s["ws"])
-            y["k_new"] = torch.randn((batch, H, HEAD_DIM), generator=g, device=dev).to(torch.bfloat16)
-            y["v_new"] = torch.randn((batch, H, HEAD_DIM), generator=g, device=dev).to(torch.bfloat16)
+            y["k_new"], y["v_new"] = tokens[i]
             del y["summ"]
     if kind == "shared":
         s["anchors"] = [torch.empty((batch, H, HEAD_DIM), dtype=torch.float32, device=dev) for _ in layers]
     if kind == "reuse":
-        stride = -(-case["vocab"] // 8) * 8
-        s["logits"] = (3 * torch.randn((batch, stride), generator=g, device=dev)).to(torch.bfloat16)
         s["entropy"] = torch.zeros(batch, dtype=torch.float32, device=dev)
         s["history"] = torch.zeros((batch, case["page_size"]), dtype=torch.float32, device=dev)
         s["count"] = torch.zeros(batch, dtype=torch.int32, device=dev)
@@ -332,3 +342,144 @@ def tolerance(case):
     # attention: bf16 inputs, fp32 accumulation, weights to 2^-17 (against itself in 64 bits: rel 2.1e-6, largest
     # difference 1.9e-5 of the rms, in every case); entropy: fp32 over the vocabulary (rel 8e-8); page lists do not differ
     return {"rel": 1e-5, "max": 1e-4}
+
+
+# ---- the same in 64 bits, with plain torch
+def _stored(case, mean):
+    """A mean as the summaries store it, as fp64."""
+    m = mean.to(torch.float32)
+    return (m.to(torch.bfloat16) if case["summaries"] == "bf16" else m).double()
+
+
+def _means(x, fan):
+    """Means over `fan` consecutive members of dim 1 (the last one over those that exist), fp64."""
+    n = -(-x.shape[1] // fan)
+    full = torch.nn.functional.pad(x, (0, 0, 0, n * fan - x.shape[1])).view(x.shape[0], n, fan, x.shape[2]).sum(2)
+    count = torch.full((n,), fan, device=x.device)
+    count[-1] = x.shape[1] - (n - 1) * fan
+    return full / count[None, :, None]
+
+
+def _sequence_means(case, k, table_row, n):
+    """Page, chunk and grid means [H, units, d] of one sequence in one layer, each over its children as stored."""
+    B, H = case["page_size"], case["n_kv_heads"]
+    pages = -(-n // B)
+    rows = k[table_row[:pages].long()].transpose(0, 1).reshape(H, pages * B, HEAD_DIM)[:, :n].double()
+    page = _means(rows, B)
+    chunk = _means(_stored(case, page), case["fan_c"])
+    return page, chunk, _means(_stored(case, chunk), case["fan_g"])
+
+
+def _top(score, active, k):
+    """Boolean mask of the k (one per row) highest active scores of every row, ties to the lower index."""
+    order = torch.where(active, score, -math.inf).sort(dim=1, descending=True, stable=True).indices
+    rank = torch.empty_like(order).scatter_(1, order, torch.arange(score.shape[1], device=score.device).expand_as(order))
+    return active & (rank < k[:, None])
+
+
+def _select(case, grid_s, chunk_s, page_s):
+    """The cascade over scores [rows, units]: ids [rows, list room] (-1 padded) and their number [rows]."""
+    fc, fg, dev = case["fan_c"], case["fan_g"], page_s.device
+    P, nc, ng = page_s.shape[1], chunk_s.shape[1], grid_s.shape[1]
+    ratio = case["plan"] == "ratio"
+    k = max(1, -(-P * case["budget_bp"] // 10000))
+    kct = -(-10 * k // fc)
+
+    def cut(score, active, rho, target):
+        n = active.sum(1)
+        return _top(score, active, torch.clamp(-(-n * rho // 10000), min=1) if ratio else torch.clamp(n, max=target))
+
+    grids = cut(grid_s, torch.ones_like(grid_s, dtype=torch.bool), 5000, -(-5 * kct // fg))
+    chunks = cut(chunk_s, grids.repeat_interleave(fg, 1)[:, :nc], 2000, kct)
+    pages = chunks.repeat_interleave(fc, 1)[:, :P].clone()
+    pages[:, :SINK] = pages[:, P - WINDOW:] = False
+    pages = cut(page_s, pages, 1000, k)
+    pages[:, :SINK] = pages[:, P - WINDOW:] = True
+    n = pages.sum(1)
+    ids = torch.full((pages.shape[0], _list_room(case)), -1, dtype=torch.int32, device=dev)
+    at = torch.nonzero(pages)
+    ids[at[:, 0], (pages.cumsum(1) - 1)[pages]] = at[:, 1].to(torch.int32)
+    return ids, n.to(torch.int32)
+
+
+def _attend(case, q, k, v, table_row, n, ids=None):
+    """Attention [n_q_heads, d] of one sequence of n tokens over the listed pages (ids [H, pages], None: all)."""
+    B, H = case["page_size"], case["n_kv_heads"]
+    pages = -(-n // B)
+    if ids is None:
+        ids = torch.arange(pages, device=q.device)[None].expand(H, pages)
+    ids = ids.long()
+    head = torch.arange(H, device=q.device)[:, None]
+    phys = table_row[ids.clamp(min=0)].long()
+    token = (ids[:, :, None] * B + torch.arange(B, device=q.device)).view(H, 1, -1)
+    there = (ids >= 0).repeat_interleave(B, 1)[:, None] & (token < n)
+    keys = k[phys, head].double().view(H, -1, HEAD_DIM)
+    values = v[phys, head].double().transpose(2, 3).reshape(H, -1, HEAD_DIM)
+    score = torch.matmul(q.double().view(H, -1, HEAD_DIM), keys.transpose(1, 2).contiguous()) / math.sqrt(HEAD_DIM)
+    p = torch.where(there, score, -math.inf).softmax(2)
+    return torch.matmul(p, values).view(-1, HEAD_DIM)
+
+
+def exact(case, seed):
+    dev = torch.device("cuda")
+    kind, batch, H, B = case["kind"], case["batch"], case["n_kv_heads"], case["page_size"]
+    layers, table, _, g = _pools(case, seed, dev)
+    lens = _lengths(case)
+    if kind == "dense":
+        return [torch.stack([_attend(case, y["q"][b], y["k"], y["v"], table[b], lens[b]) for b in range(batch)]) for y in layers]
+
+    units = [_max_pages(case)]
+    units += [-(-units[0] // case["fan_c"])]
+    units += [-(-units[1] // case["fan_g"])]
+
+    def summaries(per_seq):
+        full = [torch.zeros((batch, H, u, HEAD_DIM), dtype=torch.float64, device=dev) for u in units]
+        for b, means in enumerate(per_seq):
+            for f, m in zip(full, means):
+                f[b, :, :m.shape[1]] = m
+        return tuple(full)
+
+    def scores(means, probe):                                   # [H, units] of a level, from what is stored of it
+        return torch.matmul(_stored(case, means), probe[:, :, None])[:, :, 0]
+
+    if kind == "prefill":
+        return [summaries([_sequence_means(case, y["k"], table[b], lens[b]) for b in range(batch)]) for y in layers]
+
+    if kind == "shared":
+        lists, counts = [], []
+        for b in range(batch):
+            total = None
+            for y in layers:
+                page, chunk, grid = _sequence_means(case, y["k"], table[b], lens[b])
+                anchor = _stored(case, page)[:, -WINDOW:].mean(1).to(torch.float32).double()
+                s = [scores(m, anchor).sum(0, keepdim=True) for m in (grid, chunk, page)]
+                total = s if total is None else [t + x for t, x in zip(total, s)]
+            ids, n = _select(case, *total)
+            lists.append(ids.expand(H, -1))
+            counts.append(n.expand(H))
+        out = [torch.stack([_attend(case, y["q"][b], y["k"], y["v"], table[b], lens[b], lists[b]) for b in range(batch)]) for y in layers]
+        return {"out": out, "ids": torch.stack(lists), "n": torch.stack(counts)}
+
+    got = {}
+    if kind == "reuse":
+        tokens, logits = _tokens(case, len(layers), g, dev)
+        logp = logits[:, :case["vocab"]].double().log_softmax(1)
+        got.update({"k": None, "v": None, "history": None, "count": None, "fire": None, "entropy": -(logp.exp() * logp).sum(1)})
+    for i, y in enumerate(layers[:16]):
+        means = [_sequence_means(case, y["k"], table[b], lens[b]) for b in range(batch)]
+        if i == 0 and kind != "reuse":
+            got["summaries"] = summaries(means)
+        outs, lists, counts = [], [], []
+        for b in range(batch):
+            probe = y["q"][b].double().view(H, -1, HEAD_DIM).sum(1)
+            ids, n = _select(case, *[scores(m, probe) for m in means[b][::-1]])
+            grown = lens[b]
+            if kind == "reuse":
+                phys, tok = int(table[b, grown // B]), grown % B
+                y["k"][phys, :, tok], y["v"][phys, :, :, tok] = tokens[i][0][b], tokens[i][1][b]
+                grown += 1
+            outs.append(_attend(case, y["q"][b], y["k"], y["v"], table[b], grown, ids))
+            lists.append(ids)
+            counts.append(n)
+        got["out %d" % i], got["ids %d" % i], got["n %d" % i] = torch.stack(outs), torch.stack(lists), torch.stack(counts)
+    return got
