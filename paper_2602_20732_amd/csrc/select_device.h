@@ -20,17 +20,22 @@
 //
 // There is no barrier between the members: a key word is 0 until its owner has published it (a slot without a unit
 // is published as 1), so a member polls the words it needs until none is 0.  One memory round trip serves as
-// both the wait and the transfer.  Every member then finds the cut itself (all compute the same thing): bounds
-// from the upper key halves, a histogram over 1024 bins that are linear in the (fp32-rounded) score, a scan from
-// the top, an exact ranking by (key, slot) of the few keys in the bin the k-th largest falls in, ballots for the
-// positions in the ascending list of kept units.  Ties at the cut go to the lowest slots (= lowest indices:
-// candidates are enumerated in index order), or are all kept under the threshold rule.  A level of up to 64 slots is
-// ranked by one wave with lane reads alone, up to 256 slots by one wave with four keys per lane and no barrier
-// inside; larger levels keep their keys four (up to 1024 slots; the polled keys arrive in registers) or seventeen
-// per thread over the whole workgroup, with LDS lists between the waves.  (One wave cutting 1024 keys, sixteen per
-// lane, was measured: 8-9 us instead of 3-4, a single wave being a long chain of dependent instructions.)  Score
-// distributions that pile more than 64 keys into the bin at the cut (exact ties, mostly) take a general path: radix
-// select on the bits the keys do not share, then a ballot compaction.
+// both the wait and the transfer.  Every member then finds the cut itself (all compute the same thing), in ascending
+// slot order for the list of kept units.  Ties at the cut go to the lowest slots (= lowest indices: candidates are
+// enumerated in index order), or are all kept under the threshold rule.
+// Which cut a level takes goes by its slots, because what a cut costs is the length of its chain of dependent
+// instructions (a dependent vector instruction takes 8 cycles, an LDS read 62, a taken branch about 36):
+//   up to 64     every key is ranked against every other with lane reads, each wave taking a quarter of the comparisons
+//                (1.2 us; one wave looping over the keys took 2.5);
+//   up to 256    every wave holds all the keys and searches the cut by value, with counts alone and without LDS (2.4 us,
+//                two thirds of it reading, bounds and emission; the histogram below by one wave took 3.0);
+//   up to 1024   bounds from the upper key halves, a histogram over 1024 bins that are linear in the (fp32-rounded) score, a
+//                scan from the top, an exact ranking by (key, slot) of the few keys in the bin the k-th largest falls in:
+//                the whole workgroup, four keys per thread, which arrive in registers (3.3 us; every wave searching 16
+//                keys per lane took 5.4, the search spread over the waves with a barrier a step 4.3);
+//   up to 4352   the same with seventeen keys per thread.
+// Score distributions that pile more than 64 keys into the bin or bracket at the cut (exact ties, mostly) take a general
+// path: radix select on the bits the keys do not share, then a ballot compaction.
 //
 // The words are cleared again by the workgroup that is last to be done with them, so they are all 0 between
 // launches.  Polls are bounded: a wait that does not end raises the workspace's error flag and the workgroup
@@ -226,16 +231,18 @@ __device__ __forceinline__ double loaded(uint16_t v) { return (double)__uint_as_
 
 constexpr int kBins = 1024;                 // linear score bins of the cut
 constexpr int kSelGroups = kSelThreads / 16;  // 16-lane groups of a workgroup
-constexpr int kFastMembers = 64;            // most keys the bin at the cut may hold on the histogram paths
+constexpr int kFastMembers = 64;            // most keys the bin / bracket at the cut may hold on the fast paths
+constexpr int kSearchSteps = 14;            // steps (of two bits) a search for the cut takes before it leaves the rest to ranking
 constexpr int kRegsLarge = (4352 + kSelThreads - 1) / kSelThreads;       // keys per thread of the largest level the register path holds
 constexpr int kMaxRuns = kRegsLarge * kSelWaves;  // its 64-slot runs
-constexpr int kOneWaveSlots = 4 * kWave;    // largest level one wave cuts by itself
+constexpr int kEachWaveSlots = kSelWaves * kWave;  // largest level every wave cuts for itself
 
 struct Shared {
     int hist[kBins];
     uint64_t mem_key[kFastMembers];
     int mem_slot[kFastMembers];
     int run_gt[kMaxRuns];
+    int rank[kSelWaves][kWave];   // the waves' shares of the ranks of a level of one slot per lane
     int wave_a[kSelWaves], wave_b[kSelWaves];
     int digit, rem, cnt, n_valid, n_mem, flag;
     unsigned int or_lo, or_hi, and_lo, and_hi;
@@ -678,142 +685,183 @@ __device__ __forceinline__ int cut_in_registers(uint64_t* keys, int n_slots, con
     return sure_total + __popcll(kept_mask);
 }
 
-// Cut and ordered compaction of a level of at most 64 R slots by ONE wave, with no workgroup barrier inside: wave 0
-// holds slot x * 64 + lane of the LDS copy of the keys in key[x] and does what cut_in_registers does -- bounds from
-// the upper key halves, linear-bin histogram, scan from the top, exact ranking of the bin at the cut -- with ballots
-// and lane reads in place of the LDS lists between waves (the other waves wait at the closing barrier; LDS
-// operations of one wave complete in order, so its own histogram and member list need no barrier).  Same contract
-// as cut_in_registers; returns -1 (to every thread), having emitted nothing, when more than kFastMembers keys share
-// the bin at the cut.
+// What the search for a cut ends with: slots with f > above are kept for sure; the cnt slots with from < f <= above
+// still have to be ranked on their 64-bit keys, want of them are kept.  cnt = 0: the cut falls between two keys.
+struct Bracket {
+    float above, from;
+    int want, cnt;
+};
+
+// The bracket of the k-th largest of the n_valid scores f (0 < k < n_valid; -inf in slots without one; smallest and
+// largest finite score fmin, fmax), for one wave that holds all of them: a search by value, three thresholds a step, that
+// ends as soon as a threshold has exactly k scores above it (4 steps for 256 normally distributed scores, 10 at most in
+// 400 draws).  Counting is a compare, a ballot and a population count per threshold and register: scalar results,
+// nothing goes through LDS.  Three thresholds, because a step is a chain of dependent instructions whatever it counts.
 template <int R>
-__device__ __forceinline__ int cut_by_one_wave(uint64_t* keys, int n_slots, const ActiveRule& active, const KeepRule& k_of,
-                                               bool keep_ties, const EmitRule& emit, int cap, bool mark, Shared& sh)
+__device__ __forceinline__ Bracket search_cut(const float (&f)[R], int k, int n_valid, float fmin, float fmax)
 {
-    const int tid = opaque_tid(), lane = tid & 63;
-    if (tid < kWave) {
-        const uint64_t below = __lanemask_lt();
-        uint64_t key[R];
-        unsigned lo_h = ~0u, hi_h = 0u;
-        int n_valid = 0;
+    float lo = fmin, hi = fmax;                       // more than k scores above lo (at or above it until it moves), fewer above hi
+    float from = -INFINITY;                           // lo once it has moved
+    int c_lo = n_valid, c_hi = 0;
+#pragma unroll 1
+    for (int step = 0; step < kSearchSteps; ++step) {
+        const float t2 = 0.5f * lo + 0.5f * hi, t1 = 0.5f * lo + 0.5f * t2, t3 = 0.5f * t2 + 0.5f * hi;
+        if (!(lo < t2 && t2 < hi)) break;             // neighbouring floats (or one value): ranked by key
+        int c1 = 0, c2 = 0, c3 = 0;
 #pragma unroll
         for (int x = 0; x < R; ++x) {
-            const int i = x * kWave + lane;
-            key[x] = (i < n_slots && active(i)) ? keys[i] : 0ull;
-            const bool valid = key[x] != 0ull;
-            const unsigned h = (unsigned)(key[x] >> 32);
-            lo_h = valid ? min(lo_h, h) : lo_h;
-            hi_h = valid ? max(hi_h, h) : hi_h;
-            n_valid += __popcll(__ballot(valid));
+            c1 += __popcll(__ballot(f[x] > t1));
+            c2 += __popcll(__ballot(f[x] > t2));
+            c3 += __popcll(__ballot(f[x] > t3));
         }
-        const int k = k_of(n_valid);
-        const bool all = k >= n_valid;
-        int result = 0;
-        int bin[R];
-        int cutbin = -1, want = 0, cnt = 0;
-        if (k > 0 && !all) {
-            lo_h = (unsigned)__builtin_amdgcn_readlane((int)wave_minmax32<true>(lo_h), 63);
-            hi_h = (unsigned)__builtin_amdgcn_readlane((int)wave_minmax32<false>(hi_h), 63);
-            const float fmin = key_float(lo_h), fmax = key_float(hi_h);
-            const float scale = fmax > fmin ? (float)kBins / (fmax - fmin) : 0.f;
-#pragma unroll
-            for (int x = 0; x < R; ++x) {
-                bin[x] = -1;
-                if (key[x] != 0ull) {
-                    bin[x] = min((int)((key_float((unsigned)(key[x] >> 32)) - fmin) * scale), kBins - 1);
-                    atomicAdd(&sh.hist[hist_word(bin[x])], 1);
-                }
-            }
-            __builtin_amdgcn_wave_barrier();
-            cutbin = find_cut_bin(sh.hist, k, &want, &cnt);
-            // leave the histogram clean: this wave is its only user at this level
-#pragma unroll
-            for (int x = 0; x < R; ++x)
-                if (bin[x] >= 0) sh.hist[hist_word(bin[x])] = 0;
-        } else {
-#pragma unroll
-            for (int x = 0; x < R; ++x) bin[x] = 0;
+        if ((c1 == k) | (c2 == k) | (c3 == k)) {
+            hi = from = c1 == k ? t1 : c2 == k ? t2 : t3;
+            c_lo = c_hi = k;
+            break;
         }
-        if (cnt > kFastMembers) {
-            result = -1;
-        } else if (k > 0) {
-            // the keys of the bin at the cut, one per lane (through LDS, in slot order), ranked against each other
-            uint64_t thr = 0ull;
-            int thr_slot = -1;
-            if (cnt > 0) {
-                int at0 = 0;
-#pragma unroll
-                for (int x = 0; x < R; ++x) {
-                    const bool e = bin[x] == cutbin && key[x] != 0ull;
-                    const uint64_t eb = __ballot(e);
-                    if (e) {
-                        const int at = at0 + __popcll(eb & below);
-                        sh.mem_key[at] = key[x];
-                        sh.mem_slot[at] = x * kWave + lane;
-                    }
-                    at0 += __popcll(eb);
-                }
-                __builtin_amdgcn_wave_barrier();
-                const uint64_t mine = lane < cnt ? sh.mem_key[lane] : 0ull;
-                const int my_slot = lane < cnt ? sh.mem_slot[lane] : 0;
-                uint64_t kept_mask;
-                rank_members(mine, my_slot, cnt, want, keep_ties, &thr, &thr_slot, &kept_mask);
-            }
-            int base = 0;
-#pragma unroll
-            for (int x = 0; x < R; ++x) {
-                if (x * kWave >= n_slots) break;                  // uniform
-                const int slot = x * kWave + lane;
-                const bool valid = key[x] != 0ull;
-                const bool keep = all ? valid
-                                      : valid && (bin[x] > cutbin ||
-                                                  (bin[x] == cutbin && (key[x] > thr || (key[x] == thr && (slot <= thr_slot || keep_ties)))));
-                const uint64_t kb = __ballot(keep);
-                const int at = base + __popcll(kb & below);
-                if (keep && at < cap) emit(at, slot);
-                if (mark && slot < n_slots && !keep) keys[slot] = 0ull;
-                base += __popcll(kb);
-            }
-            result = base;
-        } else if (mark) {
-#pragma unroll
-            for (int x = 0; x < R; ++x)
-                if (x * kWave + lane < n_slots) keys[x * kWave + lane] = 0ull;
-        }
-        if (lane == 0) sh.cnt = result;
+        const bool g1 = c1 > k, g2 = c2 > k, g3 = c3 > k;                 // g3 implies g2 implies g1
+        hi = g3 ? hi : g2 ? t3 : g1 ? t2 : t1;
+        c_hi = g3 ? c_hi : g2 ? c3 : g1 ? c2 : c1;
+        lo = g3 ? t3 : g2 ? t2 : g1 ? t1 : lo;
+        from = g1 ? lo : from;
+        c_lo = g3 ? c3 : g2 ? c2 : g1 ? c1 : c_lo;
     }
-    __syncthreads();
-    return sh.cnt;
+    return Bracket{hi, from, k - c_hi, c_lo - c_hi};
 }
 
-// A level of at most 64 slots: one key per lane of wave 0, each lane counts the keys that rank before its own
-// (key descending, slot ascending) with lane reads; no histogram, no LDS.  Same contract as cut_by_one_wave (it
-// always applies).
+// Cut and ordered compaction of a level of at most 64 slots per wave of the workgroup.  EVERY wave holds all the keys
+// (slot x * 64 + lane in register x of each) and finds the cut for itself, so nothing is exchanged between waves; wave w
+// then emits the slots of register w.  Same contract as cut_in_registers; returns -1, having emitted nothing, when more
+// than kFastMembers keys share the bracket at the cut.
+__device__ __forceinline__ int cut_in_each_wave(uint64_t* keys, int n_slots, const ActiveRule& active, const KeepRule& k_of,
+                                                bool keep_ties, const EmitRule& emit, int cap, bool mark, Shared& sh)
+{
+    constexpr int R = kSelWaves;
+    const int tid = opaque_tid(), lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint64_t below = __lanemask_lt();
+    uint64_t key[R];
+    float f[R];
+    unsigned lo_h = ~0u, hi_h = 0u;
+    int n_valid = 0;
+    // (unconditional reads, all in flight: slots beyond the level repeat its last one and are dropped)
+#pragma unroll
+    for (int x = 0; x < R; ++x) key[x] = keys[min(x * kWave + lane, n_slots - 1)];
+    if (active.mask != nullptr) {                     // uniform
+        uint64_t on[R];
+#pragma unroll
+        for (int x = 0; x < R; ++x) on[x] = active.mask[div_by(min(x * kWave + lane, n_slots - 1), active.fan, active.inv)];
+#pragma unroll
+        for (int x = 0; x < R; ++x) key[x] = on[x] != 0ull ? key[x] : 0ull;
+    }
+#pragma unroll
+    for (int x = 0; x < R; ++x) {
+        const bool valid = x * kWave + lane < n_slots && key[x] != 0ull;
+        key[x] = valid ? key[x] : 0ull;
+        const unsigned h = (unsigned)(key[x] >> 32);
+        const float fx = key_float(h);
+        f[x] = valid ? fx : -INFINITY;
+        lo_h = min(lo_h, valid ? h : ~0u);
+        hi_h = max(hi_h, h);
+        n_valid += __popcll(__ballot(valid));
+    }
+    if (mark) __syncthreads();                        // every wave has its copy: the slots may be emptied
+    const int k = k_of(n_valid);
+    float above = k > 0 ? -INFINITY : INFINITY;       // every score is kept, or none
+    if (k > 0 && k < n_valid) {
+        lo_h = (unsigned)__builtin_amdgcn_readlane((int)wave_minmax32<true>(lo_h), 63);
+        hi_h = (unsigned)__builtin_amdgcn_readlane((int)wave_minmax32<false>(hi_h), 63);
+        const Bracket br = search_cut<R>(f, k, n_valid, key_float(lo_h), key_float(hi_h));
+        above = br.above;
+        if (br.cnt > kFastMembers) return -1;
+        if (br.cnt > 0) {
+            // the keys of the bracket, one per lane (through LDS, in slot order; the waves write the same words), ranked
+            // against each other; the kept ones join the scores above the bracket
+            int at0 = 0;
+#pragma unroll
+            for (int x = 0; x < R; ++x) {
+                const bool e = f[x] > br.from && !(f[x] > above);
+                const uint64_t eb = __ballot(e);
+                if (e) {
+                    const int at = at0 + __popcll(eb & below);
+                    sh.mem_key[at] = key[x];
+                    sh.mem_slot[at] = x * kWave + lane;
+                }
+                at0 += __popcll(eb);
+            }
+            __builtin_amdgcn_wave_barrier();
+            const uint64_t mine = lane < br.cnt ? sh.mem_key[lane] : 0ull;
+            const int my_slot = lane < br.cnt ? sh.mem_slot[lane] : 0;
+            uint64_t thr, kept_mask;
+            int thr_slot;
+            rank_members(mine, my_slot, br.cnt, br.want, keep_ties, &thr, &thr_slot, &kept_mask);
+#pragma unroll
+            for (int x = 0; x < R; ++x) {
+                const bool in = f[x] > br.from && !(f[x] > above) &&
+                                (key[x] > thr || (key[x] == thr && (x * kWave + lane <= thr_slot || keep_ties)));
+                f[x] = in ? INFINITY : f[x];
+            }
+        }
+    }
+    // this wave's slots: those of register `wave` (selects, not a branch per register)
+    uint64_t my_bits = 0ull;
+    int base = 0, total = 0;
+#pragma unroll
+    for (int x = 0; x < R; ++x) {
+        const uint64_t kb = __ballot(f[x] > above);
+        my_bits = x == wave ? kb : my_bits;
+        base = x == wave ? total : base;
+        total += __popcll(kb);
+    }
+    const int slot = wave * kWave + lane, at = base + __popcll(my_bits & below);
+    const bool keep = (my_bits >> lane) & 1ull;
+    if (keep && at < cap) emit(at, slot);
+    if (mark && slot < n_slots && !keep) keys[slot] = 0ull;
+    __syncthreads();                                  // emitted lists visible
+    return total;
+}
+
+// A level of at most 64 slots: every wave holds all of them, one per lane, and wave w counts for each how many of the
+// keys in lanes w, w + kSelWaves, ... rank before it (key descending, slot ascending), with lane reads; the waves' counts
+// meet in LDS.  Same contract as cut_in_each_wave (it always applies).
 __device__ __forceinline__ int cut_one_lane_each(uint64_t* keys, int n_slots, const ActiveRule& active, const KeepRule& k_of,
                                                  bool keep_ties, const EmitRule& emit, int cap, bool mark, Shared& sh)
 {
-    const int tid = opaque_tid();
-    if (tid < kWave) {
-        const int lane = tid;
-        const uint64_t key = (lane < n_slots && active(lane)) ? keys[lane] : 0ull;
-        const uint64_t valid = __ballot(key != 0ull);
-        const int k = k_of(__popcll(valid));
-        int rank = 0, above = 0;                        // keys that rank before this one; keys strictly larger
-        for (uint64_t mk = valid; mk != 0ull; mk &= mk - 1) {
-            const int j = __builtin_amdgcn_readfirstlane(__ffsll((long long)mk) - 1);
-            const uint64_t kj = lane_read64(key, j);
-            rank += kj > key || (kj == key && j < lane);
-            above += kj > key;
-        }
-        // threshold rule: a key is kept when fewer than k keys are strictly larger (it ties with or beats the k-th)
-        const uint64_t kb = __ballot(key != 0ull && (keep_ties ? above < k : rank < k));
-        const bool keep = (kb >> lane) & 1ull;
+    const int tid = opaque_tid(), lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    uint64_t key = keys[min(lane, n_slots - 1)];
+    if (active.mask != nullptr) {                     // uniform
+        const uint64_t on = active.mask[div_by(min(lane, n_slots - 1), active.fan, active.inv)];
+        key = on != 0ull ? key : 0ull;
+    }
+    key = lane < n_slots ? key : 0ull;
+    const int n_valid = __popcll(__ballot(key != 0ull));
+    const int k = k_of(n_valid);
+    int rank = 0;                                     // of the keys this wave looks at, those that rank before the lane's own
+    auto meet = [&](int j) {                          // (an empty slot's key is 0: it is never before a real one)
+        const uint64_t kj = lane_read64(key, j);
+        rank += kj > key || (kj == key && j < lane && !keep_ties);
+    };
+    constexpr int kRun = 8;                           // straight-line: a taken branch costs as much as two keys
+    for (int j0 = wave; j0 < n_slots; j0 += kRun * kSelWaves) {
+#pragma unroll
+        for (int u = 0; u < kRun; ++u) meet((j0 + u * kSelWaves) & 63);
+    }
+    sh.rank[wave][lane] = rank;
+    __syncthreads();                                  // (every wave has its copy of the keys as well)
+    int before = 0;
+#pragma unroll
+    for (int w = 0; w < kSelWaves; ++w) before += sh.rank[w][lane];
+    // threshold rule: ties do not count, so a key is kept when fewer than k keys are strictly larger
+    const bool keep = key != 0ull && before < k;
+    const uint64_t kb = __ballot(keep);
+    if (wave == 0) {
         const int at = __popcll(kb & __lanemask_lt());
         if (keep && at < cap) emit(at, lane);
         if (mark && lane < n_slots && !keep) keys[lane] = 0ull;
-        if (lane == 0) sh.cnt = __popcll(kb);
     }
     __syncthreads();
-    return sh.cnt;
+    return __popcll(kb);
 }
 
 // The cut of one level whose keys are complete in `keys` (LDS; the caller's barrier has made them visible): picks
@@ -827,7 +875,7 @@ __device__ __forceinline__ int cut_level(uint64_t* keys, int n_slots, const Acti
     int n = -1;
     if (!general) {
         if (n_slots <= kWave) n = cut_one_lane_each(keys, n_slots, active, k_of, keep_ties, emit, cap, mark, sh);
-        else if (n_slots <= kOneWaveSlots) n = cut_by_one_wave<4>(keys, n_slots, active, k_of, keep_ties, emit, cap, mark, sh);
+        else if (n_slots <= kEachWaveSlots) n = cut_in_each_wave(keys, n_slots, active, k_of, keep_ties, emit, cap, mark, sh);
         else if (n_slots <= 4 * kSelThreads && have_pre) n = cut_in_registers<4, true>(keys, n_slots, active, k_of, keep_ties, emit, cap, mark, sh, pre);
         else if (n_slots <= 4 * kSelThreads) n = cut_in_registers<4>(keys, n_slots, active, k_of, keep_ties, emit, cap, mark, sh, pre);
         else if (n_slots <= kRegsLarge * kSelThreads) n = cut_in_registers<kRegsLarge>(keys, n_slots, active, k_of, keep_ties, emit, cap, mark, sh, pre);
