@@ -103,12 +103,15 @@ bool plan_bounds(const chess_ctx* ctx, const chess_select_plan* pl, Bounds* out)
     return true;
 }
 
-struct SplitShape { int n_splits, waves; };
+// n_slots > 0: the workgroups of a KV head, dealt to the sequences by length, at most n_splits to one
+struct SplitShape { int n_splits, waves, n_slots; };
 
 // Split-K shape.  Every workgroup has four waves; tiles are dealt round-robin over splits and waves.
 // Dense (every page): enough workgroups to cover the chip a few times over; the workgroup that finishes last merges
 // ns partial rows per output, tile time falls as 1/ns and merge time grows as G*ns/32 (in units of one memory
-// round trip), so the best split count is about sqrt(8*tiles/G), within what is resident at once.
+// round trip), so the best split count is about sqrt(8*tiles/G), within what is resident at once.  With several
+// sequences that count is the most one of them gets, and the workgroups resident at once are dealt to them by their
+// lengths on the device (share_slots), as soon as there are more of them than sequences: 1.13 x at 8-64K tokens.
 // A page list (tens to hundreds of pages): the fixed latencies dominate, and the measured optimum (sweeps at batch
 // 1 .. 32, 21 .. 415 pages, G = 1 .. 7) is: no split once there is a (sequence, head) per compute unit; otherwise one
 // workgroup per compute unit, at least two tiles per workgroup, and at most 1.6 x the merge-balanced count.
@@ -119,7 +122,7 @@ SplitShape choose_splits(const chess_ctx* ctx, int batch, int64_t max_list_pages
     const int64_t tiles = std::max<int64_t>(1, cdiv(max_list_pages, ppt));
     const int64_t pairs = (int64_t)batch * g.n_kv_heads;
     const int64_t target = 4LL * ctx->n_cu;
-    if (ctx->force_splits > 0) return {ctx->force_splits, ctx->force_waves};
+    if (ctx->force_splits > 0) return {ctx->force_splits, ctx->force_waves, 0};
     const int waves = 4;
     // all workgroups resident at once: a second round of workgroups would double a short kernel
     const int64_t resident = (int64_t)ctx->dec_blocks4 * ctx->n_cu;
@@ -133,10 +136,13 @@ SplitShape choose_splits(const chess_ctx* ctx, int batch, int64_t max_list_pages
         ns = (int64_t)std::llround(balanced);
         ns = std::min<int64_t>(ns, std::max<int64_t>(1, resident / pairs));
         ns = clampi(ns, 1, cdiv(tiles, waves));
+        const int64_t most = clampi(std::llround(balanced), 1, std::min<int64_t>(std::min<int64_t>(cdiv(tiles, waves), ctx->max_splits), 1024 / g.group));
+        const int64_t slots = std::min<int64_t>(std::min<int64_t>(resident, target + pairs) / g.n_kv_heads, batch * most);
+        if (batch > 1 && slots > batch) return {(int)most, waves, (int)slots};
     }
     ns = std::min<int64_t>(ns, std::min<int64_t>(ctx->max_splits, 1024 / g.group));
     while (ns > 1 && pairs * ns > target + pairs) --ns;            // stay inside the workspace
-    return {(int)ns, waves};
+    return {(int)ns, waves, 0};
 }
 
 int decode_common(chess_ctx* ctx, const void* q, const void* k_pool, const void* v_pool, const int32_t* block_table,
@@ -154,7 +160,7 @@ int decode_common(chess_ctx* ctx, const void* q, const void* k_pool, const void*
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t e = chess::launch_decode(ctx, static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k_pool),
                                         static_cast<const uint16_t*>(v_pool), block_table, seq_lens, page_ids,
-                                        n_selected, batch, sh.n_splits, sh.waves, out, ws_acc, ws_ml, arrivals, s);
+                                        n_selected, batch, sh.n_splits, sh.waves, sh.n_slots, out, ws_acc, ws_ml, arrivals, s);
     return e == hipSuccess ? CHESS_OK : CHESS_EHIP;
 }
 
@@ -676,7 +682,7 @@ int chess_sparse_decode_static(chess_ctx* ctx, const void* q, const void* k_pool
     if (e != hipSuccess) return CHESS_EHIP;
     e = chess::launch_decode(ctx, static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k_pool),
                              static_cast<const uint16_t*>(v_pool), block_table, seq_lens, page_ids, n_selected, batch,
-                             sh.n_splits, sh.waves, out, reinterpret_cast<float*>(base + acc_off),
+                             sh.n_splits, sh.waves, 0, out, reinterpret_cast<float*>(base + acc_off),
                              reinterpret_cast<float*>(base + ml_off), reinterpret_cast<int32_t*>(base), s);
     return e == hipSuccess ? CHESS_OK : CHESS_EHIP;
 }

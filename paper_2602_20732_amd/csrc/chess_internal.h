@@ -230,7 +230,7 @@ hipError_t launch_zero(chess_ctx* ctx, int32_t* p, size_t n_words, hipStream_t s
 // KV head) to finish merges the partials and writes `out`.  `arrivals`: int32 [rows], zero before first use.
 hipError_t launch_decode(chess_ctx* ctx, const uint16_t* q, const uint16_t* k_pool, const uint16_t* v_pool,
                          const int32_t* block_table, const int32_t* seq_lens, const int32_t* page_ids,
-                         const int32_t* n_selected, int batch, int n_splits, int waves, float* out,
+                         const int32_t* n_selected, int batch, int n_splits, int waves, int n_slots, float* out,
                          float* ws_acc, float* ws_ml, int32_t* arrivals, hipStream_t stream);
 
 }  // namespace chess

@@ -391,10 +391,10 @@ struct DecodeLds {
 };
 
 // Merge the NW waves of this workgroup through LDS.  n_splits == 1: write `out` rows and return false.
-// Otherwise publish the workgroup's partial as split `split` and return true.
+// Otherwise publish the workgroup's partial as split `split` (the row's partials start at index part0) and return true.
 template <int NW>
 __device__ __forceinline__ bool combine_waves(const f32x4 (&o)[8], float m_run, float l_run, DecodeLds<NW>& lds, int G,
-                                              int n_splits, int split, size_t row, float* __restrict__ out_rows,
+                                              int n_splits, int split, size_t part0, float* __restrict__ out_rows,
                                               float* __restrict__ ws_acc, float* __restrict__ ws_ml)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -429,7 +429,7 @@ __device__ __forceinline__ bool combine_waves(const f32x4 (&o)[8], float m_run, 
             const float inv = l > 0.f ? 1.f / l : 0.f;
             *reinterpret_cast<float2*>(out_rows + (size_t)head * kHeadDim + d) = make_float2(a0 * inv, a1 * inv);
         } else {
-            const size_t pr = (row * n_splits + split) * G + head;
+            const size_t pr = (part0 + split) * G + head;
             publish_u64(acc_g + pr * (kHeadDim / 2) + d / 2, __builtin_bit_cast(uint64_t, make_float2(a0, a1)));
             if (d == 0) publish_u64(ml_g + pr, __builtin_bit_cast(uint64_t, make_float2(M, l)));
         }
@@ -444,7 +444,7 @@ __device__ __forceinline__ bool combine_waves(const f32x4 (&o)[8], float m_run, 
 // words), so the partial rows and the (m, l) pairs are requested together: one round trip to memory, no LDS,
 // no barrier.
 template <int NW>
-__device__ __forceinline__ void merge_splits(int G, int n_splits, size_t row, float* __restrict__ out_rows,
+__device__ __forceinline__ void merge_splits(int G, int n_splits, size_t part0, float* __restrict__ out_rows,
                                              const float* __restrict__ ws_acc, const float* __restrict__ ws_ml)
 {
     const uint64_t* acc_g = reinterpret_cast<const uint64_t*>(ws_acc);
@@ -458,7 +458,7 @@ __device__ __forceinline__ void merge_splits(int G, int n_splits, size_t row, fl
             uint64_t v[kChunk], ml[kChunk];
 #pragma unroll
             for (int x = 0; x < kChunk; ++x) {
-                const size_t pr = (row * n_splits + min(s0 + x, n_splits - 1)) * G + head;
+                const size_t pr = (part0 + min(s0 + x, n_splits - 1)) * G + head;
                 ml[x] = observe_u64(ml_g + pr);
                 v[x] = observe_u64(acc_g + pr * (kHeadDim / 2) + d2);
             }

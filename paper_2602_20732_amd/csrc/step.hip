@@ -237,7 +237,7 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(2))
     run_tiles<B, true, true>(acc, t, stride, n_tiles, n_sel, raw_cur, raw_nxt, ids_l, max(n_sel, 1), bt_row, phys_l, a.k_pool, a.v_pool, H, h, L, P,
                  a.scale_log2, m16, grp);
     prof.mark(15);                                                    // tiles done
-    if (!combine_waves<kStepWaves>(acc.o, acc.m_run, acc.l_run, dl, G, C, m, row, out_rows, a.ws_acc, a.ws_ml)) return;
+    if (!combine_waves<kStepWaves>(acc.o, acc.m_run, acc.l_run, dl, G, C, m, row * C, out_rows, a.ws_acc, a.ws_ml)) return;
     prof.mark(16);                                                    // partial published
     // (profiling builds keep two timelines per row: member 0's and that of the member that merges)
     if (!arrive_last(a.arrivals + row, C, &sh.flag)) {
@@ -248,7 +248,7 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(2))
         return;
     }
     prof.mark(17);                                                    // last to arrive
-    merge_splits<kStepWaves>(G, C, row, out_rows, a.ws_acc, a.ws_ml);
+    merge_splits<kStepWaves>(G, C, row * C, out_rows, a.ws_acc, a.ws_ml);
     if (C > 1) clear_published(pubs, res, tail_words);                    // every member is done with the key words
 #ifdef CHESS_PROF
     prof.mark(18);
