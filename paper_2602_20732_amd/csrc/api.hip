@@ -142,7 +142,11 @@ SplitShape choose_splits(const chess_ctx* ctx, int batch, int64_t max_list_pages
     }
     ns = std::min<int64_t>(ns, std::min<int64_t>(ctx->max_splits, 1024 / g.group));
     while (ns > 1 && pairs * ns > target + pairs) --ns;            // stay inside the workspace
-    return {(int)ns, waves, 0};
+    // a list whose workgroups would leave each compute unit at most one of four waves: eight, while there is a tile for
+    // each (the rows in flight double and a wave's chain of tiles halves, with no exchange through memory):
+    // 32 sequences of 16-32K, 8 layers and the monitor 139.8 -> 135.0 us
+    const bool wide = listed && pairs * ns <= ctx->n_cu && tiles > 4 * ns;
+    return {(int)ns, wide ? 8 : waves, 0};
 }
 
 int decode_common(chess_ctx* ctx, const void* q, const void* k_pool, const void* v_pool, const int32_t* block_table,
@@ -424,13 +428,12 @@ int chess_reuse_step(chess_ctx* ctx, const void* q, const void* k_new, const voi
          reinterpret_cast<uintptr_t>(k_new) | reinterpret_cast<uintptr_t>(v_new) | reinterpret_cast<uintptr_t>(out) |
          reinterpret_cast<uintptr_t>(workspace)) & 15)
         return CHESS_EINVAL;
-    SplitShape sh = choose_splits(ctx, batch, ctx->geom.max_sel, true);
-    if (sh.waves != 4) sh.waves = 4;
+    const SplitShape sh = choose_splits(ctx, batch, ctx->geom.max_sel, true);
     char* wb = static_cast<char*>(workspace);
     hipError_t e = chess::launch_reuse(ctx, static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k_new),
                                        static_cast<const uint16_t*>(v_new), static_cast<uint16_t*>(k_pool),
                                        static_cast<uint16_t*>(v_pool), block_table, seq_lens, page_ids, n_selected, batch,
-                                       sh.n_splits, out, reinterpret_cast<float*>(wb + ctx->ws_acc_off),
+                                       sh.n_splits, sh.waves, out, reinterpret_cast<float*>(wb + ctx->ws_acc_off),
                                        reinterpret_cast<float*>(wb + ctx->ws_ml_off),
                                        reinterpret_cast<int32_t*>(wb + ctx->ws_cnt_off), static_cast<hipStream_t>(stream));
     return e == hipSuccess ? CHESS_OK : CHESS_EHIP;

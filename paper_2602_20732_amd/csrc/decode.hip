@@ -131,11 +131,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(3))) vo
 // KV head) to finish -- after which nobody reads the tail page or the list any more -- writes the rows to the pools
 // and, when the token opens a new page, the page to the list.  The lists must end with the tail page of seq_lens
 // (as a selection on these lengths, chess_append_kv with the lists, or this call leave them).
-// grid = (n_splits, H_kv, batch), four waves.
+// grid = (n_splits, H_kv, batch), NW waves (4 or 8: see choose_splits).
 // kSingle: one tile in registers at a time; faster while a wave has only a few tiles (the host decides).
 // Two workgroups per compute unit either way (squeezed into the registers of three, the kernel was slower).
-template <int B, bool kSingle>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void reuse_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_new,
+template <int B, bool kSingle, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void reuse_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_new,
                                                     const uint16_t* __restrict__ v_new, uint16_t* __restrict__ k_pool,
                                                     uint16_t* __restrict__ v_pool, const int32_t* __restrict__ block_table,
                                                     const int32_t* __restrict__ seq_lens, int32_t* __restrict__ page_ids,
@@ -143,7 +143,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void r
                                                     float* __restrict__ out, float* __restrict__ ws_acc,
                                                     float* __restrict__ ws_ml, int32_t* __restrict__ arrivals)
 {
-    constexpr int PPT = 32 / B, NW = 4;
+    constexpr int PPT = 32 / B;
     extern __shared__ float lds_f[];
     __shared__ int lds_last;
     DecodeLds<NW> lds(lds_f, g.group);
@@ -207,18 +207,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void r
 
 hipError_t launch_reuse(chess_ctx* ctx, const uint16_t* q, const uint16_t* k_new, const uint16_t* v_new, uint16_t* k_pool,
                         uint16_t* v_pool, const int32_t* block_table, const int32_t* seq_lens, int32_t* page_ids,
-                        int32_t* n_selected, int batch, int n_splits, float* out, float* ws_acc, float* ws_ml,
+                        int32_t* n_selected, int batch, int n_splits, int waves, float* out, float* ws_acc, float* ws_ml,
                         int32_t* arrivals, hipStream_t stream)
 {
     const Geom& g = ctx->geom;
     const float scale_log2 = ctx->sm_scale * 1.4426950408889634f;
-    const dim3 grid(n_splits, g.n_kv_heads, batch), block(256);
-    const size_t lds = (size_t)(4 * g.group * kHeadDim + 2 * 4 * g.group) * sizeof(float);
+    const int nw = waves == 8 ? 8 : 4;
+    const dim3 grid(n_splits, g.n_kv_heads, batch), block(64 * nw);
+    const size_t lds = (size_t)(nw * g.group * kHeadDim + 2 * nw * g.group) * sizeof(float);
     // without the prefetch of the next tile while a wave has at most four tiles of the longest possible list
     const int tiles = (g.max_sel + kTileTokens / g.page_size - 1) / (kTileTokens / g.page_size);
-    const bool single = tiles <= 4 * 4 * n_splits;
-    auto kern = g.page_size == 16 ? (single ? reuse_kernel<16, true> : reuse_kernel<16, false>)
-                                  : (single ? reuse_kernel<32, true> : reuse_kernel<32, false>);
+    const int single = tiles <= 4 * nw * n_splits;
+    using Kern = void (*)(const uint16_t*, const uint16_t*, const uint16_t*, uint16_t*, uint16_t*, const int32_t*, const int32_t*,
+                          int32_t*, int32_t*, Geom, float, int, float*, float*, float*, int32_t*);
+    // [page size 16 / 32][waves 4 / 8][prefetch / single]
+    static const Kern table[2][2][2] = {
+        {{reuse_kernel<16, false, 4>, reuse_kernel<16, true, 4>}, {reuse_kernel<16, false, 8>, reuse_kernel<16, true, 8>}},
+        {{reuse_kernel<32, false, 4>, reuse_kernel<32, true, 4>}, {reuse_kernel<32, false, 8>, reuse_kernel<32, true, 8>}}};
+    const Kern kern = table[g.page_size == 16 ? 0 : 1][nw == 8][single];
+    if (lds > 64 * 1024) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
     return launch(kern, grid, block, lds, stream, q, k_new, v_new, k_pool, v_pool, block_table, seq_lens, page_ids, n_selected,
                   g, scale_log2, n_splits, out, ws_acc, ws_ml, arrivals);
 }
@@ -234,11 +244,13 @@ hipError_t launch_decode(chess_ctx* ctx, const uint16_t* q, const uint16_t* k_po
     const size_t lds = (size_t)(waves * g.group * kHeadDim + 2 * waves * g.group) * sizeof(float);
     using Kern = void (*)(const uint16_t*, const uint16_t*, const uint16_t*, const int32_t*, const int32_t*, const int32_t*,
                           const int32_t*, Geom, float, int, int, float*, float*, float*, int32_t*);
-    // [page size 16 / 32][waves 4 / 1][list / every page]
+    // [page size 16 / 32][waves 4 / 1][list / every page], and eight waves for a list
     static const Kern table[2][2][2] = {
         {{decode_kernel<16, 4, true>, decode_kernel<16, 4, false>}, {decode_kernel<16, 1, true>, decode_kernel<16, 1, false>}},
         {{decode_kernel<32, 4, true>, decode_kernel<32, 4, false>}, {decode_kernel<32, 1, true>, decode_kernel<32, 1, false>}}};
-    const Kern kern = table[g.page_size == 16 ? 0 : 1][waves == 4 ? 0 : 1][page_ids ? 0 : 1];
+    static const Kern wide[2] = {decode_kernel<16, 8, true>, decode_kernel<32, 8, true>};
+    const int by_page = g.page_size == 16 ? 0 : 1;
+    const Kern kern = waves == 8 ? wide[by_page] : table[by_page][waves == 4 ? 0 : 1][page_ids ? 0 : 1];
     if (lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
