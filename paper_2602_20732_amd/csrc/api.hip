@@ -106,7 +106,8 @@ bool plan_bounds(const chess_ctx* ctx, const chess_select_plan* pl, Bounds* out)
 // n_slots > 0: the workgroups of a KV head, dealt to the sequences by length, at most n_splits to one
 struct SplitShape { int n_splits, waves, n_slots; };
 
-// Split-K shape.  Every workgroup has four waves; tiles are dealt round-robin over splits and waves.
+// Split-K shape.  A workgroup has four waves (eight where `wide` below says so); tiles are dealt round-robin over
+// splits and waves.
 // Dense (every page): enough workgroups to cover the chip a few times over; the workgroup that finishes last merges
 // ns partial rows per output, tile time falls as 1/ns and merge time grows as G*ns/32 (in units of one memory
 // round trip), so the best split count is about sqrt(8*tiles/G), within what is resident at once.  With several
