@@ -45,6 +45,7 @@
 #include <type_traits>
 
 #include "chess_internal.h"
+#include "score_cut.h"
 
 namespace chess {
 
@@ -53,25 +54,6 @@ constexpr int kPollLimit = 1 << 15;         // polls (each a memory round trip, 
 constexpr int kKeepAll = 0x7fffffff;
 constexpr uint64_t kAbsentKey = 1ull;       // published for a slot that has no unit; below every real key
 constexpr uint64_t kMarkKey = 2ull;         // "this grid was kept" where no real key exists; below every real key too
-
-// Monotone map double -> uint64 (larger score = larger key); every finite or infinite score maps
-// to a key >= 2^52 - 1, so 0 can mark "not published yet" and 1 "no unit".  -0.0 is folded onto +0.0.
-__device__ __forceinline__ uint64_t order_key(double s)
-{
-    s += 0.0;
-    const uint64_t u = (uint64_t)__double_as_longlong(s);
-    return (u >> 63) ? ~u : (u | 0x8000000000000000ull);
-}
-
-// A float that never decreases when the key grows: the score with its lower 32 bits dropped, rounded to fp32,
-// kept finite.  All the binning of a cut needs is this monotonicity (a higher bin then means a strictly larger
-// score); the exact order inside a bin is settled on the 64-bit keys.
-__device__ __forceinline__ float key_float(unsigned key_hi)
-{
-    const unsigned u = (key_hi >> 31) ? (key_hi & 0x7fffffffu) : ~key_hi;
-    const float f = (float)__hiloint2double((int)u, 0);
-    return fminf(fmaxf(f, -3.0e38f), 3.0e38f);
-}
 
 __device__ __forceinline__ int ceil_div_i(int a, int b) { return (a + b - 1) / b; }
 __device__ __forceinline__ int ceil_bp(int n, int bp) { return (int)(((int64_t)n * bp + 9999) / 10000); }
@@ -232,7 +214,6 @@ __device__ __forceinline__ double loaded(uint16_t v) { return (double)__uint_as_
 constexpr int kBins = 1024;                 // linear score bins of the cut
 constexpr int kSelGroups = kSelThreads / 16;  // 16-lane groups of a workgroup
 constexpr int kFastMembers = 64;            // most keys the bin / bracket at the cut may hold on the fast paths
-constexpr int kSearchSteps = 14;            // steps (of two bits) a search for the cut takes before it leaves the rest to ranking
 constexpr int kRegsLarge = (4352 + kSelThreads - 1) / kSelThreads;       // keys per thread of the largest level the register path holds
 constexpr int kMaxRuns = kRegsLarge * kSelWaves;  // its 64-slot runs
 constexpr int kEachWaveSlots = kSelWaves * kWave;  // largest level every wave cuts for itself
@@ -521,7 +502,7 @@ __device__ __forceinline__ void rank_members(uint64_t mine, int my_slot, int cnt
     *kept_mask = __ballot(lane < cnt && (rank < want || (keep_ties && mine == *thr)));
 }
 
-// Cut and ordered compaction of one level of more than kOneWaveSlots slots, its keys R per thread over the whole
+// Cut and ordered compaction of one level of more than kEachWaveSlots slots, its keys R per thread over the whole
 // workgroup: thread t takes slot x * 256 + t of the LDS copy in key[x] (0 = empty or not competing).  k =
 // k_of(n_valid) of the n_valid competing keys are kept, by (key descending, slot ascending); emit(pos, slot) is
 // called for each kept slot with its position in ascending slot order (positions at or beyond cap are dropped).
@@ -685,50 +666,6 @@ __device__ __forceinline__ int cut_in_registers(uint64_t* keys, int n_slots, con
     return sure_total + __popcll(kept_mask);
 }
 
-// What the search for a cut ends with: slots with f > above are kept for sure; the cnt slots with from < f <= above
-// still have to be ranked on their 64-bit keys, want of them are kept.  cnt = 0: the cut falls between two keys.
-struct Bracket {
-    float above, from;
-    int want, cnt;
-};
-
-// The bracket of the k-th largest of the n_valid scores f (0 < k < n_valid; -inf in slots without one; smallest and
-// largest finite score fmin, fmax), for one wave that holds all of them: a search by value, three thresholds a step, that
-// ends as soon as a threshold has exactly k scores above it (4 steps for 256 normally distributed scores, 10 at most in
-// 400 draws).  Counting is a compare, a ballot and a population count per threshold and register: scalar results,
-// nothing goes through LDS.  Three thresholds, because a step is a chain of dependent instructions whatever it counts.
-template <int R>
-__device__ __forceinline__ Bracket search_cut(const float (&f)[R], int k, int n_valid, float fmin, float fmax)
-{
-    float lo = fmin, hi = fmax;                       // more than k scores above lo (at or above it until it moves), fewer above hi
-    float from = -INFINITY;                           // lo once it has moved
-    int c_lo = n_valid, c_hi = 0;
-#pragma unroll 1
-    for (int step = 0; step < kSearchSteps; ++step) {
-        const float t2 = 0.5f * lo + 0.5f * hi, t1 = 0.5f * lo + 0.5f * t2, t3 = 0.5f * t2 + 0.5f * hi;
-        if (!(lo < t2 && t2 < hi)) break;             // neighbouring floats (or one value): ranked by key
-        int c1 = 0, c2 = 0, c3 = 0;
-#pragma unroll
-        for (int x = 0; x < R; ++x) {
-            c1 += __popcll(__ballot(f[x] > t1));
-            c2 += __popcll(__ballot(f[x] > t2));
-            c3 += __popcll(__ballot(f[x] > t3));
-        }
-        if ((c1 == k) | (c2 == k) | (c3 == k)) {
-            hi = from = c1 == k ? t1 : c2 == k ? t2 : t3;
-            c_lo = c_hi = k;
-            break;
-        }
-        const bool g1 = c1 > k, g2 = c2 > k, g3 = c3 > k;                 // g3 implies g2 implies g1
-        hi = g3 ? hi : g2 ? t3 : g1 ? t2 : t1;
-        c_hi = g3 ? c_hi : g2 ? c3 : g1 ? c2 : c1;
-        lo = g3 ? t3 : g2 ? t2 : g1 ? t1 : lo;
-        from = g1 ? lo : from;
-        c_lo = g3 ? c3 : g2 ? c2 : g1 ? c1 : c_lo;
-    }
-    return Bracket{hi, from, k - c_hi, c_lo - c_hi};
-}
-
 // Cut and ordered compaction of a level of at most 64 slots per wave of the workgroup.  EVERY wave holds all the keys
 // (slot x * 64 + lane in register x of each) and finds the cut for itself, so nothing is exchanged between waves; wave w
 // then emits the slots of register w.  Same contract as cut_in_registers; returns -1, having emitted nothing, when more
@@ -771,7 +708,16 @@ __device__ __forceinline__ int cut_in_each_wave(uint64_t* keys, int n_slots, con
     if (k > 0 && k < n_valid) {
         lo_h = (unsigned)__builtin_amdgcn_readlane((int)wave_minmax32<true>(lo_h), 63);
         hi_h = (unsigned)__builtin_amdgcn_readlane((int)wave_minmax32<false>(hi_h), 63);
-        const Bracket br = search_cut<R>(f, k, n_valid, key_float(lo_h), key_float(hi_h));
+        // (counting is a compare, a ballot and a population count per threshold and register: scalar results, no LDS)
+        const auto count = [&](float t1, float t2, float t3, int& c1, int& c2, int& c3) {
+#pragma unroll
+            for (int x = 0; x < R; ++x) {
+                c1 += __popcll(__ballot(f[x] > t1));
+                c2 += __popcll(__ballot(f[x] > t2));
+                c3 += __popcll(__ballot(f[x] > t3));
+            }
+        };
+        const Bracket br = search_cut(count, k, n_valid, key_float(lo_h), key_float(hi_h));
         above = br.above;
         if (br.cnt > kFastMembers) return -1;
         if (br.cnt > 0) {
