@@ -32,8 +32,9 @@ int chess_debug_force_general_cut(chess_ctx* ctx, int32_t on);
 int chess_debug_set_poll_limit(chess_ctx* ctx, int32_t polls);
 
 /* Test hook: force the split-K shape of the decode entry points (n_splits in [1, 256] with n_splits * G <= 1024,
- * waves in {1, 4}); n_splits = 0 restores the automatic choice.  CHESS_EINVAL if the forced shape would
- * not fit the workspace for max_batch sequences. */
+ * waves in {1, 4, 8}; eight waves are for lists, every-page attention then takes four, and the reuse step takes four
+ * for one); n_splits = 0 restores the automatic choice.  CHESS_EINVAL if the forced shape would not fit the workspace
+ * for max_batch sequences. */
 int chess_debug_force_splits(chess_ctx* ctx, int32_t n_splits, int32_t waves);
 
 #ifdef __cplusplus

@@ -8,6 +8,7 @@
 #include <new>
 
 #include "chess_internal.h"
+#include "split_rule.h"
 
 // Device memory chess_sparse_decode_static works in instead of a caller's workspace: split partials and arrival
 // counters.  Every GPU the library runs on holds its own copy at its own address, for the life of the process.
@@ -39,9 +40,10 @@ void* scratch_of_current_device(int dev)
     return g_scratch_of_device[dev];
 }
 
-inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
+using chess::cdiv;
+using chess::clampi;
+
 inline int64_t ceil_bp(int64_t n, int64_t bp) { return (n * bp + 9999) / 10000; }
-inline int64_t clampi(int64_t x, int64_t lo, int64_t hi) { return x < lo ? lo : (x > hi ? hi : x); }
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // Largest keep-counts any sequence of at most max_pages pages can reach under `pl`.
@@ -103,51 +105,14 @@ bool plan_bounds(const chess_ctx* ctx, const chess_select_plan* pl, Bounds* out)
     return true;
 }
 
-// n_slots > 0: the workgroups of a KV head, dealt to the sequences by length, at most n_splits to one
-struct SplitShape { int n_splits, waves, n_slots; };
+using chess::SplitShape;
 
-// Split-K shape.  A workgroup has four waves (eight where `wide` below says so); tiles are dealt round-robin over
-// splits and waves.
-// Dense (every page): enough workgroups to cover the chip a few times over; the workgroup that finishes last merges
-// ns partial rows per output, tile time falls as 1/ns and merge time grows as G*ns/32 (in units of one memory
-// round trip), so the best split count is about sqrt(8*tiles/G), within what is resident at once.  With several
-// sequences that count is the most one of them gets, and the workgroups resident at once are dealt to them by their
-// lengths on the device (share_slots), as soon as there are more of them than sequences: 1.13 x at 8-64K tokens.
-// A page list (tens to hundreds of pages): the fixed latencies dominate, and the measured optimum (sweeps at batch
-// 1 .. 32, 21 .. 415 pages, G = 1 .. 7) is: no split once there is a (sequence, head) per compute unit; otherwise one
-// workgroup per compute unit, at least two tiles per workgroup, and at most 1.6 x the merge-balanced count.
 SplitShape choose_splits(const chess_ctx* ctx, int batch, int64_t max_list_pages, bool listed)
 {
     const chess::Geom& g = ctx->geom;
-    const int ppt = chess::kTileTokens / g.page_size;
-    const int64_t tiles = std::max<int64_t>(1, cdiv(max_list_pages, ppt));
-    const int64_t pairs = (int64_t)batch * g.n_kv_heads;
-    const int64_t target = 4LL * ctx->n_cu;
-    if (ctx->force_splits > 0) return {ctx->force_splits, ctx->force_waves, 0};
-    const int waves = 4;
-    // all workgroups resident at once: a second round of workgroups would double a short kernel
-    const int64_t resident = (int64_t)ctx->dec_blocks4 * ctx->n_cu;
-    const double balanced = std::sqrt(8.0 * (double)tiles / g.group);
-    int64_t ns;
-    if (listed) {
-        ns = std::min<int64_t>(ctx->n_cu / pairs, cdiv(tiles, 2));
-        ns = std::min<int64_t>(ns, (int64_t)std::llround(1.6 * balanced));
-        ns = std::max<int64_t>(ns, 1);
-    } else {
-        ns = (int64_t)std::llround(balanced);
-        ns = std::min<int64_t>(ns, std::max<int64_t>(1, resident / pairs));
-        ns = clampi(ns, 1, cdiv(tiles, waves));
-        const int64_t most = clampi(std::llround(balanced), 1, std::min<int64_t>(std::min<int64_t>(cdiv(tiles, waves), ctx->max_splits), 1024 / g.group));
-        const int64_t slots = std::min<int64_t>(std::min<int64_t>(resident, target + pairs) / g.n_kv_heads, batch * most);
-        if (batch > 1 && slots > batch) return {(int)most, waves, (int)slots};
-    }
-    ns = std::min<int64_t>(ns, std::min<int64_t>(ctx->max_splits, 1024 / g.group));
-    while (ns > 1 && pairs * ns > target + pairs) --ns;            // stay inside the workspace
-    // a list whose workgroups would leave each compute unit at most one of four waves: eight, while there is a tile for
-    // each (the rows in flight double and a wave's chain of tiles halves, with no exchange through memory):
-    // 32 sequences of 16-32K, 8 layers and the monitor 139.8 -> 135.0 us
-    const bool wide = listed && pairs * ns <= ctx->n_cu && tiles > 4 * ns;
-    return {(int)ns, wide ? 8 : waves, 0};
+    const chess::SplitLimits c{ctx->n_cu, ctx->dec_blocks4 * ctx->n_cu, ctx->max_splits, g.n_kv_heads, g.group,
+                               chess::kTileTokens / g.page_size, ctx->force_splits, ctx->force_waves};
+    return chess::choose_splits(c, batch, max_list_pages, listed);
 }
 
 int decode_common(chess_ctx* ctx, const void* q, const void* k_pool, const void* v_pool, const int32_t* block_table,
@@ -217,7 +182,7 @@ int chess_create(const chess_config* cfg, chess_ctx** out)
     c->summary_bytes = align_up(c->grid_off + rows * g.max_grids * svec, 256);
 
     c->max_splits = 256;
-    const size_t part_rows = (size_t)(4 * c->n_cu + rows) * g.group;       // see choose_splits
+    const size_t part_rows = (size_t)chess::partial_rows(c->n_cu, (int64_t)rows) * g.group;       // see choose_splits
     c->ws_acc_off = 0;
     c->ws_ml_off = align_up(part_rows * vec, 256);
     c->ws_keys_off = align_up(c->ws_ml_off + part_rows * 2 * sizeof(float), 256);
@@ -700,10 +665,10 @@ int chess_dense_decode(chess_ctx* ctx, const void* q, const void* k_pool, const 
 
 int chess_debug_force_splits(chess_ctx* ctx, int32_t n_splits, int32_t waves)
 {
-    if (!ctx || n_splits < 0 || n_splits > ctx->max_splits || (waves != 1 && waves != 4)) return CHESS_EINVAL;
+    if (!ctx || n_splits < 0 || n_splits > ctx->max_splits || (waves != 1 && waves != 4 && waves != 8)) return CHESS_EINVAL;
     if (n_splits * ctx->geom.group > 1024) return CHESS_EINVAL;
     const int64_t rows = (int64_t)ctx->cfg.max_batch * ctx->geom.n_kv_heads;
-    if (rows * n_splits > 4LL * ctx->n_cu + rows) return CHESS_EINVAL;
+    if (rows * n_splits > chess::partial_rows(ctx->n_cu, rows)) return CHESS_EINVAL;
     ctx->force_splits = n_splits;
     ctx->force_waves = waves;
     return CHESS_OK;

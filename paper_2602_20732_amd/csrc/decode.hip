@@ -131,7 +131,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(3))) vo
 // KV head) to finish -- after which nobody reads the tail page or the list any more -- writes the rows to the pools
 // and, when the token opens a new page, the page to the list.  The lists must end with the tail page of seq_lens
 // (as a selection on these lengths, chess_append_kv with the lists, or this call leave them).
-// grid = (n_splits, H_kv, batch), NW waves (4 or 8: see choose_splits).
+// grid = (n_splits, H_kv, batch), NW waves (4 or 8: see split_rule.h).
 // kSingle: one tile in registers at a time; faster while a wave has only a few tiles (the host decides).
 // Two workgroups per compute unit either way (squeezed into the registers of three, the kernel was slower).
 template <int B, bool kSingle, int NW>

@@ -1,0 +1,79 @@
+// The split-K shape of the attention kernels: how many workgroups of how many waves share the pages of a sequence and KV
+// head.  Host code without anything of the GPU in it (the CPU tests run it over the whole range of shapes).
+#pragma once
+
+#include <algorithm>
+#include <cmath>
+#include <cstdint>
+
+namespace chess {
+
+// n_slots > 0: the workgroups of a KV head, dealt to the sequences by length, at most n_splits to one
+struct SplitShape { int n_splits, waves, n_slots; };
+
+struct SplitLimits {
+    int n_cu;
+    int resident;           // four-wave workgroups of the dense kernel that fit on the device at once
+    int max_splits;
+    int n_kv_heads, group;
+    int tile_pages;         // pages of a 32-token tile
+    int force_splits, force_waves;   // test hook; force_splits 0 = automatic
+};
+
+inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
+inline int64_t clampi(int64_t x, int64_t lo, int64_t hi) { return x < lo ? lo : (x > hi ? hi : x); }
+
+// Rows of split partials a workspace for `rows` (sequence, KV head) pairs holds, in units of G vectors.
+inline int64_t partial_rows(int n_cu, int64_t rows) { return 4LL * n_cu + rows; }
+
+// A workgroup has four waves (eight where `wide` below says so); tiles are dealt round-robin over splits and waves.
+// Dense (every page): enough workgroups to cover the chip a few times over; the workgroup that finishes last merges
+// ns partial rows per output, tile time falls as 1/ns and merge time grows as G*ns/32 (in units of one memory
+// round trip), so the best split count is about sqrt(8*tiles/G), within what is resident at once.  With several
+// sequences that count is the most one of them gets, and the workgroups resident at once are dealt to them by their
+// lengths on the device (share_slots), as soon as there are more of them than sequences: 1.13 x at 8-64K tokens.
+// A page list (tens to hundreds of pages): the fixed latencies dominate, and the measured optimum (sweeps at batch
+// 1 .. 32, 21 .. 415 pages, G = 1 .. 7) is: no split once there is a (sequence, head) per compute unit; otherwise one
+// workgroup per compute unit, at least two tiles per workgroup, and at most 1.6 x the merge-balanced count.
+inline SplitShape choose_splits(const SplitLimits& c, int batch, int64_t max_list_pages, bool listed)
+{
+    const int64_t tiles = std::max<int64_t>(1, cdiv(max_list_pages, c.tile_pages));
+    const int64_t pairs = (int64_t)batch * c.n_kv_heads;
+    const int64_t room = partial_rows(c.n_cu, pairs);
+    if (c.force_splits > 0) return {c.force_splits, c.force_waves == 8 && !listed ? 4 : c.force_waves, 0};
+    const int waves = 4;
+    const double balanced = std::sqrt(8.0 * (double)tiles / c.group);
+    const int64_t limit = std::min<int64_t>(c.max_splits, 1024 / c.group);
+    int64_t ns;
+    if (listed) {
+        ns = std::min<int64_t>(c.n_cu / pairs, cdiv(tiles, 2));
+        ns = std::min<int64_t>(ns, (int64_t)std::llround(1.6 * balanced));
+        ns = std::max<int64_t>(ns, 1);
+    } else {
+        // all workgroups resident at once: a second round of workgroups would double a short kernel
+        ns = (int64_t)std::llround(balanced);
+        ns = std::min<int64_t>(ns, std::max<int64_t>(1, c.resident / pairs));
+        ns = clampi(ns, 1, cdiv(tiles, waves));
+        const int64_t most = clampi(std::llround(balanced), 1, std::min<int64_t>(cdiv(tiles, waves), limit));
+        const int64_t slots = std::min<int64_t>(std::min<int64_t>(c.resident, room) / c.n_kv_heads, batch * most);
+        if (batch > 1 && slots > batch) return {(int)most, waves, (int)slots};
+    }
+    ns = std::min<int64_t>(ns, limit);
+    while (ns > 1 && pairs * ns > room) --ns;                      // stay inside the workspace
+    // Eight waves for a list whose workgroups leave each compute unit at most one of four waves: a wave's chain of tiles
+    // halves and the rows in flight double, with no exchange through memory, but a workgroup takes about 0.2 us longer
+    // to start and to combine.  Four against eight waves over batch 1 .. 32, 8 .. 256 (sequence, head) pairs, G = 1 .. 16,
+    // both page sizes, sparse decode and reuse step:
+    //   more than four query heads and more than one split (the merge of G * ns rows is shared by twice the threads):
+    //     eight are faster from the first tile beyond four waves' (0.81 - 0.97 x the time), level beyond 64 tiles a split;
+    //   otherwise only when each of eight waves has a tile (below that 1.00 - 1.04 x; from there 0.95 - 1.00 x), and with
+    //     tiles of two pages while none has more than four (beyond that 1.01 - 1.07 x; with one-page tiles the reuse step
+    //     still gains 2 - 5 % there).
+    // 32 sequences of 16-32K, 8 layers and the monitor: 139.8 -> 135.0 us.
+    const bool big_merge = c.group > 4 && ns > 1;
+    const bool wide = listed && pairs * ns <= c.n_cu &&
+                      (big_merge ? tiles > 4 * ns : tiles >= 8 * ns && (c.tile_pages == 1 || tiles <= 32 * ns));
+    return {(int)ns, wide ? 8 : waves, 0};
+}
+
+}  // namespace chess
