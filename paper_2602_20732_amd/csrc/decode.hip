@@ -1,70 +1,177 @@
 // Paged decode attention over a list of pages read in place (sparse: the selected page ids; dense: every
 // page), split-K with an online-softmax merge; the arithmetic is in decode_device.h.
 #include "decode_device.h"
+#include "split_rule.h"
 
 namespace chess {
 
 // Workgroups dealt by length (attention over every page of a ragged batch).  A KV head has n_slots workgroups for all
-// the sequences together; a sequence of t tiles takes ceil(t / u) of them (at most `most`), with the smallest tile
-// count u per workgroup, of 64 tried, for which the slots suffice.  Every wave finds u for itself: lane i tries the
-// i-th of 63 steps from "all slots equally full" to a count that certainly fits; the last lane's is one workgroup per
-// sequence (the host calls with n_slots >= batch).  Every workgroup computes the same numbers from the lengths in
-// device memory, so a captured launch follows them.
+// the sequences together; a sequence of t tiles takes ceil(t / u) of them, with the smallest tile count u per workgroup, of
+// 64 tried, for which the slots suffice.  Lane i holds the i-th of 63 steps from "all slots equally full" to a count that
+// certainly fits; the last lane's is one workgroup per sequence (the host calls with n_slots >= batch).  Every workgroup
+// computes the same numbers from the lengths in device memory, so a captured launch follows them.
+// A workgroup gets at least a tile per wave (u >= NW), and a sequence at most 1.5 x the count at which its own tiles and
+// its merge balance (choose_splits knows the longest possible length only): split finer, 16 workgroups' partials of a
+// short sequence cost more than its tiles.
 // With the same number of workgroups for every sequence the longest one set the time (the waves of the others idle,
-// and HBM with them): 16 sequences of 8-64K, 8 KV heads, 530 -> 469 us (4.6 -> 5.2 TB/s).
-struct SlotShare { int b, split, n_splits, first; };
+// and HBM with them): 64 sequences of 1-8192 tokens, 8 KV heads, 235 us -> 195 us dealt.
+// The dealing is a chain before the first request, so it is kept short: equal lengths need no search, a search looks at
+// three candidates a step (the slots needed never grow with u), and beyond 64 sequences the waves share them.  Counting all
+// 64 candidates sequence by sequence in every wave took 18 us of 512 sequences' launch.  us, fixed splits / every candidate
+// counted / as here:
+//   8 KV heads,  16 sequences of 1024 tokens   16.4 / 18.0 / 16.3    room for 64K, 8 sequences of 1-1024   11.1 / 14.0 /  8.7
+//               64 sequences of 8192 tokens   371.6 / 380.8 / 370.3
+//   1 KV head,  512 sequences of 1-1024 tokens 27.4 / 52.7 / 29.7    512 sequences of 1-8192   244.7 / 240.8 / 215.9
+// What remains of its cost shows where there is nothing to gain: 0.3 us with equal lengths, 0.5-1.5 us with ragged ones of
+// a few tiles, 3-5 us with 512-700 of those.
+struct SlotShare { int b, split, n_splits, first, len; };
+struct Share { int tiles, most; };                    // of one sequence; 0, 0: a lane without one
 
-__device__ __forceinline__ int slots_of(int tiles, float inv_u, int most)
+__device__ __forceinline__ int slots_of(const Share& q, float inv_u) { return min(1 + (int)((float)(q.tiles - 1) * inv_u), q.most); }
+
+// Inclusive sum over the lanes (row shifts and row broadcasts, no LDS); lane 63 has the total.
+template <class T>
+__device__ __forceinline__ T lanes_upto(T v)
 {
-    return min(1 + (int)((float)(tiles - 1) * inv_u), most);
+    static_assert(sizeof(T) == 4);
+#define CHESS_UPTO(ctrl, rows) v += __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), ctrl, rows, 0xf, false));
+    CHESS_UPTO(0x111, 0xf) CHESS_UPTO(0x112, 0xf) CHESS_UPTO(0x114, 0xf) CHESS_UPTO(0x118, 0xf) CHESS_UPTO(0x142, 0xa) CHESS_UPTO(0x143, 0xc)
+#undef CHESS_UPTO
+    return v;
 }
 
-template <int B>
-__device__ __forceinline__ SlotShare share_slots(int slot, int n_slots, int batch, int most, const int32_t* __restrict__ seq_lens,
-                                                 int max_pages, int lane)
+template <class T>
+__device__ __forceinline__ T lane_of(T v, int lane)
 {
-    const auto tiles_of = [&](int b) {
-        const int L = min(max(seq_lens[min(b, batch - 1)], 0), max_pages * B);
-        return max((L + kTileTokens - 1) / kTileTokens, 1);
+    static_assert(sizeof(T) == 4);
+    return __builtin_bit_cast(T, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
+}
+
+// What the waves of a workgroup tell each other where a batch has more than 64 sequences.
+template <int NW>
+struct DealLds {
+    float total[NW];
+    int other[NW], c12[3][NW], c3[3][NW];
+    int block[kDealMost / 64];                        // workgroups of each 64 sequences
+};
+
+template <int B, int NW>
+__device__ __forceinline__ SlotShare share_slots(int slot, int n_slots, int batch, int most, int G, const int32_t* __restrict__ seq_lens,
+                                                 int max_pages, int lane, int wave, DealLds<NW>& lds)
+{
+    const auto len_of = [&](int b) { return min(max(seq_lens[min(b, batch - 1)], 0), max_pages * B); };
+    const float per_tile = 18.f / (float)G;           // (1.5 x sqrt(8 tiles / G))
+    const auto share_of = [&](int b, int L) {
+        const int n = max((L + kTileTokens - 1) / kTileTokens, 1);
+        const int balanced = max((int)__builtin_amdgcn_sqrtf((float)n * per_tile), 1);
+        return b < batch ? Share{n, min(balanced, most)} : Share{0, 0};
     };
-    float total = 0.f;                                // (an estimate that orders the candidates: fp32 is enough)
-    for (int b0 = 0; b0 < batch; b0 += 64) total += b0 + lane < batch ? (float)tiles_of(b0 + lane) : 0.f;
-#pragma unroll
-    for (int x = 1; x < 64; x <<= 1) total += __shfl_xor(total, x);
-    const float lo = fmaxf(total / (float)n_slots, 1.f), hi = fmaxf(total / fmaxf((float)(n_slots - batch), 1.f), lo);
-    const float inv_u = lane == 63 ? 0.f : 1.f / (lo + (hi - lo) * (float)lane * (1.f / 62.f));
-    int used = 0;
-    for (int b0 = 0; b0 < batch; b0 += 64) {
-        const int mine = tiles_of(b0 + lane), n = min(batch - b0, 64);
-        for (int j = 0; j < n; ++j) used += slots_of(__builtin_amdgcn_readlane(mine, j), inv_u, most);
+    // up to 64 sequences: every wave has them all, one a lane.  More: a wave takes every NW-th block of 64 (the first of
+    // them stays in registers, those beyond are read again for every pass, from the cache), and the sums meet in LDS.
+    const bool wide = batch > 64;
+    const int b00 = wide ? 64 * wave : 0, b_next = wide ? b00 + 64 * NW : batch;
+    const int len0 = len_of(b00 + lane);
+    const int len_first = len_of(0);
+    const Share mine = share_of(b00 + lane, len0);
+    const Share some = share_of(0, len_first);
+    float total = (float)mine.tiles;                  // (an estimate that orders the candidates: fp32 is enough)
+    int other = __ballot(mine.tiles != some.tiles && b00 + lane < batch) != 0;
+    for (int b0 = b_next; b0 < batch; b0 += 64 * NW) {
+        const int n = share_of(b0 + lane, len_of(b0 + lane)).tiles;
+        total += (float)n;
+        other |= __ballot(n != some.tiles && b0 + lane < batch) != 0;
     }
-    const int at = __builtin_ctzll(__ballot(used <= n_slots));            // (lane 63 always fits)
-    const float inv = __shfl(inv_u, at);
-    SlotShare s = {-1, 0, 1, 0};
-    int first = 0;
-    for (int b0 = 0; b0 < batch && s.b < 0; b0 += 64) {
-        const int n = b0 + lane < batch ? slots_of(tiles_of(b0 + lane), inv, most) : 0;
-        int upto = n;                                 // inclusive prefix sum over the lanes
+    total = lane_of(lanes_upto(total), 63);
+    if (wide) {
+        if (lane == 0) {
+            lds.total[wave] = total;
+            lds.other[wave] = other;
+        }
+        __syncthreads();
+        total = 0.f;
+        other = 0;
 #pragma unroll
-        for (int x = 1; x < 64; x <<= 1) {
-            const int v = __shfl_up(upto, x);
-            upto += lane >= x ? v : 0;
+        for (int w = 0; w < NW; ++w) {
+            total += lds.total[w];
+            other |= lds.other[w];
         }
-        const unsigned long long past = __ballot(first + upto > slot);
-        if (past != 0) {
-            const int j = __builtin_ctzll(past);
-            s.b = b0 + j;
-            s.n_splits = __builtin_amdgcn_readlane(n, j);
-            s.first = first + __builtin_amdgcn_readlane(upto, j) - s.n_splits;
+    }
+    SlotShare s = {-1, 0, 1, 0, 0};
+    if (__builtin_amdgcn_readfirstlane(other) == 0) { // all as long: no search (quotients of small whole numbers: exact)
+        s.n_splits = min(min((int)((float)n_slots / (float)batch), some.most), (some.tiles + NW - 1) / NW);
+        const int b = (int)((float)slot / (float)s.n_splits);
+        if (b < batch) {
+            s.b = b;
+            s.first = b * s.n_splits;
             s.split = slot - s.first;
+            s.len = seq_lens[b];
         }
-        first += __builtin_amdgcn_readlane(upto, 63);
+        return s;
+    }
+    const float lo = fmaxf(total / (float)n_slots, (float)NW), hi = fmaxf(total / fmaxf((float)(n_slots - batch), 1.f), lo);
+    const float inv_u = lane == 63 ? 0.f : 1.f / (lo + (hi - lo) * (float)lane * (1.f / 62.f));
+    int at = 0;
+#pragma unroll
+    for (int step = 16, i = 0; step > 0; step >>= 2, ++i) {   // the slots needed never grow with the candidate: 64 -> 16 -> 4 -> 1
+        const float i1 = lane_of(inv_u, at + step - 1), i2 = lane_of(inv_u, at + 2 * step - 1), i3 = lane_of(inv_u, at + 3 * step - 1);
+        // (two counts in one register: at most n_slots + batch each)
+        int c12 = slots_of(mine, i1) | slots_of(mine, i2) << 16, c3 = slots_of(mine, i3);
+        for (int b0 = b_next; b0 < batch; b0 += 64 * NW) {
+            const Share q = share_of(b0 + lane, len_of(b0 + lane));
+            c12 += slots_of(q, i1) | slots_of(q, i2) << 16;
+            c3 += slots_of(q, i3);
+        }
+        c12 = lane_of(lanes_upto(c12), 63);
+        c3 = lane_of(lanes_upto(c3), 63);
+        if (wide) {
+            if (lane == 0) {
+                lds.c12[i][wave] = c12;
+                lds.c3[i][wave] = c3;
+            }
+            __syncthreads();
+            c12 = c3 = 0;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                c12 += lds.c12[i][w];
+                c3 += lds.c3[i][w];
+            }
+        }
+        at += (c12 & 0xffff) <= n_slots ? 0 : (c12 >> 16) <= n_slots ? step : c3 <= n_slots ? 2 * step : 3 * step;
+        at = __builtin_amdgcn_readfirstlane(at);
+    }
+    const float inv = lane_of(inv_u, at);             // (the last candidate always fits)
+    int b0 = 0, first = 0, len = len0;
+    Share own = mine;
+    if (wide) {                                       // the block of 64 the slot falls in
+        for (b0 = b00; b0 < batch; b0 += 64 * NW) {
+            const int n = lane_of(lanes_upto(slots_of(share_of(b0 + lane, len_of(b0 + lane)), inv)), 63);
+            if (lane == 0) lds.block[b0 / 64] = n;
+        }
+        __syncthreads();
+        const int n = 64 * lane < batch ? lds.block[lane] : 0, upto = lanes_upto(n);
+        const unsigned long long past = __ballot(upto > slot);
+        if (past == 0) return s;
+        const int j = __builtin_ctzll(past);
+        b0 = 64 * j;
+        first = lane_of(upto, j) - lane_of(n, j);
+        len = len_of(b0 + lane);
+        own = share_of(b0 + lane, len);
+    }
+    const int n = slots_of(own, inv), upto = first + lanes_upto(n);
+    const unsigned long long past = __ballot(upto > slot);
+    if (past != 0) {
+        const int j = __builtin_ctzll(past);
+        s.b = b0 + j;
+        s.n_splits = lane_of(n, j);
+        s.first = lane_of(upto, j) - s.n_splits;
+        s.split = slot - s.first;
+        s.len = lane_of(len, j);
     }
     return s;
 }
 
 // Three workgroups of four waves per compute unit (at most 170 registers a lane): see run_tiles_with, kSingle.
-template <int B, int NW, bool kList>
+template <int B, int NW, bool kList, bool kDealt = false>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(3))) void decode_kernel(const uint16_t* __restrict__ q,
                                                          const uint16_t* __restrict__ k_pool,
                                                          const uint16_t* __restrict__ v_pool,
@@ -83,17 +190,19 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(3))) vo
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int m16 = lane & 15, grp = lane >> 4;
-    const int G = g.group, H = g.n_kv_heads, h = blockIdx.y;
+    const int G = g.group, H = g.n_kv_heads, h = kDealt ? blockIdx.x : blockIdx.y;
     // the workgroup's sequence, its place among that row's splits, and where the row's partials start
-    int split = blockIdx.x, b = blockIdx.z, ns = n_splits;
+    int split = blockIdx.x, b = blockIdx.z, ns = n_splits, L_raw;
     size_t part0 = ((size_t)b * H + h) * n_splits;
-    if (!kList && batch > 0) {
-        const SlotShare sh = share_slots<B>(blockIdx.x, gridDim.x, batch, n_splits, seq_lens, g.max_pages, lane);
+    if constexpr (kDealt) {                           // grid = (H_kv, n_slots): the heads of a page are read at about the same time
+        __shared__ DealLds<NW> deal_lds;
+        const SlotShare sh = share_slots<B, NW>(blockIdx.y, gridDim.y, batch, n_splits, G, seq_lens, g.max_pages, lane, wave, deal_lds);
         if (sh.b < 0) return;                         // (uniform: nobody waits for a slot without work)
         split = sh.split;
         b = sh.b;
         ns = sh.n_splits;
-        part0 = (size_t)h * gridDim.x + sh.first;
+        L_raw = sh.len;
+        part0 = (size_t)h * gridDim.y + sh.first;
     }
     const size_t row = (size_t)b * H + h;
     const int32_t* ids = kList ? page_ids + row * g.max_sel : nullptr;
@@ -103,7 +212,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(3))) vo
     const int stride = ns * NW;
     const int t = split + ns * wave;
     int raw_cur[PPT], raw_nxt[PPT];
-    const int L_raw = seq_lens[b];
+    if constexpr (!kDealt) L_raw = seq_lens[b];
     const int n_raw = kList ? n_selected[row] : 0;
     fetch_ids<B, kList>(raw_cur, t, ids, g.max_sel);
     fetch_ids<B, kList>(raw_nxt, t + stride, ids, g.max_sel);
@@ -240,23 +349,25 @@ hipError_t launch_decode(chess_ctx* ctx, const uint16_t* q, const uint16_t* k_po
 {
     const Geom& g = ctx->geom;
     const float scale_log2 = ctx->sm_scale * 1.4426950408889634f;
-    const dim3 grid = n_slots > 0 ? dim3(n_slots, g.n_kv_heads) : dim3(n_splits, g.n_kv_heads, batch), block(64 * waves);
+    const bool dealt = n_slots > 0;                   // (every page, four waves: see choose_splits)
+    const dim3 grid = dealt ? dim3(g.n_kv_heads, n_slots) : dim3(n_splits, g.n_kv_heads, batch), block(64 * waves);
     const size_t lds = (size_t)(waves * g.group * kHeadDim + 2 * waves * g.group) * sizeof(float);
     using Kern = void (*)(const uint16_t*, const uint16_t*, const uint16_t*, const int32_t*, const int32_t*, const int32_t*,
                           const int32_t*, Geom, float, int, int, float*, float*, float*, int32_t*);
-    // [page size 16 / 32][waves 4 / 1][list / every page], and eight waves for a list
+    // [page size 16 / 32][waves 4 / 1][list / every page], eight waves for a list, every page dealt by length
     static const Kern table[2][2][2] = {
         {{decode_kernel<16, 4, true>, decode_kernel<16, 4, false>}, {decode_kernel<16, 1, true>, decode_kernel<16, 1, false>}},
         {{decode_kernel<32, 4, true>, decode_kernel<32, 4, false>}, {decode_kernel<32, 1, true>, decode_kernel<32, 1, false>}}};
     static const Kern wide[2] = {decode_kernel<16, 8, true>, decode_kernel<32, 8, true>};
+    static const Kern by_length[2] = {decode_kernel<16, 4, false, true>, decode_kernel<32, 4, false, true>};
     const int by_page = g.page_size == 16 ? 0 : 1;
-    const Kern kern = waves == 8 ? wide[by_page] : table[by_page][waves == 4 ? 0 : 1][page_ids ? 0 : 1];
+    const Kern kern = dealt ? by_length[by_page] : waves == 8 ? wide[by_page] : table[by_page][waves == 4 ? 0 : 1][page_ids ? 0 : 1];
     if (lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
     return launch(kern, grid, block, lds, stream, q, k_pool, v_pool, block_table, seq_lens,
-                  page_ids, n_selected, g, scale_log2, n_splits, n_slots > 0 ? batch : 0, out, ws_acc, ws_ml, arrivals);
+                  page_ids, n_selected, g, scale_log2, n_splits, batch, out, ws_acc, ws_ml, arrivals);
 }
 
 hipError_t decode_occupancy(int page_size, int waves, int group, int* blocks_per_cu)

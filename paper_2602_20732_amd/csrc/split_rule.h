@@ -20,6 +20,8 @@ struct SplitLimits {
     int force_splits, force_waves;   // test hook; force_splits 0 = automatic
 };
 
+constexpr int kDealMost = 4096;   // most sequences whose every-page attention is dealt by length
+
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline int64_t clampi(int64_t x, int64_t lo, int64_t hi) { return x < lo ? lo : (x > hi ? hi : x); }
 
@@ -31,7 +33,8 @@ inline int64_t partial_rows(int n_cu, int64_t rows) { return 4LL * n_cu + rows; 
 // ns partial rows per output, tile time falls as 1/ns and merge time grows as G*ns/32 (in units of one memory
 // round trip), so the best split count is about sqrt(8*tiles/G), within what is resident at once.  With several
 // sequences that count is the most one of them gets, and the workgroups resident at once are dealt to them by their
-// lengths on the device (share_slots), as soon as there are more of them than sequences: 1.13 x at 8-64K tokens.
+// lengths on the device (share_slots), as soon as there are more of them than sequences: only the device knows the
+// lengths, and splits chosen for the longest possible one cost a short sequence more than the dealing does (times there).
 // A page list (tens to hundreds of pages): the fixed latencies dominate, and the measured optimum (sweeps at batch
 // 1 .. 32, 21 .. 415 pages, G = 1 .. 7) is: no split once there is a (sequence, head) per compute unit; otherwise one
 // workgroup per compute unit, at least two tiles per workgroup, and at most 1.6 x the merge-balanced count.
@@ -56,7 +59,7 @@ inline SplitShape choose_splits(const SplitLimits& c, int batch, int64_t max_lis
         ns = clampi(ns, 1, cdiv(tiles, waves));
         const int64_t most = clampi(std::llround(balanced), 1, std::min<int64_t>(cdiv(tiles, waves), limit));
         const int64_t slots = std::min<int64_t>(std::min<int64_t>(c.resident, room) / c.n_kv_heads, batch * most);
-        if (batch > 1 && slots > batch) return {(int)most, waves, (int)slots};
+        if (batch > 1 && batch <= kDealMost && slots > batch) return {(int)most, waves, (int)slots};
     }
     ns = std::min<int64_t>(ns, limit);
     while (ns > 1 && pairs * ns > room) --ns;                      // stay inside the workspace

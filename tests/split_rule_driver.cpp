@@ -22,7 +22,7 @@ int main()
                                     const char* bad = nullptr;
                                     if (ns < 1 || ns > 256 || ns * group > 1024) bad = "split count";
                                     else if ((ns > 1 || s.n_slots > 0) && used > partial_rows(n_cu, pairs)) bad = "partials outgrow the workspace";
-                                    else if (s.n_slots > 0 && (listed || batch < 2 || s.n_slots <= batch || used > blocks * n_cu)) bad = "dealt slots";
+                                    else if (s.n_slots > 0 && (listed || batch < 2 || batch > kDealMost || s.n_slots <= batch || used > blocks * n_cu)) bad = "dealt slots";
                                     else if (!listed && s.waves != 4) bad = "waves of every-page attention";
                                     else if (listed && ns > 1 && pairs * ns > n_cu) bad = "more list workgroups than compute units";
                                     else if (listed && s.waves == 8) {
