@@ -110,7 +110,7 @@ using chess::SplitShape;
 SplitShape choose_splits(const chess_ctx* ctx, int batch, int64_t max_list_pages, bool listed)
 {
     const chess::Geom& g = ctx->geom;
-    const chess::SplitLimits c{ctx->n_cu, ctx->dec_blocks4 * ctx->n_cu, ctx->max_splits, g.n_kv_heads, g.group,
+    const chess::SplitLimits c{ctx->n_cu, ctx->dense_blocks * ctx->n_cu, ctx->max_splits, g.n_kv_heads, g.group,
                                chess::kTileTokens / g.page_size, ctx->force_splits, ctx->force_waves};
     return chess::choose_splits(c, batch, max_list_pages, listed);
 }
@@ -194,9 +194,8 @@ int chess_create(const chess_config* cfg, chess_ctx** out)
     c->ws_ent_off = align_up(c->ws_err_off + 256, 256);
     c->ws_entcnt_off = align_up(c->ws_ent_off + (size_t)cfg->max_batch * chess::kEntMaxSplits * 4 * sizeof(float), 256);
     c->workspace_bytes = align_up(c->ws_entcnt_off + (size_t)cfg->max_batch * sizeof(int32_t), 256);
-    c->dec_blocks4 = c->dec_blocks1 = 2;
-    if (chess::decode_occupancy(g.page_size, 4, g.group, &v) == hipSuccess && v > 0) c->dec_blocks4 = v;
-    if (chess::decode_occupancy(g.page_size, 1, g.group, &v) == hipSuccess && v > 0) c->dec_blocks1 = v;
+    c->dense_blocks = 2;
+    if (chess::dense_occupancy(g.page_size, g.group, &v) == hipSuccess && v > 0) c->dense_blocks = v;
     c->force_cluster = 0;
     c->force_schedule = 0;
     c->force_general_cut = 0;

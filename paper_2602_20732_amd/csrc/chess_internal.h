@@ -134,7 +134,7 @@ struct chess_ctx {
     int force_schedule;                                    // 0 = automatic, 1 = lazy, 2 = merged
     int force_general_cut;                                 // 0 = automatic
     int poll_limit;                                        // 0 = the default
-    int dec_blocks4, dec_blocks1;                          // decode workgroups per CU with 4 waves / 1 wave
+    int dense_blocks;                                      // workgroups of attention over every page per CU
     int occ_lds, occ_blocks;                               // cached occupancy query of the select kernel
     int step_occ_lds, step_occ_blocks;                     // ... and of the fused step kernel
     int shared_occ_lds, shared_occ_blocks;                 // ... and of the model-wide select kernel
@@ -207,7 +207,7 @@ hipError_t launch_select_shared(chess_ctx* ctx, const SharedTable& tab, const in
                                 const SelectParams& sp, const SelectWs& ws, size_t lds_bytes, int32_t* page_ids,
                                 int32_t* n_selected, hipStream_t stream);
 size_t select_lds_bytes(const SelectParams& sp, int max_sel);
-hipError_t decode_occupancy(int page_size, int waves, int group, int* blocks_per_cu);
+hipError_t dense_occupancy(int page_size, int group, int* blocks_per_cu);
 hipError_t launch_append(chess_ctx* ctx, const uint16_t* k_new, const uint16_t* v_new, uint16_t* k_pool, uint16_t* v_pool,
                          const int32_t* block_table, const int32_t* seq_lens, int batch, int32_t* page_ids,
                          int32_t* n_selected, hipStream_t stream);

@@ -370,15 +370,20 @@ hipError_t launch_decode(chess_ctx* ctx, const uint16_t* q, const uint16_t* k_po
                   page_ids, n_selected, g, scale_log2, n_splits, batch, out, ws_acc, ws_ml, arrivals);
 }
 
-hipError_t decode_occupancy(int page_size, int waves, int group, int* blocks_per_cu)
+// Four-wave workgroups of attention over every page that fit on a compute unit, dealt or not, whichever are fewer (lists
+// go by the number of compute units alone).
+hipError_t dense_occupancy(int page_size, int group, int* blocks_per_cu)
 {
-    // (the list variant: it is the one whose split count depends on what fits)
-    const size_t lds = (size_t)(waves * group * kHeadDim + 2 * waves * group) * sizeof(float);
-    if (page_size == 16)
-        return waves == 4 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, decode_kernel<16, 4, true>, 256, lds)
-                          : hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, decode_kernel<16, 1, true>, 64, lds);
-    return waves == 4 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, decode_kernel<32, 4, true>, 256, lds)
-                      : hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, decode_kernel<32, 1, true>, 64, lds);
+    const size_t lds = (size_t)(4 * group * kHeadDim + 2 * 4 * group) * sizeof(float);
+    int fixed = 0, dealt = 0;
+    hipError_t e = page_size == 16 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&fixed, decode_kernel<16, 4, false>, 256, lds)
+                                   : hipOccupancyMaxActiveBlocksPerMultiprocessor(&fixed, decode_kernel<32, 4, false>, 256, lds);
+    if (e != hipSuccess) return e;
+    e = page_size == 16 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&dealt, decode_kernel<16, 4, false, true>, 256, lds)
+                        : hipOccupancyMaxActiveBlocksPerMultiprocessor(&dealt, decode_kernel<32, 4, false, true>, 256, lds);
+    if (e != hipSuccess) return e;
+    *blocks_per_cu = fixed < dealt ? fixed : dealt;
+    return hipSuccess;
 }
 
 // One new token per sequence into the paged pools: K row-major [phys][H][B][128], V token-minor [phys][H][128][B].
