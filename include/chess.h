@@ -289,7 +289,10 @@ int chess_sparse_decode(chess_ctx* ctx, const void* q, const void* k_pool, const
                         const int32_t* block_table, const int32_t* seq_lens, const int32_t* page_ids,
                         const int32_t* n_selected, int32_t batch, float* out, void* workspace, void* stream);
 
-/* The same attention over every page of each sequence: the paper's Full-KV baseline (Sec. 5.1). */
+/* The same attention over every page of each sequence: the paper's Full-KV baseline (Sec. 5.1).
+ * In a batch the workgroups are dealt to the sequences by all their lengths (read on the device), so the order in which a
+ * sequence's tokens are summed, and with it the last bits of its output, depends on the lengths of its batch mates;
+ * the same batch gives the same bits on every call. */
 int chess_dense_decode(chess_ctx* ctx, const void* q, const void* k_pool, const void* v_pool,
                        const int32_t* block_table, const int32_t* seq_lens, int32_t batch, float* out,
                        void* workspace, void* stream);

@@ -24,16 +24,17 @@
 // slot order for the list of kept units.  Ties at the cut go to the lowest slots (= lowest indices: candidates are
 // enumerated in index order), or are all kept under the threshold rule.
 // Which cut a level takes goes by its slots, because what a cut costs is the length of its chain of dependent
-// instructions (a dependent vector instruction takes 8 cycles, an LDS read 62, a taken branch about 36):
+// instructions (times of a grid level inside chess_select, from the phase marks of a -DCHESS_PROF build):
 //   up to 64     every key is ranked against every other with lane reads, each wave taking a quarter of the comparisons
-//                (1.2 us; one wave looping over the keys took 2.5);
-//   up to 256    every wave holds all the keys and searches the cut by value, with counts alone and without LDS (2.4 us,
-//                two thirds of it reading, bounds and emission; the histogram below by one wave took 3.0);
+//                (16 slots 1.1 us, 64 slots 1.4 us; one wave looping over the keys took 1.6 and 4.2);
+//   up to 256    every wave holds all the keys and searches the cut by value, with counts alone and without LDS (96 slots 2.3
+//                us, 256 slots 2.4 us; the histogram below by one wave took 2.2 and 2.8);
 //   up to 1024   bounds from the upper key halves, a histogram over 1024 bins that are linear in the (fp32-rounded) score, a
 //                scan from the top, an exact ranking by (key, slot) of the few keys in the bin the k-th largest falls in:
-//                the whole workgroup, four keys per thread, which arrive in registers (3.3 us; every wave searching 16
-//                keys per lane took 5.4, the search spread over the waves with a barrier a step 4.3);
-//   up to 4352   the same with seventeen keys per thread.
+//                the whole workgroup, four keys per thread, which arrive in registers (512 slots 2.9 us, 1024 slots 3.1 us;
+//                in a trial at 1024 slots, where this took 3.3, every wave searching 16 keys per lane took 5.4 and the search
+//                spread over the waves with a barrier a step 4.3);
+//   up to 4352   the same with seventeen keys per thread, read from LDS (2048 slots 6.5 us, 4096 slots 10.4 us).
 // Score distributions that pile more than 64 keys into the bin or bracket at the cut (exact ties, mostly) take a general
 // path: radix select on the bits the keys do not share, then a ballot compaction.
 //
