@@ -88,3 +88,30 @@ def test_eight_waves(page, tiles, splits, group):
     assert (four - B["out"]).abs().max() <= ATOL
     assert torch.equal(dense[0], dense[1])
     lib.close()
+
+
+def test_captured_launch_of_sixteen_heads():
+    """Eight waves of sixteen query heads ask for more than 64 KB of LDS, by an attribute of the kernel that is set at each
+    launch: also while a graph is being recorded.  Replays against the eager call, the lists changed in between."""
+    group, page, room = 16, 16, 40
+    sp = workload.WorkloadSpec("captured8", 2, (60 * page, 60 * page), 2 * group, 2, page, ("fixed", 128), (2, 2), SINK, WINDOW,
+                               budget_pages=room - SINK - WINDOW, pages_per_chunk=4, chunks_per_grid=4)
+    d = to_device(workload.generate(sp, 17))
+    lib = pk.Chess(config_of(sp, max_selected=room))
+    lib.debug_force_splits(2, 8)
+    ws = lib.new_workspace()
+    gen = torch.Generator().manual_seed(5)
+    ids = torch.stack([torch.randperm(60, generator=gen)[:room].sort().values for _ in range(4)]).view(2, 2, room).to(torch.int32).cuda()
+    nsel = torch.full((2, 2), room, dtype=torch.int32, device="cuda")
+    out, want = (torch.empty((2, sp.n_q_heads, 128), device="cuda") for _ in range(2))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        lib.sparse_decode(d.q, d.k_pool, d.v_pool, d.block_table, d.seq_lens, ids, nsel, out, ws)
+    for n in (room, 33, 1, 0, room):
+        nsel.fill_(n)
+        out.fill_(float("nan"))
+        graph.replay()
+        lib.sparse_decode(d.q, d.k_pool, d.v_pool, d.block_table, d.seq_lens, ids, nsel, want, ws)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want), n
+    lib.close()
