@@ -163,8 +163,8 @@ int chess_create(const chess_config* cfg, chess_ctx** out)
     g.max_chunks = (int32_t)cdiv(g.max_pages, g.n_c);
     g.max_grids = (int32_t)cdiv(g.max_chunks, g.n_g);
     g.max_sel = cfg->max_selected_pages;
-    g.inv_nc = g.n_c > 1 ? (uint32_t)((0x100000000ull + g.n_c - 1) / g.n_c) : 0u;
-    g.inv_ng = g.n_g > 1 ? (uint32_t)((0x100000000ull + g.n_g - 1) / g.n_g) : 0u;
+    g.inv_nc = (uint32_t)((0x80000000ull + g.n_c - 1) / g.n_c);
+    g.inv_ng = (uint32_t)((0x80000000ull + g.n_g - 1) / g.n_g);
     c->sm_scale = cfg->sm_scale > 0.f ? cfg->sm_scale : 1.0f / std::sqrt((float)kHeadDim);
 
     int dev = 0, v = 0;
@@ -293,18 +293,45 @@ static int64_t choose_cluster(const chess_ctx* ctx, int64_t pairs, int64_t capac
     return std::max<int64_t>(1, std::min<int64_t>(capacity / pairs, clampi(cdiv(tiles, 8), 8, 12)));
 }
 
-// Which schedule the levels run on (select_device.h).  merged: all chunks are scored with the grids, which saves a
-// dependent memory phase and an exchange for n_c - k_g N_g more chunk vectors; it pays while the launch is bound by
-// its chain of memory round trips rather than by bytes.  Otherwise lazy, and every member scores all grids itself
-// when they are few.
+// Which schedule the levels run on (select_device.h).
+// merged: all chunks are scored with the grids, which saves a dependent memory phase and an exchange for n_c - k_g N_g more
+// chunk vectors; it pays while the launch is bound by its chain of memory round trips rather than by bytes.  Otherwise
+// lazy, and every member scores all grids itself when they are few.
 static void choose_schedule(const chess_ctx* ctx, int64_t pairs, int64_t cluster, chess::SelectParams* sp)
 {
     const int svec = kHeadDim * (ctx->cfg.summary_dtype == CHESS_SUMMARY_BF16 ? 2 : 4);
     // measured on MI355X: merged wins when several workgroups share a (sequence, head) (an exchange is saved, not only
     // a phase) and all chunk vectors of the launch stay below about 24 MB (cfg4a: bf16 summaries yes, fp32 no)
     const int64_t chunk_bytes = pairs * ctx->geom.max_chunks * svec;
-    sp->merged = ctx->force_schedule > 0 ? ctx->force_schedule == 2 : (cluster > 1 && chunk_bytes <= (24LL << 20));
-    sp->local_grids = pairs * cluster * ctx->geom.max_grids * svec <= (4LL << 20);   // repeated grid reads stay small (measured: at 33 MB it costs 3 us)   // repeated grid reads stay small
+    const bool merged = ctx->force_schedule > 0 ? ctx->force_schedule - 1 != chess::kLazy : cluster > 1 && chunk_bytes <= (24LL << 20);
+    sp->schedule = merged ? chess::kMerged : chess::kLazy;
+    sp->local_grids = pairs * cluster * ctx->geom.max_grids * svec <= (4LL << 20);   // repeated grid reads stay small (measured: at 33 MB it costs 3 us)
+    sp->deciders = (int32_t)cluster;
+}
+
+// The fused step has one schedule more, eager: the pages are scored in the first phase as well, by up to as many members
+// as fit, most of which then leave.  It saves the page level's memory phase and exchange -- and the chunk level's, where
+// every grid is kept and merging saves nothing -- and pays while one round trip covers every member's share and the vectors
+// are few bytes.  us a step on MI355X (merged / eager; 32 query and 8 KV heads, pages of 16, fp32 vectors, MB of vectors):
+//   every grid kept:  1 x 4K  22.1 / 18.7 (1.2)   8 x 8K  27.8 / 24.3 (20)   16 x 4K  27.6 / 24.1 (20)   28 x 4K  29.7 / 32.1 (35)
+//   grids pruned:     1 x 32K  23.6 / 22.7 (9.6)  1 x 48K  25.8 / 25.7 (14)  2 x 32K  24.4 / 25.1 (19)   1 x 64K  26.8 / 29.3 (19)
+// Returns whether the schedule is eager; then *cluster members score and sp->deciders of them run the cuts and the
+// attention (half as many as the list has tiles: fewer partials to merge, a tile for every other wave).
+static bool choose_eager(const chess_ctx* ctx, int64_t pairs, int64_t capacity, int64_t list_tiles, int64_t* cluster, chess::SelectParams* sp)
+{
+    if (*cluster <= 1 || (ctx->force_schedule != 0 && ctx->force_schedule - 1 != chess::kEager)) return false;
+    const chess::Geom& g = ctx->geom;
+    const int64_t units = (int64_t)g.max_pages + g.max_chunks + g.max_grids;
+    const int64_t most = clampi(capacity / pairs, 1, chess::kSelMaxCluster);
+    const int64_t members = ctx->force_cluster > 0 ? *cluster : clampi(cdiv(units, 96), std::min<int64_t>(12, most), most);
+    const bool bf16 = ctx->cfg.summary_dtype == CHESS_SUMMARY_BF16;
+    const int64_t trip = bf16 ? 256 : 128;                                             // (HeadScorer::kTrip)
+    const int64_t bytes = pairs * units * kHeadDim * (bf16 ? 2 : 4), most_bytes = sp->cap_kg >= g.max_grids ? 20LL << 20 : 12LL << 20;
+    if (ctx->force_schedule == 0 && (cdiv(units, std::max<int64_t>(members - 1, 1)) > trip || bytes > most_bytes)) return false;
+    sp->schedule = chess::kEager;
+    sp->deciders = (int32_t)clampi(cdiv(list_tiles, 2), 1, std::min<int64_t>(members, 12));
+    *cluster = members;
+    return true;
 }
 
 // Checks a plan against the configuration and fills the kernel-side parameters.
@@ -323,6 +350,7 @@ static int prepare_select(chess_ctx* ctx, const chess_select_plan* plan, chess::
     sp.cap_keys = (int32_t)bd.slots;
     sp.cap_kg = (int32_t)bd.kg;
     sp.cap_kc = (int32_t)bd.kc;
+    sp.most_kp = (int32_t)bd.kp;
     sp.probe = plan->probe;
     sp.poll_limit = ctx->poll_limit > 0 ? ctx->poll_limit : ctx->poll_limit < 0 ? 0 : (1 << 15);   // < 0: every wait fails at once
     sp.general_cut = ctx->force_general_cut;
@@ -523,7 +551,7 @@ int chess_select_shared(chess_ctx* ctx, const float* const* probes, const void* 
     if (ctx->force_cluster > 0) cluster = std::min<int64_t>(ctx->force_cluster, cluster);
     cluster = ctx->cfg.shared_device != 0 ? 1 : clampi(cluster, 1, chess::kSharedMaxCluster);
     sp.local_grids = 0;
-    sp.merged = 0;                                   // a unit is n_layers * H_kv rows here: the launch is bound by bytes
+    sp.schedule = chess::kLazy;                      // a unit is n_layers * H_kv rows here: the launch is bound by bytes
     const chess::SelectWs ws = select_ws(ctx, workspace);
     hipError_t e = chess::launch_select_shared(ctx, tab, seq_lens, batch, (int)cluster, sp, ws, lds, page_ids, n_selected,
                                                static_cast<hipStream_t>(stream));
@@ -560,8 +588,11 @@ int chess_decode_step(chess_ctx* ctx, const void* q, const void* k_pool, const v
     int64_t cluster = choose_cluster(ctx, pairs, capacity);
     if (ctx->force_cluster > 0) cluster = std::min<int64_t>(ctx->force_cluster, capacity / pairs);
     cluster = ctx->cfg.shared_device != 0 ? 1 : clampi(cluster, 1, chess::kSelMaxCluster);
-    if (pairs * cluster > 4LL * ctx->n_cu + pairs) return CHESS_ENOTSUP;   // partial rows of the workspace
-    choose_schedule(ctx, pairs, cluster, &sp);
+    // pages the lists can hold
+    const int64_t listed = std::min<int64_t>(ctx->geom.max_sel, (int64_t)sp.sink + sp.window + sp.most_kp);
+    if (!choose_eager(ctx, pairs, capacity, cdiv(listed, chess::kTileTokens / ctx->geom.page_size), &cluster, &sp))
+        choose_schedule(ctx, pairs, cluster, &sp);
+    if (pairs * sp.deciders > 4LL * ctx->n_cu + pairs) return CHESS_ENOTSUP;   // partial rows of the workspace
 
     const chess::SelectWs ws = select_ws(ctx, workspace);
     char* sb = static_cast<char*>(summaries);
@@ -596,7 +627,7 @@ int chess_debug_force_cluster(chess_ctx* ctx, int32_t cluster)
 
 int chess_debug_force_schedule(chess_ctx* ctx, int32_t schedule)
 {
-    if (!ctx || schedule < 0 || schedule > 2) return CHESS_EINVAL;
+    if (!ctx || schedule < 0 || schedule > 3) return CHESS_EINVAL;
     ctx->force_schedule = schedule;
     return CHESS_OK;
 }

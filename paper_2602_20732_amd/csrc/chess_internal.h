@@ -21,21 +21,53 @@ struct Geom {
     int32_t n_c, n_g;                // pages per chunk, chunks per grid
     int32_t max_pages, max_chunks, max_grids;   // row strides of block table / summary arrays
     int32_t max_sel;                 // row stride of page_ids
-    uint32_t inv_nc, inv_ng;         // ceil(2^32 / n_c), ceil(2^32 / n_g) (0 for 1): divisions by n_c / n_g as a multiply-high
+    uint32_t inv_nc, inv_ng;         // ceil(2^31 / n_c), ceil(2^31 / n_g): divisions by n_c / n_g as a multiply-high (div_by)
 };
+
+enum Schedule : int32_t { kLazy = 0, kMerged = 1, kEager = 2 };
+enum ClusterMode : int { kSolo = 0, kCluster = 1, kEagerCluster = 2 };   // which code a selection kernel has (select_device.h)
 
 struct SelectParams {
     int32_t plan, sink, window, budget_pages, budget_bp, over_chunk, over_grid, rho_g_bp, rho_c_bp, rho_p_bp;
     int32_t cap2, cap3;              // most candidate slots level 2 / level 3 can have (host bound)
     int32_t cap_keys, cap_kg, cap_kc;   // LDS capacities: keys of one level, kept grids, kept chunks
+    int32_t most_kp;                 // most pages a sequence can keep
     int32_t probe;                   // CHESS_PROBE_*
     int32_t poll_limit;              // polls before a wait for published keys is given up
     int32_t general_cut;             // test hook: every level takes the general (LDS radix) cut
     int32_t local_grids;             // every member scores all grids itself (no exchange at the grid level)
-    int32_t merged;                  // all chunks are scored together with the grids (one memory phase and one exchange fewer)
+    int32_t schedule;                // which units are scored together (select_device.h)
+    int32_t deciders;                // members that run the cuts; under the eager schedule the others only score
     int32_t keep_ties;               // the threshold rule: a level keeps every unit that ties with its k-th
     const int32_t* budget_per_seq;   // device [batch] or null: a value > 0 is that sequence's page budget
 };
+
+// A kernel argument as a register of its own.  Arguments arrive in groups of up to sixteen scalar registers, and a kernel
+// that runs out of those saves and restores whole groups, sixteen lane reads for one value (step_kernel executed more of
+// these than of anything else); a value that has been through here is saved and restored alone.
+template <class V>
+__device__ __forceinline__ V own_reg(V v)
+{
+    asm("" : "+s"(v));
+    return v;
+}
+__device__ __forceinline__ Geom own_regs(const Geom& g)
+{
+    return Geom{own_reg(g.n_q_heads), own_reg(g.n_kv_heads), own_reg(g.group), own_reg(g.page_size), own_reg(g.n_c), own_reg(g.n_g),
+                own_reg(g.max_pages), own_reg(g.max_chunks), own_reg(g.max_grids), own_reg(g.max_sel), own_reg(g.inv_nc), own_reg(g.inv_ng)};
+}
+__device__ __forceinline__ SelectParams own_regs(const SelectParams& p)
+{
+    SelectParams r;
+    r.plan = own_reg(p.plan); r.sink = own_reg(p.sink); r.window = own_reg(p.window); r.budget_pages = own_reg(p.budget_pages);
+    r.budget_bp = own_reg(p.budget_bp); r.over_chunk = own_reg(p.over_chunk); r.over_grid = own_reg(p.over_grid);
+    r.rho_g_bp = own_reg(p.rho_g_bp); r.rho_c_bp = own_reg(p.rho_c_bp); r.rho_p_bp = own_reg(p.rho_p_bp);
+    r.cap2 = own_reg(p.cap2); r.cap3 = own_reg(p.cap3); r.cap_keys = own_reg(p.cap_keys); r.cap_kg = own_reg(p.cap_kg);
+    r.cap_kc = own_reg(p.cap_kc); r.most_kp = own_reg(p.most_kp); r.probe = own_reg(p.probe); r.poll_limit = own_reg(p.poll_limit);
+    r.general_cut = own_reg(p.general_cut); r.local_grids = own_reg(p.local_grids); r.schedule = own_reg(p.schedule);
+    r.deciders = own_reg(p.deciders); r.keep_ties = own_reg(p.keep_ties); r.budget_per_seq = p.budget_per_seq;   // (a pointer would lose its address space)
+    return r;
+}
 
 // The page budget the plan fixes for sequence b, or 0 when it is derived from the sequence's page count:
 // budget_per_seq[b] when given and positive (clamped to what a page_ids row can hold), else budget_pages.
@@ -114,6 +146,26 @@ __device__ __forceinline__ bool arrive_last(int32_t* counter, int expected, int*
     return *lds_flag != 0;
 }
 
+// The same where a row's workgroups are of two kinds: deciders (splits of the row's attention) and helpers (which only
+// published keys).  One word counts both, deciders in its lower half.  Returns, to every thread, kLastDecider in the
+// decider that arrives last of the deciders and kLastOfAll in whichever workgroup arrives last of all; that one re-arms
+// the counter.
+constexpr int kLastDecider = 1, kLastOfAll = 2;
+__device__ __forceinline__ int arrive_of_two(int32_t* counter, bool decider, int n_deciders, int n_helpers, int* lds_flag)
+{
+    __builtin_amdgcn_s_waitcnt(0);                   // this wave's published stores are acknowledged, its loads have returned
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const int old = __hip_atomic_fetch_add(counter, decider ? 1 : 0x10000, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int d = (old & 0xffff) + (decider ? 1 : 0), h = (old >> 16) + (decider ? 0 : 1);
+        const bool all = d == n_deciders && h == n_helpers;
+        if (all) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *lds_flag = (decider && d == n_deciders ? kLastDecider : 0) | (all ? kLastOfAll : 0);
+    }
+    __syncthreads();
+    return *lds_flag;
+}
+
 }  // namespace chess
 
 struct chess_ctx {
@@ -131,7 +183,7 @@ struct chess_ctx {
     size_t ws_keys_off, ws_tail_off, ws_meta_off, ws_cnt_off, ws_err_off, ws_prof_off;   // select scratch, decode arrival counters, error word
     int64_t key_stride;
     int force_cluster;                                     // 0 = automatic
-    int force_schedule;                                    // 0 = automatic, 1 = lazy, 2 = merged
+    int force_schedule;                                    // 0 = automatic, 1 + kLazy / kMerged / kEager
     int force_general_cut;                                 // 0 = automatic
     int poll_limit;                                        // 0 = the default
     int dense_blocks;                                      // workgroups of attention over every page per CU

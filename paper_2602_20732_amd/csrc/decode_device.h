@@ -439,51 +439,81 @@ __device__ __forceinline__ bool combine_waves(const f32x4 (&o)[8], float m_run, 
 
 // What the last split of a (sequence, KV head) to finish does: merge all splits' partials,
 // out = sum_s acc_s 2^(m_s - M) / sum_s l_s 2^(m_s - M), always in split order, so the result does not
-// depend on which workgroup happens to be last.  A thread owns one pair of adjacent outputs of one head and
-// derives that head's M and denominator itself from the (m, l) pairs (the threads of a head read the same
-// words), so the partial rows and the (m, l) pairs are requested together: one round trip to memory, no LDS,
-// no barrier.
+// depend on which workgroup happens to be last.  A thread owns kItems pairs of adjacent outputs and derives their
+// heads' M and denominator itself from the (m, l) pairs (the threads of a head read the same words), so the partial
+// rows and the (m, l) pairs are requested together, kChunk splits of every pair at a time: no LDS, no barrier.
+// Bound: memory round trips.
+template <int NW, int kItems, int kChunk>
+__device__ __forceinline__ void merge_splits_by(int G, int n_splits, size_t part0, float* __restrict__ out_rows,
+                                                const float* __restrict__ ws_acc, const float* __restrict__ ws_ml)
+{
+    const uint64_t* acc_g = reinterpret_cast<const uint64_t*>(ws_acc);
+    const uint64_t* ml_g = reinterpret_cast<const uint64_t*>(ws_ml);
+    const int n_items = G * (kHeadDim / 2);
+    for (int idx = threadIdx.x; idx < n_items; idx += 64 * NW * kItems) {
+        int head[kItems], d2[kItems];
+        float M[kItems], l[kItems], a0[kItems], a1[kItems];
+#pragma unroll
+        for (int y = 0; y < kItems; ++y) {
+            const int i = min(idx + y * 64 * NW, n_items - 1);    // (a pair beyond the last repeats it and is not stored)
+            head[y] = i / (kHeadDim / 2);
+            d2[y] = i % (kHeadDim / 2);
+            M[y] = kNegBig; l[y] = 0.f; a0[y] = 0.f; a1[y] = 0.f;
+        }
+        for (int s0 = 0; s0 < n_splits; s0 += kChunk) {
+            uint64_t v[kItems][kChunk], ml[kItems][kChunk];
+#pragma unroll
+            for (int y = 0; y < kItems; ++y) {
+#pragma unroll
+                for (int x = 0; x < kChunk; ++x) {
+                    const size_t pr = (part0 + min(s0 + x, n_splits - 1)) * G + head[y];
+                    ml[y][x] = observe_u64(ml_g + pr);
+                    v[y][x] = observe_u64(acc_g + pr * (kHeadDim / 2) + d2[y]);
+                }
+            }
+            // running maximum over the splits seen so far; what has been summed is rescaled to it
+#pragma unroll
+            for (int y = 0; y < kItems; ++y) {
+                float Mc = M[y];
+#pragma unroll
+                for (int x = 0; x < kChunk; ++x)
+                    if (s0 + x < n_splits) Mc = fmaxf(Mc, __builtin_bit_cast(float2, ml[y][x]).x);
+                const float keep = __builtin_amdgcn_exp2f(M[y] - Mc);
+                l[y] *= keep; a0[y] *= keep; a1[y] *= keep;
+                M[y] = Mc;
+#pragma unroll
+                for (int x = 0; x < kChunk; ++x) {
+                    if (s0 + x < n_splits) {
+                        const float2 mlx = __builtin_bit_cast(float2, ml[y][x]);
+                        const float2 f = __builtin_bit_cast(float2, v[y][x]);
+                        const float wt = __builtin_amdgcn_exp2f(mlx.x - M[y]);
+                        l[y] += mlx.y * wt;
+                        a0[y] += f.x * wt;
+                        a1[y] += f.y * wt;
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int y = 0; y < kItems; ++y) {
+            const float inv = l[y] > 0.f ? 1.f / l[y] : 0.f;
+            if (idx + y * 64 * NW < n_items)
+                *reinterpret_cast<float2*>(out_rows + (size_t)head[y] * kHeadDim + 2 * d2[y]) = make_float2(a0[y] * inv, a1[y] * inv);
+        }
+    }
+}
+
+// More than a pair a thread (G > NW): two at once.  More than eight splits: up to sixteen (two pairs: twelve) at once.
 template <int NW>
 __device__ __forceinline__ void merge_splits(int G, int n_splits, size_t part0, float* __restrict__ out_rows,
                                              const float* __restrict__ ws_acc, const float* __restrict__ ws_ml)
 {
-    const uint64_t* acc_g = reinterpret_cast<const uint64_t*>(ws_acc);
-    const uint64_t* ml_g = reinterpret_cast<const uint64_t*>(ws_ml);
-    constexpr int kChunk = 8;                          // splits in flight per thread
-    const int n_items = G * (kHeadDim / 2);
-    for (int idx = threadIdx.x; idx < n_items; idx += 64 * NW) {
-        const int head = idx / (kHeadDim / 2), d2 = idx % (kHeadDim / 2);
-        float M = kNegBig, l = 0.f, a0 = 0.f, a1 = 0.f;
-        for (int s0 = 0; s0 < n_splits; s0 += kChunk) {
-            uint64_t v[kChunk], ml[kChunk];
-#pragma unroll
-            for (int x = 0; x < kChunk; ++x) {
-                const size_t pr = (part0 + min(s0 + x, n_splits - 1)) * G + head;
-                ml[x] = observe_u64(ml_g + pr);
-                v[x] = observe_u64(acc_g + pr * (kHeadDim / 2) + d2);
-            }
-            // running maximum over the splits seen so far; what has been summed is rescaled to it
-            float Mc = M;
-#pragma unroll
-            for (int x = 0; x < kChunk; ++x)
-                if (s0 + x < n_splits) Mc = fmaxf(Mc, __builtin_bit_cast(float2, ml[x]).x);
-            const float keep = __builtin_amdgcn_exp2f(M - Mc);
-            l *= keep; a0 *= keep; a1 *= keep;
-            M = Mc;
-#pragma unroll
-            for (int x = 0; x < kChunk; ++x) {
-                if (s0 + x < n_splits) {
-                    const float2 mlx = __builtin_bit_cast(float2, ml[x]);
-                    const float2 f = __builtin_bit_cast(float2, v[x]);
-                    const float wt = __builtin_amdgcn_exp2f(mlx.x - M);
-                    l += mlx.y * wt;
-                    a0 += f.x * wt;
-                    a1 += f.y * wt;
-                }
-            }
-        }
-        const float inv = l > 0.f ? 1.f / l : 0.f;
-        *reinterpret_cast<float2*>(out_rows + (size_t)head * kHeadDim + 2 * d2) = make_float2(a0 * inv, a1 * inv);
+    if (G > NW) {
+        if (n_splits <= 6) merge_splits_by<NW, 2, 6>(G, n_splits, part0, out_rows, ws_acc, ws_ml);
+        else merge_splits_by<NW, 2, 12>(G, n_splits, part0, out_rows, ws_acc, ws_ml);
+    } else {
+        if (n_splits <= 8) merge_splits_by<NW, 1, 8>(G, n_splits, part0, out_rows, ws_acc, ws_ml);
+        else merge_splits_by<NW, 1, 16>(G, n_splits, part0, out_rows, ws_acc, ws_ml);
     }
 }
 

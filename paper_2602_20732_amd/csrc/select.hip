@@ -6,16 +6,18 @@
 namespace chess {
 
 // grid = (C, H_kv, batch); T = storage type of the summaries (float or bf16 bits)
-template <class T>
-__global__ __launch_bounds__(kSelThreads) void select_kernel(const uint16_t* __restrict__ q,
-                                                             const T* __restrict__ pages,
-                                                             const T* __restrict__ chunks,
-                                                             const T* __restrict__ grids,
-                                                             const int32_t* __restrict__ seq_lens, Geom g,
-                                                             SelectParams sp, SelectWs ws,
+template <class T, int kMode>
+__global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(3))) void select_kernel(const uint16_t* __restrict__ q,
+                                                             const void* __restrict__ pages_v,
+                                                             const void* __restrict__ chunks_v,
+                                                             const void* __restrict__ grids_v,
+                                                             const int32_t* __restrict__ seq_lens, Geom g_args,
+                                                             SelectParams sp_args, SelectWs ws,
                                                              int32_t* __restrict__ page_ids,
                                                              int32_t* __restrict__ n_selected)
 {
+    const Geom g = own_regs(g_args);
+    const SelectParams sp = own_regs(sp_args);
     extern __shared__ unsigned long long lds_raw[];
     uint64_t* keys = reinterpret_cast<uint64_t*>(lds_raw);                    // [cap_keys]
     int32_t* kept_grids = reinterpret_cast<int32_t*>(keys + sp.cap_keys);     // [cap_kg]
@@ -24,6 +26,9 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const uint16_t* __r
     __shared__ Shared sh;
 
     const int m = blockIdx.x, C = gridDim.x, h = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
+    const T* pages = static_cast<const T*>(pages_v);
+    const T* chunks = static_cast<const T*>(chunks_v);
+    const T* grids = static_cast<const T*>(grids_v);
     Prof prof;
     prof.mark(0);
     const size_t row = (size_t)b * g.n_kv_heads + h;
@@ -31,9 +36,10 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const uint16_t* __r
     const int B = g.page_size;
     const int L_raw = seq_lens[b];
     const int k_fixed = fixed_budget(sp, g, b);
+    const uint16_t* q_rows = q + ((size_t)b * g.n_q_heads + (size_t)h * g.group) * kHeadDim;
     double pr[8];
-    if (sp.probe == CHESS_PROBE_QUERY)                                // requested before anything waits on the length
-        load_probe<T>(q + ((size_t)b * g.n_q_heads + (size_t)h * g.group) * kHeadDim, g.group, pr);
+    ProbeRows<T> probe;
+    if (sp.probe == CHESS_PROBE_QUERY) probe.request(q_rows, 0, g.group);   // before anything waits on the length
     init_shared(sh, sp.poll_limit);
     const int L = min(max(L_raw, 0), g.max_pages * B);
     const int P = (L + B - 1) / B;
@@ -51,14 +57,15 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const uint16_t* __r
 
     const PubLayout pubs = pub_layout(ws.keys + row * ws.key_stride, g);
     CascadeResult res;
-    const bool ok = cascade<false, T>(pages + row * g.max_pages * kHeadDim, chunks + row * g.max_chunks * kHeadDim,
+    const bool ok = cascade<kMode, false, T>(pages + row * g.max_pages * kHeadDim, chunks + row * g.max_chunks * kHeadDim,
                                       grids + row * g.max_grids * kHeadDim, pr, P, g, sp, pubs, m, C, m == 0, keys,
-                                      kept_grids, kept_chunks, sel_pages, sh, &res, prof, nullptr, [] {}, k_fixed);
+                                      kept_grids, kept_chunks, sel_pages, sh, &res, prof, nullptr, 0,
+                                      [&] { if (sp.probe == CHESS_PROBE_QUERY) probe.sum(q_rows, g.group, pr); }, [] {}, k_fixed);
     if (!ok) {
         if (tid == 0) __hip_atomic_fetch_or(ws.error, kErrWait, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;
     }
-    if (C > 1) {
+    if constexpr (kMode != kSolo) {
         // whoever is last to be done with the published words clears them for the next launch
         if (arrive_last(ws.meta + row * kSelMetaStride, C, &sh.flag)) clear_published(pubs, res);
     }
@@ -86,15 +93,22 @@ size_t select_lds_bytes(const SelectParams& sp, int max_sel)
     return (size_t)sp.cap_keys * 8 + ((size_t)(sp.cap_kg + sp.cap_kc + max_sel) * 4 + 7) / 8 * 8;
 }
 
+using SelectKernel = void (*)(const uint16_t*, const void*, const void*, const void*, const int32_t*, Geom, SelectParams, SelectWs, int32_t*, int32_t*);
+static SelectKernel select_kernel_of(bool bf16, bool solo)
+{
+    if (bf16) return solo ? select_kernel<uint16_t, kSolo> : select_kernel<uint16_t, kCluster>;
+    return solo ? select_kernel<float, kSolo> : select_kernel<float, kCluster>;
+}
+
+// (a cluster of one needs no co-residency: what counts is how many of the clusters' workgroups fit)
 hipError_t select_occupancy(bool bf16, int lds_bytes, int* blocks_per_cu)
 {
-    const void* kern = bf16 ? reinterpret_cast<const void*>(select_kernel<uint16_t>) : reinterpret_cast<const void*>(select_kernel<float>);
-    if (lds_bytes > 48 * 1024) {
-        hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+    for (const bool solo : {true, false}) {
+        if (lds_bytes <= 48 * 1024) break;
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(select_kernel_of(bf16, solo)), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
         if (e != hipSuccess) return e;
     }
-    return bf16 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, select_kernel<uint16_t>, kSelThreads, lds_bytes)
-                : hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, select_kernel<float>, kSelThreads, lds_bytes);
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, select_kernel_of(bf16, false), kSelThreads, lds_bytes);
 }
 
 hipError_t launch_select(chess_ctx* ctx, const uint16_t* q, const void* pages, const void* chunks,
@@ -102,14 +116,8 @@ hipError_t launch_select(chess_ctx* ctx, const uint16_t* q, const void* pages, c
                          const SelectWs& ws, size_t lds_bytes, int32_t* page_ids, int32_t* n_selected,
                          hipStream_t stream)
 {
-    const dim3 grid(cluster, ctx->geom.n_kv_heads, batch), block(kSelThreads);
-    if (ctx->cfg.summary_dtype == CHESS_SUMMARY_BF16)
-        return launch(select_kernel<uint16_t>, grid, block, lds_bytes, stream, q, static_cast<const uint16_t*>(pages),
-                      static_cast<const uint16_t*>(chunks), static_cast<const uint16_t*>(grids), seq_lens, ctx->geom, sp, ws,
-                      page_ids, n_selected);
-    return launch(select_kernel<float>, grid, block, lds_bytes, stream, q, static_cast<const float*>(pages),
-                  static_cast<const float*>(chunks), static_cast<const float*>(grids), seq_lens, ctx->geom, sp, ws, page_ids,
-                  n_selected);
+    return launch(select_kernel_of(ctx->cfg.summary_dtype == CHESS_SUMMARY_BF16, cluster == 1), dim3(cluster, ctx->geom.n_kv_heads, batch),
+                  dim3(kSelThreads), lds_bytes, stream, q, pages, chunks, grids, seq_lens, ctx->geom, sp, ws, page_ids, n_selected);
 }
 
 }  // namespace chess

@@ -8,15 +8,18 @@
 // two 128-bit loads per lane, several units in flight per group, fp64 multiply-add, DPP row sum) and publishes an
 // order-preserving 64-bit key into the unit's word of the workspace.
 //
-// Two schedules, chosen by the host:
+// Three schedules, chosen by the host (choose_schedule in api.hip has the rule and its measurements):
 //   lazy    grids; then the chunks of kept grids; then the pages of kept chunks: three dependent memory phases,
 //           the fewest bytes (what a bandwidth-bound launch wants);
 //   merged  grids and ALL chunks in one phase, two cuts back to back, then the pages of kept chunks: two memory
 //           phases and one exchange fewer for n_c - k_g N_g more chunk vectors (what a latency-bound launch
-//           wants).  The scores are the same numbers either way, so the kept sets are too.
+//           wants);
+//   eager   grids, all chunks and all pages in one phase, the only one: a member that is needed for nothing else leaves
+//           after it, so far more members can share the scoring than the cuts and the attention would bear.
+// The scores are the same numbers whichever it is, so the kept sets are too.
 // Grid and chunk keys live in unit order (word / LDS slot = unit index, chunks behind the grids; a chunk competes
 // only if its grid was kept: the grid cut leaves a zero in the key slot of every grid it drops); page keys live in
-// slot order (N_c slots per kept chunk).
+// slot order (N_c slots per kept chunk), or by page where they are published before the kept chunks are known (eager).
 //
 // There is no barrier between the members: a key word is 0 until its owner has published it (a slot without a unit
 // is published as 1), so a member polls the words it needs until none is 0.  One memory round trip serves as
@@ -71,9 +74,10 @@ __device__ __forceinline__ int opaque_tid()
     return t;
 }
 
-// x / fan without a division: inv = ceil(2^32 / fan), computed by the host (unused for fan = 1); exact for x < 2^24 and fan <= 256 (the
-// error term x * e / 2^32 with e = fan * inv - 2^32 < fan stays below 1 / fan)
-__device__ __forceinline__ int div_by(int x, int fan, uint32_t inv) { return fan > 1 ? (int)__umulhi((unsigned)x, inv) : x; }
+// x / fan without a division or a branch: inv = ceil(2^31 / fan), computed by the host; exact for 0 <= x < 2^31 / 255 (more
+// than 2^23 + 256) and fan <= 256: 2 x inv / 2^32 exceeds x / fan by x e / (2^31 fan) with e = fan inv - 2^31 < fan, which stays
+// below 1 / fan.
+__device__ __forceinline__ int div_by(int x, uint32_t inv) { return (int)__umulhi((unsigned)x << 1, inv); }
 
 // Inclusive scan over the 64 lanes of a wave with DPP row shifts and row broadcasts (no LDS).
 // Every lane of the wave must be active.
@@ -102,19 +106,6 @@ __device__ __forceinline__ double row16_sum(double d)
     CHESS_RS_STEP(0x111) CHESS_RS_STEP(0x112) CHESS_RS_STEP(0x114) CHESS_RS_STEP(0x118)
 #undef CHESS_RS_STEP
     return d;
-}
-
-// Lane i of each row of 16 receives lane i + n of the row (n constant after unrolling; n = 0: the value itself).
-__device__ __forceinline__ unsigned row_shl_by(unsigned v, int n)
-{
-#define CHESS_SHL_CASE(k) case k: return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x100 + k, 0xf, 0xf, false);
-    switch (n) {
-        CHESS_SHL_CASE(1) CHESS_SHL_CASE(2) CHESS_SHL_CASE(3) CHESS_SHL_CASE(4) CHESS_SHL_CASE(5) CHESS_SHL_CASE(6) CHESS_SHL_CASE(7)
-        CHESS_SHL_CASE(8) CHESS_SHL_CASE(9) CHESS_SHL_CASE(10) CHESS_SHL_CASE(11) CHESS_SHL_CASE(12) CHESS_SHL_CASE(13)
-        CHESS_SHL_CASE(14) CHESS_SHL_CASE(15)
-    default: return v;
-    }
-#undef CHESS_SHL_CASE
 }
 
 __device__ __forceinline__ uint64_t lane_read64(uint64_t v, int src)
@@ -297,9 +288,8 @@ struct KeepRule {
 // competes only if the grid cut left its grid's key in place).
 struct ActiveRule {
     const uint64_t* mask;   // LDS, or null: every slot
-    int fan;
-    uint32_t inv;
-    __device__ __forceinline__ bool operator()(int i) const { return mask == nullptr || mask[div_by(i, fan, inv)] != 0ull; }
+    uint32_t inv;           // of fan (div_by)
+    __device__ __forceinline__ bool operator()(int i) const { return mask == nullptr || mask[div_by(i, inv)] != 0ull; }
 };
 
 // Where a kept slot goes, as data: out[pos] = the slot's unit (the slot itself, or parents[slot / fan] * fan +
@@ -315,7 +305,7 @@ struct EmitRule {
     {
         int unit = slot;
         if (parents != nullptr) {
-            const int pi = div_by(slot, fan, inv);
+            const int pi = div_by(slot, inv);
             unit = parents[pi] * fan + (slot - pi * fan);
         }
         out[pos] = unit;
@@ -688,7 +678,7 @@ __device__ __forceinline__ int cut_in_each_wave(uint64_t* keys, int n_slots, con
     if (active.mask != nullptr) {                     // uniform
         uint64_t on[R];
 #pragma unroll
-        for (int x = 0; x < R; ++x) on[x] = active.mask[div_by(min(x * kWave + lane, n_slots - 1), active.fan, active.inv)];
+        for (int x = 0; x < R; ++x) on[x] = active.mask[div_by(min(x * kWave + lane, n_slots - 1), active.inv)];
 #pragma unroll
         for (int x = 0; x < R; ++x) key[x] = on[x] != 0ull ? key[x] : 0ull;
     }
@@ -778,7 +768,7 @@ __device__ __forceinline__ int cut_one_lane_each(uint64_t* keys, int n_slots, co
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     uint64_t key = keys[min(lane, n_slots - 1)];
     if (active.mask != nullptr) {                     // uniform
-        const uint64_t on = active.mask[div_by(min(lane, n_slots - 1), active.fan, active.inv)];
+        const uint64_t on = active.mask[div_by(min(lane, n_slots - 1), active.inv)];
         key = on != 0ull ? key : 0ull;
     }
     key = lane < n_slots ? key : 0ull;
@@ -843,65 +833,105 @@ __device__ __forceinline__ int cut_level(uint64_t* keys, int n_slots, const Acti
     return n;
 }
 
-// One work slot of a scoring pass: where the unit's vector is (array 0 = grids, 1 = chunks, 2 = pages; unit -1 =
-// the slot has no unit) and where its key goes (index into the level's key words, in LDS or in the workspace; -1 =
-// nowhere).
+// One work slot of a scoring pass: which unit it is (array 0 = grids, 1 = chunks, 2 = pages; unit -1 = the slot has no
+// unit), where that unit's vector is (vec: vectors from the row's first page vector; a vector that exists where the slot has
+// no unit) and where its key goes (index into the level's key words, in LDS or in the workspace; -1 = nowhere).
 struct SlotRef {
-    int array, unit, dest;
+    int array, unit, vec, dest;
 };
 
 // Units a 16-lane group requests before it waits: one memory round trip covers kFly * 16 work slots of a workgroup.
 template <class T>
-constexpr int kFlyOf = sizeof(T) == 2 ? 12 : 9;      // (what the fused step's register budget holds without spilling)
+constexpr int kFlyOf = sizeof(T) == 2 ? 16 : 8;      // (64 registers either way)
+
+// One level of the sums over a group's 16 lanes, for two vectors at once: lanes whose bit (1 << kBit) is clear end with
+// a summed over the pair of lanes, the others with b.  Over the four levels each lane ends with the total of another
+// vector, in the order of row16_sum ((adjacent lanes), then pairs, quads, halves: the same bits), for one addition per
+// pair of vectors and level instead of one per vector and level.
+template <int kBit>
+__device__ __forceinline__ double fold_lanes(double a, double b, int ln)
+{
+    const bool up = (ln >> kBit) & 1;
+    const uint64_t ab = (uint64_t)__double_as_longlong(a), bb = (uint64_t)__double_as_longlong(b);
+    const uint64_t keep = up ? bb : ab, send = up ? ab : bb;
+    const int s_lo = (int)(unsigned)send, s_hi = (int)(unsigned)(send >> 32);
+    int r_lo, r_hi;
+    if constexpr (kBit == 2) {                       // lane ^ 4: banks of four lanes, up and down
+        r_lo = __builtin_amdgcn_update_dpp(0, s_lo, 0x104, 0xf, 0x5, false);
+        r_hi = __builtin_amdgcn_update_dpp(0, s_hi, 0x104, 0xf, 0x5, false);
+        r_lo = __builtin_amdgcn_update_dpp(r_lo, s_lo, 0x114, 0xf, 0xa, false);
+        r_hi = __builtin_amdgcn_update_dpp(r_hi, s_hi, 0x114, 0xf, 0xa, false);
+    } else {                                         // lane ^ 1, lane ^ 2: quad_perm; lane ^ 8: row_ror:8
+        constexpr int ctrl = kBit == 0 ? 0xB1 : kBit == 1 ? 0x4E : 0x128;
+        r_lo = __builtin_amdgcn_update_dpp(0, s_lo, ctrl, 0xf, 0xf, true);
+        r_hi = __builtin_amdgcn_update_dpp(0, s_hi, ctrl, 0xf, 0xf, true);
+    }
+    return __longlong_as_double((long long)keep) + __longlong_as_double((long long)(((uint64_t)(unsigned)r_hi << 32) | (unsigned)r_lo));
+}
+
+// Eq. 4 for four units at once (the products of dot8, its order of additions): four chains of dependent fp64
+// operations side by side, then the first two levels of their sums.  Lane i ends with vector i % 4.
+template <class T>
+__device__ __forceinline__ double dot8_quad(const double (&pr)[8], const Vec<T>* v, int ln)
+{
+    double d[4] = {0.0, 0.0, 0.0, 0.0};
+#define CHESS_DQ(i)                                                                                    \
+    d[0] = fma(pr[i], v[0].template at<i>(), d[0]); d[1] = fma(pr[i], v[1].template at<i>(), d[1]);    \
+    d[2] = fma(pr[i], v[2].template at<i>(), d[2]); d[3] = fma(pr[i], v[3].template at<i>(), d[3]);
+    CHESS_DQ(0) CHESS_DQ(1) CHESS_DQ(2) CHESS_DQ(3) CHESS_DQ(4) CHESS_DQ(5) CHESS_DQ(6) CHESS_DQ(7)
+#undef CHESS_DQ
+    return fold_lanes<1>(fold_lanes<0>(d[0], d[1], ln), fold_lanes<0>(d[2], d[3], ln), ln);
+}
 
 // Scores of the work slots [lo, hi).  `target(slot)` says which unit a slot is.  The key of a slot goes to
 // lds_keys[dest] (0 for no unit) when the level is local, else it is published in pub[dest].  (Two pointers of
 // known address space: one generic pointer for both would turn every access into a flat one.)
-template <class T, class Target>
-__device__ __forceinline__ void score_rows(const T* __restrict__ grids_row, const T* __restrict__ chunks_row,
-                                           const T* __restrict__ pages_row, int lo, int hi, Target target,
-                                           const double (&pr)[8], bool local, uint64_t* lds_keys, uint64_t* pub)
+// requested() is called once the first vectors are on their way (at once when there is nothing to score).
+// Bound: a memory round trip, then the instructions of the sums.  Four vectors' chains side by side and folded sums take a
+// quarter of the instructions of one vector after another with a DPP sum each (32 sequences of 16-32K, 8 layers: 283 ->
+// 268 us together with the reordered requests and the code split by cluster mode).
+template <class T, class Target, class Requested>
+__device__ __forceinline__ void score_rows(const T* __restrict__ pages_row, int lo, int hi, Target target,
+                                           const double (&pr)[8], bool local, uint64_t* lds_keys, uint64_t* pub,
+                                           Requested requested)
 {
     constexpr int kFly = kFlyOf<T>;
     const int tid = opaque_tid(), g16 = tid >> 4, ln = tid & 15;
-    for (int s0 = lo; s0 < hi; s0 += kSelGroups * kFly) {
-        int unit[kFly], dest[kFly];
-        Vec<T> v[kFly];
+    Vec<T> v[kFly];
+    auto ask = [&](int s0) {
 #pragma unroll
         for (int x = 0; x < kFly; ++x) {
-            unit[x] = -1;
-            dest[x] = -1;
-            const int slot = s0 + kSelGroups * x + g16;
-            const SlotRef ref = target(min(slot, hi - 1));
-            unit[x] = slot < hi ? ref.unit : -1;
-            dest[x] = slot < hi ? ref.dest : -1;
-            // no condition on the load, per lane or per row of slots (unit 0 when the slot has no unit; rows the share
+            // no condition on the load, per lane or per row of slots (some vector when the slot has no unit; rows the share
             // does not have repeat its last slot): a per-lane condition would make the compiler wait for each vector
             // before asking for the next, and a branch per row costs more than the repeated, cache-resident loads
-            const T* base = ref.array == 0 ? grids_row : ref.array == 1 ? chunks_row : pages_row;
-            v[x].load(base + (size_t)max(ref.unit, 0) * kHeadDim, ln);
+            v[x].load(pages_row + (int64_t)target(min(s0 + kSelGroups * x + g16, hi - 1)).vec * kHeadDim, ln);
         }
-        // The total of vector x ends up in lane 15 of its group; it is handed to lane x of the group, so that one key
-        // conversion and one store serve all the vectors of the trip (instead of one masked branch, conversion and
-        // store per vector).
-        static_assert(kFly <= 16, "a lane of the group per vector of a trip");
-        double mine = 0.0;
-        int my_unit = -1, my_dest = -1;
+    };
+    if (lo < hi) ask(lo);
+    // (outside the loop: what it uses need not stay in registers for a second trip)
+    requested();
+    for (int s0 = lo; s0 < hi; s0 += kSelGroups * kFly) {
+        if (s0 != lo) ask(s0);
+        // lane x of a group ends with the total of vector x (float: lanes x and x + 8)
+        double q[kFly / 4];
+        q[0] = dot8_quad<T>(pr, v, ln);
 #pragma unroll
-        for (int x = 0; x < kFly; ++x) {
-            if (s0 + kSelGroups * x >= hi) break;     // uniform over the workgroup
-            const double d = row16_sum(dot8<T>(pr, v[x]));
-            const uint64_t b = (uint64_t)__double_as_longlong(d);
-            const unsigned lo = row_shl_by((unsigned)b, 15 - x), hi32 = row_shl_by((unsigned)(b >> 32), 15 - x);
-            if (ln == x) {
-                mine = __longlong_as_double((long long)(((uint64_t)hi32 << 32) | lo));
-                my_unit = unit[x];
-                my_dest = dest[x];
-            }
+        for (int y = 1; y < kFly / 4; ++y) {
+            q[y] = 0.0;
+            if (s0 + kSelGroups * 4 * y < hi) q[y] = dot8_quad<T>(pr, v + 4 * y, ln);      // uniform over the workgroup
         }
-        if (my_dest >= 0) {
-            if (local) lds_keys[my_dest] = my_unit >= 0 ? order_key(mine) : 0ull;
-            else publish_u64(pub + my_dest, my_unit >= 0 ? order_key(mine) : kAbsentKey);
+        double mine = fold_lanes<2>(q[0], q[1], ln);
+        if constexpr (kFly == 16) mine = fold_lanes<3>(mine, fold_lanes<2>(q[2], q[3], ln), ln);
+        else mine = fold_lanes<3>(mine, mine, ln);
+        // one key conversion and one store serve all the vectors of the trip
+        const int slot = s0 + kSelGroups * (ln & (kFly - 1)) + g16;
+        if (slot < hi && ln < kFly) {
+            const SlotRef ref = target(slot);
+            const uint64_t key = order_key(mine);
+            if (ref.dest >= 0) {
+                if (local) lds_keys[ref.dest] = ref.unit >= 0 ? key : 0ull;
+                else publish_u64(pub + ref.dest, ref.unit >= 0 ? key : kAbsentKey);
+            }
         }
     }
 }
@@ -917,33 +947,31 @@ __device__ __forceinline__ uint64_t poll_word(const uint64_t* word, int limit)
     return 0ull;
 }
 
-// The published keys a level needs, into the LDS copy the cuts work on: item j of n lands in keys[dest_of(j)] (dest
-// -1: the item is skipped) and comes from pub[dest], except that dest ov_dest0 / ov_dest1 (if >= 0) come from
-// tail[ov_word0] / tail[ov_word1]: the keys of units the decode step has just refreshed, which one workgroup
-// publishes in words of their own.  The words are polled, up to eight per thread in flight, until every one of them
-// is there.  Ends with a workgroup barrier; returns false (to every thread) if a word did not arrive within the
-// poll limit.
-template <class DestOf>
-__device__ __forceinline__ bool pull_keys(const uint64_t* pub, const uint64_t* tail, int n, DestOf dest_of, int ov_dest0,
+// The published keys a level needs, into the LDS copy the cuts work on: item j of n lands in keys[j] and comes from
+// pub[word_of(j)] (-1: a slot without a unit whose word nobody publishes; its key is 0), except that items ov_dest0 /
+// ov_dest1 (if >= 0) come from tail[ov_word0] / tail[ov_word1]: the keys of units the decode step has just refreshed,
+// which one workgroup publishes in words of their own.  The words are polled, kPer per thread in flight, until every
+// one of them is there.  Ends with a workgroup barrier; returns false (to every thread) if a word did not arrive
+// within the poll limit.
+template <int kPer, class WordOf>
+__device__ __forceinline__ bool pull_keys(const uint64_t* pub, const uint64_t* tail, int n, WordOf word_of, int ov_dest0,
                                           int ov_word0, int ov_dest1, int ov_word1, uint64_t* keys, int limit)
 {
     bool ok = true;
     const int tid = opaque_tid();
-    constexpr int kPer = 8;                           // words a thread keeps in flight: one round for levels of up to 2048 slots
+    const int64_t tail_at = tail - pub;               // (one base: a choice between pointers becomes a flat access)
     for (int j0 = 0; j0 < n; j0 += kPer * kSelThreads) {
         uint64_t v[kPer];
-        int dest[kPer];
         const uint64_t* word[kPer];
+        bool none[kPer];
         // (no branch around items beyond n: they repeat the last word, which costs a few coalesced requests; a branch per
         // item costs more)
 #pragma unroll
         for (int x = 0; x < kPer; ++x) {
-            const int j = j0 + x * kSelThreads + tid;
-            const int d = dest_of(min(j, n - 1));
-            dest[x] = j < n ? d : -1;
-            word[x] = pub + max(d, 0);
-            if (d >= 0 && d == ov_dest0) word[x] = tail + ov_word0;
-            if (d >= 0 && d == ov_dest1) word[x] = tail + ov_word1;
+            const int d = min(j0 + x * kSelThreads + tid, n - 1), own = word_of(d);
+            const bool t0 = d == ov_dest0, t1 = d == ov_dest1;
+            none[x] = own < 0 && !t0 && !t1;
+            word[x] = pub + (t0 ? tail_at + ov_word0 : t1 ? tail_at + ov_word1 : (int64_t)max(own, 0));
         }
         int polls = 0;
         if (limit <= 0) { ok = false; break; }        // (a test asked for every wait to fail)
@@ -952,14 +980,16 @@ __device__ __forceinline__ bool pull_keys(const uint64_t* pub, const uint64_t* t
 #pragma unroll
             for (int x = 0; x < kPer; ++x) v[x] = observe_u64(word[x]);       // unconditional: all stay in flight
 #pragma unroll
-            for (int x = 0; x < kPer; ++x) missing = missing || (dest[x] >= 0 && v[x] == 0ull);
+            for (int x = 0; x < kPer; ++x) missing = missing || (!none[x] && v[x] == 0ull);
             if (__ballot(missing) == 0ull) break;
             if (++polls >= limit) { ok = false; break; }
             __builtin_amdgcn_s_sleep(2);
         }
 #pragma unroll
-        for (int x = 0; x < kPer; ++x)
-            if (dest[x] >= 0) keys[dest[x]] = v[x] == kAbsentKey ? 0ull : v[x];
+        for (int x = 0; x < kPer; ++x) {
+            const int j = j0 + x * kSelThreads + tid;
+            if (j < n) keys[j] = (none[x] || v[x] == kAbsentKey) ? 0ull : v[x];
+        }
     }
     return __syncthreads_and(ok) != 0;
 }
@@ -968,23 +998,23 @@ __device__ __forceinline__ bool pull_keys(const uint64_t* pub, const uint64_t* t
 // words t, t + 256, t + 512, t + 768 and KEEPS them in key[0..3] (0 = empty or beyond n) for the cut that follows,
 // and every wave leaves the bounds (upper key halves) and the count of what it saw in sh.st_* before the closing
 // barrier, so that cut_in_registers can start at once.
-__device__ __forceinline__ bool pull_keys_regs(const uint64_t* pub, const uint64_t* tail, int n, int ov_dest0, int ov_word0,
-                                               int ov_dest1, int ov_word1, uint64_t* keys, uint64_t (&key)[4], int limit, Shared& sh)
+template <class WordOf>
+__device__ __forceinline__ bool pull_keys_regs(const uint64_t* pub, const uint64_t* tail, int n, WordOf word_of, int ov_dest0,
+                                               int ov_word0, int ov_dest1, int ov_word1, uint64_t* keys, uint64_t (&key)[4],
+                                               int limit, Shared& sh)
 {
     bool ok = limit > 0;
     const int tid = opaque_tid(), lane = tid & 63, wave = tid >> 6;
     const uint64_t* word[4];
+    bool none[4];
+    const int64_t tail_at = tail - pub;
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
         key[x] = 0ull;
-        word[x] = pub;
-        {
-            const int j = x * kSelThreads + tid;
-            const int d = min(j, n - 1);
-            word[x] = pub + d;
-            if (d == ov_dest0) word[x] = tail + ov_word0;
-            if (d == ov_dest1) word[x] = tail + ov_word1;
-        }
+        const int d = min(x * kSelThreads + tid, n - 1), own = word_of(d);
+        const bool t0 = d == ov_dest0, t1 = d == ov_dest1;
+        none[x] = own < 0 && !t0 && !t1;
+        word[x] = pub + (t0 ? tail_at + ov_word0 : t1 ? tail_at + ov_word1 : (int64_t)max(own, 0));
     }
     int polls = 0;
     while (ok) {
@@ -994,7 +1024,7 @@ __device__ __forceinline__ bool pull_keys_regs(const uint64_t* pub, const uint64
             key[x] = observe_u64(word[x]);                    // unconditional (a word beyond n repeats the last one): all stay in flight
         }
 #pragma unroll
-        for (int x = 0; x < 4; ++x) missing = missing || key[x] == 0ull;
+        for (int x = 0; x < 4; ++x) missing = missing || (!none[x] && key[x] == 0ull);
         if (__ballot(missing) == 0ull) break;
         if (++polls >= limit) { ok = false; break; }
         __builtin_amdgcn_s_sleep(2);
@@ -1004,7 +1034,7 @@ __device__ __forceinline__ bool pull_keys_regs(const uint64_t* pub, const uint64
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
         const int j = x * kSelThreads + tid;
-        if (j >= n || key[x] == kAbsentKey || !ok) key[x] = 0ull;
+        if (j >= n || none[x] || key[x] == kAbsentKey || !ok) key[x] = 0ull;
         if (j < n) keys[j] = key[x];
         const bool valid = key[x] != 0ull;
         const unsigned hi = (unsigned)(key[x] >> 32);
@@ -1019,54 +1049,67 @@ __device__ __forceinline__ bool pull_keys_regs(const uint64_t* pub, const uint64
 }
 
 // The probe of a (sequence, KV head): the sum of the group's query rows in fp64, g ascending (Eq. 4 with
-// Eq. 1's Flatten restricted to the group); this lane's dims as Vec<T> arranges them.
+// Eq. 1's Flatten restricted to the group); this lane's dims as Vec<T> arranges them.  In two steps, so that what a
+// kernel asks for in between (the first vectors to score) does not wait for the rows: request, then sum.  The first four
+// rows are requested, which is all of the usual groups; sum asks for the others four at a time (all eight at once, the
+// select kernel took 246 registers instead of 168).
 template <class T>
-__device__ __forceinline__ void load_probe(const uint16_t* __restrict__ q_rows, int group, double (&pr)[8])
-{
-    const int ln = threadIdx.x & 15;
+struct ProbeRows {
+    uint2 a[4], c[4];
+    __device__ __forceinline__ void request(const uint16_t* __restrict__ q_rows, int r0, int group)
+    {
+        const int ln = threadIdx.x & 15;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) pr[i] = 0.0;
-    // four rows per request (a row beyond the group repeats the last one and is not added): the usual groups of up
-    // to four query heads cost one memory round trip, not one per row
-    for (int r0 = 0; r0 < group; r0 += 4) {
-        uint2 a[4], c[4];
-#pragma unroll
-        for (int x = 0; x < 4; ++x) {
+        for (int x = 0; x < 4; ++x) {                 // (a row beyond the group repeats the last one and is not added)
             const uint16_t* row = q_rows + (size_t)min(r0 + x, group - 1) * kHeadDim;
             a[x] = *reinterpret_cast<const uint2*>(row + Vec<T>::lane_dim(ln, 0));
             c[x] = *reinterpret_cast<const uint2*>(row + Vec<T>::lane_dim(ln, 4));
         }
+    }
+    __device__ __forceinline__ void sum(const uint16_t* __restrict__ q_rows, int group, double (&pr)[8])
+    {
 #pragma unroll
-        for (int x = 0; x < 4; ++x) {
-            if (r0 + x < group) {
-                pr[0] += (double)__uint_as_float(a[x].x << 16); pr[1] += (double)__uint_as_float(a[x].x & 0xffff0000u);
-                pr[2] += (double)__uint_as_float(a[x].y << 16); pr[3] += (double)__uint_as_float(a[x].y & 0xffff0000u);
-                pr[4] += (double)__uint_as_float(c[x].x << 16); pr[5] += (double)__uint_as_float(c[x].x & 0xffff0000u);
-                pr[6] += (double)__uint_as_float(c[x].y << 16); pr[7] += (double)__uint_as_float(c[x].y & 0xffff0000u);
+        for (int i = 0; i < 8; ++i) pr[i] = 0.0;
+        for (int r0 = 0;;) {
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                if (r0 + x < group) {
+                    pr[0] += (double)__uint_as_float(a[x].x << 16); pr[1] += (double)__uint_as_float(a[x].x & 0xffff0000u);
+                    pr[2] += (double)__uint_as_float(a[x].y << 16); pr[3] += (double)__uint_as_float(a[x].y & 0xffff0000u);
+                    pr[4] += (double)__uint_as_float(c[x].x << 16); pr[5] += (double)__uint_as_float(c[x].x & 0xffff0000u);
+                    pr[6] += (double)__uint_as_float(c[x].y << 16); pr[7] += (double)__uint_as_float(c[x].y & 0xffff0000u);
+                }
             }
+            r0 += 4;
+            if (r0 >= group) break;
+            request(q_rows, r0, group);
         }
     }
-}
+};
 
 // Which unit a work slot of each phase is, as small structs whose operator() compiles to straight-line code (the
 // scoring loop asks once per vector; a single generic version full of per-level branches cost more instructions
 // than the scoring itself).
+struct VecBases { int grids, chunks; };   // the row's first grid / chunk vector, in vectors from its first page vector
 struct GridPhaseTarget {            // level 0: grids [0, n_g), then (merged) all chunks [n_g, n_g + n_c); keys by unit
     int ng;
+    VecBases at;
     __device__ __forceinline__ SlotRef operator()(int slot) const
     {
-        return SlotRef{slot < ng ? 0 : 1, slot < ng ? slot : slot - ng, slot};
+        const bool grid = slot < ng;
+        return SlotRef{grid ? 0 : 1, grid ? slot : slot - ng, slot + (grid ? at.grids : at.chunks - ng), slot};
     }
 };
 struct ChunkPhaseTarget {           // level 1 (lazy): N_g slots per kept grid; chunk keys by slot, behind the grid keys
     const int32_t* parents;
     int fan, ng, nc;
     uint32_t inv;
+    VecBases at;
     __device__ __forceinline__ SlotRef operator()(int slot) const
     {
-        const int pi = div_by(slot, fan, inv);
+        const int pi = div_by(slot, inv);
         const int u = parents[pi] * fan + (slot - pi * fan);
-        return SlotRef{1, u < nc ? u : -1, ng + slot};
+        return SlotRef{1, u < nc ? u : -1, at.chunks + min(u, nc - 1), ng + slot};
     }
 };
 struct PagePhaseTarget {            // level 2: N_c slots per kept chunk; sink and window pages have no unit; keys by slot
@@ -1075,10 +1118,26 @@ struct PagePhaseTarget {            // level 2: N_c slots per kept chunk; sink a
     uint32_t inv;
     __device__ __forceinline__ SlotRef operator()(int slot) const
     {
-        const int pi = div_by(slot, fan, inv);
+        const int pi = div_by(slot, inv);
         const int u = parents[pi] * fan + (slot - pi * fan);
-        return SlotRef{2, (u >= u_lo && u < u_hi) ? u : -1, slot};
+        const int unit = (u >= u_lo && u < u_hi) ? u : -1;
+        return SlotRef{2, unit, max(unit, 0), slot};
     }
+};
+struct AllTarget {                  // the eager schedule's only phase: grids, chunks, candidate pages [first_page, ...); keys by unit
+    int ng, ngc, first_page, page_words;   // page_words: where the page words start, counted from the grid words
+    VecBases at;
+    __device__ __forceinline__ SlotRef operator()(int slot) const
+    {
+        const bool grid = slot < ng, page = slot >= ngc;
+        const int by = page ? first_page - ngc : grid ? 0 : -ng, unit = slot + by;
+        return SlotRef{page ? 2 : grid ? 0 : 1, unit, unit + (page ? 0 : grid ? at.grids : at.chunks), page ? page_words + unit : slot};
+    }
+};
+struct PageWords {                  // which word has the key of item j of a pull
+    PagePhaseTarget slots;
+    bool by_page;
+    __device__ __forceinline__ int operator()(int j) const { return by_page ? slots(j).unit : j; }
 };
 
 struct CascadeResult {
@@ -1090,7 +1149,7 @@ struct CascadeResult {
 // Where the published words of one (sequence, KV head) -- one sequence under the model-wide scope -- start.
 struct PubLayout {
     uint64_t* units;       // grid keys [0, n_g); behind them the chunk keys: by unit (merged) or N_g slots per kept grid (lazy)
-    uint64_t* pages;       // page slots: N_c per kept chunk
+    uint64_t* pages;       // page slots: N_c per kept chunk; by page under the eager schedule
 };
 __device__ __forceinline__ PubLayout pub_layout(uint64_t* row_words, const Geom& g)
 {
@@ -1102,7 +1161,8 @@ __device__ __forceinline__ PubLayout pub_layout(uint64_t* row_words, const Geom&
 
 // The three levels for one (sequence, KV head) with P > sink + window pages.  Member m of C scores the m-th
 // part of every phase.  With want_l3 every member ends up with the kept page numbers in sel_pages[0 .. n_kp);
-// without it a member returns as soon as its page keys are published (n_kp = 0).  sh as init_shared leaves it.
+// without it a member returns as soon as its page keys are published (n_kp = 0; eager: after the first phase, having
+// waited for nobody).  sh as init_shared leaves it.
 // Returns false if a wait was given up.  k_fixed > 0: the page budget of this sequence (fixed_budget); 0: derived
 // from its page count.
 // The cuts run through one copy of their code (a loop over the levels with the per-level parameters as data, not
@@ -1116,34 +1176,42 @@ __device__ __forceinline__ PubLayout pub_layout(uint64_t* row_words, const Geom&
 // one word per slot); sel_phys[i] then receives the physical page of sel_pages[i].
 //
 // tail_words non-null: the decode step refreshes the summaries of the tail page, its chunk and its grid in this
-// launch.  `refresh_tail()` is called in member 0 once its first vectors are requested; it leaves the three
+// launch.  `refresh_tail()` is called in member `refresher` once its share of the first phase is scored; it leaves the three
 // units' keys in tail_words[0..2] (grid, chunk, page) for the cluster and in sh.tail_key for itself.  Wherever one
 // of these units competes, its key is taken from there instead of the unit's own word (whatever was scored for it
 // from the old vector is ignored).
 //
-// How a phase's work slots are scored is the Scorer's business: scorer(lo, hi, target, local, keys, pub) leaves the
-// keys of the work slots [lo, hi) in keys[dest] (local) or publishes them in pub[dest]; a member's share of a
-// phase is a multiple of Scorer::kShareRound slots.
-template <bool kPhys, class Scorer, class TailFn>
+// How a phase's work slots are scored is the Scorer's business: scorer(lo, hi, target, local, keys, pub, requested)
+// leaves the keys of the work slots [lo, hi) in keys[dest] (local) or publishes them in pub[dest]; a member's share of
+// a phase is a multiple of Scorer::kShareRound slots.
+//
+// requested(): called once, by every thread, when the first phase's vectors are on their way and before any of them is
+// used: what needs values that were requested earlier (the probe) or asks for more (the rows of the tail units) goes
+// there and costs no round trip of its own.
+//
+// kMode: kSolo = a cluster of one, nothing is exchanged; kEagerCluster = the eager schedule; kCluster = the others.  (Each kernel
+// has the code of one only: what the other modes keep in scalar registers does not fit beside it.)
+template <int kMode, bool kPhys, class Scorer, class ReqFn, class TailFn>
 __device__ __forceinline__ bool cascade_with(const Scorer& scorer, int P, const Geom& g,
                                         const SelectParams& sp, const PubLayout& pubs, int m, int C, bool want_l3,
                                         uint64_t* keys, int32_t* kept_grids, int32_t* kept_chunks, int32_t* sel_pages,
                                         Shared& sh, CascadeResult* res, Prof& prof, const uint64_t* tail_words,
-                                        TailFn refresh_tail, int k_fixed, const int32_t* __restrict__ bt_row = nullptr,
+                                        int refresher, ReqFn requested, TailFn refresh_tail, int k_fixed,
+                                        const int32_t* __restrict__ bt_row = nullptr,
                                         int32_t* phys_by_slot = nullptr, int32_t* sel_phys = nullptr)
 {
     const int s = sp.sink, w = sp.window;
-    const uint32_t inv_ng = g.inv_ng, inv_nc = g.inv_nc;                 // (divisions by N_c / N_g: multiply-high, exact below 2^24)
-    const int nc = div_by(P + g.n_c - 1, g.n_c, inv_nc), ng = div_by(nc + g.n_g - 1, g.n_g, inv_ng);
+    const uint32_t inv_ng = g.inv_ng, inv_nc = g.inv_nc;                 // (divisions by N_c / N_g: a multiply-high)
+    const int nc = div_by(P + g.n_c - 1, inv_nc), ng = div_by(nc + g.n_g - 1, inv_ng);
     const int k_budget = k_fixed > 0 ? k_fixed : clamp_i(ceil_bp(P, sp.budget_bp), 1, P);
-    const int kc_target = div_by(min(sp.over_chunk * k_budget, 1 << 23) + g.n_c - 1, g.n_c, inv_nc);
+    const int kc_target = div_by(min(sp.over_chunk * k_budget, 1 << 23) + g.n_c - 1, inv_nc);
     const bool ratio = sp.plan == CHESS_PLAN_RATIO, flat = sp.plan == CHESS_PLAN_FLAT;
     const bool general = sp.general_cut != 0, keep_ties = sp.keep_ties != 0;
     res->n_kp = 0; res->n_a = 0; res->n_p = 0; res->overflow = false;
 
     // how many units a level keeps (built where they are used: three of them alive across the loop cost registers)
     auto rule_of = [&](int level) {
-        if (level == 0) return KeepRule{ratio ? sp.rho_g_bp : 0, flat ? kKeepAll : div_by(min(sp.over_grid * kc_target, 1 << 23) + g.n_g - 1, g.n_g, inv_ng), sp.cap_kg};
+        if (level == 0) return KeepRule{ratio ? sp.rho_g_bp : 0, flat ? kKeepAll : div_by(min(sp.over_grid * kc_target, 1 << 23) + g.n_g - 1, inv_ng), sp.cap_kg};
         if (level == 1) return KeepRule{ratio ? sp.rho_c_bp : 0, flat ? kKeepAll : kc_target, sp.cap_kc};
         return KeepRule{ratio ? sp.rho_p_bp : 0, k_budget, g.max_sel - s - w};
     };
@@ -1153,9 +1221,38 @@ __device__ __forceinline__ bool cascade_with(const Scorer& scorer, int P, const 
     // end up here.
     const bool all_grids = !general && rule_of(0)(ng) >= ng;
     const bool all_chunks = all_grids && rule_of(1)(nc) >= nc;
-    // merged: the chunks are scored together with the grids (one memory phase and one exchange fewer)
-    const bool merged = sp.merged != 0 && !all_grids;
+    // merged: the chunks are scored together with the grids (one memory phase and one exchange fewer); eager: the pages
+    // as well, so nothing is scored after the first phase
+    constexpr bool eager = kMode == kEagerCluster, solo = kMode == kSolo;
+    const bool merged = eager || (!solo && sp.schedule == kMerged && !all_grids);
     const bool tail_on = tail_words != nullptr;
+
+    // A phase is local when nothing is exchanged for it: a cluster of one; or the grid phase when all grids fit
+    // in one request, which every member then scores for itself (the same vectors, so the same keys) instead
+    // of waiting a round trip for the others' shares (the host allows it when the repeated reads are few).
+    // Otherwise a member takes its share of the phase's slots.
+    const int n_first = merged ? ng + nc : all_grids ? 0 : ng;
+    const bool local_first = solo || (!merged && sp.local_grids != 0 && n_first <= kSelGroups * 8);
+    // ---- the first phase: grids [0, n_g), behind them all chunks (merged), behind those all candidate pages (eager)
+    {
+        const int n_work = eager ? n_first + P - w - s : n_first;
+        // (the member that refreshes the tail units has a chain of dependent loads of its own to get through
+        // before the first cut: it takes no share of the first phase if the others can still cover it in one
+        // memory round trip each)
+        const bool spare = tail_on && !local_first && ceil_div_i(n_work, C - 1) <= Scorer::kTrip;
+        const int sharers = spare ? C - 1 : C, mine = spare && m > refresher ? m - 1 : m;
+        const int per = local_first ? n_work : ceil_div_i(ceil_div_i(n_work, sharers), Scorer::kShareRound) * Scorer::kShareRound;
+        const int lo = local_first ? 0 : (spare && m == refresher) ? n_work : min(n_work, mine * per), hi = min(n_work, lo + per);
+        // (one instance of the scoring loop per phase, each with straight-line slot arithmetic)
+        if constexpr (eager) scorer(lo, hi, AllTarget{ng, ng + nc, s, (int)(pubs.pages - pubs.units), scorer.at}, false, keys, pubs.units, requested);
+        else scorer(lo, hi, GridPhaseTarget{ng, scorer.at}, local_first, keys, pubs.units, requested);
+        if (!local_first) res->n_a = n_first;
+        if (eager) res->n_p = P - w;
+    }
+    prof.mark(2);
+    // (the summaries are kept current even if no cut needs one of the three keys)
+    if (tail_on && m == refresher) refresh_tail();
+    if (eager && !want_l3) return true;
 
     int n_kg = 0, n_kc = 0;                           // kept grids, kept chunks
 #pragma unroll 1
@@ -1164,36 +1261,24 @@ __device__ __forceinline__ bool cascade_with(const Scorer& scorer, int P, const 
         // numbers, addresses -- is then computed where it is used, not hoisted out of the loop over the levels and
         // kept in registers across all of them)
         const int tid_l = opaque_tid();
-        // ---- this level's work slots: the units whose scores are computed in this phase
-        //  level 0: grids [0, n_g), and with them all chunks [n_g, n_g + n_c) when merged
+        // ---- this level's work slots: the units whose keys are new in this phase
+        //  level 0: those of the first phase above (without the pages: eager has their keys, but a cut needs only some)
         //  level 1: chunks of kept grids, N_g slots per kept grid (nothing when merged: they have their keys)
         //  level 2: pages of kept chunks, N_c slots per kept chunk (sink and window pages have no unit there)
         int n_work;
-        if (level == 0) n_work = all_grids ? 0 : (merged ? ng + nc : ng);
+        if (level == 0) n_work = n_first;
         else if (level == 1) n_work = (merged || all_chunks) ? 0 : n_kg * g.n_g;
         else n_work = n_kc * g.n_c;
-        const GridPhaseTarget target0{ng};
-        const ChunkPhaseTarget target1{kept_grids, g.n_g, ng, nc, inv_ng};
+        const ChunkPhaseTarget target1{kept_grids, g.n_g, ng, nc, inv_ng, scorer.at};
         const PagePhaseTarget target2{kept_chunks, g.n_c, s, P - w, inv_nc};
         uint64_t* pub = level == 2 ? pubs.pages : pubs.units;
-        // A phase is local when nothing is exchanged for it: a cluster of one; or the grid phase when all grids fit
-        // in one request, which every member then scores for itself (the same vectors, so the same keys) instead
-        // of waiting a round trip for the others' shares (the host allows it when the repeated reads are few).
-        // Otherwise this member takes its share of the phase's slots.
-        const bool local = C == 1 || (level == 0 && !merged && sp.local_grids != 0 && n_work <= kSelGroups * 8);
-        if (n_work > 0) {
-            // (the member that refreshes the tail units has a chain of dependent loads of its own to get through
-            // before the first cut: it takes no share of the first phase if the others can still cover it in one
-            // memory round trip each)
-            const bool spare0 = tail_on && !local && level == 0 && C > 1 && ceil_div_i(n_work, C - 1) <= Scorer::kTrip;
-            const int sharers = spare0 ? C - 1 : C, mine = spare0 ? m - 1 : m;
-            const int per = local ? n_work : ceil_div_i(ceil_div_i(n_work, sharers), Scorer::kShareRound) * Scorer::kShareRound;
-            const int lo = local ? 0 : (mine < 0 ? n_work : min(n_work, mine * per)), hi = min(n_work, lo + per);
-            // (one instance of the scoring loop per phase, each with straight-line slot arithmetic)
-            if (level == 0) scorer(lo, hi, target0, local, keys, pub);
-            else if (level == 1) scorer(lo, hi, target1, local, keys, pub);
-            else scorer(lo, hi, target2, local, keys, pub);
-            if (!local) { if (level == 2) res->n_p = n_work; else res->n_a = max(res->n_a, level == 0 ? n_work : ng + n_work); }
+        const bool local = solo || (level == 0 && local_first);
+        if (!eager && level > 0 && n_work > 0) {
+            const int per = local ? n_work : ceil_div_i(ceil_div_i(n_work, C), Scorer::kShareRound) * Scorer::kShareRound;
+            const int lo = local ? 0 : min(n_work, m * per), hi = min(n_work, lo + per);
+            if (level == 1) scorer(lo, hi, target1, local, keys, pub, [] {});
+            else scorer(lo, hi, target2, local, keys, pub, [] {});
+            if (!local) { if (level == 2) res->n_p = n_work; else res->n_a = max(res->n_a, ng + n_work); }
         }
         // kPhys: the block-table entries of every page slot are requested now, behind this member's vectors, and
         // parked in LDS once the level's keys have been pulled (loads return in order: no wait of their own)
@@ -1206,11 +1291,8 @@ __device__ __forceinline__ bool cascade_with(const Scorer& scorer, int P, const 
                 if (x * kSelThreads < n_work) entry[kPhys ? x : 0] = bt_row[max(i < n_work ? target2(i).unit : -1, 0)];
             }
         }
-        prof.mark(2 + 4 * level);
+        if (level > 0) prof.mark(2 + 4 * level);
         if (level == 2 && !want_l3) return true;
-        // member 0 refreshes the tail units once its first vectors are on their way (the summaries are kept current
-        // even if no cut needs one of the three keys)
-        if (tail_on && m == 0 && level == 0) refresh_tail();
 
         // ---- the keys this level's cut needs, into LDS; where a refreshed tail unit competes, its fresh key
         // the tail grid is unit n_g - 1, the tail chunk unit n_c - 1 (key slot n_g + n_c - 1); the tail page is the
@@ -1235,8 +1317,8 @@ __device__ __forceinline__ bool cascade_with(const Scorer& scorer, int P, const 
             if (ov_dest0 >= 0) {
                 if (tid_l == 0) {
                     // a cluster of one computed the tail keys itself; otherwise they are polled like any other key
-                    const uint64_t k0 = C == 1 ? sh.tail_key[ov_word0] : poll_word(tail_words + ov_word0, sh.poll_limit);
-                    const uint64_t k1 = ov_dest1 < 0 ? kMarkKey : C == 1 ? sh.tail_key[ov_word1] : poll_word(tail_words + ov_word1, sh.poll_limit);
+                    const uint64_t k0 = solo ? sh.tail_key[ov_word0] : poll_word(tail_words + ov_word0, sh.poll_limit);
+                    const uint64_t k1 = ov_dest1 < 0 ? kMarkKey : solo ? sh.tail_key[ov_word1] : poll_word(tail_words + ov_word1, sh.poll_limit);
                     keys[ov_dest0] = k0;
                     if (ov_dest1 >= 0) keys[ov_dest1] = k1;
                     sh.flag = (k0 != 0ull && k1 != 0ull) ? 1 : 0;
@@ -1244,17 +1326,21 @@ __device__ __forceinline__ bool cascade_with(const Scorer& scorer, int P, const 
                 __syncthreads();
                 if (sh.flag == 0) return false;
             }
-        } else if (n_work > 0) {
+        } else if (!solo && n_work > 0) {
             // (every non-local phase keeps its keys in slot order; a phase of up to 1024 slots hands them to the cut
             // in registers)
             const int off = level == 1 ? ng : 0;
             const int od0 = ov_dest0 >= 0 ? ov_dest0 - off : -1, od1 = ov_dest1 >= 0 ? ov_dest1 - off : -1;
             bool ok;
+            // (the words of a page phase are in slot order, or in page order when they were published ahead)
+            const PageWords words{target2, level == 2 && eager};
             if (n_work <= 4 * kSelThreads && !merged_phase) {
-                ok = pull_keys_regs(pub + off, tail_words, n_work, od0, ov_word0, od1, ov_word1, keys + off, pulled, sh.poll_limit, sh);
+                ok = pull_keys_regs(pub + off, tail_words, n_work, words, od0, ov_word0, od1, ov_word1, keys + off, pulled, sh.poll_limit, sh);
                 have_pulled = true;
+            } else if (n_work <= 2 * kSelThreads) {
+                ok = pull_keys<2>(pub + off, tail_words, n_work, words, od0, ov_word0, od1, ov_word1, keys + off, sh.poll_limit);
             } else {
-                ok = pull_keys(pub + off, tail_words, n_work, [](int j) { return j; }, od0, ov_word0, od1, ov_word1, keys + off, sh.poll_limit);
+                ok = pull_keys<8>(pub + off, tail_words, n_work, words, od0, ov_word0, od1, ov_word1, keys + off, sh.poll_limit);
             }
             if (!ok) return false;
         }
@@ -1285,7 +1371,7 @@ __device__ __forceinline__ bool cascade_with(const Scorer& scorer, int P, const 
             // chunk keys: by unit, competing only under a kept grid (merged), or N_g slots per kept grid (lazy)
             uint64_t* lk = level == 1 ? keys + ng : keys;
             const int n_slots = level == 0 ? ng : level == 1 ? (merged ? nc : n_work) : n_work;
-            const ActiveRule active{(level == 1 && merged) ? keys : nullptr, g.n_g, inv_ng};
+            const ActiveRule active{(level == 1 && merged) ? keys : nullptr, inv_ng};
             const KeepRule rule = rule_of(level);
             const bool by_parent = level == 2 || (level == 1 && !merged);
             const EmitRule emit{level == 0 ? kept_grids : level == 1 ? kept_chunks : sel_pages,
@@ -1305,34 +1391,38 @@ __device__ __forceinline__ bool cascade_with(const Scorer& scorer, int P, const 
     return true;
 }
 
-// The scorer of one (sequence, KV head): a level's vectors are rows of one array, the probe is in registers.
+// The scorer of one (sequence, KV head): the probe is in registers.
 template <class T>
 struct HeadScorer {
     static constexpr int kShareRound = 1;
     static constexpr int kTrip = kSelGroups * kFlyOf<T>;   // slots a member scores per memory round trip
     const T* pages_row;
-    const T* chunks_row;
-    const T* grids_row;
+    VecBases at;
     const double (&pr)[8];
-    template <class Target>
-    __device__ __forceinline__ void operator()(int lo, int hi, Target target, bool local, uint64_t* keys, uint64_t* pub) const
+    // (the three arrays lie in one summary buffer, behind one another, in whole vectors)
+    __device__ __forceinline__ HeadScorer(const T* pages, const T* chunks, const T* grids, const double (&probe)[8])
+        : pages_row(pages), at{(int)((grids - pages) / kHeadDim), (int)((chunks - pages) / kHeadDim)}, pr(probe) {}
+    template <class Target, class Requested>
+    __device__ __forceinline__ void operator()(int lo, int hi, Target target, bool local, uint64_t* keys, uint64_t* pub,
+                                               Requested requested) const
     {
-        score_rows<T>(grids_row, chunks_row, pages_row, lo, hi, target, pr, local, keys, pub);
+        score_rows<T>(pages_row, lo, hi, target, pr, local, keys, pub, requested);
     }
 };
 
-template <bool kPhys, class T, class TailFn>
+template <int kMode, bool kPhys, class T, class ReqFn, class TailFn>
 __device__ __forceinline__ bool cascade(const T* __restrict__ pages_row, const T* __restrict__ chunks_row,
                                         const T* __restrict__ grids_row, const double (&pr)[8], int P, const Geom& g,
                                         const SelectParams& sp, const PubLayout& pubs, int m, int C, bool want_l3,
                                         uint64_t* keys, int32_t* kept_grids, int32_t* kept_chunks, int32_t* sel_pages,
                                         Shared& sh, CascadeResult* res, Prof& prof, const uint64_t* tail_words,
-                                        TailFn refresh_tail, int k_fixed, const int32_t* __restrict__ bt_row = nullptr,
+                                        int refresher, ReqFn requested, TailFn refresh_tail, int k_fixed,
+                                        const int32_t* __restrict__ bt_row = nullptr,
                                         int32_t* phys_by_slot = nullptr, int32_t* sel_phys = nullptr)
 {
-    const HeadScorer<T> scorer{pages_row, chunks_row, grids_row, pr};
-    return cascade_with<kPhys>(scorer, P, g, sp, pubs, m, C, want_l3, keys, kept_grids, kept_chunks, sel_pages, sh, res,
-                               prof, tail_words, refresh_tail, k_fixed, bt_row, phys_by_slot, sel_phys);
+    const HeadScorer<T> scorer(pages_row, chunks_row, grids_row, pr);
+    return cascade_with<kMode, kPhys>(scorer, P, g, sp, pubs, m, C, want_l3, keys, kept_grids, kept_chunks, sel_pages, sh, res,
+                                      prof, tail_words, refresher, requested, refresh_tail, k_fixed, bt_row, phys_by_slot, sel_phys);
 }
 
 // Clear the published words of one (sequence, KV head) after everybody is done with them.

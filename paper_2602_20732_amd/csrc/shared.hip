@@ -54,6 +54,7 @@ struct SharedScorer {
     int b;
     const Geom& g;
     double* red;                                     // LDS [16 groups][kSharedSlots]
+    VecBases at{0, 0};                               // (a slot's array and unit say where its rows are)
 
     // One pass: the N work slots s0 .. s0 + N - 1, all of one level (N is a template parameter so that exactly N
     // vectors per row are requested, all before the first is used: a run-time count would make the compiler wait
@@ -126,8 +127,8 @@ struct SharedScorer {
         __syncthreads();                              // red is reused by the next pass
     }
 
-    template <class Target>
-    __device__ __forceinline__ void operator()(int lo, int hi, Target target, bool local, uint64_t* keys, uint64_t* pub) const
+    template <class Target, class Requested>
+    __device__ __forceinline__ void operator()(int lo, int hi, Target target, bool local, uint64_t* keys, uint64_t* pub, Requested) const
     {
         // the share in passes of equal size (the last may be shorter), at most kSharedSlots slots each
         const int n_pass = (hi - lo + kSharedSlots - 1) / kSharedSlots;
@@ -149,7 +150,7 @@ struct SharedScorer {
 static_assert(kSharedSlots == 8, "the dispatch in SharedScorer lists the pass sizes");
 
 // grid = (C, 1, batch); T = storage type of the summaries
-template <class T>
+template <class T, int kMode>
 __global__ __launch_bounds__(kSelThreads) void select_shared_kernel(SharedTable tab, const int32_t* __restrict__ seq_lens,
                                                                     Geom g, SelectParams sp, SelectWs ws,
                                                                     int32_t* __restrict__ page_ids,
@@ -188,8 +189,8 @@ __global__ __launch_bounds__(kSelThreads) void select_shared_kernel(SharedTable 
     const PubLayout pubs = pub_layout(ws.keys + (size_t)b * ws.key_stride, g);
     CascadeResult res;
     const SharedScorer<T> scorer{tab, b, g, red};
-    const bool ok = cascade_with<false>(scorer, P, g, sp, pubs, m, C, m == 0, keys, kept_grids, kept_chunks, sel_pages, sh,
-                                        &res, prof, nullptr, [] {}, k_fixed);
+    const bool ok = cascade_with<kMode, false>(scorer, P, g, sp, pubs, m, C, m == 0, keys, kept_grids, kept_chunks, sel_pages, sh,
+                                        &res, prof, nullptr, 0, [] {}, [] {}, k_fixed);
     if (!ok) {
         if (tid == 0) __hip_atomic_fetch_or(ws.error, kErrWait, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;
@@ -213,28 +214,30 @@ __global__ __launch_bounds__(kSelThreads) void select_shared_kernel(SharedTable 
     if (tid < H) n_selected[b * H + tid] = n_sel;
 }
 
+using SharedKernel = void (*)(SharedTable, const int32_t*, Geom, SelectParams, SelectWs, int32_t*, int32_t*);
+static SharedKernel shared_kernel_of(bool bf16, bool solo)
+{
+    if (bf16) return solo ? select_shared_kernel<uint16_t, kSolo> : select_shared_kernel<uint16_t, kCluster>;
+    return solo ? select_shared_kernel<float, kSolo> : select_shared_kernel<float, kCluster>;
+}
+
+// (a cluster of one needs no co-residency: what counts is how many of the clusters' workgroups fit)
 hipError_t select_shared_occupancy(bool bf16, int lds_bytes, int* blocks_per_cu)
 {
-    const void* kern = bf16 ? reinterpret_cast<const void*>(select_shared_kernel<uint16_t>)
-                            : reinterpret_cast<const void*>(select_shared_kernel<float>);
-    if (lds_bytes > 48 * 1024) {
-        hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+    for (const bool solo : {true, false}) {
+        if (lds_bytes <= 48 * 1024) break;
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(shared_kernel_of(bf16, solo)), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
         if (e != hipSuccess) return e;
     }
-    return bf16 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, select_shared_kernel<uint16_t>, kSelThreads, lds_bytes)
-                : hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, select_shared_kernel<float>, kSelThreads, lds_bytes);
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, shared_kernel_of(bf16, false), kSelThreads, lds_bytes);
 }
 
 hipError_t launch_select_shared(chess_ctx* ctx, const SharedTable& tab, const int32_t* seq_lens, int batch, int cluster,
                                 const SelectParams& sp, const SelectWs& ws, size_t lds_bytes, int32_t* page_ids,
                                 int32_t* n_selected, hipStream_t stream)
 {
-    const dim3 grid(cluster, 1, batch), block(kSelThreads);
-    if (ctx->cfg.summary_dtype == CHESS_SUMMARY_BF16)
-        return launch(select_shared_kernel<uint16_t>, grid, block, lds_bytes, stream, tab, seq_lens, ctx->geom, sp, ws, page_ids,
-                      n_selected);
-    return launch(select_shared_kernel<float>, grid, block, lds_bytes, stream, tab, seq_lens, ctx->geom, sp, ws, page_ids,
-                  n_selected);
+    return launch(shared_kernel_of(ctx->cfg.summary_dtype == CHESS_SUMMARY_BF16, cluster == 1), dim3(cluster, 1, batch), dim3(kSelThreads),
+                  lds_bytes, stream, tab, seq_lens, ctx->geom, sp, ws, page_ids, n_selected);
 }
 
 }  // namespace chess

@@ -1,10 +1,10 @@
 // The whole decode step of one layer in one launch: coarse-to-fine page selection (Sec. 3.2, Alg. 1 stage 2)
 // followed at once by block-sparse attention over the selected pages, read in place (Sec. 4.3, App. B).
 //
-// A cluster of C workgroups per (sequence, KV head) runs the three selection levels (select_device.h); every
-// member ends up with the same page list in its LDS, so the list never travels through memory: member m
-// goes straight on to decode tiles m, m + C, ... of it (decode_device.h) as split m of C, and the last
-// member to finish merges the C partials.  Compared with chess_select + chess_sparse_decode this saves a
+// A cluster of C workgroups per (sequence, KV head) runs the three selection levels (select_device.h); the D of them
+// that run the cuts (all, unless the schedule is eager) end up with the same page list in their LDS, so the list never
+// travels through memory: member m goes straight on to decode tiles m, m + D, ... of it (decode_device.h) as split m of
+// D, and the last of them to finish merges the D partials.  Compared with chess_select + chess_sparse_decode this saves a
 // kernel boundary, the round trip of the list through HBM and the second kernel's start-up loads.
 // Member 0 also writes the list to page_ids / n_selected when the caller wants it.
 #include "decode_device.h"
@@ -41,89 +41,98 @@ struct StepArgs {
 // the storage type per vector; a parent averages its children as they are stored), so the vectors are the ones
 // chess_summarize_tail writes.  They go to the summaries and to `fresh` (LDS, [3][128]: page, chunk, grid); their
 // scores against the probe are published as keys in tail_words[0..2] (grid, chunk, page) when `publish` is set (a
-// cluster of one has nobody to tell) and kept in sh.tail_key.  Every thread of the workgroup must call it.
+// cluster of one has nobody to tell) and kept in sh.tail_key.  In two steps, so that the rows' round trip hides behind
+// the scoring of the grids: request, then finish.  Every thread of the workgroup must call both.
 template <int B, class T>
-__device__ __forceinline__ void refresh_tail_units(const uint16_t* __restrict__ k_pool, int64_t phys, T* pages_row,
-                                                   T* chunks_row, T* grids_row, int h, int H, int L, int P,
-                                                   const Geom& g, const double (&pr)[8], T* fresh,
-                                                   uint64_t* tail_words, bool publish, Shared& sh)
-{
-    const int tid = threadIdx.x;
-    const int tp = P - 1, tc = div_by(tp, g.n_c, g.inv_nc), tg = div_by(tc, g.n_g, g.inv_ng);
-    const int n_tok = L - tp * B;
-    if (tid < kHeadDim) {
-        const int c = tid;
-        // the page's key rows, all requested at once (rows past the last token repeat it and are not added)
+struct TailUnits {
+    static constexpr int kSib = 8;
+    uint16_t kr[B];          // this thread's column of the page's key rows
+    T sp[kSib], sc[kSib];    // ... of the first other pages of the chunk and the first other chunks of the grid
+    // all requested at once: one round trip for the usual hierarchy of 8 x 8
+    __device__ __forceinline__ void request(const uint16_t* __restrict__ k_pool, int64_t phys, const T* pages_row,
+                                            const T* chunks_row, int h, int H, int L, int P, const Geom& g)
+    {
+        const int c = threadIdx.x;
+        if (c >= kHeadDim) return;
+        const int tp = P - 1, tc = div_by(tp, g.inv_nc), tg = div_by(tc, g.inv_ng);
+        const int n_tok = L - tp * B, p_lo = tc * g.n_c, c_lo = tg * g.n_g;
+        // (rows past the last token repeat it, children past the tail unit -- the last of each -- repeat it: neither is added)
         const uint16_t* rows = k_pool + ((phys * H + h) * B) * kHeadDim + c;
-        uint16_t kr[B];
 #pragma unroll
         for (int t = 0; t < B; ++t) kr[t] = rows[(size_t)min(t, n_tok - 1) * kHeadDim];
-        // the other pages of the chunk and the other chunks of the grid (the tail unit is the last child of each),
-        // eight at a time and the first eight of each together with the key rows: one round trip for the usual
-        // hierarchy of 8 x 8
-        constexpr int kSib = 8;
-        const int p_lo = tc * g.n_c, c_lo = tg * g.n_g;
-        T sp[kSib], sc[kSib];
 #pragma unroll
         for (int x = 0; x < kSib; ++x) {
             sp[x] = pages_row[(size_t)min(p_lo + x, tp) * kHeadDim + c];
             sc[x] = chunks_row[(size_t)min(c_lo + x, tc) * kHeadDim + c];
         }
-        double acc_c = 0.0, acc_g = 0.0;
-#pragma unroll
-        for (int x = 0; x < kSib; ++x) {
-            if (p_lo + x < tp) acc_c += loaded(sp[x]);
-            if (c_lo + x < tc) acc_g += loaded(sc[x]);
-        }
-        for (int j0 = p_lo + kSib; j0 < tp; j0 += kSib) {
-#pragma unroll
-            for (int x = 0; x < kSib; ++x) sp[x] = pages_row[(size_t)min(j0 + x, tp) * kHeadDim + c];
-#pragma unroll
-            for (int x = 0; x < kSib; ++x)
-                if (j0 + x < tp) acc_c += loaded(sp[x]);
-        }
-        for (int j0 = c_lo + kSib; j0 < tc; j0 += kSib) {
-#pragma unroll
-            for (int x = 0; x < kSib; ++x) sc[x] = chunks_row[(size_t)min(j0 + x, tc) * kHeadDim + c];
-#pragma unroll
-            for (int x = 0; x < kSib; ++x)
-                if (j0 + x < tc) acc_g += loaded(sc[x]);
-        }
-        double acc_p = 0.0;
-#pragma unroll
-        for (int t = 0; t < B; ++t)
-            if (t < n_tok) acc_p += loaded(kr[t]);
-        const T vp = stored<T>(acc_p / (double)n_tok);
-        const T vc = stored<T>((acc_c + loaded(vp)) / (double)(tp - tc * g.n_c + 1));
-        const T vg = stored<T>((acc_g + loaded(vc)) / (double)(tc - tg * g.n_g + 1));
-        pages_row[(size_t)tp * kHeadDim + c] = vp;
-        chunks_row[(size_t)tc * kHeadDim + c] = vc;
-        grids_row[(size_t)tg * kHeadDim + c] = vg;
-        fresh[c] = vp;
-        fresh[kHeadDim + c] = vc;
-        fresh[2 * kHeadDim + c] = vg;
     }
-    __syncthreads();
-    // scores of the three vectors, one 16-lane group each, with the arithmetic of score_rows
-    const int g16 = tid >> 4, ln = tid & 15;
-    if (g16 < 3) {
-        Vec<T> v;
-        v.load(fresh + g16 * kHeadDim, ln);
-        const double d = row16_sum(dot8<T>(pr, v));
-        if (ln == 15) {
-            const uint64_t key = order_key(d);
-            const int level = 2 - g16;                            // fresh[0] is the page, fresh[2] the grid
-            if (publish) publish_u64(tail_words + level, key);
-            sh.tail_key[level] = key;
+    __device__ __forceinline__ void finish(T* pages_row, T* chunks_row, T* grids_row, int L, int P, const Geom& g,
+                                           const double (&pr)[8], T* fresh, uint64_t* tail_words, bool publish, Shared& sh)
+    {
+        const int tid = threadIdx.x;
+        const int tp = P - 1, tc = div_by(tp, g.inv_nc), tg = div_by(tc, g.inv_ng);
+        const int n_tok = L - tp * B, p_lo = tc * g.n_c, c_lo = tg * g.n_g;
+        if (tid < kHeadDim) {
+            const int c = tid;
+            double acc_c = 0.0, acc_g = 0.0;
+#pragma unroll
+            for (int x = 0; x < kSib; ++x) {
+                if (p_lo + x < tp) acc_c += loaded(sp[x]);
+                if (c_lo + x < tc) acc_g += loaded(sc[x]);
+            }
+            // fan-outs beyond eight: the other children, eight at a time
+            for (int j0 = p_lo + kSib; j0 < tp; j0 += kSib) {
+#pragma unroll
+                for (int x = 0; x < kSib; ++x) sp[x] = pages_row[(size_t)min(j0 + x, tp) * kHeadDim + c];
+#pragma unroll
+                for (int x = 0; x < kSib; ++x)
+                    if (j0 + x < tp) acc_c += loaded(sp[x]);
+            }
+            for (int j0 = c_lo + kSib; j0 < tc; j0 += kSib) {
+#pragma unroll
+                for (int x = 0; x < kSib; ++x) sc[x] = chunks_row[(size_t)min(j0 + x, tc) * kHeadDim + c];
+#pragma unroll
+                for (int x = 0; x < kSib; ++x)
+                    if (j0 + x < tc) acc_g += loaded(sc[x]);
+            }
+            double acc_p = 0.0;
+#pragma unroll
+            for (int t = 0; t < B; ++t)
+                if (t < n_tok) acc_p += loaded(kr[t]);
+            const T vp = stored<T>(acc_p / (double)n_tok);
+            const T vc = stored<T>((acc_c + loaded(vp)) / (double)(tp - tc * g.n_c + 1));
+            const T vg = stored<T>((acc_g + loaded(vc)) / (double)(tc - tg * g.n_g + 1));
+            pages_row[(size_t)tp * kHeadDim + c] = vp;
+            chunks_row[(size_t)tc * kHeadDim + c] = vc;
+            grids_row[(size_t)tg * kHeadDim + c] = vg;
+            fresh[c] = vp;
+            fresh[kHeadDim + c] = vc;
+            fresh[2 * kHeadDim + c] = vg;
         }
+        __syncthreads();
+        // scores of the three vectors, one 16-lane group each, with the arithmetic of score_rows
+        const int g16 = tid >> 4, ln = tid & 15;
+        if (g16 < 3) {
+            Vec<T> v;
+            v.load(fresh + g16 * kHeadDim, ln);
+            const double d = row16_sum(dot8<T>(pr, v));
+            if (ln == 15) {
+                const uint64_t key = order_key(d);
+                const int level = 2 - g16;                            // fresh[0] is the page, fresh[2] the grid
+                if (publish) publish_u64(tail_words + level, key);
+                sh.tail_key[level] = key;
+            }
+        }
+        __syncthreads();
     }
-    __syncthreads();
-}
+};
 
-// grid = (C, H_kv, batch); T = storage type of the summaries (float or bf16 bits)
-template <int B, class T>
-__global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(2))) void step_kernel(StepArgs a, Geom g, SelectParams sp, SelectWs ws)
+// grid = (C, H_kv, batch); T = storage type of the summaries (float or bf16 bits); kMode: see cascade_with
+template <int B, class T, int kMode>
+__global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(2))) void step_kernel(StepArgs a, Geom g_args, SelectParams sp_args, SelectWs ws)
 {
+    const Geom g = own_regs(g_args);
+    const SelectParams sp = own_regs(sp_args);
     constexpr int PPT = 32 / B;
     extern __shared__ unsigned long long lds_raw[];
     int32_t* ids_l = reinterpret_cast<int32_t*>(lds_raw);                                  // [max_sel] the page list
@@ -137,7 +146,8 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(2))
     DecodeLds<kStepWaves> dl(reinterpret_cast<float*>(un));                                // decode's view
     __shared__ Shared sh;
 
-    const int m = blockIdx.x, C = gridDim.x, h = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
+    // C members score; the first D of them go on to the cuts and the attention (all of them unless the schedule is eager)
+    const int m = kMode == kSolo ? 0 : blockIdx.x, C = kMode == kSolo ? 1 : gridDim.x, D = kMode == kEagerCluster ? sp.deciders : C, h = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6, m16 = lane & 15, grp = lane >> 4;
     const int G = g.group, H = g.n_kv_heads;
     Prof prof;
@@ -148,7 +158,8 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(2))
     const int L_raw = a.seq_lens[b];
     const int k_fixed = fixed_budget(sp, g, b);
     double pr[8];
-    if (sp.probe == CHESS_PROBE_QUERY) load_probe<T>(q_rows, G, pr);  // requested before anything waits on the length
+    ProbeRows<T> probe;
+    if (sp.probe == CHESS_PROBE_QUERY) probe.request(q_rows, 0, G);   // before anything waits on the length
     init_shared(sh, sp.poll_limit);
     const int L = min(max(L_raw, 0), g.max_pages * B);
     const int P = (L + B - 1) / B;
@@ -166,14 +177,18 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(2))
     T* chunks_row = static_cast<T*>(a.chunks) + row * g.max_chunks * kHeadDim;
     T* grids_row = static_cast<T*>(a.grids) + row * g.max_grids * kHeadDim;
     if (sp.probe == CHESS_PROBE_ANCHOR) load_anchor<T>(pages_row, P, w, pr);
-    // member 0 refreshes the tail units: its block-table entry is requested now
+    // one member refreshes the tail units, a helper if there are any: its block-table entry is requested now
+    const int refresher = D < C ? C - 1 : 0;
     const bool tail_on = a.refresh_tail != 0;
     uint64_t* tail_words = tail_on ? ws.tail + row * 4 : nullptr;
     int tail_phys = 0;
-    if (tail_on && m == 0) tail_phys = bt_row[P - 1];
-    auto refresh_tail = [&]() {
-        refresh_tail_units<B, T>(a.k_pool, tail_phys, pages_row, chunks_row, grids_row, h, H, L, P, g, pr, fresh, tail_words, C > 1, sh);
+    if (tail_on && m == refresher) tail_phys = bt_row[P - 1];
+    TailUnits<B, T> tail;
+    auto requested = [&]() {                                          // (the first vectors to score are on their way)
+        if (sp.probe == CHESS_PROBE_QUERY) probe.sum(q_rows, G, pr);
+        if (tail_on && m == refresher) tail.request(a.k_pool, tail_phys, pages_row, chunks_row, h, H, L, P, g);
     };
+    auto refresh_tail = [&]() { tail.finish(pages_row, chunks_row, grids_row, L, P, g, pr, fresh, tail_words, C > 1 && P > s + w, sh); };
     __syncthreads();
     prof.mark(1);                                                     // prologue done
 
@@ -183,9 +198,13 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(2))
     res.n_kp = 0; res.n_a = 0; res.n_p = 0; res.overflow = false;
     int n_sel;
     if (P <= s + w) {                                                 // safety pages cover the sequence
+        if (tail_on && m == refresher) {                              // nobody reads the keys; the summaries are kept current
+            requested();
+            refresh_tail();
+        }
+        if (m >= D) return;
         n_sel = min(P, g.max_sel);
         for (int i = tid; i < n_sel; i += kSelThreads) { ids_l[i] = i; phys_l[i] = bt_row[i]; }
-        if (tail_on && m == 0) refresh_tail();                        // nobody reads the keys; the summaries are kept current
     } else {
         // the block-table entries of the safety pages are requested now and used after the selection
         const bool safety_early = s + w <= kSelThreads;
@@ -193,11 +212,15 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(2))
         int safety_phys = 0;
         if (safety_early && tid < s + w) safety_phys = bt_row[safety_lp];
         // kept pages and their physical pages go straight to their places in the list, behind the sinks
-        const bool ok = cascade<true, T>(pages_row, chunks_row, grids_row, pr, P, g, sp, pubs, m, C, true, keys, kept_grids,
-                                         kept_chunks, ids_l + s, sh, &res, prof, tail_words, refresh_tail, k_fixed, bt_row,
+        const bool ok = cascade<kMode, true, T>(pages_row, chunks_row, grids_row, pr, P, g, sp, pubs, m, C, m < D, keys, kept_grids,
+                                         kept_chunks, ids_l + s, sh, &res, prof, tail_words, refresher, requested, refresh_tail, k_fixed, bt_row,
                                          phys_by_slot, phys_l + s);
         if (!ok) {
             if (tid == 0) __hip_atomic_fetch_or(ws.error, kErrWait, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return;
+        }
+        if (m >= D) {                                                 // a helper is done; normally long before the deciders are
+            if (arrive_of_two(a.arrivals + row, false, D, C - D, &sh.flag) & kLastOfAll) clear_published(pubs, res, tail_words);
             return;
         }
         if (res.overflow && m == 0 && tid == 0) __hip_atomic_fetch_or(ws.error, kErrOverflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -225,10 +248,10 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(2))
     }
     prof.mark(14);                                                    // list built
 
-    // ---- attention over this member's tiles of the list: split m of C
+    // ---- attention over this member's tiles of the list: split m of D
     const int n_tiles = (n_sel + PPT - 1) / PPT;
-    const int stride = C * kStepWaves;
-    const int t = m + C * wave;
+    const int stride = D * kStepWaves;
+    const int t = m + D * wave;
     int raw_cur[PPT], raw_nxt[PPT];
     fetch_ids<B, true>(raw_cur, t, ids_l, max(n_sel, 1));
     fetch_ids<B, true>(raw_nxt, t + stride, ids_l, max(n_sel, 1));
@@ -237,31 +260,32 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(2))
     run_tiles<B, true, true>(acc, t, stride, n_tiles, n_sel, raw_cur, raw_nxt, ids_l, max(n_sel, 1), bt_row, phys_l, a.k_pool, a.v_pool, H, h, L, P,
                  a.scale_log2, m16, grp);
     prof.mark(15);                                                    // tiles done
-    if (!combine_waves<kStepWaves>(acc.o, acc.m_run, acc.l_run, dl, G, C, m, row * C, out_rows, a.ws_acc, a.ws_ml)) return;
-    prof.mark(16);                                                    // partial published
+    const bool split_up = combine_waves<kStepWaves>(acc.o, acc.m_run, acc.l_run, dl, G, D, m, row * D, out_rows, a.ws_acc, a.ws_ml);
+    prof.mark(16);                                                    // partial published (or, alone, the output written)
     // (profiling builds keep two timelines per row: member 0's and that of the member that merges)
-    if (!arrive_last(a.arrivals + row, C, &sh.flag)) {
-#ifdef CHESS_PROF
-        prof.mark(17);
-        if (tid == 0 && m == 0) prof.store(ws.prof + (row * 2) * Prof::kSlots);
-#endif
-        return;
-    }
-    prof.mark(17);                                                    // last to arrive
-    merge_splits<kStepWaves>(G, C, row * C, out_rows, a.ws_acc, a.ws_ml);
-    if (C > 1) clear_published(pubs, res, tail_words);                    // every member is done with the key words
+    const int n_helpers = P <= s + w ? 0 : C - D;                     // (without a selection they have left)
+    const int last = split_up || n_helpers > 0 ? arrive_of_two(a.arrivals + row, true, D, n_helpers, &sh.flag) : 0;
+    prof.mark(17);
+    // every member is done with the key words (the stores' way to memory hides behind the merge)
+    if (last & kLastOfAll) clear_published(pubs, res, tail_words);
+    if (split_up && (last & kLastDecider)) merge_splits<kStepWaves>(G, D, row * D, out_rows, a.ws_acc, a.ws_ml);
 #ifdef CHESS_PROF
     prof.mark(18);
-    if (tid == 0) prof.store(ws.prof + (row * 2 + 1) * Prof::kSlots);
+    if (tid == 0 && (!split_up || (last & kLastDecider))) prof.store(ws.prof + (row * 2 + 1) * Prof::kSlots);
     if (tid == 0 && m == 0) prof.store(ws.prof + (row * 2) * Prof::kSlots);
 #endif
 }
 
 using StepKernel = void (*)(StepArgs, Geom, SelectParams, SelectWs);
-static StepKernel step_kernel_of(int page_size, bool bf16)
+static StepKernel step_kernel_of(int page_size, bool bf16, int mode)
 {
-    if (bf16) return page_size == 16 ? step_kernel<16, uint16_t> : step_kernel<32, uint16_t>;
-    return page_size == 16 ? step_kernel<16, float> : step_kernel<32, float>;
+    // [page size 16 / 32][fp32 / bf16][mode]
+    static const StepKernel table[2][2][3] = {
+        {{step_kernel<16, float, kSolo>, step_kernel<16, float, kCluster>, step_kernel<16, float, kEagerCluster>},
+         {step_kernel<16, uint16_t, kSolo>, step_kernel<16, uint16_t, kCluster>, step_kernel<16, uint16_t, kEagerCluster>}},
+        {{step_kernel<32, float, kSolo>, step_kernel<32, float, kCluster>, step_kernel<32, float, kEagerCluster>},
+         {step_kernel<32, uint16_t, kSolo>, step_kernel<32, uint16_t, kCluster>, step_kernel<32, uint16_t, kEagerCluster>}}};
+    return table[page_size == 16 ? 0 : 1][bf16 ? 1 : 0][mode];
 }
 
 // Dynamic LDS of the fused kernel and where its shared region starts.
@@ -274,12 +298,20 @@ size_t step_lds_bytes(const SelectParams& sp, int max_sel, int* union_off)
     return list + (sel > dec ? sel : dec);
 }
 
+// Workgroups of any mode that fit on a compute unit.
 hipError_t step_occupancy(int page_size, bool bf16, int lds_bytes, int* blocks_per_cu)
 {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(step_kernel_of(page_size, bf16)),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
-    if (e != hipSuccess) return e;
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, step_kernel_of(page_size, bf16), kSelThreads, lds_bytes);
+    int least = 0;
+    for (const int mode : {kSolo, kCluster, kEagerCluster}) {
+        int n = 0;
+        const StepKernel kern = step_kernel_of(page_size, bf16, mode);
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+        if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kern, kSelThreads, lds_bytes);
+        if (e != hipSuccess) return e;
+        least = mode == kSolo || n < least ? n : least;
+    }
+    *blocks_per_cu = least;
+    return hipSuccess;
 }
 
 hipError_t launch_step(chess_ctx* ctx, const StepLaunch& sl, int batch, int cluster, const SelectParams& sp,
@@ -294,7 +326,8 @@ hipError_t launch_step(chess_ctx* ctx, const StepLaunch& sl, int batch, int clus
     a.union_off = union_off;
     a.refresh_tail = sl.refresh_tail;
     const dim3 grid(cluster, g.n_kv_heads, batch), block(kSelThreads);
-    return launch(step_kernel_of(g.page_size, ctx->cfg.summary_dtype == CHESS_SUMMARY_BF16), grid, block, lds_bytes, stream, a, g, sp, ws);
+    const int mode = cluster == 1 ? kSolo : sp.schedule == kEager ? kEagerCluster : kCluster;
+    return launch(step_kernel_of(g.page_size, ctx->cfg.summary_dtype == CHESS_SUMMARY_BF16, mode), grid, block, lds_bytes, stream, a, g, sp, ws);
 }
 
 }  // namespace chess

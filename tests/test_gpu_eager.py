@@ -1,0 +1,74 @@
+"""The eager schedule (grids, chunks and pages scored in one phase, members that only score) at the sizes where it can go
+wrong: more and fewer members than have work, members that only score and none, the tail page among the candidates,
+sequences that the safety pages cover, levels that keep everything, a page level beyond 1024 slots; against the oracle,
+twice on one workspace (the second launch finds what the first one cleared)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2602_20732_amd as pk
+import workload
+from gpu_common import assert_summaries_equal, config_of, gpu_plan, host_views, run_oracle, to_device
+from helpers import plan_of
+
+pytestmark = pytest.mark.gpu
+ATOL_TIGHT = 2e-3     # fp32 accumulation of bf16 inputs gives about 1e-6; the stated bar of the path is 1e-2
+
+
+def check(sp, lens, plan, cluster, refresh, general=False):
+    wl = workload.generate(sp, 4201, seq_lens=lens)
+    d = to_device(wl)
+    max_sel = sp.max_pages
+    lib = pk.Chess(config_of(sp, max_selected=max_sel))
+    lib.debug_force_schedule(3)
+    lib.debug_force_cluster(cluster)
+    lib.debug_force_general_cut(general)
+    ref = run_oracle(wl, plan, max_sel, dense=False)
+    summ, ws = lib.new_summaries(), lib.new_workspace()
+    lib.summarize(d.k_pool, d.block_table, d.seq_lens, summ)
+    for turn in range(2):
+        ids = torch.full((len(lens), sp.n_kv_heads, max_sel), -7, dtype=torch.int32, device="cuda")
+        nsel = torch.full((len(lens), sp.n_kv_heads), -7, dtype=torch.int32, device="cuda")
+        out = torch.full((len(lens), sp.n_q_heads, 128), float("nan"), device="cuda")
+        ids2, nsel2 = ids.clone(), nsel.clone()
+        if refresh:                                               # stale tail vectors: the step has to renew them
+            pv, cv, gv = lib.summary_views(summ)
+            for b, L in enumerate(lens):
+                if L > 0:
+                    p = -(-L // sp.page_size) - 1
+                    pv[b, :, p] = 5.0; cv[b, :, p // sp.pages_per_chunk] = -9.0
+                    gv[b, :, p // sp.pages_per_chunk // sp.chunks_per_grid] = 3.0
+        lib.decode_step(d.q, d.k_pool, d.v_pool, d.block_table, d.seq_lens, summ, gpu_plan(plan), ids, nsel, out, ws, refresh_tail=refresh)
+        lib.select(d.q, summ, d.seq_lens, gpu_plan(plan), ids2, nsel2, ws)
+        torch.cuda.synchronize()
+        assert lib.workspace_error(ws) == 0
+        for i, n in ((ids, nsel), (ids2, nsel2)):
+            assert np.array_equal(n.cpu().numpy(), ref.nsel) and np.array_equal(i.cpu().numpy(), ref.ids), turn
+        assert np.abs(out.cpu().numpy() - ref.out).max() <= ATOL_TIGHT
+
+        class Got:
+            pages, chunks, grids = host_views(lib, summ, len(lens))
+        assert_summaries_equal(Got, ref, sp, lens)
+    lib.close()
+
+
+LENS = [2900, 1, 16 * 16 + 1, 0, 80, 16 * 65]
+RATIO = dict(plan=oracle.PLAN_RATIO, rho_g_bp=3000, rho_c_bp=3000, rho_p_bp=1000)
+
+
+@pytest.mark.parametrize("cluster", [1, 2, 3, 9, 32])
+@pytest.mark.parametrize("page,group", [(16, 1), (16, 7), (32, 4)])
+@pytest.mark.parametrize("refresh", [False, True])
+def test_eager_step_and_select(cluster, page, group, refresh):
+    sp = workload.WorkloadSpec("eager", len(LENS), (0, 3000), 2 * group, 2, page, ("fixed", 96), (1, 2), 1, 2, budget_pages=6,
+                               pages_per_chunk=4, chunks_per_grid=2)
+    for kw in ({}, dict(sink_pages=0, window_pages=0), dict(budget_pages=60), RATIO, dict(RATIO, cut_rule=oracle.CUT_THRESHOLD)):
+        check(sp, LENS, plan_of(sp, **kw), cluster, refresh)
+
+
+@pytest.mark.parametrize("bp,general", [(100, False), (100, True), (1500, False), (9000, False)])
+def test_eager_page_levels_beyond_a_pull_in_registers(bp, general):
+    """2048 pages: 216, 2048 and 2048 page slots (fan 8 x 8), the general cut as well."""
+    sp = workload.WorkloadSpec("eager_long", 1, (32768, 32768), 8, 2, 16, ("geometric", 256), (1, 3), 1, 4, budget_bp=bp)
+    check(sp, [32751], plan_of(sp), 0, True, general)
