@@ -334,6 +334,12 @@ static bool choose_eager(const chess_ctx* ctx, int64_t pairs, int64_t capacity, 
     return true;
 }
 
+static void set_members(int64_t cluster, chess::SelectParams* sp)
+{
+    sp->inv_members = (uint32_t)cdiv(0x80000000ll, cluster);
+    sp->inv_others = cluster > 1 ? (uint32_t)cdiv(0x80000000ll, cluster - 1) : 0u;
+}
+
 // Checks a plan against the configuration and fills the kernel-side parameters.
 static int prepare_select(chess_ctx* ctx, const chess_select_plan* plan, chess::SelectParams* out)
 {
@@ -401,6 +407,7 @@ int chess_select(chess_ctx* ctx, const void* q, const void* summaries, const int
     cluster = ctx->cfg.shared_device != 0 ? 1 : clampi(cluster, 1, chess::kSelMaxCluster);
 
     choose_schedule(ctx, pairs, cluster, &sp);
+    set_members(cluster, &sp);
     const chess::SelectWs ws = select_ws(ctx, workspace);
     const char* sb = static_cast<const char*>(summaries);
     hipError_t e = chess::launch_select(ctx, static_cast<const uint16_t*>(q), sb + ctx->page_off, sb + ctx->chunk_off,
@@ -551,6 +558,7 @@ int chess_select_shared(chess_ctx* ctx, const float* const* probes, const void* 
     if (ctx->force_cluster > 0) cluster = std::min<int64_t>(ctx->force_cluster, cluster);
     cluster = ctx->cfg.shared_device != 0 ? 1 : clampi(cluster, 1, chess::kSharedMaxCluster);
     sp.local_grids = 0;
+    set_members(cluster, &sp);
     sp.schedule = chess::kLazy;                      // a unit is n_layers * H_kv rows here: the launch is bound by bytes
     const chess::SelectWs ws = select_ws(ctx, workspace);
     hipError_t e = chess::launch_select_shared(ctx, tab, seq_lens, batch, (int)cluster, sp, ws, lds, page_ids, n_selected,
@@ -592,6 +600,7 @@ int chess_decode_step(chess_ctx* ctx, const void* q, const void* k_pool, const v
     const int64_t listed = std::min<int64_t>(ctx->geom.max_sel, (int64_t)sp.sink + sp.window + sp.most_kp);
     if (!choose_eager(ctx, pairs, capacity, cdiv(listed, chess::kTileTokens / ctx->geom.page_size), &cluster, &sp))
         choose_schedule(ctx, pairs, cluster, &sp);
+    set_members(cluster, &sp);
     if (pairs * sp.deciders > 4LL * ctx->n_cu + pairs) return CHESS_ENOTSUP;   // partial rows of the workspace
 
     const chess::SelectWs ws = select_ws(ctx, workspace);

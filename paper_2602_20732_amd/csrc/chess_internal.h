@@ -37,6 +37,7 @@ struct SelectParams {
     int32_t general_cut;             // test hook: every level takes the general (LDS radix) cut
     int32_t local_grids;             // every member scores all grids itself (no exchange at the grid level)
     int32_t schedule;                // which units are scored together (select_device.h)
+    uint32_t inv_members, inv_others;   // of the members of a cluster, of all but one of them (div_by; 0 for none)
     int32_t deciders;                // members that run the cuts; under the eager schedule the others only score
     int32_t keep_ties;               // the threshold rule: a level keeps every unit that ties with its k-th
     const int32_t* budget_per_seq;   // device [batch] or null: a value > 0 is that sequence's page budget
@@ -65,7 +66,7 @@ __device__ __forceinline__ SelectParams own_regs(const SelectParams& p)
     r.cap2 = own_reg(p.cap2); r.cap3 = own_reg(p.cap3); r.cap_keys = own_reg(p.cap_keys); r.cap_kg = own_reg(p.cap_kg);
     r.cap_kc = own_reg(p.cap_kc); r.most_kp = own_reg(p.most_kp); r.probe = own_reg(p.probe); r.poll_limit = own_reg(p.poll_limit);
     r.general_cut = own_reg(p.general_cut); r.local_grids = own_reg(p.local_grids); r.schedule = own_reg(p.schedule);
-    r.deciders = own_reg(p.deciders); r.keep_ties = own_reg(p.keep_ties); r.budget_per_seq = p.budget_per_seq;   // (a pointer would lose its address space)
+    r.deciders = own_reg(p.deciders); r.inv_members = own_reg(p.inv_members); r.inv_others = own_reg(p.inv_others); r.keep_ties = own_reg(p.keep_ties); r.budget_per_seq = p.budget_per_seq;   // (a pointer would lose its address space)
     return r;
 }
 

@@ -38,8 +38,6 @@ CHESS_HD float key_float(unsigned key_hi)
     return (float)__builtin_bit_cast(double, (uint64_t)u << 32);
 }
 
-constexpr int kSearchSteps = 14;            // steps (of two bits) a search for the cut takes before it leaves the rest to ranking
-
 // What the search for a cut ends with: slots with f > above are kept for sure; the cnt slots with from < f <= above
 // still have to be ranked on their 64-bit keys, want of them are kept.  cnt = 0: the cut falls between two keys.
 struct Bracket {
@@ -47,36 +45,36 @@ struct Bracket {
     int want, cnt;
 };
 
+constexpr int kSearchBits = 24;             // thresholds the search tells apart: 2^24 steps from the smallest to the largest score
+
 // The bracket of the k-th largest of n_valid scores f (0 < k < n_valid; fmin and fmax: the smallest and the largest of
-// them, finite).  count(t1, t2, t3, c1, c2, c3) says how many scores are above each of three thresholds.  A search by
-// value, three thresholds a step, that ends as soon as a threshold has exactly k scores above it (4 steps for 256 normally
-// distributed scores, 10 at most in 400 draws).  Three thresholds, because a step is a chain of dependent instructions
-// whatever it counts.
+// them, finite).  count(t1, t2, t3, c1, c2, c3) says how many scores are above each of three thresholds.  The number of the
+// highest threshold with at least k scores above it, two bits a step, the highest first, until a threshold has exactly k (5 steps
+// for 256 normally distributed scores).  Two bits, because a step is a chain of dependent instructions whatever it
+// counts; thresholds by number (they never decrease with it, whatever is rounded), so that all a step decides is scalar and
+// nothing in it branches: as a search that kept the bounds themselves a step took 600 cycles of a wave with 256 keys.
 template <class Count>
 CHESS_HD Bracket search_cut(Count count, int k, int n_valid, float fmin, float fmax)
 {
-    float lo = fmin, hi = fmax;                       // more than k scores above lo (at or above it until it moves), fewer above hi
-    float from = -INFINITY;                           // lo once it has moved
-    int c_lo = n_valid, c_hi = 0;
+    const float step = (fmax - fmin) * (1.f / (float)(1 << kSearchBits));
+    const auto threshold = [&](unsigned j) { return __builtin_fmaf((float)j, step, fmin); };
+    unsigned t = 0;                                   // at least k scores above threshold t; 0: all of them
+    int c_t = n_valid;
 #pragma unroll 1
-    for (int step = 0; step < kSearchSteps; ++step) {
-        const float t2 = 0.5f * lo + 0.5f * hi, t1 = 0.5f * lo + 0.5f * t2, t3 = 0.5f * t2 + 0.5f * hi;
-        if (!(lo < t2 && t2 < hi)) break;             // neighbouring floats (or one value): ranked by key
+    for (unsigned h = 1u << (kSearchBits - 2); h != 0; h >>= 2) {
         int c1 = 0, c2 = 0, c3 = 0;
-        count(t1, t2, t3, c1, c2, c3);
-        if ((c1 == k) | (c2 == k) | (c3 == k)) {
-            hi = from = c1 == k ? t1 : c2 == k ? t2 : t3;
-            c_lo = c_hi = k;
-            break;
-        }
-        const bool g1 = c1 > k, g2 = c2 > k, g3 = c3 > k;                 // g3 implies g2 implies g1
-        hi = g3 ? hi : g2 ? t3 : g1 ? t2 : t1;
-        c_hi = g3 ? c_hi : g2 ? c3 : g1 ? c2 : c1;
-        lo = g3 ? t3 : g2 ? t2 : g1 ? t1 : lo;
-        from = g1 ? lo : from;
-        c_lo = g3 ? c3 : g2 ? c2 : g1 ? c1 : c_lo;
+        count(threshold(t + h), threshold(t + 2 * h), threshold(t + 3 * h), c1, c2, c3);
+        const int n1 = c1 >= k, n2 = c2 >= k, n3 = c3 >= k;                // n3 implies n2 implies n1
+        t += h * (unsigned)(n1 + n2 + n3);
+        c_t = n3 ? c3 : n2 ? c2 : n1 ? c1 : c_t;
+        if (c_t == k) break;
     }
-    return Bracket{hi, from, k - c_hi, c_lo - c_hi};
+    const float from = t == 0 ? -INFINITY : threshold(t);
+    if (c_t == k) return Bracket{from, from, 0, 0};
+    const float above = t + 1 == 1u << kSearchBits ? fmax : threshold(t + 1);
+    int c1 = 0, c2 = 0, c3 = 0;
+    count(above, above, above, c1, c2, c3);
+    return Bracket{above, from, k - c1, c_t - c1};
 }
 
 }  // namespace chess

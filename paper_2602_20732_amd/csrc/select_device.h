@@ -28,17 +28,16 @@
 // enumerated in index order), or are all kept under the threshold rule.
 // Which cut a level takes goes by its slots, because what a cut costs is the length of its chain of dependent
 // instructions (times of a grid level inside chess_select, from the phase marks of a -DCHESS_PROF build):
-//   up to 64     every key is ranked against every other with lane reads, each wave taking a quarter of the comparisons
-//                (16 slots 1.1 us, 64 slots 1.4 us; one wave looping over the keys took 1.6 and 4.2);
-//   up to 256    every wave holds all the keys and searches the cut by value, with counts alone and without LDS (96 slots 2.3
-//                us, 256 slots 2.4 us; the histogram below by one wave took 2.2 and 2.8);
+//   up to 256    every wave holds all the keys, one or four a lane, and searches the cut by value with counts alone, without
+//                LDS or barriers (16 slots 1.0 us, 64 slots 1.1 us, 96 to 256 slots 1.9 us; ranking every key of up to 64 against
+//                every other, shared by the waves, took 1.1 and 1.4);
 //   up to 1024   bounds from the upper key halves, a histogram over 1024 bins that are linear in the (fp32-rounded) score, a
 //                scan from the top, an exact ranking by (key, slot) of the few keys in the bin the k-th largest falls in:
-//                the whole workgroup, four keys per thread, which arrive in registers (512 slots 2.9 us, 1024 slots 3.1 us;
-//                in a trial at 1024 slots, where this took 3.3, every wave searching 16 keys per lane took 5.4 and the search
-//                spread over the waves with a barrier a step 4.3);
-//   up to 4352   the same with seventeen keys per thread, read from LDS (2048 slots 6.5 us, 4096 slots 10.4 us).
-// Score distributions that pile more than 64 keys into the bin or bracket at the cut (exact ties, mostly) take a general
+//                the whole workgroup, four keys per thread, which arrive in registers where the level was pulled (512 slots 2.7
+//                us, 1024 slots 3.0 us; in the decode step the search, the waves' counts meeting in LDS every step, took 4.5 for
+//                832 slots where this takes 3.3);
+//   up to 4352   the same with seventeen keys per thread, read from LDS (2048 slots 6.2 us, 4096 slots 9.6 us; the search 13.4).
+// Score distributions that leave more than 64 keys undecided at the cut (exact ties, mostly) take a general
 // path: radix select on the bits the keys do not share, then a ballot compaction.
 //
 // The words are cleared again by the workgroup that is last to be done with them, so they are all 0 between
@@ -215,9 +214,8 @@ struct Shared {
     uint64_t mem_key[kFastMembers];
     int mem_slot[kFastMembers];
     int run_gt[kMaxRuns];
-    int rank[kSelWaves][kWave];   // the waves' shares of the ranks of a level of one slot per lane
     int wave_a[kSelWaves], wave_b[kSelWaves];
-    int digit, rem, cnt, n_valid, n_mem, flag;
+    int digit, rem, cnt, n_valid, n_mem, flag, gave_up;
     unsigned int or_lo, or_hi, and_lo, and_hi;
     unsigned st_min[kSelWaves], st_max[kSelWaves];   // upper halves of the waves' smallest / largest key of a level
     int st_cnt[kSelWaves];
@@ -225,11 +223,10 @@ struct Shared {
     uint64_t tail_key[3];   // keys of the refreshed tail grid / chunk / page when this workgroup computed them, else 0
 };
 
-// What the kernels do to a Shared before the first level: the histogram all zero, no collected members.
+// What the kernels do to a Shared before the first level: no collected members, no wait given up.
 __device__ __forceinline__ void init_shared(Shared& sh, int poll_limit)
 {
-    for (int i = threadIdx.x; i < kBins; i += kSelThreads) sh.hist[i] = 0;
-    if (threadIdx.x == 0) { sh.n_mem = 0; sh.poll_limit = poll_limit; }
+    if (threadIdx.x == 0) { sh.n_mem = 0; sh.gave_up = 0; sh.poll_limit = poll_limit; }
     if (threadIdx.x < 3) sh.tail_key[threadIdx.x] = 0ull;
 }
 
@@ -473,7 +470,7 @@ __device__ __forceinline__ int find_cut_bin(const int* hist, int k, int* want, i
     return 16 * (63 - src) + 15 - at;
 }
 
-// Rank the members of the bin at the cut (lane j < cnt holds member j: key `mine`, slot `my_slot`) by (key
+// Rank the members of the bracket at the cut (lane j < cnt holds member j: key `mine`, slot `my_slot`) by (key
 // descending, slot ascending) with lane reads; returns the key and slot of the member that is last to be kept
 // (rank want - 1) and, in *kept_mask, the lanes whose members are kept: rank < want, or under the threshold rule
 // every member whose key is at least that member's.
@@ -493,21 +490,26 @@ __device__ __forceinline__ void rank_members(uint64_t mine, int my_slot, int cnt
     *kept_mask = __ballot(lane < cnt && (rank < want || (keep_ties && mine == *thr)));
 }
 
+__device__ __forceinline__ void empty_histogram(Shared& sh)
+{
+    for (int i = opaque_tid(); i < kBins; i += kSelThreads) sh.hist[i] = 0;
+}
+
 // Cut and ordered compaction of one level of more than kEachWaveSlots slots, its keys R per thread over the whole
 // workgroup: thread t takes slot x * 256 + t of the LDS copy in key[x] (0 = empty or not competing).  k =
 // k_of(n_valid) of the n_valid competing keys are kept, by (key descending, slot ascending); emit(pos, slot) is
 // called for each kept slot with its position in ascending slot order (positions at or beyond cap are dropped).
 // Returns the number kept, or -1, having emitted nothing, when this path does not apply (more than kFastMembers
 // keys share the bin at the cut).  Uniform over the workgroup: every thread must call it, after a barrier that
-// made `keys` complete.  sh.hist must be all zero and sh.n_mem zero on entry, and they are again on a return >= 0.
+// made `keys` complete.  sh.n_mem must be zero on entry, and it is again on a return >= 0.
 //
 // The kBins bins are LINEAR in key_float between the smallest and the largest key: a monotone map, so a higher bin
 // means a strictly larger score.  A scan from the top finds the bin the k-th largest key falls in, and the few
 // keys of that bin are ranked exactly by (key, slot).
 //
 // kPre: the thread's keys come in `pre` (the pull left them in registers, together with every wave's bounds and count
-// in sh.st_*, before its closing barrier): nothing is re-read and the first barrier here falls away.  Only for
-// levels in which every slot competes.
+// in sh.st_* and an empty histogram, before its closing barrier): nothing is re-read and the first barrier here falls
+// away.  Only for levels in which every slot competes.
 template <int R, bool kPre = false>
 __device__ __forceinline__ int cut_in_registers(uint64_t* keys, int n_slots, const ActiveRule& active, const KeepRule& k_of,
                                                 bool keep_ties, const EmitRule& emit, int cap, bool mark, Shared& sh,
@@ -528,17 +530,30 @@ __device__ __forceinline__ int cut_in_registers(uint64_t* keys, int n_slots, con
     } else {
         unsigned a = ~0u, b = 0u;
         int n = 0;
+empty_histogram(sh);
+        // (four keys at a time, all read before the first is looked at; slots beyond the level repeat its last one)
 #pragma unroll
-        for (int x = 0; x < R; ++x) {
-            key[x] = 0ull;
-            if (R > 4 && x * kSelThreads >= n_slots) continue;    // uniform (a branch per key only pays when there are many)
-            const int i = x * kSelThreads + tid;
-            key[x] = (i < n_slots && active(i)) ? keys[i] : 0ull;
-            const bool valid = key[x] != 0ull;
-            const unsigned hi = (unsigned)(key[x] >> 32);
-            a = valid ? min(a, hi) : a;
-            b = valid ? max(b, hi) : b;
-            n += __popcll(__ballot(valid));
+        for (int x0 = 0; x0 < R; x0 += 4) {
+            if (R > 4 && x0 * kSelThreads >= n_slots) {           // uniform
+#pragma unroll
+                for (int x = x0; x < x0 + 4 && x < R; ++x) key[x] = 0ull;
+                continue;
+            }
+#pragma unroll
+            for (int x = x0; x < x0 + 4 && x < R; ++x) key[x] = keys[min(x * kSelThreads + tid, n_slots - 1)];
+            if (active.mask != nullptr) {                         // uniform
+#pragma unroll
+                for (int x = x0; x < x0 + 4 && x < R; ++x) key[x] = active(min(x * kSelThreads + tid, n_slots - 1)) ? key[x] : 0ull;
+            }
+#pragma unroll
+            for (int x = x0; x < x0 + 4 && x < R; ++x) {
+                const bool valid = x * kSelThreads + tid < n_slots && key[x] != 0ull;
+                key[x] = valid ? key[x] : 0ull;
+                const unsigned hi = (unsigned)(key[x] >> 32);
+                a = valid ? min(a, hi) : a;
+                b = valid ? max(b, hi) : b;
+                n += __popcll(__ballot(valid));
+            }
         }
         a = wave_minmax32<true>(a);
         b = wave_minmax32<false>(b);
@@ -605,9 +620,7 @@ __device__ __forceinline__ int cut_in_registers(uint64_t* keys, int n_slots, con
     }
     __syncthreads();
 
-    // leave the histogram clean for the next level (its readers are past the barrier above)
-    for (int i = tid; i < kBins; i += kSelThreads) sh.hist[i] = 0;
-    if (tid == 0) sh.n_mem = 0;
+    if (tid == 0) sh.n_mem = 0;                                   // (everybody is past the barrier above)
 
     // every wave ranks the cut bin's keys: lane j takes member j and meets the others through lane reads
     uint64_t thr = 0;
@@ -650,21 +663,33 @@ __device__ __forceinline__ int cut_in_registers(uint64_t* keys, int n_slots, con
         const uint64_t ab = __ballot(a);
         const bool keep = a || (e && (key[x] > thr || (key[x] == thr && (slot <= thr_slot || keep_ties))));
         const int at = base + __popcll(ab & below) + before[x];
-        if (keep && at < cap) emit(at, slot);
+        if (keep && at < cap) {
+            if constexpr (R > 4) emit.out[at] = slot;
+            else emit(at, slot);
+        }
         if (mark && slot < n_slots && !keep) keys[slot] = 0ull;
     }
+    const int n_kept = sure_total + __popcll(kept_mask);
+    if constexpr (R > 4) {
+        // (what becomes of a slot is a chain of LDS reads: one for every key here would be seventeen in a row, most of them of
+        // keys that are not kept)
+        __syncthreads();
+        for (int i = tid; i < min(n_kept, cap); i += kSelThreads) emit(i, emit.out[i]);
+    }
     __syncthreads();                                              // mem_key / run_gt readers are done; emitted lists visible
-    return sure_total + __popcll(kept_mask);
+    return n_kept;
 }
 
-// Cut and ordered compaction of a level of at most 64 slots per wave of the workgroup.  EVERY wave holds all the keys
-// (slot x * 64 + lane in register x of each) and finds the cut for itself, so nothing is exchanged between waves; wave w
+// Cut and ordered compaction of a level of at most 64 R slots, R <= kSelWaves.  EVERY wave holds all the keys (slot
+// x * 64 + lane in register x of each) and finds the cut for itself, so nothing is exchanged between waves; wave w
 // then emits the slots of register w.  Same contract as cut_in_registers; returns -1, having emitted nothing, when more
 // than kFastMembers keys share the bracket at the cut.
+// Bound: the chain of instructions (times at the head of this file).
+template <int R>
 __device__ __forceinline__ int cut_in_each_wave(uint64_t* keys, int n_slots, const ActiveRule& active, const KeepRule& k_of,
                                                 bool keep_ties, const EmitRule& emit, int cap, bool mark, Shared& sh)
 {
-    constexpr int R = kSelWaves;
+    static_assert(R <= kSelWaves, "a wave emits one register");
     const int tid = opaque_tid(), lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint64_t below = __lanemask_lt();
@@ -694,7 +719,7 @@ __device__ __forceinline__ int cut_in_each_wave(uint64_t* keys, int n_slots, con
         n_valid += __popcll(__ballot(valid));
     }
     if (mark) __syncthreads();                        // every wave has its copy: the slots may be emptied
-    const int k = k_of(n_valid);
+    const int k = __builtin_amdgcn_readfirstlane(k_of(n_valid));
     float above = k > 0 ? -INFINITY : INFINITY;       // every score is kept, or none
     if (k > 0 && k < n_valid) {
         lo_h = (unsigned)__builtin_amdgcn_readlane((int)wave_minmax32<true>(lo_h), 63);
@@ -703,21 +728,23 @@ __device__ __forceinline__ int cut_in_each_wave(uint64_t* keys, int n_slots, con
         const auto count = [&](float t1, float t2, float t3, int& c1, int& c2, int& c3) {
 #pragma unroll
             for (int x = 0; x < R; ++x) {
-                c1 += __popcll(__ballot(f[x] > t1));
-                c2 += __popcll(__ballot(f[x] > t2));
-                c3 += __popcll(__ballot(f[x] > t3));
+                uint64_t b1 = __ballot(f[x] > t1), b2 = __ballot(f[x] > t2), b3 = __ballot(f[x] > t3);
+                asm("" : "+s"(b1), "+s"(b2), "+s"(b3));           // (three register pairs: through one, each compare waits for the count before)
+                c1 += __popcll(b1);
+                c2 += __popcll(b2);
+                c3 += __popcll(b3);
             }
         };
-        const Bracket br = search_cut(count, k, n_valid, key_float(lo_h), key_float(hi_h));
-        above = br.above;
-        if (br.cnt > kFastMembers) return -1;
-        if (br.cnt > 0) {
+        const Bracket cut = search_cut(count, k, n_valid, key_float(lo_h), key_float(hi_h));
+        above = cut.above;
+        if (cut.cnt > kFastMembers) return -1;
+        if (cut.cnt > 0) {
             // the keys of the bracket, one per lane (through LDS, in slot order; the waves write the same words), ranked
-            // against each other; the kept ones join the scores above the bracket
+            // against each other; the kept ones join the scores above
             int at0 = 0;
 #pragma unroll
             for (int x = 0; x < R; ++x) {
-                const bool e = f[x] > br.from && !(f[x] > above);
+                const bool e = f[x] > cut.from && !(f[x] > above);
                 const uint64_t eb = __ballot(e);
                 if (e) {
                     const int at = at0 + __popcll(eb & below);
@@ -727,14 +754,14 @@ __device__ __forceinline__ int cut_in_each_wave(uint64_t* keys, int n_slots, con
                 at0 += __popcll(eb);
             }
             __builtin_amdgcn_wave_barrier();
-            const uint64_t mine = lane < br.cnt ? sh.mem_key[lane] : 0ull;
-            const int my_slot = lane < br.cnt ? sh.mem_slot[lane] : 0;
+            const uint64_t mine = lane < cut.cnt ? sh.mem_key[lane] : 0ull;
+            const int my_slot = lane < cut.cnt ? sh.mem_slot[lane] : 0;
             uint64_t thr, kept_mask;
             int thr_slot;
-            rank_members(mine, my_slot, br.cnt, br.want, keep_ties, &thr, &thr_slot, &kept_mask);
+            rank_members(mine, my_slot, cut.cnt, cut.want, keep_ties, &thr, &thr_slot, &kept_mask);
 #pragma unroll
             for (int x = 0; x < R; ++x) {
-                const bool in = f[x] > br.from && !(f[x] > above) &&
+                const bool in = f[x] > cut.from && !(f[x] > above) &&
                                 (key[x] > thr || (key[x] == thr && (x * kWave + lane <= thr_slot || keep_ties)));
                 f[x] = in ? INFINITY : f[x];
             }
@@ -750,70 +777,31 @@ __device__ __forceinline__ int cut_in_each_wave(uint64_t* keys, int n_slots, con
         base = x == wave ? total : base;
         total += __popcll(kb);
     }
-    const int slot = wave * kWave + lane, at = base + __popcll(my_bits & below);
-    const bool keep = (my_bits >> lane) & 1ull;
-    if (keep && at < cap) emit(at, slot);
-    if (mark && slot < n_slots && !keep) keys[slot] = 0ull;
+    if (wave < R) {
+        const int slot = wave * kWave + lane, at = base + __popcll(my_bits & below);
+        const bool keep = (my_bits >> lane) & 1ull;
+        if (keep && at < cap) emit(at, slot);
+        if (mark && slot < n_slots && !keep) keys[slot] = 0ull;
+    }
     __syncthreads();                                  // emitted lists visible
     return total;
-}
-
-// A level of at most 64 slots: every wave holds all of them, one per lane, and wave w counts for each how many of the
-// keys in lanes w, w + kSelWaves, ... rank before it (key descending, slot ascending), with lane reads; the waves' counts
-// meet in LDS.  Same contract as cut_in_each_wave (it always applies).
-__device__ __forceinline__ int cut_one_lane_each(uint64_t* keys, int n_slots, const ActiveRule& active, const KeepRule& k_of,
-                                                 bool keep_ties, const EmitRule& emit, int cap, bool mark, Shared& sh)
-{
-    const int tid = opaque_tid(), lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    uint64_t key = keys[min(lane, n_slots - 1)];
-    if (active.mask != nullptr) {                     // uniform
-        const uint64_t on = active.mask[div_by(min(lane, n_slots - 1), active.inv)];
-        key = on != 0ull ? key : 0ull;
-    }
-    key = lane < n_slots ? key : 0ull;
-    const int n_valid = __popcll(__ballot(key != 0ull));
-    const int k = k_of(n_valid);
-    int rank = 0;                                     // of the keys this wave looks at, those that rank before the lane's own
-    auto meet = [&](int j) {                          // (an empty slot's key is 0: it is never before a real one)
-        const uint64_t kj = lane_read64(key, j);
-        rank += kj > key || (kj == key && j < lane && !keep_ties);
-    };
-    constexpr int kRun = 8;                           // straight-line: a taken branch costs as much as two keys
-    for (int j0 = wave; j0 < n_slots; j0 += kRun * kSelWaves) {
-#pragma unroll
-        for (int u = 0; u < kRun; ++u) meet((j0 + u * kSelWaves) & 63);
-    }
-    sh.rank[wave][lane] = rank;
-    __syncthreads();                                  // (every wave has its copy of the keys as well)
-    int before = 0;
-#pragma unroll
-    for (int w = 0; w < kSelWaves; ++w) before += sh.rank[w][lane];
-    // threshold rule: ties do not count, so a key is kept when fewer than k keys are strictly larger
-    const bool keep = key != 0ull && before < k;
-    const uint64_t kb = __ballot(keep);
-    if (wave == 0) {
-        const int at = __popcll(kb & __lanemask_lt());
-        if (keep && at < cap) emit(at, lane);
-        if (mark && lane < n_slots && !keep) keys[lane] = 0ull;
-    }
-    __syncthreads();
-    return __popcll(kb);
 }
 
 // The cut of one level whose keys are complete in `keys` (LDS; the caller's barrier has made them visible): picks
 // the path by the level's size.  Returns the number kept (what would have been emitted; positions at or beyond
 // `cap` are not written: the caller treats a count above cap as an overflow).  Every thread must call it.
-// have_pre: the pull handed this thread's four keys over in registers (pull_keys_regs), in `pre`.
+// kPulled: levels of more than kEachWaveSlots slots, up to four a thread, may have been handed over in registers
+// (pull_keys_regs), in `pre`, if have_pre says so.
+template <bool kPulled>
 __device__ __forceinline__ int cut_level(uint64_t* keys, int n_slots, const ActiveRule& active, const KeepRule& k_of,
                                          bool keep_ties, bool general, const EmitRule& emit, int cap, bool mark, Shared& sh,
                                          bool have_pre, const uint64_t (&pre)[4])
 {
     int n = -1;
     if (!general) {
-        if (n_slots <= kWave) n = cut_one_lane_each(keys, n_slots, active, k_of, keep_ties, emit, cap, mark, sh);
-        else if (n_slots <= kEachWaveSlots) n = cut_in_each_wave(keys, n_slots, active, k_of, keep_ties, emit, cap, mark, sh);
-        else if (n_slots <= 4 * kSelThreads && have_pre) n = cut_in_registers<4, true>(keys, n_slots, active, k_of, keep_ties, emit, cap, mark, sh, pre);
+        if (n_slots <= kWave) n = cut_in_each_wave<1>(keys, n_slots, active, k_of, keep_ties, emit, cap, mark, sh);
+        else if (n_slots <= kEachWaveSlots) n = cut_in_each_wave<kSelWaves>(keys, n_slots, active, k_of, keep_ties, emit, cap, mark, sh);
+        else if (kPulled && have_pre) n = cut_in_registers<4, true>(keys, n_slots, active, k_of, keep_ties, emit, cap, mark, sh, pre);
         else if (n_slots <= 4 * kSelThreads) n = cut_in_registers<4>(keys, n_slots, active, k_of, keep_ties, emit, cap, mark, sh, pre);
         else if (n_slots <= kRegsLarge * kSelThreads) n = cut_in_registers<kRegsLarge>(keys, n_slots, active, k_of, keep_ties, emit, cap, mark, sh, pre);
     }
@@ -826,11 +814,7 @@ __device__ __forceinline__ int cut_level(uint64_t* keys, int n_slots, const Acti
     }
     __syncthreads();
     const Cut cut = find_cut_radix(keys, n_slots, k_of, keep_ties, sh);
-    n = compact_kept(keys, n_slots, cut, emit, cap, mark, sh);
-    for (int i = tid; i < kBins; i += kSelThreads) sh.hist[i] = 0;
-    if (tid == 0) sh.n_mem = 0;
-    __syncthreads();
-    return n;
+    return compact_kept(keys, n_slots, cut, emit, cap, mark, sh);
 }
 
 // One work slot of a scoring pass: which unit it is (array 0 = grids, 1 = chunks, 2 = pages; unit -1 = the slot has no
@@ -955,8 +939,9 @@ __device__ __forceinline__ uint64_t poll_word(const uint64_t* word, int limit)
 // within the poll limit.
 template <int kPer, class WordOf>
 __device__ __forceinline__ bool pull_keys(const uint64_t* pub, const uint64_t* tail, int n, WordOf word_of, int ov_dest0,
-                                          int ov_word0, int ov_dest1, int ov_word1, uint64_t* keys, int limit)
+                                          int ov_word0, int ov_dest1, int ov_word1, uint64_t* keys, Shared& sh)
 {
+    const int limit = sh.poll_limit;
     bool ok = true;
     const int tid = opaque_tid();
     const int64_t tail_at = tail - pub;               // (one base: a choice between pointers becomes a flat access)
@@ -991,7 +976,9 @@ __device__ __forceinline__ bool pull_keys(const uint64_t* pub, const uint64_t* t
             if (j < n) keys[j] = (none[x] || v[x] == kAbsentKey) ? 0ull : v[x];
         }
     }
-    return __syncthreads_and(ok) != 0;
+    if (!ok) sh.gave_up = 1;
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(sh.gave_up) == 0;
 }
 
 // The same for a level of at most 1024 slots whose keys sit in slot order (item j lands in keys[j]): thread t polls
@@ -1000,10 +987,11 @@ __device__ __forceinline__ bool pull_keys(const uint64_t* pub, const uint64_t* t
 // barrier, so that cut_in_registers can start at once.
 template <class WordOf>
 __device__ __forceinline__ bool pull_keys_regs(const uint64_t* pub, const uint64_t* tail, int n, WordOf word_of, int ov_dest0,
-                                               int ov_word0, int ov_dest1, int ov_word1, uint64_t* keys, uint64_t (&key)[4],
-                                               int limit, Shared& sh)
+                                               int ov_word0, int ov_dest1, int ov_word1, uint64_t* keys, uint64_t (&key)[4], Shared& sh)
 {
+    const int limit = sh.poll_limit;
     bool ok = limit > 0;
+    empty_histogram(sh);
     const int tid = opaque_tid(), lane = tid & 63, wave = tid >> 6;
     const uint64_t* word[4];
     bool none[4];
@@ -1045,7 +1033,9 @@ __device__ __forceinline__ bool pull_keys_regs(const uint64_t* pub, const uint64
     a = wave_minmax32<true>(a);
     b = wave_minmax32<false>(b);
     if (lane == 63) { sh.st_min[wave] = a; sh.st_max[wave] = b; sh.st_cnt[wave] = cnt; }
-    return __syncthreads_and(ok) != 0;
+    if (!ok) sh.gave_up = 1;
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(sh.gave_up) == 0;
 }
 
 // The probe of a (sequence, KV head): the sum of the group's query rows in fp64, g ascending (Eq. 4 with
@@ -1182,8 +1172,7 @@ __device__ __forceinline__ PubLayout pub_layout(uint64_t* row_words, const Geom&
 // from the old vector is ignored).
 //
 // How a phase's work slots are scored is the Scorer's business: scorer(lo, hi, target, local, keys, pub, requested)
-// leaves the keys of the work slots [lo, hi) in keys[dest] (local) or publishes them in pub[dest]; a member's share of
-// a phase is a multiple of Scorer::kShareRound slots.
+// leaves the keys of the work slots [lo, hi) in keys[dest] (local) or publishes them in pub[dest].
 //
 // requested(): called once, by every thread, when the first phase's vectors are on their way and before any of them is
 // used: what needs values that were requested earlier (the probe) or asks for more (the rows of the tail units) goes
@@ -1224,6 +1213,7 @@ __device__ __forceinline__ bool cascade_with(const Scorer& scorer, int P, const 
     // merged: the chunks are scored together with the grids (one memory phase and one exchange fewer); eager: the pages
     // as well, so nothing is scored after the first phase
     constexpr bool eager = kMode == kEagerCluster, solo = kMode == kSolo;
+    constexpr bool by_regs = kMode == kCluster;       // (few levels of an eager launch are that large, and the code costs the others)
     const bool merged = eager || (!solo && sp.schedule == kMerged && !all_grids);
     const bool tail_on = tail_words != nullptr;
 
@@ -1239,9 +1229,10 @@ __device__ __forceinline__ bool cascade_with(const Scorer& scorer, int P, const 
         // (the member that refreshes the tail units has a chain of dependent loads of its own to get through
         // before the first cut: it takes no share of the first phase if the others can still cover it in one
         // memory round trip each)
-        const bool spare = tail_on && !local_first && ceil_div_i(n_work, C - 1) <= Scorer::kTrip;
-        const int sharers = spare ? C - 1 : C, mine = spare && m > refresher ? m - 1 : m;
-        const int per = local_first ? n_work : ceil_div_i(ceil_div_i(n_work, sharers), Scorer::kShareRound) * Scorer::kShareRound;
+        const int without = div_by(n_work + C - 2, sp.inv_others);
+        const bool spare = tail_on && !local_first && without <= Scorer::kTrip;
+        const int mine = spare && m > refresher ? m - 1 : m;
+        const int per = local_first ? n_work : spare ? without : div_by(n_work + C - 1, sp.inv_members);
         const int lo = local_first ? 0 : (spare && m == refresher) ? n_work : min(n_work, mine * per), hi = min(n_work, lo + per);
         // (one instance of the scoring loop per phase, each with straight-line slot arithmetic)
         if constexpr (eager) scorer(lo, hi, AllTarget{ng, ng + nc, s, (int)(pubs.pages - pubs.units), scorer.at}, false, keys, pubs.units, requested);
@@ -1274,7 +1265,7 @@ __device__ __forceinline__ bool cascade_with(const Scorer& scorer, int P, const 
         uint64_t* pub = level == 2 ? pubs.pages : pubs.units;
         const bool local = solo || (level == 0 && local_first);
         if (!eager && level > 0 && n_work > 0) {
-            const int per = local ? n_work : ceil_div_i(ceil_div_i(n_work, C), Scorer::kShareRound) * Scorer::kShareRound;
+            const int per = local ? n_work : div_by(n_work + C - 1, sp.inv_members);
             const int lo = local ? 0 : min(n_work, m * per), hi = min(n_work, lo + per);
             if (level == 1) scorer(lo, hi, target1, local, keys, pub, [] {});
             else scorer(lo, hi, target2, local, keys, pub, [] {});
@@ -1300,7 +1291,6 @@ __device__ __forceinline__ bool cascade_with(const Scorer& scorer, int P, const 
         int ov_dest0 = -1, ov_word0 = 0, ov_dest1 = -1, ov_word1 = 0;
         uint64_t pulled[4] = {0ull, 0ull, 0ull, 0ull};
         bool have_pulled = false;
-        const bool merged_phase = merged && level == 0;
         if (tail_on && n_work > 0) {
             if (level == 0) {
                 ov_dest0 = ng - 1; ov_word0 = 0;
@@ -1327,20 +1317,21 @@ __device__ __forceinline__ bool cascade_with(const Scorer& scorer, int P, const 
                 if (sh.flag == 0) return false;
             }
         } else if (!solo && n_work > 0) {
-            // (every non-local phase keeps its keys in slot order; a phase of up to 1024 slots hands them to the cut
-            // in registers)
+            // (every non-local phase keeps its keys in slot order; a phase of 257 to 1024 slots hands them to the cut in registers)
             const int off = level == 1 ? ng : 0;
             const int od0 = ov_dest0 >= 0 ? ov_dest0 - off : -1, od1 = ov_dest1 >= 0 ? ov_dest1 - off : -1;
-            bool ok;
             // (the words of a page phase are in slot order, or in page order when they were published ahead)
             const PageWords words{target2, level == 2 && eager};
-            if (n_work <= 4 * kSelThreads && !merged_phase) {
-                ok = pull_keys_regs(pub + off, tail_words, n_work, words, od0, ov_word0, od1, ov_word1, keys + off, pulled, sh.poll_limit, sh);
+            bool ok;
+            if (n_work <= kEachWaveSlots) {
+                ok = pull_keys<1>(pub + off, tail_words, n_work, words, od0, ov_word0, od1, ov_word1, keys + off, sh);
+            } else if (by_regs && n_work <= 4 * kSelThreads && !(merged && level == 0)) {
+                ok = pull_keys_regs(pub + off, tail_words, n_work, words, od0, ov_word0, od1, ov_word1, keys + off, pulled, sh);
                 have_pulled = true;
-            } else if (n_work <= 2 * kSelThreads) {
-                ok = pull_keys<2>(pub + off, tail_words, n_work, words, od0, ov_word0, od1, ov_word1, keys + off, sh.poll_limit);
+            } else if (n_work <= 4 * kSelThreads) {
+                ok = pull_keys<4>(pub + off, tail_words, n_work, words, od0, ov_word0, od1, ov_word1, keys + off, sh);
             } else {
-                ok = pull_keys<8>(pub + off, tail_words, n_work, words, od0, ov_word0, od1, ov_word1, keys + off, sh.poll_limit);
+                ok = pull_keys<eager ? 8 : kRegsLarge>(pub + off, tail_words, n_work, words, od0, ov_word0, od1, ov_word1, keys + off, sh);
             }
             if (!ok) return false;
         }
@@ -1379,8 +1370,7 @@ __device__ __forceinline__ bool cascade_with(const Scorer& scorer, int P, const 
                                 level == 1 ? inv_ng : inv_nc,
                                 (kPhys && level == 2) ? sel_phys : nullptr, (kPhys && level == 2) ? phys_by_slot : nullptr};
             const int cap = level == 0 ? sp.cap_kg : level == 1 ? sp.cap_kc : g.max_sel - s - w;
-            n_kept = cut_level(lk, n_slots, active, rule, keep_ties, general, emit, cap, level == 0 && merged, sh,
-                               have_pulled, pulled);
+            n_kept = cut_level<by_regs>(lk, n_slots, active, rule, keep_ties, general, emit, cap, level == 0 && merged, sh, have_pulled, pulled);
             if (n_kept > cap) { res->overflow = true; n_kept = cap; }
         }
         prof.mark(4 + 4 * level);
@@ -1394,14 +1384,19 @@ __device__ __forceinline__ bool cascade_with(const Scorer& scorer, int P, const 
 // The scorer of one (sequence, KV head): the probe is in registers.
 template <class T>
 struct HeadScorer {
-    static constexpr int kShareRound = 1;
     static constexpr int kTrip = kSelGroups * kFlyOf<T>;   // slots a member scores per memory round trip
     const T* pages_row;
     VecBases at;
     const double (&pr)[8];
     // (the three arrays lie in one summary buffer, behind one another, in whole vectors)
     __device__ __forceinline__ HeadScorer(const T* pages, const T* chunks, const T* grids, const double (&probe)[8])
-        : pages_row(pages), at{(int)((grids - pages) / kHeadDim), (int)((chunks - pages) / kHeadDim)}, pr(probe) {}
+        : pages_row(pages), at{vectors(pages, grids), vectors(pages, chunks)}, pr(probe) {}
+    static __device__ __forceinline__ int vectors(const T* from, const T* to)   // (to lies behind from)
+    {
+        constexpr int kLog = sizeof(T) == 4 ? 9 : 8;
+        static_assert(kHeadDim * sizeof(T) == 1u << kLog, "bytes of a vector");
+        return (int)((uint64_t)(reinterpret_cast<const char*>(to) - reinterpret_cast<const char*>(from)) >> kLog);
+    }
     template <class Target, class Requested>
     __device__ __forceinline__ void operator()(int lo, int hi, Target target, bool local, uint64_t* keys, uint64_t* pub,
                                                Requested requested) const
