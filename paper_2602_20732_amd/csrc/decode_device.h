@@ -342,7 +342,16 @@ __device__ __forceinline__ void run_tiles_with(WaveAcc<B>& acc, int t, int strid
         acc.l_run += __shfl_xor(acc.l_run, 32);
         return;
     }
-    if (t < n_tiles) {
+    if constexpr (kSingle) {
+        Tile<B> cur;
+        for (; t < n_tiles; t += stride) {
+            load_tile<B, kPhysList>(cur, t, n_pages, raw_cur, bt_row, phys_list, k_pool, v_pool, H, h, L, P, m16, grp);
+#pragma unroll
+            for (int s = 0; s < PPT; ++s) raw_cur[s] = raw_nxt[s];
+            fetch_ids<B, kList>(raw_nxt, t + 2 * stride, ids, max_sel);
+            acc.process(cur, scale_log2, grp);
+        }
+    } else if (t < n_tiles) {
         Tile<B> cur, nxt;
         load_tile<B, kPhysList>(cur, t, n_pages, raw_cur, bt_row, phys_list, k_pool, v_pool, H, h, L, P, m16, grp);
         for (; t < n_tiles; t += stride) {
@@ -362,7 +371,7 @@ __device__ __forceinline__ void run_tiles_with(WaveAcc<B>& acc, int t, int strid
     acc.l_run += __shfl_xor(acc.l_run, 32);
 }
 
-template <int B, bool kList, bool kPhysList>
+template <int B, bool kList, bool kPhysList, bool kSingle = false>
 __device__ __forceinline__ void run_tiles(WaveAcc<B>& acc, int t, int stride, int n_tiles, int n_pages,
                                           int (&raw_cur)[32 / B], int (&raw_nxt)[32 / B], const int32_t* ids, int max_sel,
                                           const int32_t* bt_row, const int32_t* phys_list, const uint16_t* k_pool,
@@ -371,7 +380,7 @@ __device__ __forceinline__ void run_tiles(WaveAcc<B>& acc, int t, int stride, in
 {
     NewToken<B> none;
     none.tile = -1;
-    run_tiles_with<B, kList, kPhysList, false>(acc, t, stride, n_tiles, n_pages, raw_cur, raw_nxt, ids, max_sel, bt_row,
+    run_tiles_with<B, kList, kPhysList, false, kSingle>(acc, t, stride, n_tiles, n_pages, raw_cur, raw_nxt, ids, max_sel, bt_row,
                                                phys_list, k_pool, v_pool, H, h, L, P, scale_log2, m16, grp, none, 1 << 30);
 }
 

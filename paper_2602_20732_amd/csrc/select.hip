@@ -57,7 +57,7 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(3))
 
     const PubLayout pubs = pub_layout(ws.keys + row * ws.key_stride, g);
     CascadeResult res;
-    const bool ok = cascade<kMode, false, T>(pages + row * g.max_pages * kHeadDim, chunks + row * g.max_chunks * kHeadDim,
+    const bool ok = cascade<kMode, false, T, false>(pages + row * g.max_pages * kHeadDim, chunks + row * g.max_chunks * kHeadDim,
                                       grids + row * g.max_grids * kHeadDim, pr, P, g, sp, pubs, m, C, m == 0, keys,
                                       kept_grids, kept_chunks, sel_pages, sh, &res, prof, nullptr, 0,
                                       [&] { if (sp.probe == CHESS_PROBE_QUERY) probe.sum(q_rows, g.group, pr); }, [] {}, k_fixed);

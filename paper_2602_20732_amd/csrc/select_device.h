@@ -825,8 +825,9 @@ struct SlotRef {
 };
 
 // Units a 16-lane group requests before it waits: one memory round trip covers kFly * 16 work slots of a workgroup.
-template <class T>
-constexpr int kFlyOf = sizeof(T) == 2 ? 16 : 8;      // (64 registers either way)
+// (64 registers either way; half of that where three workgroups share a compute unit)
+template <class T, bool kLean>
+constexpr int kFlyOf = (sizeof(T) == 2 ? 16 : 8) / (kLean ? 2 : 1);
 
 // One level of the sums over a group's 16 lanes, for two vectors at once: lanes whose bit (1 << kBit) is clear end with
 // a summed over the pair of lanes, the others with b.  Over the four levels each lane ends with the total of another
@@ -874,12 +875,11 @@ __device__ __forceinline__ double dot8_quad(const double (&pr)[8], const Vec<T>*
 // Bound: a memory round trip, then the instructions of the sums.  Four vectors' chains side by side and folded sums take a
 // quarter of the instructions of one vector after another with a DPP sum each (32 sequences of 16-32K, 8 layers: 283 ->
 // 268 us together with the reordered requests and the code split by cluster mode).
-template <class T, class Target, class Requested>
+template <class T, int kFly, class Target, class Requested>
 __device__ __forceinline__ void score_rows(const T* __restrict__ pages_row, int lo, int hi, Target target,
                                            const double (&pr)[8], bool local, uint64_t* lds_keys, uint64_t* pub,
                                            Requested requested)
 {
-    constexpr int kFly = kFlyOf<T>;
     const int tid = opaque_tid(), g16 = tid >> 4, ln = tid & 15;
     Vec<T> v[kFly];
     auto ask = [&](int s0) {
@@ -896,7 +896,7 @@ __device__ __forceinline__ void score_rows(const T* __restrict__ pages_row, int 
     requested();
     for (int s0 = lo; s0 < hi; s0 += kSelGroups * kFly) {
         if (s0 != lo) ask(s0);
-        // lane x of a group ends with the total of vector x (float: lanes x and x + 8)
+        // lane x of a group ends with the total of vector x (lanes x, x + kFly, ... where kFly < 16)
         double q[kFly / 4];
         q[0] = dot8_quad<T>(pr, v, ln);
 #pragma unroll
@@ -904,7 +904,7 @@ __device__ __forceinline__ void score_rows(const T* __restrict__ pages_row, int 
             q[y] = 0.0;
             if (s0 + kSelGroups * 4 * y < hi) q[y] = dot8_quad<T>(pr, v + 4 * y, ln);      // uniform over the workgroup
         }
-        double mine = fold_lanes<2>(q[0], q[1], ln);
+        double mine = fold_lanes<2>(q[0], q[kFly > 4 ? 1 : 0], ln);
         if constexpr (kFly == 16) mine = fold_lanes<3>(mine, fold_lanes<2>(q[2], q[3], ln), ln);
         else mine = fold_lanes<3>(mine, mine, ln);
         // one key conversion and one store serve all the vectors of the trip
@@ -1382,9 +1382,9 @@ __device__ __forceinline__ bool cascade_with(const Scorer& scorer, int P, const 
 }
 
 // The scorer of one (sequence, KV head): the probe is in registers.
-template <class T>
+template <class T, bool kLean>
 struct HeadScorer {
-    static constexpr int kTrip = kSelGroups * kFlyOf<T>;   // slots a member scores per memory round trip
+    static constexpr int kTrip = kSelGroups * kFlyOf<T, kLean>;   // slots a member scores per memory round trip
     const T* pages_row;
     VecBases at;
     const double (&pr)[8];
@@ -1401,11 +1401,11 @@ struct HeadScorer {
     __device__ __forceinline__ void operator()(int lo, int hi, Target target, bool local, uint64_t* keys, uint64_t* pub,
                                                Requested requested) const
     {
-        score_rows<T>(pages_row, lo, hi, target, pr, local, keys, pub, requested);
+        score_rows<T, kFlyOf<T, kLean>>(pages_row, lo, hi, target, pr, local, keys, pub, requested);
     }
 };
 
-template <int kMode, bool kPhys, class T, class ReqFn, class TailFn>
+template <int kMode, bool kPhys, class T, bool kLean, class ReqFn, class TailFn>
 __device__ __forceinline__ bool cascade(const T* __restrict__ pages_row, const T* __restrict__ chunks_row,
                                         const T* __restrict__ grids_row, const double (&pr)[8], int P, const Geom& g,
                                         const SelectParams& sp, const PubLayout& pubs, int m, int C, bool want_l3,
@@ -1415,7 +1415,7 @@ __device__ __forceinline__ bool cascade(const T* __restrict__ pages_row, const T
                                         const int32_t* __restrict__ bt_row = nullptr,
                                         int32_t* phys_by_slot = nullptr, int32_t* sel_phys = nullptr)
 {
-    const HeadScorer<T> scorer(pages_row, chunks_row, grids_row, pr);
+    const HeadScorer<T, kLean> scorer(pages_row, chunks_row, grids_row, pr);
     return cascade_with<kMode, kPhys>(scorer, P, g, sp, pubs, m, C, want_l3, keys, kept_grids, kept_chunks, sel_pages, sh, res,
                                       prof, tail_words, refresher, requested, refresh_tail, k_fixed, bt_row, phys_by_slot, sel_phys);
 }

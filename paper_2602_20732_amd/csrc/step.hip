@@ -127,9 +127,10 @@ struct TailUnits {
     }
 };
 
-// grid = (C, H_kv, batch); T = storage type of the summaries (float or bf16 bits); kMode: see cascade_with
-template <int B, class T, int kMode>
-__global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(2))) void step_kernel(StepArgs a, Geom g_args, SelectParams sp_args, SelectWs ws)
+// grid = (C, H_kv, batch); T = storage type of the summaries (float or bf16 bits); kMode: see cascade_with; kLean: three
+// workgroups on a compute unit instead of two (see launch_step)
+template <int B, class T, int kMode, bool kLean>
+__global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(kLean ? 3 : 2))) void step_kernel(StepArgs a, Geom g_args, SelectParams sp_args, SelectWs ws)
 {
     const Geom g = own_regs(g_args);
     const SelectParams sp = own_regs(sp_args);
@@ -186,9 +187,12 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(2))
     TailUnits<B, T> tail;
     auto requested = [&]() {                                          // (the first vectors to score are on their way)
         if (sp.probe == CHESS_PROBE_QUERY) probe.sum(q_rows, G, pr);
-        if (tail_on && m == refresher) tail.request(a.k_pool, tail_phys, pages_row, chunks_row, h, H, L, P, g);
+        if (!kLean && tail_on && m == refresher) tail.request(a.k_pool, tail_phys, pages_row, chunks_row, h, H, L, P, g);
     };
-    auto refresh_tail = [&]() { tail.finish(pages_row, chunks_row, grids_row, L, P, g, pr, fresh, tail_words, C > 1 && P > s + w, sh); };
+    auto refresh_tail = [&]() {
+        if (kLean) tail.request(a.k_pool, tail_phys, pages_row, chunks_row, h, H, L, P, g);   // (no registers for it before)
+        tail.finish(pages_row, chunks_row, grids_row, L, P, g, pr, fresh, tail_words, C > 1 && P > s + w, sh);
+    };
     __syncthreads();
     prof.mark(1);                                                     // prologue done
 
@@ -212,7 +216,7 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(2))
         int safety_phys = 0;
         if (safety_early && tid < s + w) safety_phys = bt_row[safety_lp];
         // kept pages and their physical pages go straight to their places in the list, behind the sinks
-        const bool ok = cascade<kMode, true, T>(pages_row, chunks_row, grids_row, pr, P, g, sp, pubs, m, C, m < D, keys, kept_grids,
+        const bool ok = cascade<kMode, true, T, kLean>(pages_row, chunks_row, grids_row, pr, P, g, sp, pubs, m, C, m < D, keys, kept_grids,
                                          kept_chunks, ids_l + s, sh, &res, prof, tail_words, refresher, requested, refresh_tail, k_fixed, bt_row,
                                          phys_by_slot, phys_l + s);
         if (!ok) {
@@ -257,7 +261,7 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(2))
     fetch_ids<B, true>(raw_nxt, t + stride, ids_l, max(n_sel, 1));
     WaveAcc<B> acc;
     acc.init(q_rows, G, m16, grp);
-    run_tiles<B, true, true>(acc, t, stride, n_tiles, n_sel, raw_cur, raw_nxt, ids_l, max(n_sel, 1), bt_row, phys_l, a.k_pool, a.v_pool, H, h, L, P,
+    run_tiles<B, true, true, kLean>(acc, t, stride, n_tiles, n_sel, raw_cur, raw_nxt, ids_l, max(n_sel, 1), bt_row, phys_l, a.k_pool, a.v_pool, H, h, L, P,
                  a.scale_log2, m16, grp);
     prof.mark(15);                                                    // tiles done
     const bool split_up = combine_waves<kStepWaves>(acc.o, acc.m_run, acc.l_run, dl, G, D, m, row * D, out_rows, a.ws_acc, a.ws_ml);
@@ -277,14 +281,20 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(2))
 }
 
 using StepKernel = void (*)(StepArgs, Geom, SelectParams, SelectWs);
+constexpr int kSoloLean = 3;                          // a cluster of one with three workgroups on a compute unit (see launch_step)
+constexpr int kStepModes = 4;
 static StepKernel step_kernel_of(int page_size, bool bf16, int mode)
 {
     // [page size 16 / 32][fp32 / bf16][mode]
-    static const StepKernel table[2][2][3] = {
-        {{step_kernel<16, float, kSolo>, step_kernel<16, float, kCluster>, step_kernel<16, float, kEagerCluster>},
-         {step_kernel<16, uint16_t, kSolo>, step_kernel<16, uint16_t, kCluster>, step_kernel<16, uint16_t, kEagerCluster>}},
-        {{step_kernel<32, float, kSolo>, step_kernel<32, float, kCluster>, step_kernel<32, float, kEagerCluster>},
-         {step_kernel<32, uint16_t, kSolo>, step_kernel<32, uint16_t, kCluster>, step_kernel<32, uint16_t, kEagerCluster>}}};
+    static const StepKernel table[2][2][kStepModes] = {
+        {{step_kernel<16, float, kSolo, false>, step_kernel<16, float, kCluster, false>, step_kernel<16, float, kEagerCluster, false>,
+          step_kernel<16, float, kSolo, true>},
+         {step_kernel<16, uint16_t, kSolo, false>, step_kernel<16, uint16_t, kCluster, false>, step_kernel<16, uint16_t, kEagerCluster, false>,
+          step_kernel<16, uint16_t, kSolo, true>}},
+        {{step_kernel<32, float, kSolo, false>, step_kernel<32, float, kCluster, false>, step_kernel<32, float, kEagerCluster, false>,
+          step_kernel<32, float, kSolo, true>},
+         {step_kernel<32, uint16_t, kSolo, false>, step_kernel<32, uint16_t, kCluster, false>, step_kernel<32, uint16_t, kEagerCluster, false>,
+          step_kernel<32, uint16_t, kSolo, true>}}};
     return table[page_size == 16 ? 0 : 1][bf16 ? 1 : 0][mode];
 }
 
@@ -298,11 +308,11 @@ size_t step_lds_bytes(const SelectParams& sp, int max_sel, int* union_off)
     return list + (sel > dec ? sel : dec);
 }
 
-// Workgroups of any mode that fit on a compute unit.
+// Workgroups of any mode that fit on a compute unit (the members of a cluster wait for each other).
 hipError_t step_occupancy(int page_size, bool bf16, int lds_bytes, int* blocks_per_cu)
 {
     int least = 0;
-    for (const int mode : {kSolo, kCluster, kEagerCluster}) {
+    for (int mode = 0; mode < kStepModes; ++mode) {
         int n = 0;
         const StepKernel kern = step_kernel_of(page_size, bf16, mode);
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
@@ -326,7 +336,13 @@ hipError_t launch_step(chess_ctx* ctx, const StepLaunch& sl, int batch, int clus
     a.union_off = union_off;
     a.refresh_tail = sl.refresh_tail;
     const dim3 grid(cluster, g.n_kv_heads, batch), block(kSelThreads);
-    const int mode = cluster == 1 ? kSolo : sp.schedule == kEager ? kEagerCluster : kCluster;
+    // Alone on their rows, more workgroups than two a compute unit would run in two rounds, the second nearly empty: from there on
+    // the kernel that fits three times (half the vectors in flight, no tile ahead, the tail unit's rows requested when they are
+    // needed: 151-168 registers instead of 205-224).  us a layer, two / three a compute unit: 576 rows of 8-16K 59.8 / 45.8,
+    // 768 of 4-21K 73.2 / 58.2 (ratios and bf16 vectors 52.7 / 39.4), 1024 of 8K 61.8 / 57.3, 1536 of 4-8K 79.6 / 67.9, 2048 of 4K
+    // 89.8 / 86.5.  Below, it depends: 512 of 8-16K 39.5 / 37.7, 512 of 16K with bf16 vectors 38.5 / 43.4, 256 of 16-32K 41.0 / 41.0.
+    const bool lean = (int64_t)batch * g.n_kv_heads > 2LL * ctx->n_cu;
+    const int mode = cluster == 1 ? (lean ? kSoloLean : kSolo) : sp.schedule == kEager ? kEagerCluster : kCluster;
     return launch(step_kernel_of(g.page_size, ctx->cfg.summary_dtype == CHESS_SUMMARY_BF16, mode), grid, block, lds_bytes, stream, a, g, sp, ws);
 }
 
