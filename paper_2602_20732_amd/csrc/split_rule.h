@@ -37,7 +37,10 @@ inline int64_t partial_rows(int n_cu, int64_t rows) { return 4LL * n_cu + rows; 
 // lengths, and splits chosen for the longest possible one cost a short sequence more than the dealing does (times there).
 // A page list (tens to hundreds of pages): the fixed latencies dominate, and the measured optimum (sweeps at batch
 // 1 .. 32, 21 .. 415 pages, G = 1 .. 7) is: no split once there is a (sequence, head) per compute unit; otherwise one
-// workgroup per compute unit, at least two tiles per workgroup, and at most 1.6 x the merge-balanced count.
+// workgroup per compute unit, at least two tiles per workgroup, at most 1.6 x the merge-balanced count, and no more splits
+// than the last one of them can ask for in one round trip (merge_splits): eight, or sixteen (twelve with more than four query
+// heads) for lists long enough that eight leave a wave several tiles.  us a reuse step, uncapped / capped: one sequence of
+// 32K 7.54 / 7.02, two of 32K 8.83 / 7.73, 128 pages with G = 1 10.9 / 8.7, 87 pages of 32 with G = 7 12.1 / 10.7.
 inline SplitShape choose_splits(const SplitLimits& c, int batch, int64_t max_list_pages, bool listed)
 {
     const int64_t tiles = std::max<int64_t>(1, cdiv(max_list_pages, c.tile_pages));
@@ -51,6 +54,7 @@ inline SplitShape choose_splits(const SplitLimits& c, int batch, int64_t max_lis
     if (listed) {
         ns = std::min<int64_t>(c.n_cu / pairs, cdiv(tiles, 2));
         ns = std::min<int64_t>(ns, (int64_t)std::llround(1.6 * balanced));
+        ns = std::min<int64_t>(ns, tiles <= 48 ? 8 : c.group > 4 ? 12 : 16);
         ns = std::max<int64_t>(ns, 1);
     } else {
         // all workgroups resident at once: a second round of workgroups would double a short kernel
