@@ -9,7 +9,10 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libchess.so")
 SOURCES = ["api.hip", "summarize.hip", "select.hip", "decode.hip", "step.hip", "shared.hip", "trigger.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-fno-gpu-rdc",
-         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-command-line-argument"]
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # the first arguments of a kernel (as far as they are pointers and numbers, not structs) are in registers when it starts:
+         # its first loads need no argument fetch (32 layers of a reuse step 236.5 -> 231.8 us)
+         "-mllvm", "-amdgpu-kernarg-preload-count=16", "-Wall", "-Wno-unused-command-line-argument"]
 
 
 def build(verbose: bool = False) -> str:

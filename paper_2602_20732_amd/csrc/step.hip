@@ -16,14 +16,11 @@ static_assert(kSelThreads % kWave == 0 && kSelThreads >= 256, "the fused step de
 constexpr int kStepWaves = kSelThreads / kWave;
 
 struct StepArgs {
-    const uint16_t* q;
     void* pages;             // summaries (fp32 or bf16): read; the tail units are rewritten when refresh_tail is set
     void* chunks;
     void* grids;
     const uint16_t* k_pool;
     const uint16_t* v_pool;
-    const int32_t* block_table;
-    const int32_t* seq_lens;
     int32_t* page_ids;       // may be null
     int32_t* n_selected;     // may be null
     float* out;
@@ -130,8 +127,15 @@ struct TailUnits {
 // grid = (C, H_kv, batch); T = storage type of the summaries (float or bf16 bits); kMode: see cascade_with; kLean: three
 // workgroups on a compute unit instead of two (see launch_step)
 template <int B, class T, int kMode, bool kLean>
-__global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(kLean ? 3 : 2))) void step_kernel(StepArgs a, Geom g_args, SelectParams sp_args, SelectWs ws)
+__global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(kLean ? 3 : 2))) void step_kernel(const uint16_t* __restrict__ q, const int32_t* __restrict__ seq_lens, const int32_t* __restrict__ block_table, int n_q_heads,
+                            int n_kv_heads, int group, int max_pages, int query_probe, StepArgs a, Geom g_args, SelectParams sp_args, SelectWs ws)
 {
+    // (what the first loads need comes in registers, ahead of the structs: see build.py)
+    const int L_raw = seq_lens[blockIdx.z];
+    const uint16_t* q_rows = q + ((size_t)blockIdx.z * n_q_heads + (size_t)blockIdx.y * group) * kHeadDim;
+    double pr[8];
+    ProbeRows<T> probe;
+    if (query_probe) probe.request(q_rows, 0, group);                 // before anything waits on the length
     const Geom g = own_regs(g_args);
     const SelectParams sp = own_regs(sp_args);
     constexpr int PPT = 32 / B;
@@ -150,22 +154,17 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(kLe
     // C members score; the first D of them go on to the cuts and the attention (all of them unless the schedule is eager)
     const int m = kMode == kSolo ? 0 : blockIdx.x, C = kMode == kSolo ? 1 : gridDim.x, D = kMode == kEagerCluster ? sp.deciders : C, h = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6, m16 = lane & 15, grp = lane >> 4;
-    const int G = g.group, H = g.n_kv_heads;
+    const int G = group, H = n_kv_heads;
     Prof prof;
     prof.mark(0);
     const size_t row = (size_t)b * H + h;
-    const uint16_t* q_rows = a.q + ((size_t)b * g.n_q_heads + (size_t)h * G) * kHeadDim;
-    float* out_rows = a.out + ((size_t)b * g.n_q_heads + (size_t)h * G) * kHeadDim;
-    const int L_raw = a.seq_lens[b];
+    float* out_rows = a.out + ((size_t)b * n_q_heads + (size_t)h * G) * kHeadDim;
     const int k_fixed = fixed_budget(sp, g, b);
-    double pr[8];
-    ProbeRows<T> probe;
-    if (sp.probe == CHESS_PROBE_QUERY) probe.request(q_rows, 0, G);   // before anything waits on the length
     init_shared(sh, sp.poll_limit);
     const int L = min(max(L_raw, 0), g.max_pages * B);
     const int P = (L + B - 1) / B;
     const int s = sp.sink, w = sp.window;
-    const int32_t* bt_row = a.block_table + (size_t)b * g.max_pages;
+    const int32_t* bt_row = block_table + (size_t)b * max_pages;
     if (P == 0) {                                                     // empty sequence: no pages, zero output
         if (m == 0) {
             if (a.page_ids) for (int i = tid; i < g.max_sel; i += kSelThreads) a.page_ids[row * g.max_sel + i] = -1;
@@ -177,7 +176,7 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(kLe
     T* pages_row = static_cast<T*>(a.pages) + row * g.max_pages * kHeadDim;
     T* chunks_row = static_cast<T*>(a.chunks) + row * g.max_chunks * kHeadDim;
     T* grids_row = static_cast<T*>(a.grids) + row * g.max_grids * kHeadDim;
-    if (sp.probe == CHESS_PROBE_ANCHOR) load_anchor<T>(pages_row, P, w, pr);
+    if (!query_probe) load_anchor<T>(pages_row, P, w, pr);
     // one member refreshes the tail units, a helper if there are any: its block-table entry is requested now
     const int refresher = D < C ? C - 1 : 0;
     const bool tail_on = a.refresh_tail != 0;
@@ -186,7 +185,7 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(kLe
     if (tail_on && m == refresher) tail_phys = bt_row[P - 1];
     TailUnits<B, T> tail;
     auto requested = [&]() {                                          // (the first vectors to score are on their way)
-        if (sp.probe == CHESS_PROBE_QUERY) probe.sum(q_rows, G, pr);
+        if (query_probe) probe.sum(q_rows, G, pr);
         if (!kLean && tail_on && m == refresher) tail.request(a.k_pool, tail_phys, pages_row, chunks_row, h, H, L, P, g);
     };
     auto refresh_tail = [&]() {
@@ -280,7 +279,7 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(kLe
 #endif
 }
 
-using StepKernel = void (*)(StepArgs, Geom, SelectParams, SelectWs);
+using StepKernel = void (*)(const uint16_t*, const int32_t*, const int32_t*, int, int, int, int, int, StepArgs, Geom, SelectParams, SelectWs);
 constexpr int kSoloLean = 3;                          // a cluster of one with three workgroups on a compute unit (see launch_step)
 constexpr int kStepModes = 4;
 static StepKernel step_kernel_of(int page_size, bool bf16, int mode)
@@ -329,8 +328,8 @@ hipError_t launch_step(chess_ctx* ctx, const StepLaunch& sl, int batch, int clus
 {
     const Geom& g = ctx->geom;
     StepArgs a;
-    a.q = sl.q; a.pages = sl.pages; a.chunks = sl.chunks; a.grids = sl.grids; a.k_pool = sl.k_pool; a.v_pool = sl.v_pool;
-    a.block_table = sl.block_table; a.seq_lens = sl.seq_lens; a.page_ids = sl.page_ids; a.n_selected = sl.n_selected;
+    a.pages = sl.pages; a.chunks = sl.chunks; a.grids = sl.grids; a.k_pool = sl.k_pool; a.v_pool = sl.v_pool;
+    a.page_ids = sl.page_ids; a.n_selected = sl.n_selected;
     a.out = sl.out; a.ws_acc = sl.ws_acc; a.ws_ml = sl.ws_ml; a.arrivals = sl.arrivals;
     a.scale_log2 = ctx->sm_scale * 1.4426950408889634f;
     a.union_off = union_off;
@@ -343,7 +342,9 @@ hipError_t launch_step(chess_ctx* ctx, const StepLaunch& sl, int batch, int clus
     // 89.8 / 86.5.  Below, it depends: 512 of 8-16K 39.5 / 37.7, 512 of 16K with bf16 vectors 38.5 / 43.4, 256 of 16-32K 41.0 / 41.0.
     const bool lean = (int64_t)batch * g.n_kv_heads > 2LL * ctx->n_cu;
     const int mode = cluster == 1 ? (lean ? kSoloLean : kSolo) : sp.schedule == kEager ? kEagerCluster : kCluster;
-    return launch(step_kernel_of(g.page_size, ctx->cfg.summary_dtype == CHESS_SUMMARY_BF16, mode), grid, block, lds_bytes, stream, a, g, sp, ws);
+    return launch(step_kernel_of(g.page_size, ctx->cfg.summary_dtype == CHESS_SUMMARY_BF16, mode), grid, block, lds_bytes, stream,
+                  sl.q, sl.seq_lens, sl.block_table, g.n_q_heads, g.n_kv_heads, g.group, g.max_pages, sp.probe == CHESS_PROBE_QUERY ? 1 : 0, a, g,
+                  sp, ws);
 }
 
 }  // namespace chess
