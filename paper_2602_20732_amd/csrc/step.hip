@@ -32,6 +32,31 @@ struct StepArgs {
     int32_t refresh_tail;    // recompute the summaries of the tail page, its chunk and its grid first
 };
 
+// The kernel's arguments as they lie in memory.
+struct StepKernarg {
+    const void* q;
+    const void* seq_lens;
+    const void* block_table;
+    int32_t n_q_heads, n_kv_heads, group, max_pages, query_probe;
+    StepArgs a;
+};
+
+// StepArgs read again where they are needed: what only the attention uses would otherwise be in scalar registers -- or, as there are
+// too few, saved and restored -- all through the selection (lane reads in the eager kernel's code: 930, so 440).  us, kept /
+// read again: eager 1 x 4K 15.9 / 15.1, 32 layers of 1 x 32K 663 / 639; lean, reselection of 96 sequences, 116.1 / 109.0; but solo, 8
+// layers of 32 x 16-32K, 259.8 / 262.8 and in clusters 8 x 128K 82.6 / 84.1: those two keep them.
+template <bool kAgain>
+__device__ __forceinline__ StepArgs late_args(const StepArgs& a)
+{
+    if constexpr (!kAgain) return a;
+    typedef __attribute__((address_space(4))) const char* kernarg;
+    kernarg p = (kernarg)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));                       // (not the loads the kernel began with)
+    StepArgs r;
+    __builtin_memcpy(&r, (const void*)(p + offsetof(StepKernarg, a)), sizeof(r));
+    return r;
+}
+
 // The per-step refresh of the summaries (Sec. 3.1, Eq. 1-2) of the tail page, its chunk and its grid, done by one
 // workgroup per (sequence, KV head) inside the step: thread c < 128 owns column c and adds in the same order as
 // the summarize kernel (tokens, then the chunk's pages, then the grid's chunks, ascending, fp64, one rounding to
@@ -158,7 +183,6 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(kLe
     Prof prof;
     prof.mark(0);
     const size_t row = (size_t)b * H + h;
-    float* out_rows = a.out + ((size_t)b * n_q_heads + (size_t)h * G) * kHeadDim;
     const int k_fixed = fixed_budget(sp, g, b);
     init_shared(sh, sp.poll_limit);
     const int L = min(max(L_raw, 0), g.max_pages * B);
@@ -169,7 +193,7 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(kLe
         if (m == 0) {
             if (a.page_ids) for (int i = tid; i < g.max_sel; i += kSelThreads) a.page_ids[row * g.max_sel + i] = -1;
             if (a.n_selected && tid == 0) a.n_selected[row] = 0;
-            for (int i = tid; i < G * kHeadDim; i += kSelThreads) out_rows[i] = 0.f;
+            for (int i = tid; i < G * kHeadDim; i += kSelThreads) (a.out + ((size_t)b * n_q_heads + (size_t)h * G) * kHeadDim)[i] = 0.f;
         }
         return;
     }
@@ -245,9 +269,11 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(kLe
         }
     }
     __syncthreads();
+    const StepArgs late = late_args<kMode == kEagerCluster || kLean>(a);
+    float* late_out = late.out + ((size_t)b * n_q_heads + (size_t)h * G) * kHeadDim;
     if (m == 0) {
-        if (a.page_ids) for (int i = tid; i < g.max_sel; i += kSelThreads) a.page_ids[row * g.max_sel + i] = i < n_sel ? ids_l[i] : -1;
-        if (a.n_selected && tid == 0) a.n_selected[row] = n_sel;
+        if (late.page_ids) for (int i = tid; i < g.max_sel; i += kSelThreads) late.page_ids[row * g.max_sel + i] = i < n_sel ? ids_l[i] : -1;
+        if (late.n_selected && tid == 0) late.n_selected[row] = n_sel;
     }
     prof.mark(14);                                                    // list built
 
@@ -260,18 +286,18 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(kLe
     fetch_ids<B, true>(raw_nxt, t + stride, ids_l, max(n_sel, 1));
     WaveAcc<B> acc;
     acc.init(q_rows, G, m16, grp);
-    run_tiles<B, true, true, kLean>(acc, t, stride, n_tiles, n_sel, raw_cur, raw_nxt, ids_l, max(n_sel, 1), bt_row, phys_l, a.k_pool, a.v_pool, H, h, L, P,
-                 a.scale_log2, m16, grp);
+    run_tiles<B, true, true, kLean>(acc, t, stride, n_tiles, n_sel, raw_cur, raw_nxt, ids_l, max(n_sel, 1), bt_row, phys_l, late.k_pool, late.v_pool, H, h, L, P,
+                 late.scale_log2, m16, grp);
     prof.mark(15);                                                    // tiles done
-    const bool split_up = combine_waves<kStepWaves>(acc.o, acc.m_run, acc.l_run, dl, G, D, m, row * D, out_rows, a.ws_acc, a.ws_ml);
+    const bool split_up = combine_waves<kStepWaves>(acc.o, acc.m_run, acc.l_run, dl, G, D, m, row * D, late_out, late.ws_acc, late.ws_ml);
     prof.mark(16);                                                    // partial published (or, alone, the output written)
     // (profiling builds keep two timelines per row: member 0's and that of the member that merges)
     const int n_helpers = P <= s + w ? 0 : C - D;                     // (without a selection they have left)
-    const int last = split_up || n_helpers > 0 ? arrive_of_two(a.arrivals + row, true, D, n_helpers, &sh.flag) : 0;
+    const int last = split_up || n_helpers > 0 ? arrive_of_two(late.arrivals + row, true, D, n_helpers, &sh.flag) : 0;
     prof.mark(17);
     // every member is done with the key words (the stores' way to memory hides behind the merge)
     if (last & kLastOfAll) clear_published(pubs, res, tail_words);
-    if (split_up && (last & kLastDecider)) merge_splits<kStepWaves>(G, D, row * D, out_rows, a.ws_acc, a.ws_ml);
+    if (split_up && (last & kLastDecider)) merge_splits<kStepWaves>(G, D, row * D, late_out, late.ws_acc, late.ws_ml);
 #ifdef CHESS_PROF
     prof.mark(18);
     if (tid == 0 && (!split_up || (last & kLastDecider))) prof.store(ws.prof + (row * 2 + 1) * Prof::kSlots);
