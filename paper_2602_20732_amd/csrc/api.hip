@@ -584,18 +584,23 @@ int chess_decode_step(chess_ctx* ctx, const void* q, const void* k_pool, const v
     const size_t lds = chess::step_lds_bytes(sp, ctx->geom.max_sel, &union_off);
     if (lds + 8192 > (size_t)ctx->lds_per_block) return CHESS_ENOTSUP;
 
-    if (ctx->step_occ_lds != (int)lds) {
-        int blocks = 0;
-        if (chess::step_occupancy(ctx->geom.page_size, ctx->cfg.summary_dtype == CHESS_SUMMARY_BF16, (int)lds, &blocks) != hipSuccess) return CHESS_EHIP;
-        ctx->step_occ_lds = (int)lds;
-        ctx->step_occ_blocks = blocks;
-    }
-    if (ctx->step_occ_blocks < 1) return CHESS_ENOTSUP;
+    // (rows that are a workgroup's own wait for nobody: nothing has to be asked of the device for them)
     const int64_t pairs = (int64_t)batch * ctx->geom.n_kv_heads;
-    const int64_t capacity = (int64_t)ctx->step_occ_blocks * ctx->n_cu;
-    int64_t cluster = choose_cluster(ctx, pairs, capacity);
-    if (ctx->force_cluster > 0) cluster = std::min<int64_t>(ctx->force_cluster, capacity / pairs);
-    cluster = ctx->cfg.shared_device != 0 ? 1 : clampi(cluster, 1, chess::kSelMaxCluster);
+    const bool alone = ctx->cfg.shared_device != 0 || (ctx->force_cluster <= 0 && pairs >= ctx->n_cu);
+    int64_t cluster = 1, capacity = pairs;
+    if (!alone) {
+        if (ctx->step_occ_lds != (int)lds) {
+            int blocks = 0;
+            if (chess::step_occupancy(ctx->geom.page_size, ctx->cfg.summary_dtype == CHESS_SUMMARY_BF16, (int)lds, &blocks) != hipSuccess) return CHESS_EHIP;
+            ctx->step_occ_lds = (int)lds;
+            ctx->step_occ_blocks = blocks;
+        }
+        if (ctx->step_occ_blocks < 1) return CHESS_ENOTSUP;
+        capacity = (int64_t)ctx->step_occ_blocks * ctx->n_cu;
+        cluster = choose_cluster(ctx, pairs, capacity);
+        if (ctx->force_cluster > 0) cluster = std::min<int64_t>(ctx->force_cluster, capacity / pairs);
+        cluster = clampi(cluster, 1, chess::kSelMaxCluster);
+    }
     // pages the lists can hold
     const int64_t listed = std::min<int64_t>(ctx->geom.max_sel, (int64_t)sp.sink + sp.window + sp.most_kp);
     if (!choose_eager(ctx, pairs, capacity, cdiv(listed, chess::kTileTokens / ctx->geom.page_size), &cluster, &sp))

@@ -333,19 +333,17 @@ size_t step_lds_bytes(const SelectParams& sp, int max_sel, int* union_off)
     return list + (sel > dec ? sel : dec);
 }
 
-// Workgroups of any mode that fit on a compute unit (the members of a cluster wait for each other).
+// Workgroups that fit on a compute unit, of the kernels whose workgroups wait for each other.
 hipError_t step_occupancy(int page_size, bool bf16, int lds_bytes, int* blocks_per_cu)
 {
-    int least = 0;
-    for (int mode = 0; mode < kStepModes; ++mode) {
-        int n = 0;
+    int fit[2] = {0, 0};
+    for (const int mode : {kCluster, kEagerCluster}) {
         const StepKernel kern = step_kernel_of(page_size, bf16, mode);
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
-        if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kern, kSelThreads, lds_bytes);
+        if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit[mode == kEagerCluster], kern, kSelThreads, lds_bytes);
         if (e != hipSuccess) return e;
-        least = mode == kSolo || n < least ? n : least;
     }
-    *blocks_per_cu = least;
+    *blocks_per_cu = fit[0] < fit[1] ? fit[0] : fit[1];
     return hipSuccess;
 }
 
@@ -368,7 +366,12 @@ hipError_t launch_step(chess_ctx* ctx, const StepLaunch& sl, int batch, int clus
     // 89.8 / 86.5.  Below, it depends: 512 of 8-16K 39.5 / 37.7, 512 of 16K with bf16 vectors 38.5 / 43.4, 256 of 16-32K 41.0 / 41.0.
     const bool lean = (int64_t)batch * g.n_kv_heads > 2LL * ctx->n_cu;
     const int mode = cluster == 1 ? (lean ? kSoloLean : kSolo) : sp.schedule == kEager ? kEagerCluster : kCluster;
-    return launch(step_kernel_of(g.page_size, ctx->cfg.summary_dtype == CHESS_SUMMARY_BF16, mode), grid, block, lds_bytes, stream,
+    const StepKernel kern = step_kernel_of(g.page_size, ctx->cfg.summary_dtype == CHESS_SUMMARY_BF16, mode);
+    if (lds_bytes > 48 * 1024) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+        if (e != hipSuccess) return e;
+    }
+    return launch(kern, grid, block, lds_bytes, stream,
                   sl.q, sl.seq_lens, sl.block_table, g.n_q_heads, g.n_kv_heads, g.group, g.max_pages, sp.probe == CHESS_PROBE_QUERY ? 1 : 0, a, g,
                   sp, ws);
 }
