@@ -231,7 +231,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(3))) vo
     float* out_rows = out + ((size_t)b * g.n_q_heads + (size_t)h * G) * kHeadDim;
     if (!combine_waves<NW>(acc.o, acc.m_run, acc.l_run, lds, G, ns, split, part0, out_rows, ws_acc, ws_ml)) return;
     if (!arrive_last(arrivals + row, ns, &lds_last)) return;
-    merge_splits<NW>(G, ns, part0, out_rows, ws_acc, ws_ml);
+    if constexpr (kDealt) {                           // (the same in every lane, which the compiler cannot tell)
+        ns = own_reg(__builtin_amdgcn_readfirstlane(ns));
+        part0 = own_reg((unsigned)__builtin_amdgcn_readfirstlane((int)part0));
+    }
+    merge_splits<NW, kDealt ? kMergeDealt : kMergePlain>(G, ns, part0, out_rows, ws_acc, ws_ml);
 }
 
 // The step between reselections (Sec. 3.3) in one launch: attention over the kept list for the sequence WITH the
@@ -311,7 +315,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
             n_selected[row] = n_stored + 1;
         }
     }
-    if (split_up) merge_splits<NW>(G, n_splits, row * n_splits, out_rows, ws_acc, ws_ml);
+    if (split_up) merge_splits<NW, kMergePlain>(G, n_splits, row * n_splits, out_rows, ws_acc, ws_ml);
 }
 
 hipError_t launch_reuse(chess_ctx* ctx, const uint16_t* q, const uint16_t* k_new, const uint16_t* v_new, uint16_t* k_pool,

@@ -450,34 +450,40 @@ __device__ __forceinline__ bool combine_waves(const f32x4 (&o)[8], float m_run, 
 // out = sum_s acc_s 2^(m_s - M) / sum_s l_s 2^(m_s - M), always in split order, so the result does not
 // depend on which workgroup happens to be last.  A thread owns kItems pairs of adjacent outputs and derives their
 // heads' M and denominator itself from the (m, l) pairs (the threads of a head read the same words), so the partial
-// rows and the (m, l) pairs are requested together, kChunk splits of every pair at a time: no LDS, no barrier.
-// Bound: memory round trips.
-template <int NW, int kItems, int kChunk>
+// rows and the (m, l) pairs are requested together, kChunk splits of every pair at a time: no LDS, no barrier.  n_splits
+// and part0 have to be in scalar registers (kept per lane, an address costs 64-bit multiplies and a skipped split its selects).
+// Bound: memory round trips and, as the code runs once or a few times, its length; splits beyond the last are not asked for
+// where that would be more than kGroup - 1 requests (repeats of one row from all workgroups at once: 9 sequences of 16K with
+// sixteen heads took 53 instead of 48 us with eight of them).
+template <int NW, int kItems, int kChunk, int kGroup>
 __device__ __forceinline__ void merge_splits_by(int G, int n_splits, size_t part0, float* __restrict__ out_rows,
                                                 const float* __restrict__ ws_acc, const float* __restrict__ ws_ml)
 {
-    const uint64_t* acc_g = reinterpret_cast<const uint64_t*>(ws_acc);
-    const uint64_t* ml_g = reinterpret_cast<const uint64_t*>(ws_ml);
+    const uint64_t* acc_g = reinterpret_cast<const uint64_t*>(ws_acc) + part0 * G * (kHeadDim / 2);
+    const uint64_t* ml_g = reinterpret_cast<const uint64_t*>(ws_ml) + part0 * G;
     const int n_items = G * (kHeadDim / 2);
     for (int idx = threadIdx.x; idx < n_items; idx += 64 * NW * kItems) {
-        int head[kItems], d2[kItems];
+        unsigned item[kItems];                         // head * (kHeadDim / 2) + pair, in a partial row as in out_rows
         float M[kItems], l[kItems], a0[kItems], a1[kItems];
 #pragma unroll
         for (int y = 0; y < kItems; ++y) {
-            const int i = min(idx + y * 64 * NW, n_items - 1);    // (a pair beyond the last repeats it and is not stored)
-            head[y] = i / (kHeadDim / 2);
-            d2[y] = i % (kHeadDim / 2);
+            item[y] = min(idx + y * 64 * NW, n_items - 1);        // (a pair beyond the last repeats it and is not stored)
             M[y] = kNegBig; l[y] = 0.f; a0[y] = 0.f; a1[y] = 0.f;
         }
         for (int s0 = 0; s0 < n_splits; s0 += kChunk) {
             uint64_t v[kItems][kChunk], ml[kItems][kChunk];
 #pragma unroll
-            for (int y = 0; y < kItems; ++y) {
+            for (int x0 = 0; x0 < kChunk; x0 += kGroup) {
+                if (x0 == 0 || s0 + x0 < n_splits) {
 #pragma unroll
-                for (int x = 0; x < kChunk; ++x) {
-                    const size_t pr = (part0 + min(s0 + x, n_splits - 1)) * G + head[y];
-                    ml[y][x] = observe_u64(ml_g + pr);
-                    v[y][x] = observe_u64(acc_g + pr * (kHeadDim / 2) + d2[y]);
+                    for (int x = x0; x < x0 + kGroup; ++x) {
+                        const int at = min(s0 + x, n_splits - 1) * G;
+#pragma unroll
+                        for (int y = 0; y < kItems; ++y) {
+                            ml[y][x] = observe_u64(ml_g + at + item[y] / (kHeadDim / 2));
+                            v[y][x] = observe_u64(acc_g + (int64_t)at * (kHeadDim / 2) + item[y]);
+                        }
+                    }
                 }
             }
             // running maximum over the splits seen so far; what has been summed is rescaled to it
@@ -506,24 +512,25 @@ __device__ __forceinline__ void merge_splits_by(int G, int n_splits, size_t part
 #pragma unroll
         for (int y = 0; y < kItems; ++y) {
             const float inv = l[y] > 0.f ? 1.f / l[y] : 0.f;
-            if (idx + y * 64 * NW < n_items)
-                *reinterpret_cast<float2*>(out_rows + (size_t)head[y] * kHeadDim + 2 * d2[y]) = make_float2(a0[y] * inv, a1[y] * inv);
+            if (idx + y * 64 * NW < n_items) reinterpret_cast<float2*>(out_rows)[item[y]] = make_float2(a0[y] * inv, a1[y] * inv);
         }
     }
 }
 
-// More than a pair a thread (G > NW): two at once.  More than eight splits: up to sixteen (two pairs: twelve) at once.
-template <int NW>
+// Who merges: a list or one sequence's every page (any number of splits), every page dealt by length, or the fused step (at
+// most twelve splits).  More than a pair a thread (G > NW): two at once.  us, eight / twelve splits of both at once: the step,
+// 28 query and 4 KV heads, pages of 32, 1 x 64K 23.7 / 22.9, 1 x 256K 36.0 / 35.0; every page, 2 sequences of 11-90K 35.4 / 36.4.
+// One pair: eight splits at once where they are dealt (a sequence of 8K in a ragged batch has 23 splits: 22.1 / 22.5 us with
+// sixteen), one round trip for up to eight, and sixteen at once beyond (one sequence of 16K, G = 1: 24.2 / 22.7 us).
+enum MergeUse : int { kMergePlain, kMergeDealt, kMergeStep };
+template <int NW, int kUse>
 __device__ __forceinline__ void merge_splits(int G, int n_splits, size_t part0, float* __restrict__ out_rows,
                                              const float* __restrict__ ws_acc, const float* __restrict__ ws_ml)
 {
-    if (G > NW) {
-        if (n_splits <= 6) merge_splits_by<NW, 2, 6>(G, n_splits, part0, out_rows, ws_acc, ws_ml);
-        else merge_splits_by<NW, 2, 12>(G, n_splits, part0, out_rows, ws_acc, ws_ml);
-    } else {
-        if (n_splits <= 8) merge_splits_by<NW, 1, 8>(G, n_splits, part0, out_rows, ws_acc, ws_ml);
-        else merge_splits_by<NW, 1, 16>(G, n_splits, part0, out_rows, ws_acc, ws_ml);
-    }
+    if (G > NW) merge_splits_by<NW, 2, kUse == kMergeStep ? 12 : 8, kUse == kMergeStep ? 4 : 2>(G, n_splits, part0, out_rows, ws_acc, ws_ml);
+    else if (kUse == kMergeDealt) merge_splits_by<NW, 1, 8, 4>(G, n_splits, part0, out_rows, ws_acc, ws_ml);
+    else if (n_splits <= 8) merge_splits_by<NW, 1, 8, 8>(G, n_splits, part0, out_rows, ws_acc, ws_ml);
+    else merge_splits_by<NW, 1, 16, 8>(G, n_splits, part0, out_rows, ws_acc, ws_ml);
 }
 
 }  // namespace chess

@@ -1,0 +1,64 @@
+"""What the compiler made of the kernels, read from the code objects in the built library: things that cost time without
+changing a result."""
+from __future__ import annotations
+
+import os
+import re
+import struct
+import subprocess
+
+import pytest
+
+import paper_2602_20732_amd as pk
+
+READELF = "/opt/rocm/llvm/bin/llvm-readelf"
+pytestmark = pytest.mark.skipif(not os.path.exists(READELF), reason="llvm-readelf of the ROCm toolchain is not there")
+
+
+def code_objects(path):
+    """The gfx950 code objects bundled into a library."""
+    blob = open(path, "rb").read()
+    magic, at = b"__CLANG_OFFLOAD_BUNDLE__", 0
+    while (at := blob.find(magic, at)) >= 0:
+        (n,) = struct.unpack_from("<Q", blob, at + 24)
+        p = at + 32
+        for _ in range(n):
+            off, size, name = struct.unpack_from("<QQQ", blob, p)
+            if b"gfx950" in blob[p + 24:p + 24 + name] and size:
+                yield blob[at + off:at + off + size]
+            p += 24 + name
+        at += 24
+
+
+@pytest.fixture(scope="module")
+def listings(tmp_path_factory):
+    """(symbols, notes) of every code object, names demangled."""
+    if not os.path.exists(pk.library_path()):
+        from paper_2602_20732_amd.build import build
+        build()
+    out = []
+    for i, obj in enumerate(code_objects(pk.library_path())):
+        f = tmp_path_factory.mktemp("co") / f"{i}.co"
+        f.write_bytes(obj)
+        out.append(tuple(subprocess.run([READELF, flag, "-W", "-C", str(f)], capture_output=True, text=True, check=True).stdout
+                         for flag in ("--symbols", "--notes")))
+    assert out
+    return out
+
+
+def code_bytes(listings):
+    sizes = {}
+    for symbols, _ in listings:
+        for m in re.finditer(r"\s(\d+) FUNC .*?chess::(\w+(?:<[^(]*>)?)\(", symbols):
+            sizes[m.group(2)] = int(m.group(1))
+    return sizes
+
+
+def test_the_merge_does_not_swell_attention_over_every_page(listings):
+    """The last workgroup of a sequence runs the merge once, from cold code: four inlined variants of it (19 KB a kernel) cost 1 to 9 %
+    of attention over every page."""
+    sizes = code_bytes(listings)
+    dense = {n: s for n, s in sizes.items() if re.match(r"decode_kernel<\d+, 4, false, ", n)}
+    assert len(dense) == 4, sorted(sizes)
+    for name, size in dense.items():
+        assert size <= (14 if name.endswith("true>") else 12) * 1024, (name, size)
