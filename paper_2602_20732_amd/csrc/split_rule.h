@@ -28,6 +28,23 @@ inline int64_t clampi(int64_t x, int64_t lo, int64_t hi) { return x < lo ? lo : 
 // Rows of split partials a workspace for `rows` (sequence, KV head) pairs holds, in units of G vectors.
 inline int64_t partial_rows(int n_cu, int64_t rows) { return 4LL * n_cu + rows; }
 
+// Most splits of a page list: what its tiles can use.  A split more costs the last workgroup requests (up to eight splits are
+// one round trip, beyond that it asks for eight or sixteen at a time), and pays as long as waves have several tiles: eight splits
+// for up to 48 tiles, sixteen (twelve with more than four query heads, where sixteen would fill the chip) for up to some 200; then as
+// many as leave each of eight waves a tile, up to 2 sqrt(tiles), in eights.  us of attention over a list (8 / 16 / 24 / 32 / 64 splits,
+// the better of four and eight waves):
+//   one (sequence, head), G = 4, pages of 16    48 pages   6.1 /  6.6 /  7.3              150 pages   8.3 /  7.7 /  8.0 /  8.1
+//                                              500 pages  15.6 / 11.9 / 11.2 / 10.6      4000 pages  99.7 / 55.1 / 40.6 / 33.0 / 23.9
+//   eight, G = 4, pages of 16                  260 pages  11.7 / 10.5 / 11.7 / 12.4      1000 pages  32.6 / 21.9 / 20.5 / 20.7
+//   one, G = 7, pages of 32                     90 pages   9.9 /  9.0 /  9.3 /  9.5       500 pages  27.9 / 18.4 / 16.0 / 14.9 / 15.3
+// (A fixed most of 8 / 16 took 63 us of the 4000 pages and 133 of 4000 pages of 32.)
+inline int64_t list_cap(const SplitLimits& c, int64_t pairs, int64_t tiles)
+{
+    if (tiles <= 48) return 8;
+    const int64_t grown = std::min(tiles / 8, (int64_t)(2.0 * std::sqrt((double)tiles))) / 8 * 8;
+    return std::max<int64_t>(c.group > 4 && 64 * pairs > 3LL * c.n_cu ? 12 : 16, grown);
+}
+
 // A workgroup has four waves (eight where `wide` below says so); tiles are dealt round-robin over splits and waves.
 // Dense (every page): enough workgroups to cover the chip a few times over; the workgroup that finishes last merges
 // ns partial rows per output, tile time falls as 1/ns and merge time grows as G*ns/32 (in units of one memory
@@ -35,12 +52,9 @@ inline int64_t partial_rows(int n_cu, int64_t rows) { return 4LL * n_cu + rows; 
 // sequences that count is the most one of them gets, and the workgroups resident at once are dealt to them by their
 // lengths on the device (share_slots), as soon as there are more of them than sequences: only the device knows the
 // lengths, and splits chosen for the longest possible one cost a short sequence more than the dealing does (times there).
-// A page list (tens to hundreds of pages): the fixed latencies dominate, and the measured optimum (sweeps at batch
-// 1 .. 32, 21 .. 415 pages, G = 1 .. 7) is: no split once there is a (sequence, head) per compute unit; otherwise one
-// workgroup per compute unit, at least two tiles per workgroup, at most 1.6 x the merge-balanced count, and no more splits
-// than the last one of them can ask for in one round trip (merge_splits): eight, or sixteen (twelve with more than four query
-// heads) for lists long enough that eight leave a wave several tiles.  us a reuse step, uncapped / capped: one sequence of
-// 32K 7.54 / 7.02, two of 32K 8.83 / 7.73, 128 pages with G = 1 10.9 / 8.7, 87 pages of 32 with G = 7 12.1 / 10.7.
+// A page list: the fixed latencies dominate, and the measured optimum (sweeps at 1 .. 128 (sequence, head) pairs, 16 .. 12000
+// pages, G = 1 .. 7, both page sizes) is: no split once there is a (sequence, head) per compute unit; otherwise one workgroup per
+// compute unit, at least two tiles per workgroup, at most 1.6 x the merge-balanced count, and at most list_cap.
 inline SplitShape choose_splits(const SplitLimits& c, int batch, int64_t max_list_pages, bool listed)
 {
     const int64_t tiles = std::max<int64_t>(1, cdiv(max_list_pages, c.tile_pages));
@@ -54,7 +68,7 @@ inline SplitShape choose_splits(const SplitLimits& c, int batch, int64_t max_lis
     if (listed) {
         ns = std::min<int64_t>(c.n_cu / pairs, cdiv(tiles, 2));
         ns = std::min<int64_t>(ns, (int64_t)std::llround(1.6 * balanced));
-        ns = std::min<int64_t>(ns, tiles <= 48 ? 8 : c.group > 4 ? 12 : 16);
+        ns = std::min<int64_t>(ns, list_cap(c, pairs, tiles));
         ns = std::max<int64_t>(ns, 1);
     } else {
         // all workgroups resident at once: a second round of workgroups would double a short kernel

@@ -1,4 +1,4 @@
-"""How many splits a page list gets (``split_rule.h``), on the host: at most what one round trip of the merge covers."""
+"""How many splits a page list gets (``split_rule.h``), on the host, against the measured ranges."""
 from __future__ import annotations
 
 import os
@@ -7,7 +7,7 @@ import subprocess
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-def test_lists_are_not_split_beyond_one_round_trip_of_the_merge(tmp_path):
+def test_lists_are_split_as_their_tiles_can_use(tmp_path):
     exe = str(tmp_path / "list_splits")
     cmd = ["g++", "-std=c++17", "-O1", "-fsanitize=undefined", "-fno-sanitize-recover=all",
            "-I", os.path.join(ROOT, "paper_2602_20732_amd", "csrc"), os.path.join(ROOT, "tests", "list_splits_driver.cpp"), "-o", exe]
