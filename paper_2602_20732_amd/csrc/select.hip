@@ -6,6 +6,9 @@
 namespace chess {
 
 // grid = (C, H_kv, batch); T = storage type of the summaries (float or bf16 bits)
+// Three workgroups a compute unit.  Alone on its row, with fp32 vectors, a workgroup has half as many of them in flight: with all, the
+// registers of three do not suffice (eight spilled), and of two make a second round.  us, spilled / two / half in flight: 32
+// sequences of 8K 11.8 / 11.3 / 11.0, 96 of 4-21K 20.9 / 27.5 / 19.0, 128 of 2K 16.8 / 17.3 / 13.0 (four fit then).
 template <class T, int kMode>
 __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(3))) void select_kernel(const uint16_t* __restrict__ q,
                                                              const void* __restrict__ pages_v,
@@ -57,7 +60,7 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(3))
 
     const PubLayout pubs = pub_layout(ws.keys + row * ws.key_stride, g);
     CascadeResult res;
-    const bool ok = cascade<kMode, false, T, false>(pages + row * g.max_pages * kHeadDim, chunks + row * g.max_chunks * kHeadDim,
+    const bool ok = cascade<kMode, false, T, kMode == kSolo && sizeof(T) == 4>(pages + row * g.max_pages * kHeadDim, chunks + row * g.max_chunks * kHeadDim,
                                       grids + row * g.max_grids * kHeadDim, pr, P, g, sp, pubs, m, C, m == 0, keys,
                                       kept_grids, kept_chunks, sel_pages, sh, &res, prof, nullptr, 0,
                                       [&] { if (sp.probe == CHESS_PROBE_QUERY) probe.sum(q_rows, g.group, pr); }, [] {}, k_fixed);

@@ -54,7 +54,13 @@ def code_bytes(listings):
     return sizes
 
 
-def test_the_merge_does_not_swell_attention_over_every_page(listings):
+def scratch_bytes(listings):
+    """Scratch memory a lane, by mangled kernel name: spilled registers, or an array with a run-time index."""
+    return {m.group(1): int(m.group(2)) for _, notes in listings
+            for m in re.finditer(r"\.name:\s+(\S+)\n\s+\.private_segment_fixed_size:\s+(\d+)", notes)}
+
+
+def test_the_does_not_swell_attention_over_every_page(listings):
     """The last workgroup of a sequence runs the merge once, from cold code: four inlined variants of it (19 KB a kernel) cost 1 to 9 %
     of attention over every page."""
     sizes = code_bytes(listings)
@@ -62,3 +68,9 @@ def test_the_merge_does_not_swell_attention_over_every_page(listings):
     assert len(dense) == 4, sorted(sizes)
     for name, size in dense.items():
         assert size <= (14 if name.endswith("true>") else 12) * 1024, (name, size)
+
+
+def test_selection_kernels_need_no_scratch_memory(listings):
+    """A kernel with scratch memory starts 2-3 us later, however little it is."""
+    scratch = {n: b for n, b in scratch_bytes(listings).items() if "13select_kernel" in n}
+    assert len(scratch) == 4 and not any(scratch.values()), scratch
