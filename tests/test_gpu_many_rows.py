@@ -52,3 +52,42 @@ def test_more_rows_than_two_workgroups_a_compute_unit(page, group, fans, refresh
                 pages, chunks, grids = host_views(lib, summ, batch)
             assert_summaries_equal(Got, ref, sp, lens)
         lib.close()
+
+
+RATIO = dict(plan=oracle.PLAN_RATIO, rho_g_bp=4000, rho_c_bp=5000, rho_p_bp=3000)
+
+
+@pytest.mark.parametrize("page,group,fans,pages,kw", [
+    (16, 1, (1, 1), 1100, {}),                             # levels of 1100, some 300 and 60 slots
+    (16, 4, (2, 2), 1100, RATIO),                          # 275, 220 and 220
+    (16, 4, (4, 4), 1100, dict(plan=oracle.PLAN_FLAT)),    # every page in one level
+    (32, 7, (1, 1), 600, RATIO),                           # 600, 240 and 120
+    (32, 16, (8, 8), 1100, dict(budget_pages=40)),         # 18 of 18, 50 of 138, 400 slots
+])
+def test_long_rows_among_many(page, group, fans, pages, kw):
+    """A few long sequences among rows enough for the leaner kernel: several trips of its scoring, and every cut but the smallest.
+    The selection by itself as well, alone on its rows there."""
+    batch = 2 * torch.cuda.get_device_properties(0).multi_processor_count + 5
+    lens = [pages * page, pages * page - 7, (pages // 2) * page + 1] + [(7 * b) % (5 * page) for b in range(batch - 3)]
+    sp = workload.WorkloadSpec("long_rows", batch, (0, pages * page), group, 1, page, ("geometric", 128), (1, 3), 1, 2, budget_pages=6,
+                               pages_per_chunk=fans[0], chunks_per_grid=fans[1])
+    wl = workload.generate(sp, 67, seq_lens=lens)
+    d = to_device(wl)
+    plan = plan_of(sp, **kw)
+    max_sel = 400
+    ref = run_oracle(wl, plan, max_sel, dense=False)
+    lib = pk.Chess(config_of(sp, max_selected=max_sel))
+    summ, ws = lib.new_summaries(), lib.new_workspace()
+    lib.summarize(d.k_pool, d.block_table, d.seq_lens, summ)
+    for turn in range(2):
+        ids = torch.full((batch, 1, max_sel), -7, dtype=torch.int32, device="cuda")
+        nsel = torch.full((batch, 1), -7, dtype=torch.int32, device="cuda")
+        ids2, nsel2 = ids.clone(), nsel.clone()
+        out = torch.full((batch, group, 128), float("nan"), device="cuda")
+        lib.decode_step(d.q, d.k_pool, d.v_pool, d.block_table, d.seq_lens, summ, gpu_plan(plan), ids, nsel, out, ws, refresh_tail=True)
+        lib.select(d.q, summ, d.seq_lens, gpu_plan(plan), ids2, nsel2, ws)
+        torch.cuda.synchronize()
+        for i, n in ((ids, nsel), (ids2, nsel2)):
+            assert np.array_equal(n.cpu().numpy(), ref.nsel) and np.array_equal(i.cpu().numpy(), ref.ids), turn
+        assert np.abs(out.cpu().numpy() - ref.out).max() <= ATOL_TIGHT
+    lib.close()
