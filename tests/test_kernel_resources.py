@@ -70,7 +70,7 @@ def test_the_does_not_swell_attention_over_every_page(listings):
         assert size <= (14 if name.endswith("true>") else 12) * 1024, (name, size)
 
 
-def test_selection_kernels_need_no_scratch_memory(listings):
+def test_no_kernel_needs_scratch_memory(listings):
     """A kernel with scratch memory starts 2-3 us later, however little it is."""
-    scratch = {n: b for n, b in scratch_bytes(listings).items() if "13select_kernel" in n}
-    assert len(scratch) == 4 and not any(scratch.values()), scratch
+    scratch = scratch_bytes(listings)
+    assert len(scratch) > 50 and not any(scratch.values()), {n: b for n, b in scratch.items() if b}
