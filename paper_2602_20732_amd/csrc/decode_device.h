@@ -520,14 +520,16 @@ __device__ __forceinline__ void merge_splits_by(int G, int n_splits, size_t part
 // Who merges: a list or one sequence's every page (any number of splits), every page dealt by length, or the fused step (at
 // most twelve splits).  More than a pair a thread (G > NW): two at once.  us, eight / twelve splits of both at once: the step,
 // 28 query and 4 KV heads, pages of 32, 1 x 64K 23.7 / 22.9, 1 x 256K 36.0 / 35.0; every page, 2 sequences of 11-90K 35.4 / 36.4.
-// One pair: eight splits at once where they are dealt (a sequence of 8K in a ragged batch has 23 splits: 22.1 / 22.5 us with
-// sixteen), one round trip for up to eight, and sixteen at once beyond (one sequence of 16K, G = 1: 24.2 / 22.7 us).
+// One pair: where the splits are dealt, eight at once if all waves have outputs (a sequence of 8K in a ragged batch has 23 splits,
+// G = 4: 22.1 / 22.5 us with sixteen) and sixteen if at most half have (2 x 9000 tokens, G = 1: 27.0 / 26.1 us); otherwise one
+// round trip for up to eight, and sixteen at once beyond (one sequence of 16K, G = 1: 24.2 / 22.7 us).
 enum MergeUse : int { kMergePlain, kMergeDealt, kMergeStep };
 template <int NW, int kUse>
 __device__ __forceinline__ void merge_splits(int G, int n_splits, size_t part0, float* __restrict__ out_rows,
                                              const float* __restrict__ ws_acc, const float* __restrict__ ws_ml)
 {
     if (G > NW) merge_splits_by<NW, 2, kUse == kMergeStep ? 12 : 8, kUse == kMergeStep ? 4 : 2>(G, n_splits, part0, out_rows, ws_acc, ws_ml);
+    else if (kUse == kMergeDealt && G <= NW / 2) merge_splits_by<NW, 1, 16, 4>(G, n_splits, part0, out_rows, ws_acc, ws_ml);
     else if (kUse == kMergeDealt) merge_splits_by<NW, 1, 8, 4>(G, n_splits, part0, out_rows, ws_acc, ws_ml);
     else if (n_splits <= 8) merge_splits_by<NW, 1, 8, 8>(G, n_splits, part0, out_rows, ws_acc, ws_ml);
     else merge_splits_by<NW, 1, 16, 8>(G, n_splits, part0, out_rows, ws_acc, ws_ml);

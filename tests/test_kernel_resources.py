@@ -67,7 +67,7 @@ def test_the_does_not_swell_attention_over_every_page(listings):
     dense = {n: s for n, s in sizes.items() if re.match(r"decode_kernel<\d+, 4, false, ", n)}
     assert len(dense) == 4, sorted(sizes)
     for name, size in dense.items():
-        assert size <= (14 if name.endswith("true>") else 12) * 1024, (name, size)
+        assert size <= (16 if name.endswith("true>") else 12) * 1024, (name, size)
 
 
 def test_no_kernel_needs_scratch_memory(listings):
