@@ -28,6 +28,16 @@ inline int64_t clampi(int64_t x, int64_t lo, int64_t hi) { return x < lo ? lo : 
 // Rows of split partials a workspace for `rows` (sequence, KV head) pairs holds, in units of G vectors.
 inline int64_t partial_rows(int n_cu, int64_t rows) { return 4LL * n_cu + rows; }
 
+// The fused step with rows of its own (one workgroup each): whether its lean kernel, made for three workgroups a compute unit, is the
+// one to launch.  Only where the rows outnumber two a compute unit; and not where the levels are so long that what they keep in
+// LDS (`level_bytes`; allocated in pieces of 1280) leaves no room for three in 160 KB: two of the lean kind score with half the
+// vectors in flight.  us a layer, lean / not: 80 sequences of 64K at a budget of 10 % 690 / 669, with bf16 vectors 566 / 519.  (A long
+// page list, which also takes LDS, says nothing about the levels: 96 sequences of 30-32K at 1 % with room for 1950 pages 75.7 / 78.3.)
+inline bool lean_step(int n_cu, int64_t rows, int64_t level_bytes)
+{
+    return rows > 2LL * n_cu && 3 * cdiv(level_bytes, 1280) * 1280 <= 160 * 1024;
+}
+
 // Most splits of a page list: what its tiles can use.  A split more costs the last workgroup requests (up to eight splits are
 // one round trip, beyond that it asks for eight or sixteen at a time), and pays as long as waves have several tiles: eight splits
 // for up to 48 tiles, sixteen (twelve with more than four query heads, where sixteen would fill the chip) for up to some 200; then as

@@ -8,6 +8,7 @@
 // kernel boundary, the round trip of the list through HBM and the second kernel's start-up loads.
 // Member 0 also writes the list to page_ids / n_selected when the caller wants it.
 #include "decode_device.h"
+#include "split_rule.h"
 #include "select_device.h"
 
 namespace chess {
@@ -329,14 +330,20 @@ static StepKernel step_kernel_of(int page_size, bool bf16, int mode)
     return table[page_size == 16 ? 0 : 1][bf16 ? 1 : 0][mode];
 }
 
+// The region that the selection's levels and then the attention take.
+static size_t step_level_bytes(const SelectParams& sp)
+{
+    const size_t sel = (size_t)sp.cap_keys * 8 + ((size_t)(sp.cap_kg + sp.cap_kc + sp.cap3) * 4 + 7) / 8 * 8;
+    const size_t dec = (size_t)DecodeLds<kStepWaves>::kFloats * sizeof(float);
+    return sel > dec ? sel : dec;
+}
+
 // Dynamic LDS of the fused kernel and where its shared region starts.
 size_t step_lds_bytes(const SelectParams& sp, int max_sel, int* union_off)
 {
     const size_t list = ((size_t)max_sel * 2 * 4 + 15) / 16 * 16 + 3 * kHeadDim * sizeof(float);   // page list, physical pages, refreshed tail vectors
-    const size_t sel = (size_t)sp.cap_keys * 8 + ((size_t)(sp.cap_kg + sp.cap_kc + sp.cap3) * 4 + 7) / 8 * 8;
-    const size_t dec = (size_t)DecodeLds<kStepWaves>::kFloats * sizeof(float);
     *union_off = (int)list;
-    return list + (sel > dec ? sel : dec);
+    return list + step_level_bytes(sp);
 }
 
 // Workgroups that fit on a compute unit, of the kernels whose workgroups wait for each other.
@@ -370,7 +377,7 @@ hipError_t launch_step(chess_ctx* ctx, const StepLaunch& sl, int batch, int clus
     // needed: 151-168 registers instead of 205-224).  us a layer, two / three a compute unit: 576 rows of 8-16K 59.8 / 45.8,
     // 768 of 4-21K 73.2 / 58.2 (ratios and bf16 vectors 52.7 / 39.4), 1024 of 8K 61.8 / 57.3, 1536 of 4-8K 79.6 / 67.9, 2048 of 4K
     // 89.8 / 86.5.  Below, it depends: 512 of 8-16K 39.5 / 37.7, 512 of 16K with bf16 vectors 38.5 / 43.4, 256 of 16-32K 41.0 / 41.0.
-    const bool lean = (int64_t)batch * g.n_kv_heads > 2LL * ctx->n_cu;
+    const bool lean = lean_step(ctx->n_cu, (int64_t)batch * g.n_kv_heads, step_level_bytes(sp) + sizeof(Shared));
     const int mode = cluster == 1 ? (lean ? kSoloLean : kSolo) : sp.schedule == kEager ? kEagerCluster : kCluster;
     const StepKernel kern = step_kernel_of(g.page_size, ctx->cfg.summary_dtype == CHESS_SUMMARY_BF16, mode);
     if (lds_bytes > 48 * 1024) {
