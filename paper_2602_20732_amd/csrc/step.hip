@@ -11,6 +11,8 @@
 #include "split_rule.h"
 #include "select_device.h"
 
+#include <type_traits>
+
 namespace chess {
 
 static_assert(kSelThreads % kWave == 0 && kSelThreads >= 256, "the fused step decodes with every wave of the workgroup");
@@ -33,14 +35,23 @@ struct StepArgs {
     int32_t refresh_tail;    // recompute the summaries of the tail page, its chunk and its grid first
 };
 
-// The kernel's arguments as they lie in memory.
-struct StepKernarg {
-    const void* q;
-    const void* seq_lens;
-    const void* block_table;
-    int32_t n_q_heads, n_kv_heads, group, max_pages, query_probe;
-    StepArgs a;
-};
+// The kernel's parameters (the table in step_kernel_of holds every instance to them), and where in the argument segment the first one of
+// type Arg lies: in order, each at the next multiple of its alignment.
+using StepKernel = void (*)(const uint16_t*, const int32_t*, const int32_t*, int, int, int, int, int, StepArgs, Geom, SelectParams, SelectWs);
+template <class Arg, class... Args>
+constexpr size_t kernarg_offset(void (*)(Args...))
+{
+    size_t at = 0, found = ~(size_t)0;
+    const auto place = [&](size_t size, size_t align, bool it) {
+        at = (at + align - 1) / align * align;
+        found = it && found == ~(size_t)0 ? at : found;
+        at += size;
+    };
+    (place(sizeof(Args), alignof(Args), std::is_same_v<Args, Arg>), ...);
+    return found;
+}
+constexpr size_t kStepArgsAt = kernarg_offset<StepArgs>(StepKernel(nullptr));
+static_assert(kStepArgsAt != ~(size_t)0, "the kernel has no such parameter");
 
 // StepArgs read again where they are needed: what only the attention uses would otherwise be in scalar registers -- or, as there are
 // too few, saved and restored -- all through the selection (lane reads in the eager kernel's code: 930, so 440).  us, kept /
@@ -54,7 +65,7 @@ __device__ __forceinline__ StepArgs late_args(const StepArgs& a)
     kernarg p = (kernarg)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(p));                       // (not the loads the kernel began with)
     StepArgs r;
-    __builtin_memcpy(&r, (const void*)(p + offsetof(StepKernarg, a)), sizeof(r));
+    __builtin_memcpy(&r, (const void*)(p + kStepArgsAt), sizeof(r));
     return r;
 }
 
@@ -312,7 +323,6 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(kLe
 #endif
 }
 
-using StepKernel = void (*)(const uint16_t*, const int32_t*, const int32_t*, int, int, int, int, int, StepArgs, Geom, SelectParams, SelectWs);
 constexpr int kSoloLean = 3;                          // a cluster of one with three workgroups on a compute unit (see launch_step)
 constexpr int kStepModes = 4;
 static StepKernel step_kernel_of(int page_size, bool bf16, int mode)
