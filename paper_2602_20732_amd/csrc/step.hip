@@ -37,7 +37,7 @@ struct StepArgs {
 
 // The kernel's parameters (the table in step_kernel_of holds every instance to them), and where in the argument segment the first one of
 // type Arg lies: in order, each at the next multiple of its alignment.
-using StepKernel = void (*)(const uint16_t*, const int32_t*, const int32_t*, int, int, int, int, int, StepArgs, Geom, SelectParams, SelectWs);
+using StepKernel = void (*)(uint64_t, uint64_t, uint64_t, int, int, int, int, int, StepArgs, Geom, SelectParams, SelectWs);
 template <class Arg, class... Args>
 constexpr size_t kernarg_offset(void (*)(Args...))
 {
@@ -167,13 +167,25 @@ struct TailUnits {
     }
 };
 
+// The three pointers that the first loads need are numbers in the kernel's signature: a pointer among the arguments is looked up by the
+// runtime at each launch, and the first launch with memory that it has not seen as an argument yet took 20-120 us of host time (a first
+// pass of 96 ragged sequences, two layers, 130-290 us instead of 125-165).
+template <class V>
+__device__ __forceinline__ V* device_pointer(uint64_t at)
+{
+    return (V*)(__attribute__((address_space(1))) V*)at;
+}
+
 // grid = (C, H_kv, batch); T = storage type of the summaries (float or bf16 bits); kMode: see cascade_with; kLean: three
 // workgroups on a compute unit instead of two (see launch_step)
 template <int B, class T, int kMode, bool kLean>
-__global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(kLean ? 3 : 2))) void step_kernel(const uint16_t* __restrict__ q, const int32_t* __restrict__ seq_lens, const int32_t* __restrict__ block_table, int n_q_heads,
+__global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(kLean ? 3 : 2))) void step_kernel(uint64_t q_at, uint64_t seq_lens_at, uint64_t block_table_at, int n_q_heads,
                             int n_kv_heads, int group, int max_pages, int query_probe, StepArgs a, Geom g_args, SelectParams sp_args, SelectWs ws)
 {
     // (what the first loads need comes in registers, ahead of the structs: see build.py)
+    const uint16_t* q = device_pointer<const uint16_t>(q_at);
+    const int32_t* seq_lens = device_pointer<const int32_t>(seq_lens_at);
+    const int32_t* block_table = device_pointer<const int32_t>(block_table_at);
     const int L_raw = seq_lens[blockIdx.z];
     const uint16_t* q_rows = q + ((size_t)blockIdx.z * n_q_heads + (size_t)blockIdx.y * group) * kHeadDim;
     double pr[8];
@@ -395,7 +407,7 @@ hipError_t launch_step(chess_ctx* ctx, const StepLaunch& sl, int batch, int clus
         if (e != hipSuccess) return e;
     }
     return launch(kern, grid, block, lds_bytes, stream,
-                  sl.q, sl.seq_lens, sl.block_table, g.n_q_heads, g.n_kv_heads, g.group, g.max_pages, sp.probe == CHESS_PROBE_QUERY ? 1 : 0, a, g,
+                  (uint64_t)sl.q, (uint64_t)sl.seq_lens, (uint64_t)sl.block_table, g.n_q_heads, g.n_kv_heads, g.group, g.max_pages, sp.probe == CHESS_PROBE_QUERY ? 1 : 0, a, g,
                   sp, ws);
 }
 

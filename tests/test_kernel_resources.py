@@ -74,3 +74,10 @@ def test_no_kernel_needs_scratch_memory(listings):
     """A kernel with scratch memory starts 2-3 us later, however little it is."""
     scratch = scratch_bytes(listings)
     assert len(scratch) > 50 and not any(scratch.values()), {n: b for n, b in scratch.items() if b}
+
+
+def test_the_runtime_sees_no_pointers_in_the_step(listings):
+    """A pointer argument is looked up at each launch, and memory seen for the first time cost 20-120 us there: the fused step takes its
+    pointers as numbers and inside structs."""
+    kernels = [b for _, notes in listings for b in notes.split("- .agpr_count:")[1:] if "11step_kernel" in b]
+    assert len(kernels) == 16 and not any("global_buffer" in b for b in kernels)
