@@ -340,8 +340,8 @@ static void set_members(int64_t cluster, chess::SelectParams* sp)
     sp->inv_others = cluster > 1 ? (uint32_t)cdiv(0x80000000ll, cluster - 1) : 0u;
 }
 
-// Checks a plan against the configuration and fills the kernel-side parameters.
-static int prepare_select(chess_ctx* ctx, const chess_select_plan* plan, chess::SelectParams* out)
+// Checks a plan against the configuration and fills the kernel-side parameters; *most_kp: the most pages a sequence can keep.
+static int prepare_select(chess_ctx* ctx, const chess_select_plan* plan, chess::SelectParams* out, int64_t* most_kp = nullptr)
 {
     Bounds bd;
     if (!plan_bounds(ctx, plan, &bd)) return CHESS_EINVAL;
@@ -356,7 +356,7 @@ static int prepare_select(chess_ctx* ctx, const chess_select_plan* plan, chess::
     sp.cap_keys = (int32_t)bd.slots;
     sp.cap_kg = (int32_t)bd.kg;
     sp.cap_kc = (int32_t)bd.kc;
-    sp.most_kp = (int32_t)bd.kp;
+    if (most_kp != nullptr) *most_kp = bd.kp;
     sp.probe = plan->probe;
     sp.poll_limit = ctx->poll_limit > 0 ? ctx->poll_limit : ctx->poll_limit < 0 ? 0 : (1 << 15);   // < 0: every wait fails at once
     sp.general_cut = ctx->force_general_cut;
@@ -578,7 +578,8 @@ int chess_decode_step(chess_ctx* ctx, const void* q, const void* k_pool, const v
          reinterpret_cast<uintptr_t>(summaries) | reinterpret_cast<uintptr_t>(out) | reinterpret_cast<uintptr_t>(workspace)) & 15)
         return CHESS_EINVAL;
     chess::SelectParams sp;
-    if (int rc = prepare_select(ctx, plan, &sp)) return rc;
+    int64_t most_kp = 0;
+    if (int rc = prepare_select(ctx, plan, &sp, &most_kp)) return rc;
     if (sp.probe == CHESS_PROBE_ANCHOR && refresh_tail != 0) return CHESS_ENOTSUP;
     int union_off = 0;
     const size_t lds = chess::step_lds_bytes(sp, ctx->geom.max_sel, &union_off);
@@ -602,7 +603,7 @@ int chess_decode_step(chess_ctx* ctx, const void* q, const void* k_pool, const v
         cluster = clampi(cluster, 1, chess::kSelMaxCluster);
     }
     // pages the lists can hold
-    const int64_t listed = std::min<int64_t>(ctx->geom.max_sel, (int64_t)sp.sink + sp.window + sp.most_kp);
+    const int64_t listed = std::min<int64_t>(ctx->geom.max_sel, (int64_t)sp.sink + sp.window + most_kp);
     if (!choose_eager(ctx, pairs, capacity, cdiv(listed, chess::kTileTokens / ctx->geom.page_size), &cluster, &sp))
         choose_schedule(ctx, pairs, cluster, &sp);
     set_members(cluster, &sp);

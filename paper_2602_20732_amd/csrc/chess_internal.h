@@ -31,7 +31,6 @@ struct SelectParams {
     int32_t plan, sink, window, budget_pages, budget_bp, over_chunk, over_grid, rho_g_bp, rho_c_bp, rho_p_bp;
     int32_t cap2, cap3;              // most candidate slots level 2 / level 3 can have (host bound)
     int32_t cap_keys, cap_kg, cap_kc;   // LDS capacities: keys of one level, kept grids, kept chunks
-    int32_t most_kp;                 // most pages a sequence can keep
     int32_t probe;                   // CHESS_PROBE_*
     int32_t poll_limit;              // polls before a wait for published keys is given up
     int32_t general_cut;             // test hook: every level takes the general (LDS radix) cut
@@ -64,7 +63,7 @@ __device__ __forceinline__ SelectParams own_regs(const SelectParams& p)
     r.budget_bp = own_reg(p.budget_bp); r.over_chunk = own_reg(p.over_chunk); r.over_grid = own_reg(p.over_grid);
     r.rho_g_bp = own_reg(p.rho_g_bp); r.rho_c_bp = own_reg(p.rho_c_bp); r.rho_p_bp = own_reg(p.rho_p_bp);
     r.cap2 = own_reg(p.cap2); r.cap3 = own_reg(p.cap3); r.cap_keys = own_reg(p.cap_keys); r.cap_kg = own_reg(p.cap_kg);
-    r.cap_kc = own_reg(p.cap_kc); r.most_kp = own_reg(p.most_kp); r.probe = own_reg(p.probe); r.poll_limit = own_reg(p.poll_limit);
+    r.cap_kc = own_reg(p.cap_kc); r.probe = own_reg(p.probe); r.poll_limit = own_reg(p.poll_limit);
     r.general_cut = own_reg(p.general_cut); r.local_grids = own_reg(p.local_grids); r.schedule = own_reg(p.schedule);
     r.deciders = own_reg(p.deciders); r.inv_members = own_reg(p.inv_members); r.inv_others = own_reg(p.inv_others); r.keep_ties = own_reg(p.keep_ties); r.budget_per_seq = p.budget_per_seq;   // (a pointer would lose its address space)
     return r;

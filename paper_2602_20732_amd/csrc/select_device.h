@@ -75,7 +75,8 @@ __device__ __forceinline__ int opaque_tid()
 
 // x / fan without a division or a branch: inv = ceil(2^31 / fan), computed by the host; exact for 0 <= x < 2^31 / 255 (more
 // than 2^23 + 256) and fan <= 256: 2 x inv / 2^32 exceeds x / fan by x e / (2^31 fan) with e = fan inv - 2^31 < fan, which stays
-// below 1 / fan.
+// below 1 / fan.  No x here is larger: the keys of all grids and chunks of a row have to fit in LDS (at most 20480 of 8 bytes), and a
+// grid has at most 256 pages, so a row whose selection is accepted has at most 5.3 million.
 __device__ __forceinline__ int div_by(int x, uint32_t inv) { return (int)__umulhi((unsigned)x << 1, inv); }
 
 // Inclusive scan over the 64 lanes of a wave with DPP row shifts and row broadcasts (no LDS).
@@ -530,7 +531,7 @@ __device__ __forceinline__ int cut_in_registers(uint64_t* keys, int n_slots, con
     } else {
         unsigned a = ~0u, b = 0u;
         int n = 0;
-empty_histogram(sh);
+        empty_histogram(sh);
         // (four keys at a time, all read before the first is looked at; slots beyond the level repeat its last one)
 #pragma unroll
         for (int x0 = 0; x0 < R; x0 += 4) {
