@@ -300,7 +300,7 @@ class Chess:
         self._check(self.lib.chess_debug_force_cluster(self._h, cluster))
 
     def debug_force_schedule(self, schedule: int):
-        """0 = automatic, 1 = lazy, 2 = merged."""
+        """0 = automatic, 1 = lazy, 2 = merged, 3 = eager."""
         self._check(self.lib.chess_debug_force_schedule(self._h, schedule))
 
     def debug_force_general_cut(self, on: bool):

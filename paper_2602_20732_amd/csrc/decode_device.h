@@ -452,10 +452,11 @@ __device__ __forceinline__ bool combine_waves(const f32x4 (&o)[8], float m_run, 
 // heads' M and denominator itself from the (m, l) pairs (the threads of a head read the same words), so the partial
 // rows and the (m, l) pairs are requested together, kChunk splits of every pair at a time: no LDS, no barrier.  n_splits
 // and part0 have to be in scalar registers (kept per lane, an address costs 64-bit multiplies and a skipped split its selects).
+// kByLane: addresses from the lane's row all the same, for a kernel that has no scalar registers to spare.
 // Bound: memory round trips and, as the code runs once or a few times, its length; splits beyond the last are not asked for
 // where that would be more than kGroup - 1 requests (repeats of one row from all workgroups at once: 9 sequences of 16K with
 // sixteen heads took 53 instead of 48 us with eight of them).
-template <int NW, int kItems, int kChunk, int kGroup>
+template <int NW, int kItems, int kChunk, int kGroup, bool kByLane = false>
 __device__ __forceinline__ void merge_splits_by(int G, int n_splits, size_t part0, float* __restrict__ out_rows,
                                                 const float* __restrict__ ws_acc, const float* __restrict__ ws_ml)
 {
@@ -480,8 +481,14 @@ __device__ __forceinline__ void merge_splits_by(int G, int n_splits, size_t part
                         const int at = min(s0 + x, n_splits - 1) * G;
 #pragma unroll
                         for (int y = 0; y < kItems; ++y) {
-                            ml[y][x] = observe_u64(ml_g + at + item[y] / (kHeadDim / 2));
-                            v[y][x] = observe_u64(acc_g + (int64_t)at * (kHeadDim / 2) + item[y]);
+                            if constexpr (kByLane) {
+                                const size_t row = (part0 + min(s0 + x, n_splits - 1)) * G + item[y] / (kHeadDim / 2);
+                                ml[y][x] = observe_u64(reinterpret_cast<const uint64_t*>(ws_ml) + row);
+                                v[y][x] = observe_u64(reinterpret_cast<const uint64_t*>(ws_acc) + row * (kHeadDim / 2) + item[y] % (kHeadDim / 2));
+                            } else {
+                                ml[y][x] = observe_u64(ml_g + at + item[y] / (kHeadDim / 2));
+                                v[y][x] = observe_u64(acc_g + (int64_t)at * (kHeadDim / 2) + item[y]);
+                            }
                         }
                     }
                 }
@@ -517,18 +524,26 @@ __device__ __forceinline__ void merge_splits_by(int G, int n_splits, size_t part
     }
 }
 
-// Who merges: a list or one sequence's every page (any number of splits), every page dealt by length, or the fused step (at
-// most twelve splits).  More than a pair a thread (G > NW): two at once.  us, eight / twelve splits of both at once: the step,
-// 28 query and 4 KV heads, pages of 32, 1 x 64K 23.7 / 22.9, 1 x 256K 36.0 / 35.0; every page, 2 sequences of 11-90K 35.4 / 36.4.
+// Who merges: a list or one sequence's every page (any number of splits); every page dealt by length; the fused step (at most twelve
+// splits), whose cluster kernel saves and restores scalar registers as it is.  More than a pair a thread (G > NW): two at once.
+// us, eight / twelve splits of both at once: the step, 28 query and 4 KV heads, pages of 32, 1 x 64K 23.7 / 22.9, 1 x 256K 36.0 / 35.0;
+// every page, 2 sequences of 11-90K 35.4 / 36.4.
 // One pair: where the splits are dealt, eight at once if all waves have outputs (a sequence of 8K in a ragged batch has 23 splits,
 // G = 4: 22.1 / 22.5 us with sixteen) and sixteen if at most half have (2 x 9000 tokens, G = 1: 27.0 / 26.1 us); otherwise one
 // round trip for up to eight, and sixteen at once beyond (one sequence of 16K, G = 1: 24.2 / 22.7 us).
-enum MergeUse : int { kMergePlain, kMergeDealt, kMergeStep };
+// The cluster kernel by lane / by scalar addresses: 2 layers of 8 x 128K 80.1 / 81.4 us.
+enum MergeUse : int { kMergePlain, kMergeDealt, kMergeStep, kMergeCluster };
 template <int NW, int kUse>
 __device__ __forceinline__ void merge_splits(int G, int n_splits, size_t part0, float* __restrict__ out_rows,
                                              const float* __restrict__ ws_acc, const float* __restrict__ ws_ml)
 {
-    if (G > NW) merge_splits_by<NW, 2, kUse == kMergeStep ? 12 : 8, kUse == kMergeStep ? 4 : 2>(G, n_splits, part0, out_rows, ws_acc, ws_ml);
+    if constexpr (kUse == kMergeCluster) {
+        if (G > NW) {
+            if (n_splits <= 6) merge_splits_by<NW, 2, 6, 6, true>(G, n_splits, part0, out_rows, ws_acc, ws_ml);
+            else merge_splits_by<NW, 2, 12, 12, true>(G, n_splits, part0, out_rows, ws_acc, ws_ml);
+        } else if (n_splits <= 8) merge_splits_by<NW, 1, 8, 8, true>(G, n_splits, part0, out_rows, ws_acc, ws_ml);
+        else merge_splits_by<NW, 1, 16, 16, true>(G, n_splits, part0, out_rows, ws_acc, ws_ml);
+    } else if (G > NW) merge_splits_by<NW, 2, kUse == kMergeStep ? 12 : 8, kUse == kMergeStep ? 4 : 2>(G, n_splits, part0, out_rows, ws_acc, ws_ml);
     else if (kUse == kMergeDealt && G <= NW / 2) merge_splits_by<NW, 1, 16, 4>(G, n_splits, part0, out_rows, ws_acc, ws_ml);
     else if (kUse == kMergeDealt) merge_splits_by<NW, 1, 8, 4>(G, n_splits, part0, out_rows, ws_acc, ws_ml);
     else if (n_splits <= 8) merge_splits_by<NW, 1, 8, 8>(G, n_splits, part0, out_rows, ws_acc, ws_ml);

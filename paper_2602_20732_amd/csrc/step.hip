@@ -327,7 +327,7 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(kLe
     prof.mark(17);
     // every member is done with the key words (the stores' way to memory hides behind the merge)
     if (last & kLastOfAll) clear_published(pubs, res, tail_words);
-    if (split_up && (last & kLastDecider)) merge_splits<kStepWaves, kMergeStep>(G, D, row * D, late_out, late.ws_acc, late.ws_ml);
+    if (split_up && (last & kLastDecider)) merge_splits<kStepWaves, kMode == kCluster ? kMergeCluster : kMergeStep>(G, D, row * D, late_out, late.ws_acc, late.ws_ml);
 #ifdef CHESS_PROF
     prof.mark(18);
     if (tid == 0 && (!split_up || (last & kLastDecider))) prof.store(ws.prof + (row * 2 + 1) * Prof::kSlots);
