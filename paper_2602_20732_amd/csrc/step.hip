@@ -396,7 +396,7 @@ hipError_t launch_step(chess_ctx* ctx, const StepLaunch& sl, int batch, int clus
     const dim3 grid(cluster, g.n_kv_heads, batch), block(kSelThreads);
     // Alone on their rows, more workgroups than two a compute unit would run in two rounds, the second nearly empty: from there on
     // the kernel that fits three times (half the vectors in flight, no tile ahead, the tail unit's rows requested when they are
-    // needed: 151-168 registers instead of 205-224).  us a layer, two / three a compute unit: 576 rows of 8-16K 59.8 / 45.8,
+    // needed: 142-154 registers instead of 198-212).  us a layer, two / three a compute unit: 576 rows of 8-16K 59.8 / 45.8,
     // 768 of 4-21K 73.2 / 58.2 (ratios and bf16 vectors 52.7 / 39.4), 1024 of 8K 61.8 / 57.3, 1536 of 4-8K 79.6 / 67.9, 2048 of 4K
     // 89.8 / 86.5.  Below, it depends: 512 of 8-16K 39.5 / 37.7, 512 of 16K with bf16 vectors 38.5 / 43.4, 256 of 16-32K 41.0 / 41.0.
     const bool lean = lean_step(ctx->n_cu, (int64_t)batch * g.n_kv_heads, step_level_bytes(sp) + sizeof(Shared));
