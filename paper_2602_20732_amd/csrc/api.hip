@@ -319,17 +319,18 @@ static void choose_schedule(const chess_ctx* ctx, int64_t pairs, int64_t cluster
 // attention (half as many as the list has tiles: fewer partials to merge, a tile for every other wave).
 static bool choose_eager(const chess_ctx* ctx, int64_t pairs, int64_t capacity, int64_t list_tiles, int64_t* cluster, chess::SelectParams* sp)
 {
-    if (*cluster <= 1 || (ctx->force_schedule != 0 && ctx->force_schedule - 1 != chess::kEager)) return false;
+    if (*cluster <= 1 || capacity < 2 * pairs || (ctx->force_schedule != 0 && ctx->force_schedule - 1 != chess::kEager)) return false;
     const chess::Geom& g = ctx->geom;
     const int64_t units = (int64_t)g.max_pages + g.max_chunks + g.max_grids;
     const int64_t most = clampi(capacity / pairs, 1, chess::kSelMaxCluster);
-    const int64_t members = ctx->force_cluster > 0 ? *cluster : clampi(cdiv(units, 96), std::min<int64_t>(12, most), most);
+    const int64_t members = std::max<int64_t>(2, ctx->force_cluster > 0 ? std::min<int64_t>(*cluster, most) : clampi(cdiv(units, 96), std::min<int64_t>(12, most), most));
     const bool bf16 = ctx->cfg.summary_dtype == CHESS_SUMMARY_BF16;
     const int64_t trip = bf16 ? 256 : 128;                                             // (HeadScorer::kTrip)
     const int64_t bytes = pairs * units * kHeadDim * (bf16 ? 2 : 4), most_bytes = sp->cap_kg >= g.max_grids ? 20LL << 20 : 12LL << 20;
-    if (ctx->force_schedule == 0 && (cdiv(units, std::max<int64_t>(members - 1, 1)) > trip || bytes > most_bytes)) return false;
+    if (ctx->force_schedule == 0 && (cdiv(units, members - 1) > trip || bytes > most_bytes)) return false;
     sp->schedule = chess::kEager;
-    sp->deciders = (int32_t)clampi(cdiv(list_tiles, 2), 1, std::min<int64_t>(members, 12));
+    // (the last member only refreshes the tail units, or scores)
+    sp->deciders = (int32_t)clampi(cdiv(list_tiles, 2), 1, std::min<int64_t>(members - 1, 12));
     *cluster = members;
     return true;
 }
@@ -612,7 +613,7 @@ int chess_decode_step(chess_ctx* ctx, const void* q, const void* k_pool, const v
     const chess::SelectWs ws = select_ws(ctx, workspace);
     char* sb = static_cast<char*>(summaries);
     char* wb = static_cast<char*>(workspace);
-    chess::StepLaunch sl{static_cast<const uint16_t*>(q), sb + ctx->page_off, sb + ctx->chunk_off, sb + ctx->grid_off,
+    chess::StepLaunch sl{static_cast<const uint16_t*>(q), sb + ctx->page_off,
                          static_cast<const uint16_t*>(k_pool), static_cast<const uint16_t*>(v_pool), block_table, seq_lens,
                          page_ids, n_selected, out, reinterpret_cast<float*>(wb + ctx->ws_acc_off),
                          reinterpret_cast<float*>(wb + ctx->ws_ml_off), reinterpret_cast<int32_t*>(wb + ctx->ws_cnt_off),

@@ -99,6 +99,15 @@ struct SelectWs {
 constexpr int kErrWait = 1;          // a wait for published keys was given up
 constexpr int kErrOverflow = 2;      // the threshold rule kept more units than a list has room for (the list was cut short)
 
+// One word that every lane needs, as a vector load: the first of a kernel is back after 0.93 us, a scalar load after 1.25 (the lengths
+// in the fused step, the phase marks of a profiling build).  The same value in every lane.
+__device__ __forceinline__ int load_by_lane(const int32_t* p)
+{
+    int zero = 0;
+    asm("" : "+v"(zero));
+    return p[zero];
+}
+
 // Values that cross workgroups inside one launch travel as agent-scope atomics: on gfx950 these are loads and
 // stores with the sc1 bit, which do not live in the per-XCD L2s as cached copies (a store is written through to
 // the memory side that all eight XCDs share before it is acknowledged, a load is served from there), so they are
@@ -217,9 +226,7 @@ hipError_t launch_select(chess_ctx* ctx, const uint16_t* q, const void* pages, c
 // Device pointers of one fused decode-step launch.
 struct StepLaunch {
     const uint16_t* q;
-    void* pages;
-    void* chunks;
-    void* grids;
+    void* pages;             // the summary buffer: pages, chunks and grids behind one another
     const uint16_t* k_pool;
     const uint16_t* v_pool;
     const int32_t* block_table;

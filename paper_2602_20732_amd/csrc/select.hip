@@ -60,10 +60,13 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(3))
 
     const PubLayout pubs = pub_layout(ws.keys + row * ws.key_stride, g);
     CascadeResult res;
-    const bool ok = cascade<kMode, false, T, kMode == kSolo && sizeof(T) == 4>(pages + row * g.max_pages * kHeadDim, chunks + row * g.max_chunks * kHeadDim,
-                                      grids + row * g.max_grids * kHeadDim, pr, P, g, sp, pubs, m, C, m == 0, keys,
-                                      kept_grids, kept_chunks, sel_pages, sh, &res, prof, nullptr, 0,
-                                      [&] { if (sp.probe == CHESS_PROBE_QUERY) probe.sum(q_rows, g.group, pr); }, [] {}, k_fixed);
+    constexpr bool kHalf = kMode == kSolo && sizeof(T) == 4;
+    Vec<T> fly[kFlyOf<T, kHalf>];
+    const T* pages_row = pages + row * g.max_pages * kHeadDim;
+    const auto vectors = [&](const T* to) { return (int)((to - pages_row) / kHeadDim); };
+    const HeadScorer<T, kHalf> scorer{pages_row, VecBases{vectors(grids + row * g.max_grids * kHeadDim), vectors(chunks + row * g.max_chunks * kHeadDim)}, pr, fly};
+    const bool ok = cascade_with<kMode, false>(scorer, P, g, sp, pubs, m, C, m == 0, keys, kept_grids, kept_chunks, sel_pages, sh, &res, prof, nullptr, false,
+                                      [&] { if (sp.probe == CHESS_PROBE_QUERY) probe.sum(q_rows, g.group, pr); }, [] {}, k_fixed, FirstShare{});
     if (!ok) {
         if (tid == 0) __hip_atomic_fetch_or(ws.error, kErrWait, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;

@@ -869,34 +869,39 @@ __device__ __forceinline__ double dot8_quad(const double (&pr)[8], const Vec<T>*
     return fold_lanes<1>(fold_lanes<0>(d[0], d[1], ln), fold_lanes<0>(d[2], d[3], ln), ln);
 }
 
+// Request the vectors of slots s0, s0 + 1, ... of a share that ends at hi (lane group g16 takes every kSelGroups-th).
+template <class T, int kFly, class VecOf>
+__device__ __forceinline__ void ask_rows(const T* __restrict__ pages_row, int s0, int hi, VecOf vec_of, int g16, int ln, Vec<T> (&v)[kFly])
+{
+#pragma unroll
+    for (int x = 0; x < kFly; ++x) {
+        // no condition on the load, per lane or per row of slots (some vector when the slot has no unit; rows the share
+        // does not have repeat its last slot): a per-lane condition would make the compiler wait for each vector
+        // before asking for the next, and a branch per row costs more than the repeated, cache-resident loads
+        v[x].load(pages_row + (int64_t)vec_of(min(s0 + kSelGroups * x + g16, hi - 1)) * kHeadDim, ln);
+    }
+}
+
 // Scores of the work slots [lo, hi).  `target(slot)` says which unit a slot is.  The key of a slot goes to
 // lds_keys[dest] (0 for no unit) when the level is local, else it is published in pub[dest].  (Two pointers of
 // known address space: one generic pointer for both would turn every access into a flat one.)
 // requested() is called once the first vectors are on their way (at once when there is nothing to score).
+// v: what is in flight; asked: the vectors of the first trip (slots lo .. lo + kSelGroups * kFly - 1) are already on their way there.
 // Bound: a memory round trip, then the instructions of the sums.  Four vectors' chains side by side and folded sums take a
 // quarter of the instructions of one vector after another with a DPP sum each (32 sequences of 16-32K, 8 layers: 283 ->
 // 268 us together with the reordered requests and the code split by cluster mode).
 template <class T, int kFly, class Target, class Requested>
 __device__ __forceinline__ void score_rows(const T* __restrict__ pages_row, int lo, int hi, Target target,
                                            const double (&pr)[8], bool local, uint64_t* lds_keys, uint64_t* pub,
-                                           Requested requested)
+                                           Requested requested, Vec<T> (&v)[kFly], bool asked)
 {
     const int tid = opaque_tid(), g16 = tid >> 4, ln = tid & 15;
-    Vec<T> v[kFly];
-    auto ask = [&](int s0) {
-#pragma unroll
-        for (int x = 0; x < kFly; ++x) {
-            // no condition on the load, per lane or per row of slots (some vector when the slot has no unit; rows the share
-            // does not have repeat its last slot): a per-lane condition would make the compiler wait for each vector
-            // before asking for the next, and a branch per row costs more than the repeated, cache-resident loads
-            v[x].load(pages_row + (int64_t)target(min(s0 + kSelGroups * x + g16, hi - 1)).vec * kHeadDim, ln);
-        }
-    };
-    if (lo < hi) ask(lo);
+    const auto vec_of = [&](int slot) { return target(slot).vec; };
+    if (lo < hi && !asked) ask_rows<T, kFly>(pages_row, lo, hi, vec_of, g16, ln, v);
     // (outside the loop: what it uses need not stay in registers for a second trip)
     requested();
     for (int s0 = lo; s0 < hi; s0 += kSelGroups * kFly) {
-        if (s0 != lo) ask(s0);
+        if (s0 != lo) ask_rows<T, kFly>(pages_row, s0, hi, vec_of, g16, ln, v);
         // lane x of a group ends with the total of vector x (lanes x, x + kFly, ... where kFly < 16)
         double q[kFly / 4];
         q[0] = dot8_quad<T>(pr, v, ln);
@@ -956,8 +961,8 @@ __device__ __forceinline__ bool pull_keys(const uint64_t* pub, const uint64_t* t
         for (int x = 0; x < kPer; ++x) {
             const int d = min(j0 + x * kSelThreads + tid, n - 1), own = word_of(d);
             const bool t0 = d == ov_dest0, t1 = d == ov_dest1;
-            none[x] = own < 0 && !t0 && !t1;
-            word[x] = pub + (t0 ? tail_at + ov_word0 : t1 ? tail_at + ov_word1 : (int64_t)max(own, 0));
+            none[x] = !WordOf::kAll && own < 0 && !t0 && !t1;
+            word[x] = pub + (t0 ? tail_at + ov_word0 : t1 ? tail_at + ov_word1 : (int64_t)(WordOf::kAll ? own : max(own, 0)));
         }
         int polls = 0;
         if (limit <= 0) { ok = false; break; }        // (a test asked for every wait to fail)
@@ -982,12 +987,11 @@ __device__ __forceinline__ bool pull_keys(const uint64_t* pub, const uint64_t* t
     return __builtin_amdgcn_readfirstlane(sh.gave_up) == 0;
 }
 
-// The same for a level of at most 1024 slots whose keys sit in slot order (item j lands in keys[j]): thread t polls
+// The same for a level of at most 1024 slots: thread t polls
 // words t, t + 256, t + 512, t + 768 and KEEPS them in key[0..3] (0 = empty or beyond n) for the cut that follows,
 // and every wave leaves the bounds (upper key halves) and the count of what it saw in sh.st_* before the closing
 // barrier, so that cut_in_registers can start at once.
-template <class WordOf>
-__device__ __forceinline__ bool pull_keys_regs(const uint64_t* pub, const uint64_t* tail, int n, WordOf word_of, int ov_dest0,
+__device__ __forceinline__ bool pull_keys_regs(const uint64_t* pub, const uint64_t* tail, int n, int ov_dest0,
                                                int ov_word0, int ov_dest1, int ov_word1, uint64_t* keys, uint64_t (&key)[4], Shared& sh)
 {
     const int limit = sh.poll_limit;
@@ -995,15 +999,12 @@ __device__ __forceinline__ bool pull_keys_regs(const uint64_t* pub, const uint64
     empty_histogram(sh);
     const int tid = opaque_tid(), lane = tid & 63, wave = tid >> 6;
     const uint64_t* word[4];
-    bool none[4];
     const int64_t tail_at = tail - pub;
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
         key[x] = 0ull;
-        const int d = min(x * kSelThreads + tid, n - 1), own = word_of(d);
-        const bool t0 = d == ov_dest0, t1 = d == ov_dest1;
-        none[x] = own < 0 && !t0 && !t1;
-        word[x] = pub + (t0 ? tail_at + ov_word0 : t1 ? tail_at + ov_word1 : (int64_t)max(own, 0));
+        const int d = min(x * kSelThreads + tid, n - 1);
+        word[x] = pub + (d == ov_dest0 ? tail_at + ov_word0 : d == ov_dest1 ? tail_at + ov_word1 : (int64_t)d);
     }
     int polls = 0;
     while (ok) {
@@ -1013,7 +1014,7 @@ __device__ __forceinline__ bool pull_keys_regs(const uint64_t* pub, const uint64
             key[x] = observe_u64(word[x]);                    // unconditional (a word beyond n repeats the last one): all stay in flight
         }
 #pragma unroll
-        for (int x = 0; x < 4; ++x) missing = missing || (!none[x] && key[x] == 0ull);
+        for (int x = 0; x < 4; ++x) missing = missing || key[x] == 0ull;
         if (__ballot(missing) == 0ull) break;
         if (++polls >= limit) { ok = false; break; }
         __builtin_amdgcn_s_sleep(2);
@@ -1023,7 +1024,7 @@ __device__ __forceinline__ bool pull_keys_regs(const uint64_t* pub, const uint64
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
         const int j = x * kSelThreads + tid;
-        if (j >= n || none[x] || key[x] == kAbsentKey || !ok) key[x] = 0ull;
+        if (j >= n || key[x] == kAbsentKey || !ok) key[x] = 0ull;
         if (j < n) keys[j] = key[x];
         const bool valid = key[x] != 0ull;
         const unsigned hi = (unsigned)(key[x] >> 32);
@@ -1057,6 +1058,11 @@ struct ProbeRows {
             c[x] = *reinterpret_cast<const uint2*>(row + Vec<T>::lane_dim(ln, 4));
         }
     }
+    __device__ __forceinline__ void arrived() const               // (waits for them)
+    {
+#pragma unroll
+        for (int x = 0; x < 4; ++x) asm volatile("" : : "v"(a[x].x), "v"(a[x].y), "v"(c[x].x), "v"(c[x].y));
+    }
     __device__ __forceinline__ void sum(const uint16_t* __restrict__ q_rows, int group, double (&pr)[8])
     {
 #pragma unroll
@@ -1082,13 +1088,18 @@ struct ProbeRows {
 // scoring loop asks once per vector; a single generic version full of per-level branches cost more instructions
 // than the scoring itself).
 struct VecBases { int grids, chunks; };   // the row's first grid / chunk vector, in vectors from its first page vector
-struct GridPhaseTarget {            // level 0: grids [0, n_g), then (merged) all chunks [n_g, n_g + n_c); keys by unit
-    int ng;
+// (The first phase's slots may be counted in the configuration's units, so that its vectors can be asked for before the sequence's
+// length is known: slots of units that the sequence does not have then go nowhere.)
+struct GridPhaseTarget {            // level 0: grids [0, slots_g), then (merged) all chunks; keys by unit, chunks behind the n_g grids
+    int slots_g, ng, nc;
     VecBases at;
+    __device__ __forceinline__ int vec(int slot) const { return slot + (slot < slots_g ? at.grids : at.chunks - slots_g); }
     __device__ __forceinline__ SlotRef operator()(int slot) const
     {
-        const bool grid = slot < ng;
-        return SlotRef{grid ? 0 : 1, grid ? slot : slot - ng, slot + (grid ? at.grids : at.chunks - ng), slot};
+        const bool grid = slot < slots_g;
+        const int unit = grid ? slot : slot - slots_g;
+        const bool there = unit < (grid ? ng : nc);
+        return SlotRef{grid ? 0 : 1, there ? unit : -1, vec(slot), there ? (grid ? unit : ng + unit) : -1};
     }
 };
 struct ChunkPhaseTarget {           // level 1 (lazy): N_g slots per kept grid; chunk keys by slot, behind the grid keys
@@ -1115,17 +1126,34 @@ struct PagePhaseTarget {            // level 2: N_c slots per kept chunk; sink a
         return SlotRef{2, unit, max(unit, 0), slot};
     }
 };
-struct AllTarget {                  // the eager schedule's only phase: grids, chunks, candidate pages [first_page, ...); keys by unit
-    int ng, ngc, first_page, page_words;   // page_words: where the page words start, counted from the grid words
+struct AllTarget {                  // the eager schedule's only phase: grids [0, slots_g), chunks [.., slots_gc), pages; keys by unit
+    int slots_g, slots_gc, ng, nc, first_page, last_page, page_words;   // page_words: where the page words start, counted from the grid words
     VecBases at;
+    __device__ __forceinline__ int vec(int slot) const
+    {
+        const bool grid = slot < slots_g, page = slot >= slots_gc;
+        return slot + (page ? -slots_gc : grid ? at.grids : at.chunks - slots_g);
+    }
     __device__ __forceinline__ SlotRef operator()(int slot) const
     {
-        const bool grid = slot < ng, page = slot >= ngc;
-        const int by = page ? first_page - ngc : grid ? 0 : -ng, unit = slot + by;
-        return SlotRef{page ? 2 : grid ? 0 : 1, unit, unit + (page ? 0 : grid ? at.grids : at.chunks), page ? page_words + unit : slot};
+        const bool grid = slot < slots_g, page = slot >= slots_gc;
+        const int unit = slot - (page ? slots_gc : grid ? 0 : slots_g);
+        const bool there = page ? unit >= first_page && unit < last_page : unit < (grid ? ng : nc);
+        return SlotRef{page ? 2 : grid ? 0 : 1, there ? unit : -1, vec(slot), there ? (page ? page_words + unit : grid ? unit : ng + unit) : -1};
     }
 };
-struct PageWords {                  // which word has the key of item j of a pull
+// A member's share of the first phase where it is counted in the configuration's units; its first trip of vectors has been asked for.
+struct FirstShare {
+    bool asked, local;                // local: every member scores all of it
+    int lo, hi;
+};
+
+struct SlotWords {                  // which word has the key of item j of a pull
+    static constexpr bool kAll = true;                // every item has one
+    __device__ __forceinline__ int operator()(int j) const { return j; }
+};
+struct PageWords {
+    static constexpr bool kAll = false;
     PagePhaseTarget slots;
     bool by_page;
     __device__ __forceinline__ int operator()(int j) const { return by_page ? slots(j).unit : j; }
@@ -1167,13 +1195,16 @@ __device__ __forceinline__ PubLayout pub_layout(uint64_t* row_words, const Geom&
 // one word per slot); sel_phys[i] then receives the physical page of sel_pages[i].
 //
 // tail_words non-null: the decode step refreshes the summaries of the tail page, its chunk and its grid in this
-// launch.  `refresh_tail()` is called in member `refresher` once its share of the first phase is scored; it leaves the three
-// units' keys in tail_words[0..2] (grid, chunk, page) for the cluster and in sh.tail_key for itself.  Wherever one
+// launch.  `refresh_tail()` is called in the member that `refreshes` (member 0) once its share of the first phase is scored; it leaves the three
+// units' keys in tail_words[0..2] (grid, chunk, page) for the cluster and in sh.tail_key for itself.  (Under the eager schedule a member
+// that does nothing else, and does not come here, does so.)  Wherever one
 // of these units competes, its key is taken from there instead of the unit's own word (whatever was scored for it
 // from the old vector is ignored).
 //
 // How a phase's work slots are scored is the Scorer's business: scorer(lo, hi, target, local, keys, pub, requested)
 // leaves the keys of the work slots [lo, hi) in keys[dest] (local) or publishes them in pub[dest].
+//
+// first: see FirstShare (asked is false where the caller knows the length first).
 //
 // requested(): called once, by every thread, when the first phase's vectors are on their way and before any of them is
 // used: what needs values that were requested earlier (the probe) or asks for more (the rows of the tail units) goes
@@ -1186,7 +1217,7 @@ __device__ __forceinline__ bool cascade_with(const Scorer& scorer, int P, const 
                                         const SelectParams& sp, const PubLayout& pubs, int m, int C, bool want_l3,
                                         uint64_t* keys, int32_t* kept_grids, int32_t* kept_chunks, int32_t* sel_pages,
                                         Shared& sh, CascadeResult* res, Prof& prof, const uint64_t* tail_words,
-                                        int refresher, ReqFn requested, TailFn refresh_tail, int k_fixed,
+                                        bool refreshes, ReqFn requested, TailFn refresh_tail, int k_fixed, const FirstShare& first,
                                         const int32_t* __restrict__ bt_row = nullptr,
                                         int32_t* phys_by_slot = nullptr, int32_t* sel_phys = nullptr)
 {
@@ -1223,27 +1254,32 @@ __device__ __forceinline__ bool cascade_with(const Scorer& scorer, int P, const 
     // of waiting a round trip for the others' shares (the host allows it when the repeated reads are few).
     // Otherwise a member takes its share of the phase's slots.
     const int n_first = merged ? ng + nc : all_grids ? 0 : ng;
-    const bool local_first = solo || (!merged && sp.local_grids != 0 && n_first <= kSelGroups * 8);
-    // ---- the first phase: grids [0, n_g), behind them all chunks (merged), behind those all candidate pages (eager)
+    const bool local_first = solo || (first.asked ? first.local : !merged && sp.local_grids != 0 && n_first <= kSelGroups * 8);
+    // ---- the first phase: grids [0, n_g), behind them all chunks (merged), behind those all pages (eager)
     {
-        const int n_work = eager ? n_first + P - w - s : n_first;
         // (the member that refreshes the tail units has a chain of dependent loads of its own to get through
         // before the first cut: it takes no share of the first phase if the others can still cover it in one
         // memory round trip each)
+        const int n_work = eager ? n_first + P - w : n_first;
         const int without = div_by(n_work + C - 2, sp.inv_others);
         const bool spare = tail_on && !local_first && without <= Scorer::kTrip;
-        const int mine = spare && m > refresher ? m - 1 : m;
+        const int mine = spare ? m - 1 : m;           // (member 0 refreshes; the eager kernel's shares are all asked for)
         const int per = local_first ? n_work : spare ? without : div_by(n_work + C - 1, sp.inv_members);
-        const int lo = local_first ? 0 : (spare && m == refresher) ? n_work : min(n_work, mine * per), hi = min(n_work, lo + per);
+        int lo = local_first ? 0 : (spare && m == 0) ? n_work : min(n_work, mine * per), hi = min(n_work, lo + per);
+        if (first.asked) {
+            lo = first.lo;
+            hi = n_first > 0 ? first.hi : lo;
+        }
+        const int slots_g = first.asked ? g.max_grids : ng, slots_gc = slots_g + (first.asked ? g.max_chunks : nc);
         // (one instance of the scoring loop per phase, each with straight-line slot arithmetic)
-        if constexpr (eager) scorer(lo, hi, AllTarget{ng, ng + nc, s, (int)(pubs.pages - pubs.units), scorer.at}, false, keys, pubs.units, requested);
-        else scorer(lo, hi, GridPhaseTarget{ng, scorer.at}, local_first, keys, pubs.units, requested);
+        if constexpr (eager) scorer(lo, hi, AllTarget{slots_g, slots_gc, ng, nc, s, P - w, (int)(pubs.pages - pubs.units), scorer.at}, false, keys, pubs.units, requested, first.asked);
+        else scorer(lo, hi, GridPhaseTarget{slots_g, ng, nc, scorer.at}, local_first, keys, pubs.units, requested, first.asked);
         if (!local_first) res->n_a = n_first;
         if (eager) res->n_p = P - w;
     }
     prof.mark(2);
     // (the summaries are kept current even if no cut needs one of the three keys)
-    if (tail_on && m == refresher) refresh_tail();
+    if (!eager && refreshes) refresh_tail();
     if (eager && !want_l3) return true;
 
     int n_kg = 0, n_kc = 0;                           // kept grids, kept chunks
@@ -1268,8 +1304,8 @@ __device__ __forceinline__ bool cascade_with(const Scorer& scorer, int P, const 
         if (!eager && level > 0 && n_work > 0) {
             const int per = local ? n_work : div_by(n_work + C - 1, sp.inv_members);
             const int lo = local ? 0 : min(n_work, m * per), hi = min(n_work, lo + per);
-            if (level == 1) scorer(lo, hi, target1, local, keys, pub, [] {});
-            else scorer(lo, hi, target2, local, keys, pub, [] {});
+            if (level == 1) scorer(lo, hi, target1, local, keys, pub, [] {}, false);
+            else scorer(lo, hi, target2, local, keys, pub, [] {}, false);
             if (!local) { if (level == 2) res->n_p = n_work; else res->n_a = max(res->n_a, ng + n_work); }
         }
         // kPhys: the block-table entries of every page slot are requested now, behind this member's vectors, and
@@ -1317,22 +1353,30 @@ __device__ __forceinline__ bool cascade_with(const Scorer& scorer, int P, const 
                 __syncthreads();
                 if (sh.flag == 0) return false;
             }
+        } else if constexpr (eager) {
+            if (n_work > 0) {
+                // (the page keys were published ahead, by page)
+                const PageWords words{target2, level == 2};
+                const bool ok = n_work <= kEachWaveSlots ? pull_keys<1>(pub, tail_words, n_work, words, ov_dest0, ov_word0, ov_dest1, ov_word1, keys, sh)
+                                : n_work <= 4 * kSelThreads ? pull_keys<4>(pub, tail_words, n_work, words, ov_dest0, ov_word0, ov_dest1, ov_word1, keys, sh)
+                                                            : pull_keys<8>(pub, tail_words, n_work, words, ov_dest0, ov_word0, ov_dest1, ov_word1, keys, sh);
+                if (!ok) return false;
+            }
         } else if (!solo && n_work > 0) {
             // (every non-local phase keeps its keys in slot order; a phase of 257 to 1024 slots hands them to the cut in registers)
             const int off = level == 1 ? ng : 0;
             const int od0 = ov_dest0 >= 0 ? ov_dest0 - off : -1, od1 = ov_dest1 >= 0 ? ov_dest1 - off : -1;
-            // (the words of a page phase are in slot order, or in page order when they were published ahead)
-            const PageWords words{target2, level == 2 && eager};
+            const SlotWords words;
             bool ok;
             if (n_work <= kEachWaveSlots) {
                 ok = pull_keys<1>(pub + off, tail_words, n_work, words, od0, ov_word0, od1, ov_word1, keys + off, sh);
             } else if (by_regs && n_work <= 4 * kSelThreads && !(merged && level == 0)) {
-                ok = pull_keys_regs(pub + off, tail_words, n_work, words, od0, ov_word0, od1, ov_word1, keys + off, pulled, sh);
+                ok = pull_keys_regs(pub + off, tail_words, n_work, od0, ov_word0, od1, ov_word1, keys + off, pulled, sh);
                 have_pulled = true;
             } else if (n_work <= 4 * kSelThreads) {
                 ok = pull_keys<4>(pub + off, tail_words, n_work, words, od0, ov_word0, od1, ov_word1, keys + off, sh);
             } else {
-                ok = pull_keys<eager ? 8 : kRegsLarge>(pub + off, tail_words, n_work, words, od0, ov_word0, od1, ov_word1, keys + off, sh);
+                ok = pull_keys<kRegsLarge>(pub + off, tail_words, n_work, words, od0, ov_word0, od1, ov_word1, keys + off, sh);
             }
             if (!ok) return false;
         }
@@ -1382,43 +1426,29 @@ __device__ __forceinline__ bool cascade_with(const Scorer& scorer, int P, const 
     return true;
 }
 
-// The scorer of one (sequence, KV head): the probe is in registers.
+// The scorer of one (sequence, KV head): the probe is in registers, and the vectors in flight.
 template <class T, bool kLean>
 struct HeadScorer {
-    static constexpr int kTrip = kSelGroups * kFlyOf<T, kLean>;   // slots a member scores per memory round trip
+    static constexpr int kFly = kFlyOf<T, kLean>;
+    static constexpr int kTrip = kSelGroups * kFly;               // slots a member scores per memory round trip
     const T* pages_row;
     VecBases at;
     const double (&pr)[8];
-    // (the three arrays lie in one summary buffer, behind one another, in whole vectors)
-    __device__ __forceinline__ HeadScorer(const T* pages, const T* chunks, const T* grids, const double (&probe)[8])
-        : pages_row(pages), at{vectors(pages, grids), vectors(pages, chunks)}, pr(probe) {}
-    static __device__ __forceinline__ int vectors(const T* from, const T* to)   // (to lies behind from)
-    {
-        constexpr int kLog = sizeof(T) == 4 ? 9 : 8;
-        static_assert(kHeadDim * sizeof(T) == 1u << kLog, "bytes of a vector");
-        return (int)((uint64_t)(reinterpret_cast<const char*>(to) - reinterpret_cast<const char*>(from)) >> kLog);
-    }
+    Vec<T> (&v)[kFly];
     template <class Target, class Requested>
     __device__ __forceinline__ void operator()(int lo, int hi, Target target, bool local, uint64_t* keys, uint64_t* pub,
-                                               Requested requested) const
+                                               Requested requested, bool asked) const
     {
-        score_rows<T, kFlyOf<T, kLean>>(pages_row, lo, hi, target, pr, local, keys, pub, requested);
+        score_rows<T, kFly>(pages_row, lo, hi, target, pr, local, keys, pub, requested, v, asked);
     }
 };
 
-template <int kMode, bool kPhys, class T, bool kLean, class ReqFn, class TailFn>
-__device__ __forceinline__ bool cascade(const T* __restrict__ pages_row, const T* __restrict__ chunks_row,
-                                        const T* __restrict__ grids_row, const double (&pr)[8], int P, const Geom& g,
-                                        const SelectParams& sp, const PubLayout& pubs, int m, int C, bool want_l3,
-                                        uint64_t* keys, int32_t* kept_grids, int32_t* kept_chunks, int32_t* sel_pages,
-                                        Shared& sh, CascadeResult* res, Prof& prof, const uint64_t* tail_words,
-                                        int refresher, ReqFn requested, TailFn refresh_tail, int k_fixed,
-                                        const int32_t* __restrict__ bt_row = nullptr,
-                                        int32_t* phys_by_slot = nullptr, int32_t* sel_phys = nullptr)
+// Where a row's chunk and grid vectors start, in vectors from its first page vector: the three arrays lie in one summary buffer, behind
+// one another, in whole vectors (rows: of the buffer).
+__device__ __forceinline__ VecBases bases_of(int rows, int row, int max_pages, int max_chunks, int max_grids)
 {
-    const HeadScorer<T, kLean> scorer(pages_row, chunks_row, grids_row, pr);
-    return cascade_with<kMode, kPhys>(scorer, P, g, sp, pubs, m, C, want_l3, keys, kept_grids, kept_chunks, sel_pages, sh, res,
-                                      prof, tail_words, refresher, requested, refresh_tail, k_fixed, bt_row, phys_by_slot, sel_phys);
+    const int to_chunks = rows * max_pages + row * (max_chunks - max_pages);
+    return VecBases{to_chunks + rows * max_chunks + row * (max_grids - max_chunks), to_chunks};
 }
 
 // Clear the published words of one (sequence, KV head) after everybody is done with them.

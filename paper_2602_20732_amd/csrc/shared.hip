@@ -127,7 +127,7 @@ struct SharedScorer {
     }
 
     template <class Target, class Requested>
-    __device__ __forceinline__ void operator()(int lo, int hi, Target target, bool local, uint64_t* keys, uint64_t* pub, Requested) const
+    __device__ __forceinline__ void operator()(int lo, int hi, Target target, bool local, uint64_t* keys, uint64_t* pub, Requested, bool) const
     {
         // the share in passes of equal size (the last may be shorter), at most kSharedSlots slots each
         const int n_pass = (hi - lo + kSharedSlots - 1) / kSharedSlots;
@@ -189,7 +189,7 @@ __global__ __launch_bounds__(kSelThreads) void select_shared_kernel(SharedTable 
     CascadeResult res;
     const SharedScorer<T> scorer{tab, b, g, red};
     const bool ok = cascade_with<kMode, false>(scorer, P, g, sp, pubs, m, C, m == 0, keys, kept_grids, kept_chunks, sel_pages, sh,
-                                        &res, prof, nullptr, 0, [] {}, [] {}, k_fixed);
+                                        &res, prof, nullptr, false, [] {}, [] {}, k_fixed, FirstShare{});
     if (!ok) {
         if (tid == 0) __hip_atomic_fetch_or(ws.error, kErrWait, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;

@@ -19,9 +19,6 @@ static_assert(kSelThreads % kWave == 0 && kSelThreads >= 256, "the fused step de
 constexpr int kStepWaves = kSelThreads / kWave;
 
 struct StepArgs {
-    void* pages;             // summaries (fp32 or bf16): read; the tail units are rewritten when refresh_tail is set
-    void* chunks;
-    void* grids;
     const uint16_t* k_pool;
     const uint16_t* v_pool;
     int32_t* page_ids;       // may be null
@@ -37,7 +34,7 @@ struct StepArgs {
 
 // The kernel's parameters (the table in step_kernel_of holds every instance to them), and where in the argument segment the first one of
 // type Arg lies: in order, each at the next multiple of its alignment.
-using StepKernel = void (*)(uint64_t, uint64_t, uint64_t, int, int, int, int, int, StepArgs, Geom, SelectParams, SelectWs);
+using StepKernel = void (*)(uint64_t, uint64_t, uint64_t, uint64_t, int, int, int, int, int, int, StepArgs, Geom, SelectParams, SelectWs);
 template <class Arg, class... Args>
 constexpr size_t kernarg_offset(void (*)(Args...))
 {
@@ -50,23 +47,63 @@ constexpr size_t kernarg_offset(void (*)(Args...))
     (place(sizeof(Args), alignof(Args), std::is_same_v<Args, Arg>), ...);
     return found;
 }
-constexpr size_t kStepArgsAt = kernarg_offset<StepArgs>(StepKernel(nullptr));
-static_assert(kStepArgsAt != ~(size_t)0, "the kernel has no such parameter");
 
-// StepArgs read again where they are needed: what only the attention uses would otherwise be in scalar registers -- or, as there are
-// too few, saved and restored -- all through the selection (lane reads in the eager kernel's code: 930, so 440).  us, kept /
+// A struct among the kernel's arguments, read where this stands and not when the kernel starts: what comes before does not wait for it,
+// and what the compiler would keep in scalar registers meanwhile -- or, as there are too few, save and restore -- can be read again.
+// With kAgain StepArgs are read again behind the selection (lane reads in the eager kernel's code: 930, so 440).  us, kept /
 // read again: eager 1 x 4K 15.9 / 15.1, 32 layers of 1 x 32K 663 / 639; lean, reselection of 96 sequences, 116.1 / 109.0; but solo, 8
 // layers of 32 x 16-32K, 259.8 / 262.8 and in clusters 8 x 128K 82.6 / 84.1: those two keep them.
+template <class Arg>
+__device__ __forceinline__ Arg late_arg()
+{
+    constexpr size_t at = kernarg_offset<Arg>(StepKernel(nullptr));
+    static_assert(at != ~(size_t)0 && at % 4 == 0 && sizeof(Arg) % 4 == 0, "the kernel has no such parameter");
+    typedef __attribute__((address_space(4))) const uint32_t* kernarg;
+    kernarg p = (kernarg)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p) : : "memory");          // (nothing is moved across: not these loads, and not those before)
+    struct Words { uint32_t w[sizeof(Arg) / 4]; } r;
+#pragma unroll
+    for (size_t i = 0; i < sizeof(Arg) / 4; ++i) r.w[i] = p[at / 4 + i];
+    return __builtin_bit_cast(Arg, r);
+}
+// The lines of the structs, asked for when the kernel starts: late_arg finds them in the scalar cache (a first read of an argument takes
+// 1.2 us).  hold() goes where the structs are read.
+struct ArgLines {
+    static constexpr size_t kFrom = kernarg_offset<StepArgs>(StepKernel(nullptr)) / 64, kTo = (kernarg_offset<SelectWs>(StepKernel(nullptr)) + sizeof(SelectWs) - 1) / 64;
+    static_assert(kTo - kFrom < 6, "a line more");
+    uint32_t w[6];
+    __device__ __forceinline__ void ask()
+    {
+        typedef __attribute__((address_space(4))) const volatile uint32_t* kernarg;     // (volatile: not moved to where they are held)
+        kernarg p = (kernarg)__builtin_amdgcn_kernarg_segment_ptr();
+#pragma unroll
+        for (size_t i = 0; i < 6; ++i) w[i] = p[(kFrom + i < kTo ? kFrom + i : kTo) * 16];
+    }
+    __device__ __forceinline__ void hold() const
+    {
+        asm volatile("" : : "s"(w[0]), "s"(w[1]), "s"(w[2]), "s"(w[3]), "s"(w[4]), "s"(w[5]) : "memory");
+    }
+};
+// (a pointer put together from words has no address space, and accesses through it would be flat ones)
+template <class V>
+__device__ __forceinline__ V* device_pointer(uint64_t at)
+{
+    return (V*)(__attribute__((address_space(1))) V*)at;
+}
+template <class V>
+__device__ __forceinline__ void in_device(V*& p) { p = device_pointer<V>((uint64_t)p); }
+__device__ __forceinline__ StepArgs late_step_args()
+{
+    StepArgs a = late_arg<StepArgs>();
+    in_device(a.k_pool); in_device(a.v_pool); in_device(a.page_ids); in_device(a.n_selected);
+    in_device(a.out); in_device(a.ws_acc); in_device(a.ws_ml); in_device(a.arrivals);
+    return a;
+}
 template <bool kAgain>
 __device__ __forceinline__ StepArgs late_args(const StepArgs& a)
 {
-    if constexpr (!kAgain) return a;
-    typedef __attribute__((address_space(4))) const char* kernarg;
-    kernarg p = (kernarg)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(p));                       // (not the loads the kernel began with)
-    StepArgs r;
-    __builtin_memcpy(&r, (const void*)(p + kStepArgsAt), sizeof(r));
-    return r;
+    if constexpr (kAgain) return late_step_args();
+    else return a;
 }
 
 // The per-step refresh of the summaries (Sec. 3.1, Eq. 1-2) of the tail page, its chunk and its grid, done by one
@@ -82,23 +119,34 @@ struct TailUnits {
     static constexpr int kSib = 8;
     uint16_t kr[B];          // this thread's column of the page's key rows
     T sp[kSib], sc[kSib];    // ... of the first other pages of the chunk and the first other chunks of the grid
-    // all requested at once: one round trip for the usual hierarchy of 8 x 8
-    __device__ __forceinline__ void request(const uint16_t* __restrict__ k_pool, int64_t phys, const T* pages_row,
-                                            const T* chunks_row, int h, int H, int L, int P, const Geom& g)
+    // (rows past the last token repeat it, children past the tail unit -- the last of each -- repeat it: neither is added)
+    __device__ __forceinline__ void request_siblings(const T* pages_row, const T* chunks_row, int P, const Geom& g)
     {
         const int c = threadIdx.x;
         if (c >= kHeadDim) return;
         const int tp = P - 1, tc = div_by(tp, g.inv_nc), tg = div_by(tc, g.inv_ng);
-        const int n_tok = L - tp * B, p_lo = tc * g.n_c, c_lo = tg * g.n_g;
-        // (rows past the last token repeat it, children past the tail unit -- the last of each -- repeat it: neither is added)
-        const uint16_t* rows = k_pool + ((phys * H + h) * B) * kHeadDim + c;
-#pragma unroll
-        for (int t = 0; t < B; ++t) kr[t] = rows[(size_t)min(t, n_tok - 1) * kHeadDim];
+        const int p_lo = tc * g.n_c, c_lo = tg * g.n_g;
 #pragma unroll
         for (int x = 0; x < kSib; ++x) {
             sp[x] = pages_row[(size_t)min(p_lo + x, tp) * kHeadDim + c];
             sc[x] = chunks_row[(size_t)min(c_lo + x, tc) * kHeadDim + c];
         }
+    }
+    __device__ __forceinline__ void request_rows(const uint16_t* __restrict__ k_pool, int64_t phys, int h, int H, int L, int P)
+    {
+        const int c = threadIdx.x;
+        if (c >= kHeadDim) return;
+        const int n_tok = L - (P - 1) * B;
+        const uint16_t* rows = k_pool + ((phys * H + h) * B) * kHeadDim + c;
+#pragma unroll
+        for (int t = 0; t < B; ++t) kr[t] = rows[(size_t)min(t, n_tok - 1) * kHeadDim];
+    }
+    // all requested at once: one round trip for the usual hierarchy of 8 x 8
+    __device__ __forceinline__ void request(const uint16_t* __restrict__ k_pool, int64_t phys, const T* pages_row,
+                                            const T* chunks_row, int h, int H, int L, int P, const Geom& g)
+    {
+        request_rows(k_pool, phys, h, H, L, P);
+        request_siblings(pages_row, chunks_row, P, g);
     }
     __device__ __forceinline__ void finish(T* pages_row, T* chunks_row, T* grids_row, int L, int P, const Geom& g,
                                            const double (&pr)[8], T* fresh, uint64_t* tail_words, bool publish, Shared& sh)
@@ -167,30 +215,129 @@ struct TailUnits {
     }
 };
 
-// The three pointers that the first loads need are numbers in the kernel's signature: a pointer among the arguments is looked up by the
-// runtime at each launch, and the first launch with memory that it has not seen as an argument yet took 20-120 us of host time (a first
-// pass of 96 ragged sequences, two layers, 130-290 us instead of 125-165).
-template <class V>
-__device__ __forceinline__ V* device_pointer(uint64_t at)
+// What the first loads need beside pointers, in few registers: KV heads, the group, and how the first phase is shared (see
+// choose_first_share): units a member takes, whether every member takes the same, whether the refreshing member takes none, which it is.
+struct FirstLoads {
+    static constexpr int kLocal = 1, kSpare = 2, kLastRefreshes = 4, kQueryProbe = 8, kGrids = 16, kChunks = 32, kFlagBits = 6, kPerBits = 12;
+    int heads, share;        // n_kv_heads << 8 | group; per << kPerBits | members << kFlagBits | flags
+};
+static_assert(kSelMaxCluster < 1 << (FirstLoads::kPerBits - FirstLoads::kFlagBits), "members fit their bits");
+
+// The eager schedule's last member, where the tail units are refreshed: it does that and nothing else.  Its keys are the last to be
+// published, so its chain of loads (length, block table, key rows) waits for nothing of the others': with a share's vectors requested
+// ahead of the block-table entry, the others waited 2 us more for its keys (32 layers of 1 x 32K 655 us).
+template <int B, class T>
+__device__ __forceinline__ void refresh_only(int L_lane, const int32_t* bt_row, T* pages_row, const VecBases& bases, ProbeRows<T>& probe, const uint16_t* q_rows, int G, int H,
+                                             int h, size_t row, int C, int max_pages, const ArgLines& lines, Shared& sh)
 {
-    return (V*)(__attribute__((address_space(1))) V*)at;
+    __shared__ T fresh[3 * kHeadDim];
+    const int L = min(max(__builtin_amdgcn_readfirstlane(L_lane), 0), max_pages * B), P = (L + B - 1) / B;
+    if (P == 0) return;
+    const int phys = load_by_lane(bt_row + P - 1);
+    lines.hold();
+    const StepArgs a = late_step_args();
+    const Geom g = late_arg<Geom>();
+    const SelectParams sp = late_arg<SelectParams>();
+    SelectWs ws = late_arg<SelectWs>();
+    in_device(ws.keys); in_device(ws.tail);
+    T* chunks_row = pages_row + (int64_t)bases.chunks * kHeadDim;
+    T* grids_row = pages_row + (int64_t)bases.grids * kHeadDim;
+    TailUnits<B, T> tail;
+    tail.request_siblings(pages_row, chunks_row, P, g);
+    double pr[8];
+    probe.sum(q_rows, G, pr);
+    tail.request_rows(a.k_pool, __builtin_amdgcn_readfirstlane(phys), h, H, L, P);
+    uint64_t* tail_words = ws.tail + row * 4;
+    const bool compete = P > sp.sink + sp.window;     // (otherwise nobody reads the keys; the summaries are kept current)
+    tail.finish(pages_row, chunks_row, grids_row, L, P, g, pr, fresh, tail_words, compete, sh);
+    if (!compete) return;
+    const int nc = div_by(P + g.n_c - 1, g.inv_nc), ng = div_by(nc + g.n_g - 1, g.inv_ng);
+    if (arrive_of_two(a.arrivals + row, false, sp.deciders, C - sp.deciders, &sh.flag) & kLastOfAll)
+        clear_published(pub_layout(ws.keys + row * ws.key_stride, g), CascadeResult{0, ng + nc, P - sp.window, false}, tail_words);
 }
 
 // grid = (C, H_kv, batch); T = storage type of the summaries (float or bf16 bits); kMode: see cascade_with; kLean: three
 // workgroups on a compute unit instead of two (see launch_step)
+// The pointers that the first loads need are numbers in the kernel's signature: a pointer among the arguments is looked up by the
+// runtime at each launch, and the first launch with memory that it has not seen as an argument yet took 20-120 us of host time (a first
+// pass of 96 ragged sequences, two layers, 130-290 us instead of 125-165).
+// The first loads need nothing but preloaded registers, and nothing waits for the other arguments before they are on their way: units of
+// the first phase are counted in the configuration's (max_grids, then max_chunks, then max_pages), so that their vectors can be requested
+// while the sequence's length is still on its way (0.93 us; 1.25 as a scalar load, which came back with the arguments).
+// us a layer, with the vectors asked for behind the length and the arguments / as here: 1 x 4K 14.7 / 14.0, 32 layers of 1 x 32K 20.0 /
+// 18.6, 8 of 32 x 16-32K 32.5 / 31.1, 2 of 8 x 128K 41.0 / 39.0, 8 of 1 x 256K with pages of 32 33.6 / 31.6.
 template <int B, class T, int kMode, bool kLean>
-__global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(kLean ? 3 : 2))) void step_kernel(uint64_t q_at, uint64_t seq_lens_at, uint64_t block_table_at, int n_q_heads,
-                            int n_kv_heads, int group, int max_pages, int query_probe, StepArgs a, Geom g_args, SelectParams sp_args, SelectWs ws)
+__global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(kLean ? 3 : 2))) void step_kernel(uint64_t q_at, uint64_t seq_lens_at, uint64_t pages_at, uint64_t block_table_at,
+                            int heads, int share, int max_pages, int max_chunks, int max_grids, int summary_rows, StepArgs, Geom, SelectParams, SelectWs)
 {
     // (what the first loads need comes in registers, ahead of the structs: see build.py)
     const uint16_t* q = device_pointer<const uint16_t>(q_at);
     const int32_t* seq_lens = device_pointer<const int32_t>(seq_lens_at);
-    const int32_t* block_table = device_pointer<const int32_t>(block_table_at);
-    const int L_raw = seq_lens[blockIdx.z];
-    const uint16_t* q_rows = q + ((size_t)blockIdx.z * n_q_heads + (size_t)blockIdx.y * group) * kHeadDim;
+    __shared__ Shared sh;
+    Prof prof;
+    prof.mark(0);
+    const int h = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
+    const int H = heads >> 8, G = heads & 255, n_q_heads = H * G;
+    const bool query_probe = (share & FirstLoads::kQueryProbe) != 0;
+    ArgLines lines;
+    lines.ask();
+    __builtin_amdgcn_sched_barrier(0);
+    int L_raw = load_by_lane(seq_lens + b);                           // (scalar when it is used)
+    const uint16_t* q_rows = q + ((size_t)b * n_q_heads + (size_t)h * G) * kHeadDim;
     double pr[8];
     ProbeRows<T> probe;
-    if (query_probe) probe.request(q_rows, 0, group);                 // before anything waits on the length
+    probe.request(q_rows, 0, G);
+    // ---- the first trip of the first phase's vectors
+    const int m = kMode == kSolo ? 0 : blockIdx.x, C = kMode == kSolo ? 1 : (share >> FirstLoads::kFlagBits) & ((1 << (FirstLoads::kPerBits - FirstLoads::kFlagBits)) - 1);
+    const size_t row = (size_t)b * H + h;
+    T* pages_row = device_pointer<T>(pages_at) + row * max_pages * kHeadDim;
+    const VecBases bases = bases_of(summary_rows, (int)row, max_pages, max_chunks, max_grids);
+    const int32_t* bt_row = device_pointer<const int32_t>(block_table_at) + (size_t)b * max_pages;
+    int tail_phys = 0;                                                // of the last page, where member 0 refreshes the tail units
+    Vec<T> fly[kFlyOf<T, kLean>];
+    const int n_static = (share & FirstLoads::kGrids ? max_grids : 0) + (share & FirstLoads::kChunks ? max_chunks : 0) + (kMode == kEagerCluster ? max_pages : 0);
+    FirstShare first{n_static > 0, kMode == kSolo || (share & FirstLoads::kLocal) != 0, 0, n_static};
+    {
+        const int per = share >> FirstLoads::kPerBits, who = (share & FirstLoads::kLastRefreshes) ? C - 1 : 0;
+        const bool spare = (share & FirstLoads::kSpare) != 0;
+        if (!first.local) {
+            first.lo = spare && m == who ? n_static : min(n_static, (spare && m > who ? m - 1 : m) * per);
+            first.hi = min(n_static, first.lo + per);
+        }
+        const auto vec_of = [&](int slot) {
+            if constexpr (kMode == kEagerCluster) return AllTarget{max_grids, max_grids + max_chunks, 0, 0, 0, 0, 0, bases}.vec(slot);
+            else return GridPhaseTarget{max_grids, 0, 0, bases}.vec(slot);
+        };
+        if constexpr (kMode == kEagerCluster) {
+            if (spare && m == who) {                                  // (what it asks for comes behind nothing)
+                refresh_only<B, T>(L_raw, bt_row, pages_row, bases, probe, q_rows, G, H, h, row, C,
+                                   max_pages, lines, sh);
+                return;
+            }
+        }
+        const auto ask = [&]() { ask_rows<T, kFlyOf<T, kLean>>(pages_row, first.lo, max(first.hi, 1), vec_of, tid >> 4, tid & 15, fly); };
+        // The member that refreshes the tail units asks for the last block-table entry ahead of the vectors, or instead of them: the
+        // key rows, which wait for it, are what its first cut waits for (loads return in order).
+        const auto ask_last = [&]() { tail_phys = load_by_lane(bt_row + max((min(max(L_raw, 0), max_pages * B) + B - 1) / B - 1, 0)); };
+        // (the length is waited for on either side of a branch: behind it, the wait would be for every load of the other side)
+        if (kMode == kSolo || (kMode == kCluster && (!first.asked || (spare && m == 0)))) {
+            L_raw = __builtin_amdgcn_readfirstlane(L_raw);
+            if (m == 0) ask_last();
+            probe.arrived();
+            if (kMode == kSolo && first.asked) ask();
+        } else {
+            ask();                                                    // (of an empty share: some vector, which nobody looks at)
+            L_raw = __builtin_amdgcn_readfirstlane(L_raw);
+            if (kMode == kCluster && m == 0) ask_last();
+        }
+    }
+    lines.hold();
+    const StepArgs a = late_step_args();
+    const Geom g_args = late_arg<Geom>();
+    SelectParams sp_args = late_arg<SelectParams>();
+    in_device(sp_args.budget_per_seq);
+    SelectWs ws = late_arg<SelectWs>();
+    in_device(ws.keys); in_device(ws.tail); in_device(ws.meta); in_device(ws.error);
     const Geom g = own_regs(g_args);
     const SelectParams sp = own_regs(sp_args);
     constexpr int PPT = 32 / B;
@@ -204,21 +351,14 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(kLe
     int32_t* kept_chunks = kept_grids + sp.cap_kg;
     int32_t* phys_by_slot = kept_chunks + sp.cap_kc;                                       // [cap3]
     DecodeLds<kStepWaves> dl(reinterpret_cast<float*>(un));                                // decode's view
-    __shared__ Shared sh;
-
     // C members score; the first D of them go on to the cuts and the attention (all of them unless the schedule is eager)
-    const int m = kMode == kSolo ? 0 : blockIdx.x, C = kMode == kSolo ? 1 : gridDim.x, D = kMode == kEagerCluster ? sp.deciders : C, h = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
+    const int D = kMode == kEagerCluster ? sp.deciders : C;
     const int lane = tid & 63, wave = tid >> 6, m16 = lane & 15, grp = lane >> 4;
-    const int G = group, H = n_kv_heads;
-    Prof prof;
-    prof.mark(0);
-    const size_t row = (size_t)b * H + h;
     const int k_fixed = fixed_budget(sp, g, b);
     init_shared(sh, sp.poll_limit);
-    const int L = min(max(L_raw, 0), g.max_pages * B);
+    const int L = min(max(L_raw, 0), max_pages * B);
     const int P = (L + B - 1) / B;
     const int s = sp.sink, w = sp.window;
-    const int32_t* bt_row = block_table + (size_t)b * max_pages;
     if (P == 0) {                                                     // empty sequence: no pages, zero output
         if (m == 0) {
             if (a.page_ids) for (int i = tid; i < g.max_sel; i += kSelThreads) a.page_ids[row * g.max_sel + i] = -1;
@@ -227,23 +367,20 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(kLe
         }
         return;
     }
-    T* pages_row = static_cast<T*>(a.pages) + row * g.max_pages * kHeadDim;
-    T* chunks_row = static_cast<T*>(a.chunks) + row * g.max_chunks * kHeadDim;
-    T* grids_row = static_cast<T*>(a.grids) + row * g.max_grids * kHeadDim;
+    T* chunks_row = pages_row + (int64_t)bases.chunks * kHeadDim;
+    T* grids_row = pages_row + (int64_t)bases.grids * kHeadDim;
     if (!query_probe) load_anchor<T>(pages_row, P, w, pr);
-    // one member refreshes the tail units, a helper if there are any: its block-table entry is requested now
-    const int refresher = D < C ? C - 1 : 0;
+    // one member refreshes the tail units (eager: refresh_only's)
     const bool tail_on = a.refresh_tail != 0;
+    const bool refreshes = kMode != kEagerCluster && tail_on && m == 0;
     uint64_t* tail_words = tail_on ? ws.tail + row * 4 : nullptr;
-    int tail_phys = 0;
-    if (tail_on && m == refresher) tail_phys = bt_row[P - 1];
     TailUnits<B, T> tail;
     auto requested = [&]() {                                          // (the first vectors to score are on their way)
         if (query_probe) probe.sum(q_rows, G, pr);
-        if (!kLean && tail_on && m == refresher) tail.request(a.k_pool, tail_phys, pages_row, chunks_row, h, H, L, P, g);
+        if (!kLean && refreshes) tail.request(a.k_pool, __builtin_amdgcn_readfirstlane(tail_phys), pages_row, chunks_row, h, H, L, P, g);
     };
     auto refresh_tail = [&]() {
-        if (kLean) tail.request(a.k_pool, tail_phys, pages_row, chunks_row, h, H, L, P, g);   // (no registers for it before)
+        if (kLean) tail.request(a.k_pool, __builtin_amdgcn_readfirstlane(tail_phys), pages_row, chunks_row, h, H, L, P, g);   // (no registers for it before)
         tail.finish(pages_row, chunks_row, grids_row, L, P, g, pr, fresh, tail_words, C > 1 && P > s + w, sh);
     };
     __syncthreads();
@@ -255,7 +392,7 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(kLe
     res.n_kp = 0; res.n_a = 0; res.n_p = 0; res.overflow = false;
     int n_sel;
     if (P <= s + w) {                                                 // safety pages cover the sequence
-        if (tail_on && m == refresher) {                              // nobody reads the keys; the summaries are kept current
+        if (refreshes) {                                              // nobody reads the keys; the summaries are kept current
             requested();
             refresh_tail();
         }
@@ -269,8 +406,9 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(kLe
         int safety_phys = 0;
         if (safety_early && tid < s + w) safety_phys = bt_row[safety_lp];
         // kept pages and their physical pages go straight to their places in the list, behind the sinks
-        const bool ok = cascade<kMode, true, T, kLean>(pages_row, chunks_row, grids_row, pr, P, g, sp, pubs, m, C, m < D, keys, kept_grids,
-                                         kept_chunks, ids_l + s, sh, &res, prof, tail_words, refresher, requested, refresh_tail, k_fixed, bt_row,
+        const HeadScorer<T, kLean> scorer{pages_row, bases, pr, fly};
+        const bool ok = cascade_with<kMode, true>(scorer, P, g, sp, pubs, m, C, m < D, keys, kept_grids,
+                                         kept_chunks, ids_l + s, sh, &res, prof, tail_words, refreshes, requested, refresh_tail, k_fixed, first, bt_row,
                                          phys_by_slot, phys_l + s);
         if (!ok) {
             if (tid == 0) __hip_atomic_fetch_or(ws.error, kErrWait, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -382,12 +520,34 @@ hipError_t step_occupancy(int page_size, bool bf16, int lds_bytes, int* blocks_p
     return hipSuccess;
 }
 
+// Which of the first phase's vectors are requested before the lengths are known: units counted in the configuration's, dealt as
+// the phase deals them; only where the first trip is all of them and, beside the eager schedule (whose bytes choose_eager bounds), they are
+// few: of sequences much shorter than the configuration's most of them do not exist (8 MB take 1.3 us; us a layer with room for 4 to 32
+// times the length, behind the length / as here: 1 x 4K 16.5 / 16.3 and 18.9 / 18.0, 8 x 8K 25.6 / 23.9, 32 x 4K 19.1 / 18.5).
+static void choose_first_share(const Geom& g, const SelectParams& sp, int mode, int64_t rows, int cluster, bool bf16, int refresh_tail, FirstLoads* f)
+{
+    const bool solo = mode == kSolo || mode == kSoloLean, eager = mode == kEagerCluster;
+    const int trip = kSelGroups * (bf16 ? 16 : 8) / (mode == kSoloLean ? 2 : 1);             // (HeadScorer::kTrip)
+    int n = g.max_grids;
+    if (sp.schedule == kMerged && !solo) n += g.max_chunks;
+    if (eager) n += g.max_chunks + g.max_pages;
+    const bool local = solo || (!eager && sp.schedule != kMerged && sp.local_grids != 0 && n <= kSelGroups * 8);
+    const int without = cluster > 1 ? (n + cluster - 2) / (cluster - 1) : n;
+    const bool spare = refresh_tail != 0 && !local && (eager || without <= trip);
+    const int per = local ? n : spare ? without : (n + cluster - 1) / cluster;
+    const int64_t bytes = rows * (local ? (int64_t)n * cluster : n) * kHeadDim * (bf16 ? 2 : 4);
+    f->share |= cluster << FirstLoads::kFlagBits;
+    if (!eager && (sp.cap_kg >= g.max_grids || per > trip || bytes > (8LL << 20))) return;      // (a grid level that keeps every grid is not scored)
+    f->share |= per << FirstLoads::kPerBits | FirstLoads::kGrids | (n > g.max_grids ? FirstLoads::kChunks : 0) | (local ? FirstLoads::kLocal : 0) |
+                (spare ? FirstLoads::kSpare : 0) | (eager ? FirstLoads::kLastRefreshes : 0);
+}
+
 hipError_t launch_step(chess_ctx* ctx, const StepLaunch& sl, int batch, int cluster, const SelectParams& sp,
                        const SelectWs& ws, size_t lds_bytes, int union_off, hipStream_t stream)
 {
     const Geom& g = ctx->geom;
     StepArgs a;
-    a.pages = sl.pages; a.chunks = sl.chunks; a.grids = sl.grids; a.k_pool = sl.k_pool; a.v_pool = sl.v_pool;
+    a.k_pool = sl.k_pool; a.v_pool = sl.v_pool;
     a.page_ids = sl.page_ids; a.n_selected = sl.n_selected;
     a.out = sl.out; a.ws_acc = sl.ws_acc; a.ws_ml = sl.ws_ml; a.arrivals = sl.arrivals;
     a.scale_log2 = ctx->sm_scale * 1.4426950408889634f;
@@ -401,14 +561,16 @@ hipError_t launch_step(chess_ctx* ctx, const StepLaunch& sl, int batch, int clus
     // 89.8 / 86.5.  Below, it depends: 512 of 8-16K 39.5 / 37.7, 512 of 16K with bf16 vectors 38.5 / 43.4, 256 of 16-32K 41.0 / 41.0.
     const bool lean = lean_step(ctx->n_cu, (int64_t)batch * g.n_kv_heads, step_level_bytes(sp) + sizeof(Shared));
     const int mode = cluster == 1 ? (lean ? kSoloLean : kSolo) : sp.schedule == kEager ? kEagerCluster : kCluster;
-    const StepKernel kern = step_kernel_of(g.page_size, ctx->cfg.summary_dtype == CHESS_SUMMARY_BF16, mode);
+    const bool bf16 = ctx->cfg.summary_dtype == CHESS_SUMMARY_BF16;
+    FirstLoads first{g.n_kv_heads << 8 | g.group, sp.probe == CHESS_PROBE_QUERY ? FirstLoads::kQueryProbe : 0};
+    choose_first_share(g, sp, mode, (int64_t)batch * g.n_kv_heads, cluster, bf16, sl.refresh_tail, &first);
+    const StepKernel kern = step_kernel_of(g.page_size, bf16, mode);
     if (lds_bytes > 48 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         if (e != hipSuccess) return e;
     }
-    return launch(kern, grid, block, lds_bytes, stream,
-                  (uint64_t)sl.q, (uint64_t)sl.seq_lens, (uint64_t)sl.block_table, g.n_q_heads, g.n_kv_heads, g.group, g.max_pages, sp.probe == CHESS_PROBE_QUERY ? 1 : 0, a, g,
-                  sp, ws);
+    return launch(kern, grid, block, lds_bytes, stream, (uint64_t)sl.q, (uint64_t)sl.seq_lens, (uint64_t)sl.pages, (uint64_t)sl.block_table,
+                  first.heads, first.share, g.max_pages, g.max_chunks, g.max_grids, ctx->cfg.max_batch * g.n_kv_heads, a, g, sp, ws);
 }
 
 }  // namespace chess
