@@ -99,6 +99,34 @@ struct SelectWs {
 constexpr int kErrWait = 1;          // a wait for published keys was given up
 constexpr int kErrOverflow = 2;      // the threshold rule kept more units than a list has room for (the list was cut short)
 
+// The 64-byte lines of a kernel's arguments that hold bytes [kBegin, kEnd), asked for with the kernel's first instructions, so that the
+// arguments are in the scalar cache when they are read: a first read takes 1.2 us, and the compiler puts it in front of its use.
+template <size_t kBegin, size_t kEnd>
+struct ArgLines {
+    static constexpr size_t kFirst = kBegin / 64, kLines = (kEnd - 1) / 64 - kFirst + 1;
+    uint32_t w[kLines];
+    __device__ __forceinline__ void ask()
+    {
+        typedef __attribute__((address_space(4))) const volatile uint32_t* kernarg;     // (volatile: not moved to where they are held)
+        kernarg p = (kernarg)__builtin_amdgcn_kernarg_segment_ptr();
+#pragma unroll
+        for (size_t i = 0; i < kLines; ++i) w[i] = p[(kFirst + i) * 16];
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    __device__ __forceinline__ void hold() const
+    {
+#pragma unroll
+        for (size_t i = 0; i < kLines; ++i) asm volatile("" : : "s"(w[i]) : "memory");
+    }
+};
+
+// A pointer that travels as a number.
+template <class V>
+__device__ __forceinline__ V* device_pointer(uint64_t at)
+{
+    return (V*)(__attribute__((address_space(1))) V*)at;
+}
+
 // One word that every lane needs, as a vector load: the first of a kernel is back after 0.93 us, a scalar load after 1.25 (the lengths
 // in the fused step, the phase marks of a profiling build).  The same value in every lane.
 __device__ __forceinline__ int load_by_lane(const int32_t* p)

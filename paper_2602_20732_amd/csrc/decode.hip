@@ -170,33 +170,52 @@ __device__ __forceinline__ SlotShare share_slots(int slot, int n_slots, int batc
     return s;
 }
 
+// What the attention kernels need later than their first loads.  Those (lengths, lists, block table, queries) have their pointers and
+// sizes in preloaded registers: an argument that has to be fetched is there after 1.2 us, and a length or a list asked for behind it 0.9 us
+// later.  us, the pools first and loads moved behind the length / as here: reuse step, 32 layers of 1 x 32K 231.7 / 208.4, 8 layers of 32 x
+// 16-32K 128.6 / 123.4; 32 layers of 4 x 24-32K and their selection 314 / 306; every page 461 / 461.  Numbers, not pointers: see step.hip.
+struct DecodeArgs {
+    uint16_t* k_pool;        // (written by the reuse kernel only, as v_pool)
+    uint16_t* v_pool;
+    float* out;
+    float* ws_acc;
+    float* ws_ml;
+    int32_t* arrivals;
+    float scale_log2;
+    int batch;
+    const uint16_t* k_new;   // reuse
+    const uint16_t* v_new;
+};
+constexpr size_t kDecodeArgsAt = 5 * 8 + 4 * 4;       // (in the kernels' arguments, behind five numbers of 8 and four of 4 bytes)
+static_assert(kDecodeArgsAt % alignof(DecodeArgs) == 0);
+using DecodeLines = ArgLines<kDecodeArgsAt, kDecodeArgsAt + sizeof(DecodeArgs)>;
+// What stands before is requested before what stands behind (the compiler moves a load that only a branch uses into the branch).
+__device__ __forceinline__ void requested_by_here() { asm volatile("" : : : "memory"); }
+
 // Three workgroups of four waves per compute unit (at most 170 registers a lane): see run_tiles_with, kSingle.
+// heads: KV heads << 8 | group.
 template <int B, int NW, bool kList, bool kDealt = false>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(3))) void decode_kernel(const uint16_t* __restrict__ q,
-                                                         const uint16_t* __restrict__ k_pool,
-                                                         const uint16_t* __restrict__ v_pool,
-                                                         const int32_t* __restrict__ block_table,
-                                                         const int32_t* __restrict__ seq_lens,
-                                                         const int32_t* __restrict__ page_ids,
-                                                         const int32_t* __restrict__ n_selected, Geom g,
-                                                         float scale_log2, int n_splits, int batch,
-                                                         float* __restrict__ out, float* __restrict__ ws_acc,
-                                                         float* __restrict__ ws_ml, int32_t* __restrict__ arrivals)
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(3))) void decode_kernel(uint64_t seq_lens_at, uint64_t block_table_at, uint64_t q_at,
+                                                         uint64_t page_ids_at, uint64_t n_selected_at, int heads, int max_sel, int max_pages,
+                                                         int n_splits, DecodeArgs a)
 {
     constexpr int PPT = 32 / B;
     extern __shared__ float lds_f[];                  // DecodeLds<NW>::floats(G)
     __shared__ int lds_last;
-    DecodeLds<NW> lds(lds_f, g.group);
+    const int G = heads & 255, H = heads >> 8, h = kDealt ? blockIdx.x : blockIdx.y;
+    DecodeLines lines;
+    lines.ask();
+    DecodeLds<NW> lds(lds_f, G);
+    const int32_t* seq_lens = device_pointer<const int32_t>(seq_lens_at);
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int m16 = lane & 15, grp = lane >> 4;
-    const int G = g.group, H = g.n_kv_heads, h = kDealt ? blockIdx.x : blockIdx.y;
     // the workgroup's sequence, its place among that row's splits, and where the row's partials start
     int split = blockIdx.x, b = blockIdx.z, ns = n_splits, L_raw;
     size_t part0 = ((size_t)b * H + h) * n_splits;
     if constexpr (kDealt) {                           // grid = (H_kv, n_slots): the heads of a page are read at about the same time
         __shared__ DealLds<NW> deal_lds;
-        const SlotShare sh = share_slots<B, NW>(blockIdx.y, gridDim.y, batch, n_splits, G, seq_lens, g.max_pages, lane, wave, deal_lds);
+        const SlotShare sh = share_slots<B, NW>(blockIdx.y, gridDim.y, a.batch, n_splits, G, seq_lens, max_pages, lane, wave, deal_lds);
         if (sh.b < 0) return;                         // (uniform: nobody waits for a slot without work)
         split = sh.split;
         b = sh.b;
@@ -205,37 +224,42 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(3))) vo
         part0 = (size_t)h * gridDim.y + sh.first;
     }
     const size_t row = (size_t)b * H + h;
-    const int32_t* ids = kList ? page_ids + row * g.max_sel : nullptr;
-    const int32_t* bt_row = block_table + (size_t)b * g.max_pages;
+    const int32_t* ids = kList ? device_pointer<const int32_t>(page_ids_at) + row * max_sel : nullptr;
+    const int32_t* bt_row = device_pointer<const int32_t>(block_table_at) + (size_t)b * max_pages;
     // tiles are dealt round-robin: tile = split + n_splits * (wave + NW * i), so the first tile of a wave
     // is known before the list length is, and its page numbers can be fetched alongside the lengths
     const int stride = ns * NW;
     const int t = split + ns * wave;
     int raw_cur[PPT], raw_nxt[PPT];
-    if constexpr (!kDealt) L_raw = seq_lens[b];
-    const int n_raw = kList ? n_selected[row] : 0;
-    fetch_ids<B, kList>(raw_cur, t, ids, g.max_sel);
-    fetch_ids<B, kList>(raw_nxt, t + stride, ids, g.max_sel);
-    const int L = min(max(L_raw, 0), g.max_pages * B);
+    if constexpr (!kDealt) L_raw = load_by_lane(seq_lens + b);
+    int n_raw = kList ? load_by_lane(device_pointer<const int32_t>(n_selected_at) + row) : 0;
+    fetch_ids<B, kList>(raw_cur, t, ids, max_sel);
+    fetch_ids<B, kList>(raw_nxt, t + stride, ids, max_sel);
+    WaveAcc<B> acc;
+    acc.request(device_pointer<const uint16_t>(q_at) + ((size_t)b * H * G + (size_t)h * G) * kHeadDim, G, m16, grp);
+    requested_by_here();
+    if constexpr (!kDealt) L_raw = __builtin_amdgcn_readfirstlane(L_raw);
+    if (kList) n_raw = __builtin_amdgcn_readfirstlane(n_raw);
+    const int L = min(max(L_raw, 0), max_pages * B);
     const int P = (L + B - 1) / B;
-    const int n_pages = P == 0 ? 0 : (kList ? min(max(n_raw, 0), g.max_sel) : P);
+    const int n_pages = P == 0 ? 0 : (kList ? min(max(n_raw, 0), max_sel) : P);
     const int n_tiles = (n_pages + PPT - 1) / PPT;
 
-    WaveAcc<B> acc;
-    acc.init(q + ((size_t)b * g.n_q_heads + (size_t)h * G) * kHeadDim, G, m16, grp);
+    lines.hold();
+    acc.start(G, m16);
     NewToken<B> none;
     none.tile = -1;
-    run_tiles_with<B, kList, false, false, true>(acc, t, stride, n_tiles, n_pages, raw_cur, raw_nxt, ids, g.max_sel, bt_row, nullptr,
-                                                 k_pool, v_pool, H, h, L, P, scale_log2, m16, grp, none, 1 << 30);
+    run_tiles_with<B, kList, false, false, true>(acc, t, stride, n_tiles, n_pages, raw_cur, raw_nxt, ids, max_sel, bt_row, nullptr,
+                                                 a.k_pool, a.v_pool, H, h, L, P, a.scale_log2, m16, grp, none, 1 << 30);
 
-    float* out_rows = out + ((size_t)b * g.n_q_heads + (size_t)h * G) * kHeadDim;
-    if (!combine_waves<NW>(acc.o, acc.m_run, acc.l_run, lds, G, ns, split, part0, out_rows, ws_acc, ws_ml)) return;
-    if (!arrive_last(arrivals + row, ns, &lds_last)) return;
+    float* out_rows = a.out + ((size_t)b * H * G + (size_t)h * G) * kHeadDim;
+    if (!combine_waves<NW>(acc.o, acc.m_run, acc.l_run, lds, G, ns, split, part0, out_rows, a.ws_acc, a.ws_ml)) return;
+    if (!arrive_last(a.arrivals + row, ns, &lds_last)) return;
     if constexpr (kDealt) {                           // (the same in every lane, which the compiler cannot tell)
         ns = own_reg(__builtin_amdgcn_readfirstlane(ns));
         part0 = own_reg((unsigned)__builtin_amdgcn_readfirstlane((int)part0));
     }
-    merge_splits<NW, kDealt ? kMergeDealt : kMergePlain>(G, ns, part0, out_rows, ws_acc, ws_ml);
+    merge_splits<NW, kDealt ? kMergeDealt : kMergePlain>(G, ns, part0, out_rows, a.ws_acc, a.ws_ml);
 }
 
 // The step between reselections (Sec. 3.3) in one launch: attention over the kept list for the sequence WITH the
@@ -248,42 +272,47 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(3))) vo
 // kSingle: one tile in registers at a time; faster while a wave has only a few tiles (the host decides).
 // Two workgroups per compute unit either way (squeezed into the registers of three, the kernel was slower).
 template <int B, bool kSingle, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void reuse_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_new,
-                                                    const uint16_t* __restrict__ v_new, uint16_t* __restrict__ k_pool,
-                                                    uint16_t* __restrict__ v_pool, const int32_t* __restrict__ block_table,
-                                                    const int32_t* __restrict__ seq_lens, int32_t* __restrict__ page_ids,
-                                                    int32_t* __restrict__ n_selected, Geom g, float scale_log2, int n_splits,
-                                                    float* __restrict__ out, float* __restrict__ ws_acc,
-                                                    float* __restrict__ ws_ml, int32_t* __restrict__ arrivals)
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void reuse_kernel(uint64_t seq_lens_at, uint64_t block_table_at, uint64_t q_at,
+                                                    uint64_t page_ids_at, uint64_t n_selected_at, int heads, int max_sel, int max_pages,
+                                                    int n_splits, DecodeArgs a)
 {
     constexpr int PPT = 32 / B;
     extern __shared__ float lds_f[];
     __shared__ int lds_last;
-    DecodeLds<NW> lds(lds_f, g.group);
+    const int G = heads & 255, H = heads >> 8;
+    DecodeLines lines;
+    lines.ask();
+    DecodeLds<NW> lds(lds_f, G);
 
     const int split = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int m16 = lane & 15, grp = lane >> 4;
-    const int G = g.group, H = g.n_kv_heads;
     const size_t row = (size_t)b * H + h;
-    int32_t* ids = page_ids + row * g.max_sel;
-    const int32_t* bt_row = block_table + (size_t)b * g.max_pages;
+    int32_t* ids = device_pointer<int32_t>(page_ids_at) + row * max_sel;
+    int32_t* n_selected = device_pointer<int32_t>(n_selected_at) + row;
+    const int32_t* bt_row = device_pointer<const int32_t>(block_table_at) + (size_t)b * max_pages;
     const int stride = n_splits * NW;
     const int t = split + n_splits * wave;
     int raw_cur[PPT], raw_nxt[PPT];
-    const int L_before = seq_lens[b];
-    const int n_raw = n_selected[row];
-    fetch_ids<B, true>(raw_cur, t, ids, g.max_sel);
-    fetch_ids<B, true>(raw_nxt, t + stride, ids, g.max_sel);
+    int L_before = load_by_lane(device_pointer<const int32_t>(seq_lens_at) + b);
+    int n_raw = load_by_lane(n_selected);
+    fetch_ids<B, true>(raw_cur, t, ids, max_sel);
+    fetch_ids<B, true>(raw_nxt, t + stride, ids, max_sel);
+    WaveAcc<B> acc;
+    acc.request(device_pointer<const uint16_t>(q_at) + ((size_t)b * H * G + (size_t)h * G) * kHeadDim, G, m16, grp);
+    requested_by_here();
+    L_before = __builtin_amdgcn_readfirstlane(L_before);
+    n_raw = __builtin_amdgcn_readfirstlane(n_raw);
+    lines.hold();
     NewToken<B> nt;
-    nt.k_row = k_new + row * kHeadDim;
-    nt.v_row = v_new + row * kHeadDim;
+    nt.k_row = a.k_new + row * kHeadDim;
+    nt.v_row = a.v_new + row * kHeadDim;
 
-    const bool room = L_before >= 0 && L_before < g.max_pages * B;
-    const int L = room ? L_before + 1 : min(max(L_before, 0), g.max_pages * B);
+    const bool room = L_before >= 0 && L_before < max_pages * B;
+    const int L = room ? L_before + 1 : min(max(L_before, 0), max_pages * B);
     const int P = (L + B - 1) / B;
-    const int n_stored = min(max(n_raw, 0), g.max_sel);
-    const bool grow = room && L_before % B == 0 && n_stored < g.max_sel;     // the token opens a page
+    const int n_stored = min(max(n_raw, 0), max_sel);
+    const bool grow = room && L_before % B == 0 && n_stored < max_sel;       // the token opens a page
     const int n_pages = P == 0 ? 0 : n_stored + (grow ? 1 : 0);
     const int n_tiles = (n_pages + PPT - 1) / PPT;
     // the tail page is the list's last entry -- unless the token opens a page and the row has no room for it: then
@@ -292,31 +321,35 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     nt.tile = room && n_pages > 0 && (grow || L_before % B != 0) ? (n_pages - 1) / PPT : -1;
     nt.T = ((n_pages - 1) % PPT) * B + L_before % B;
 
-    WaveAcc<B> acc;
-    acc.init(q + ((size_t)b * g.n_q_heads + (size_t)h * G) * kHeadDim, G, m16, grp);
-    run_tiles_with<B, true, false, true, kSingle>(acc, t, stride, n_tiles, n_pages, raw_cur, raw_nxt, ids, g.max_sel, bt_row, nullptr, k_pool,
-                                         v_pool, H, h, L, P, scale_log2, m16, grp, nt, n_stored);
+    // what the last split to finish stores, and where: asked for ahead of the rows (behind the last arrival it was two round trips, 0.6 us)
+    const int dim = min((int)threadIdx.x, kHeadDim - 1), page = room ? L_before / B : 0;
+    const uint16_t k_tok = nt.k_row[dim], v_tok = nt.v_row[dim];
+    const int tok_phys = load_by_lane(bt_row + page);
 
-    float* out_rows = out + ((size_t)b * g.n_q_heads + (size_t)h * G) * kHeadDim;
-    const bool split_up = combine_waves<NW>(acc.o, acc.m_run, acc.l_run, lds, G, n_splits, split, row * n_splits, out_rows, ws_acc, ws_ml);
-    if (split_up && !arrive_last(arrivals + row, n_splits, &lds_last)) return;
+    acc.start(G, m16);
+    run_tiles_with<B, true, false, true, kSingle>(acc, t, stride, n_tiles, n_pages, raw_cur, raw_nxt, ids, max_sel, bt_row, nullptr, a.k_pool,
+                                         a.v_pool, H, h, L, P, a.scale_log2, m16, grp, nt, n_stored);
+
+    float* out_rows = a.out + ((size_t)b * H * G + (size_t)h * G) * kHeadDim;
+    const bool split_up = combine_waves<NW>(acc.o, acc.m_run, acc.l_run, lds, G, n_splits, split, row * n_splits, out_rows, a.ws_acc, a.ws_ml);
+    if (split_up && !arrive_last(a.arrivals + row, n_splits, &lds_last)) return;
     // every split of the row is past its reads: the token and the page go where the next step looks for them
     if (room) {
-        const int tid = threadIdx.x;
-        if (tid < kHeadDim) {
-            const int64_t phys = bt_row[L_before / B];
-            const size_t blk = ((size_t)phys * H + h) * B * kHeadDim;
+        if (threadIdx.x < kHeadDim) {
+            const size_t blk = ((size_t)__builtin_amdgcn_readfirstlane(tok_phys) * H + h) * B * kHeadDim;
             const int tok = L_before % B;
-            k_pool[blk + (size_t)tok * kHeadDim + tid] = k_new[row * kHeadDim + tid];
-            v_pool[blk + (size_t)tid * B + tok] = v_new[row * kHeadDim + tid];
+            a.k_pool[blk + (size_t)tok * kHeadDim + dim] = k_tok;
+            a.v_pool[blk + (size_t)dim * B + tok] = v_tok;
         }
-        if (grow && tid == 0) {
+        if (grow && threadIdx.x == 0) {
             ids[n_stored] = P - 1;
-            n_selected[row] = n_stored + 1;
+            *n_selected = n_stored + 1;
         }
     }
-    if (split_up) merge_splits<NW, kMergePlain>(G, n_splits, row * n_splits, out_rows, ws_acc, ws_ml);
+    if (split_up) merge_splits<NW, kMergePlain>(G, n_splits, row * n_splits, out_rows, a.ws_acc, a.ws_ml);
 }
+
+using DecodeKernel = void (*)(uint64_t, uint64_t, uint64_t, uint64_t, uint64_t, int, int, int, int, DecodeArgs);
 
 hipError_t launch_reuse(chess_ctx* ctx, const uint16_t* q, const uint16_t* k_new, const uint16_t* v_new, uint16_t* k_pool,
                         uint16_t* v_pool, const int32_t* block_table, const int32_t* seq_lens, int32_t* page_ids,
@@ -331,19 +364,18 @@ hipError_t launch_reuse(chess_ctx* ctx, const uint16_t* q, const uint16_t* k_new
     // without the prefetch of the next tile while a wave has at most four tiles of the longest possible list
     const int tiles = (g.max_sel + kTileTokens / g.page_size - 1) / (kTileTokens / g.page_size);
     const int single = tiles <= 4 * nw * n_splits;
-    using Kern = void (*)(const uint16_t*, const uint16_t*, const uint16_t*, uint16_t*, uint16_t*, const int32_t*, const int32_t*,
-                          int32_t*, int32_t*, Geom, float, int, float*, float*, float*, int32_t*);
     // [page size 16 / 32][waves 4 / 8][prefetch / single]
-    static const Kern table[2][2][2] = {
+    static const DecodeKernel table[2][2][2] = {
         {{reuse_kernel<16, false, 4>, reuse_kernel<16, true, 4>}, {reuse_kernel<16, false, 8>, reuse_kernel<16, true, 8>}},
         {{reuse_kernel<32, false, 4>, reuse_kernel<32, true, 4>}, {reuse_kernel<32, false, 8>, reuse_kernel<32, true, 8>}}};
-    const Kern kern = table[g.page_size == 16 ? 0 : 1][nw == 8][single];
+    const DecodeKernel kern = table[g.page_size == 16 ? 0 : 1][nw == 8][single];
     if (lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    return launch(kern, grid, block, lds, stream, q, k_new, v_new, k_pool, v_pool, block_table, seq_lens, page_ids, n_selected,
-                  g, scale_log2, n_splits, out, ws_acc, ws_ml, arrivals);
+    return launch(kern, grid, block, lds, stream, (uint64_t)seq_lens, (uint64_t)block_table, (uint64_t)q, (uint64_t)page_ids, (uint64_t)n_selected,
+                  g.n_kv_heads << 8 | g.group, g.max_sel, g.max_pages, n_splits,
+                  DecodeArgs{k_pool, v_pool, out, ws_acc, ws_ml, arrivals, scale_log2, batch, k_new, v_new});
 }
 
 hipError_t launch_decode(chess_ctx* ctx, const uint16_t* q, const uint16_t* k_pool, const uint16_t* v_pool,
@@ -356,22 +388,21 @@ hipError_t launch_decode(chess_ctx* ctx, const uint16_t* q, const uint16_t* k_po
     const bool dealt = n_slots > 0;                   // (every page, four waves: see choose_splits)
     const dim3 grid = dealt ? dim3(g.n_kv_heads, n_slots) : dim3(n_splits, g.n_kv_heads, batch), block(64 * waves);
     const size_t lds = (size_t)(waves * g.group * kHeadDim + 2 * waves * g.group) * sizeof(float);
-    using Kern = void (*)(const uint16_t*, const uint16_t*, const uint16_t*, const int32_t*, const int32_t*, const int32_t*,
-                          const int32_t*, Geom, float, int, int, float*, float*, float*, int32_t*);
     // [page size 16 / 32][waves 4 / 1][list / every page], eight waves for a list, every page dealt by length
-    static const Kern table[2][2][2] = {
+    static const DecodeKernel table[2][2][2] = {
         {{decode_kernel<16, 4, true>, decode_kernel<16, 4, false>}, {decode_kernel<16, 1, true>, decode_kernel<16, 1, false>}},
         {{decode_kernel<32, 4, true>, decode_kernel<32, 4, false>}, {decode_kernel<32, 1, true>, decode_kernel<32, 1, false>}}};
-    static const Kern wide[2] = {decode_kernel<16, 8, true>, decode_kernel<32, 8, true>};
-    static const Kern by_length[2] = {decode_kernel<16, 4, false, true>, decode_kernel<32, 4, false, true>};
+    static const DecodeKernel wide[2] = {decode_kernel<16, 8, true>, decode_kernel<32, 8, true>};
+    static const DecodeKernel by_length[2] = {decode_kernel<16, 4, false, true>, decode_kernel<32, 4, false, true>};
     const int by_page = g.page_size == 16 ? 0 : 1;
-    const Kern kern = dealt ? by_length[by_page] : waves == 8 ? wide[by_page] : table[by_page][waves == 4 ? 0 : 1][page_ids ? 0 : 1];
+    const DecodeKernel kern = dealt ? by_length[by_page] : waves == 8 ? wide[by_page] : table[by_page][waves == 4 ? 0 : 1][page_ids ? 0 : 1];
     if (lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    return launch(kern, grid, block, lds, stream, q, k_pool, v_pool, block_table, seq_lens,
-                  page_ids, n_selected, g, scale_log2, n_splits, batch, out, ws_acc, ws_ml, arrivals);
+    return launch(kern, grid, block, lds, stream, (uint64_t)seq_lens, (uint64_t)block_table, (uint64_t)q, (uint64_t)page_ids, (uint64_t)n_selected,
+                  g.n_kv_heads << 8 | g.group, g.max_sel, g.max_pages, n_splits,
+                  DecodeArgs{const_cast<uint16_t*>(k_pool), const_cast<uint16_t*>(v_pool), out, ws_acc, ws_ml, arrivals, scale_log2, batch, nullptr, nullptr});
 }
 
 // Four-wave workgroups of attention over every page that fit on a compute unit, dealt or not, whichever are fewer (lists

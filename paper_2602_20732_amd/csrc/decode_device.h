@@ -203,13 +203,19 @@ struct WaveAcc {
     float m_run, l_run;
     f32x4 o[8];
 
-    __device__ __forceinline__ void init(const uint16_t* __restrict__ q_rows, int G, int m16, int grp)
+    // in two steps, so that what a kernel asks for in between does not wait for the rows
+    __device__ __forceinline__ void request(const uint16_t* __restrict__ q_rows, int G, int m16, int grp)
     {
         const uint4* src = reinterpret_cast<const uint4*>(q_rows + (size_t)(m16 < G ? m16 : 0) * kHeadDim) + grp;
+#pragma unroll
+        for (int st = 0; st < 4; ++st) qop[st] = as_bf16x8(src[st * 4]);
+    }
+    __device__ __forceinline__ void start(int G, int m16)
+    {
         const uint32_t keep = m16 < G ? 0xffffffffu : 0u;     // (a select between the load and a zero vector made
 #pragma unroll                                                //  the compiler select between two addresses instead)
         for (int st = 0; st < 4; ++st) {
-            uint4 v = src[st * 4];
+            uint4 v = __builtin_bit_cast(uint4, qop[st]);
             v.x &= keep; v.y &= keep; v.z &= keep; v.w &= keep;
             qop[st] = as_bf16x8(v);
         }
@@ -217,6 +223,11 @@ struct WaveAcc {
         l_run = 0.f;
 #pragma unroll
         for (int i = 0; i < 8; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    __device__ __forceinline__ void init(const uint16_t* __restrict__ q_rows, int G, int m16, int grp)
+    {
+        request(q_rows, G, m16, grp);
+        start(G, m16);
     }
 
     // one tile: scores, online softmax, P.V

@@ -66,30 +66,9 @@ __device__ __forceinline__ Arg late_arg()
     for (size_t i = 0; i < sizeof(Arg) / 4; ++i) r.w[i] = p[at / 4 + i];
     return __builtin_bit_cast(Arg, r);
 }
-// The lines of the structs, asked for when the kernel starts: late_arg finds them in the scalar cache (a first read of an argument takes
-// 1.2 us).  hold() goes where the structs are read.
-struct ArgLines {
-    static constexpr size_t kFrom = kernarg_offset<StepArgs>(StepKernel(nullptr)) / 64, kTo = (kernarg_offset<SelectWs>(StepKernel(nullptr)) + sizeof(SelectWs) - 1) / 64;
-    static_assert(kTo - kFrom < 6, "a line more");
-    uint32_t w[6];
-    __device__ __forceinline__ void ask()
-    {
-        typedef __attribute__((address_space(4))) const volatile uint32_t* kernarg;     // (volatile: not moved to where they are held)
-        kernarg p = (kernarg)__builtin_amdgcn_kernarg_segment_ptr();
-#pragma unroll
-        for (size_t i = 0; i < 6; ++i) w[i] = p[(kFrom + i < kTo ? kFrom + i : kTo) * 16];
-    }
-    __device__ __forceinline__ void hold() const
-    {
-        asm volatile("" : : "s"(w[0]), "s"(w[1]), "s"(w[2]), "s"(w[3]), "s"(w[4]), "s"(w[5]) : "memory");
-    }
-};
+// The structs' lines (see ArgLines; hold() goes where they are read).
+using StepLines = ArgLines<kernarg_offset<StepArgs>(StepKernel(nullptr)), kernarg_offset<SelectWs>(StepKernel(nullptr)) + sizeof(SelectWs)>;
 // (a pointer put together from words has no address space, and accesses through it would be flat ones)
-template <class V>
-__device__ __forceinline__ V* device_pointer(uint64_t at)
-{
-    return (V*)(__attribute__((address_space(1))) V*)at;
-}
 template <class V>
 __device__ __forceinline__ void in_device(V*& p) { p = device_pointer<V>((uint64_t)p); }
 __device__ __forceinline__ StepArgs late_step_args()
@@ -228,7 +207,7 @@ static_assert(kSelMaxCluster < 1 << (FirstLoads::kPerBits - FirstLoads::kFlagBit
 // ahead of the block-table entry, the others waited 2 us more for its keys (32 layers of 1 x 32K 655 us).
 template <int B, class T>
 __device__ __forceinline__ void refresh_only(int L_lane, const int32_t* bt_row, T* pages_row, const VecBases& bases, ProbeRows<T>& probe, const uint16_t* q_rows, int G, int H,
-                                             int h, size_t row, int C, int max_pages, const ArgLines& lines, Shared& sh)
+                                             int h, size_t row, int C, int max_pages, const StepLines& lines, Shared& sh)
 {
     __shared__ T fresh[3 * kHeadDim];
     const int L = min(max(__builtin_amdgcn_readfirstlane(L_lane), 0), max_pages * B), P = (L + B - 1) / B;
@@ -279,9 +258,8 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(kLe
     const int h = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
     const int H = heads >> 8, G = heads & 255, n_q_heads = H * G;
     const bool query_probe = (share & FirstLoads::kQueryProbe) != 0;
-    ArgLines lines;
+    StepLines lines;
     lines.ask();
-    __builtin_amdgcn_sched_barrier(0);
     int L_raw = load_by_lane(seq_lens + b);                           // (scalar when it is used)
     const uint16_t* q_rows = q + ((size_t)b * n_q_heads + (size_t)h * G) * kHeadDim;
     double pr[8];
