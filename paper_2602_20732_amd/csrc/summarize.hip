@@ -8,7 +8,7 @@
 // the grid stay in LDS, chunk and grid means are formed from them without re-reading HBM.
 #include <algorithm>
 
-#include "chess_internal.h"
+#include "select_device.h"
 
 namespace chess {
 
@@ -153,11 +153,121 @@ __global__ __launch_bounds__(256) void summarize_kernel(const uint16_t* __restri
     }
 }
 
+// The same for the last few pages of every sequence (the per-step refresh, the catch-up before a reselection): one workgroup per
+// (sequence, KV head), a 16-lane group per page and per unchanged page or chunk that a refreshed chunk or grid still averages, so
+// everything is requested in two round trips behind the length (block-table entries, siblings; key rows) and the sums meet in LDS
+// once a level.  The kernel above walks a grid's pages sixteen at a time and asks for an unchanged chunk when it comes to it.
+// Bound: that chain.  us, 8 KV heads, the kernel above / this one, 1 page, 10 and 16: 96 sequences of 4-21K 7.9 / 5.8, 19.9 / 11.9, 24.2 /
+// 14.6; 32 of 16-32K 7.3 / 5.3, 11.5 / 6.1, 14.4 / 7.6; one of 32K 6.1 / 5.3, 5.9 / 5.2, 5.9 / 5.3; pages of 32, 32 of 32K 7.2 / 6.9, 11.2 /
+// 9.1, 13.1 / 12.4.
+// shape: recent | n_c << 5 | n_g << 10 | KV heads << 15.  The arguments up to inv_ng are preloaded (see build.py).
+constexpr int kRecentMost = 16;                       // pages, and children of a unit: one per group
+template <int B, class T>
+__global__ __launch_bounds__(256) void summarize_recent_kernel(uint64_t seq_lens_at, uint64_t block_table_at, uint64_t k_pool_at, uint64_t pages_at,
+                                                               int max_pages, int shape, int rows, int max_chunks, uint32_t inv_nc,
+                                                               uint32_t inv_ng, int max_grids)
+{
+    extern __shared__ float lds_f[];                  // page vectors from the first refreshed chunk's first page on, then chunk vectors
+    const int h = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, grp = tid >> 4, ln = tid & 15;
+    const int recent = shape & 31, n_c = (shape >> 5) & 31, n_g = (shape >> 10) & 31, H = shape >> 15;
+    T* lds_page = reinterpret_cast<T*>(lds_f);
+    T* lds_chunk = lds_page + (n_c - 1 + recent) * kHeadDim;
+    const int L = min(__builtin_amdgcn_readfirstlane(load_by_lane(device_pointer<const int32_t>(seq_lens_at) + b)), max_pages * B);
+    if (L <= 0) return;
+    const int P = (L + B - 1) / B, fp = max(P - recent, 0), n_new = P - fp;
+    const int fc = div_by(fp, inv_nc), lc = div_by(P - 1, inv_nc), fg = div_by(fc, inv_ng), lg = div_by(lc, inv_ng);
+    const int p0 = fc * n_c, c0 = fg * n_g;
+    const int j = fp + min(grp, n_new - 1);           // this group's page
+    const int64_t phys = device_pointer<const int32_t>(block_table_at)[(size_t)b * max_pages + j];
+    const int row = b * H + h;
+    const VecBases at = bases_of(rows, row, max_pages, max_chunks, max_grids);
+    T* pg = device_pointer<T>(pages_at) + (size_t)row * max_pages * kHeadDim;
+    T* cg = pg + (int64_t)at.chunks * kHeadDim;
+    T* gg = pg + (int64_t)at.grids * kHeadDim;
+    // (as words, not as Row8 and not as arrays: those went through scratch memory)
+    constexpr int kHi = sizeof(T) == 4 ? 1 : 0;       // eight elements are two 16-byte words, or one
+    const uint4* from_page = reinterpret_cast<const uint4*>(pg + (size_t)min(p0 + grp, P - 1) * kHeadDim + ln * 8);
+    const uint4* from_chunk = reinterpret_cast<const uint4*>(cg + (size_t)min(c0 + grp, lc) * kHeadDim + ln * 8);
+    const uint4 page_lo = from_page[0], page_hi = from_page[kHi], chunk_lo = from_chunk[0], chunk_hi = from_chunk[kHi];
+    asm volatile("" : : : "memory");                  // (requested here, not where they are stored)
+    if (grp < n_new) {                                // (a wave whose groups have no page skips the rows)
+        const int n = j == P - 1 ? L - j * B : B;
+        const uint4* src = reinterpret_cast<const uint4*>(device_pointer<const uint16_t>(k_pool_at) + ((phys * H + h) * B) * kHeadDim) + ln;
+        uint4 r[B];
+#pragma unroll
+        for (int t = 0; t < B; ++t) r[t] = src[min(t, n - 1) * 16];  // (rows past the last token repeat it and are not added)
+        double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0}, mean[8];
+#pragma unroll
+        for (int t = 0; t < B; ++t)
+            if (t < n) add_row(acc, r[t]);
+        const double dn = (double)n;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) mean[i] = acc[i] / dn;
+        Row8<T> mean8;
+        mean8.set(mean);
+        mean8.store(lds_page + (j - p0) * kHeadDim + ln * 8);
+        mean8.store(pg + (size_t)j * kHeadDim + ln * 8);
+    }
+    if (p0 + grp < fp) {
+        uint4* to = reinterpret_cast<uint4*>(lds_page + grp * kHeadDim + ln * 8);
+        to[0] = page_lo;
+        if (kHi) to[kHi] = page_hi;
+    }
+    if (c0 + grp < fc) {
+        uint4* to = reinterpret_cast<uint4*>(lds_chunk + grp * kHeadDim + ln * 8);
+        to[0] = chunk_lo;
+        if (kHi) to[kHi] = chunk_hi;
+    }
+    __syncthreads();
+
+    // a unit's mean, one dim a thread: its children [lo, hi), in order, eight read at a time
+    const int dim = tid % kHeadDim;
+    const auto mean_of = [&](const T* children, int lo, int hi, int from) {
+        double sum = 0.0;
+        for (int k0 = lo; k0 < hi; k0 += 8) {
+            T v[8];
+#pragma unroll
+            for (int x = 0; x < 8; ++x) v[x] = children[(min(k0 + x, hi - 1) - from) * kHeadDim + dim];
+#pragma unroll
+            for (int x = 0; x < 8; ++x)
+                if (k0 + x < hi) sum += as_f64(v[x]);
+        }
+        T m;
+        put_mean(&m, sum / (double)(hi - lo));
+        return m;
+    };
+    for (int c = fc + tid / kHeadDim; c <= lc; c += 2) {
+        const T v = mean_of(lds_page, c * n_c, min(P, c * n_c + n_c), p0);
+        cg[(size_t)c * kHeadDim + dim] = v;
+        lds_chunk[(c - c0) * kHeadDim + dim] = v;
+    }
+    __syncthreads();
+    for (int k = fg + tid / kHeadDim; k <= lg; k += 2) gg[(size_t)k * kHeadDim + dim] = mean_of(lds_chunk, k * n_g, min(lc + 1, k * n_g + n_g), c0);
+}
+
+static hipError_t launch_recent(chess_ctx* ctx, const uint16_t* k_pool, const int32_t* block_table, const int32_t* seq_lens, int batch, int recent,
+                                void* pages, hipStream_t stream)
+{
+    const Geom& g = ctx->geom;
+    const bool bf16 = ctx->cfg.summary_dtype == CHESS_SUMMARY_BF16;
+    // pages of the first refreshed chunk and the new ones, chunks of the first refreshed grid and the new ones
+    const int new_chunks = (recent + g.n_c - 2) / g.n_c + 1;
+    const size_t lds = (size_t)(g.n_c - 1 + recent + g.n_g - 1 + new_chunks) * kHeadDim * (bf16 ? sizeof(uint16_t) : sizeof(float));
+    const auto kern = bf16 ? (g.page_size == 16 ? summarize_recent_kernel<16, uint16_t> : summarize_recent_kernel<32, uint16_t>)
+                           : (g.page_size == 16 ? summarize_recent_kernel<16, float> : summarize_recent_kernel<32, float>);
+    return launch(kern, dim3(g.n_kv_heads, batch), dim3(256), lds, stream, (uint64_t)seq_lens, (uint64_t)block_table, (uint64_t)k_pool, (uint64_t)pages,
+                  g.max_pages, recent | g.n_c << 5 | g.n_g << 10 | g.n_kv_heads << 15, ctx->cfg.max_batch * g.n_kv_heads, g.max_chunks, g.inv_nc,
+                  g.inv_ng, g.max_grids);
+}
+
 hipError_t launch_summarize(chess_ctx* ctx, const uint16_t* k_pool, const int32_t* block_table,
                             const int32_t* seq_lens, int batch, const int32_t* from_page, int recent,
                             void* pages, void* chunks, void* grids, hipStream_t stream)
 {
     const Geom& g = ctx->geom;
+    // (more than ten pages of 32 are a long stream for one workgroup: 16 of one sequence, 4 KV heads, 6.7 us with the kernel above, 7.4)
+    if (recent > 0 && recent <= kRecentMost && recent * g.page_size <= 320 && g.n_c <= kRecentMost && g.n_g <= kRecentMost && g.n_kv_heads < 1 << 16)
+        return launch_recent(ctx, k_pool, block_table, seq_lens, batch, recent, pages, stream);
     const bool bf16 = ctx->cfg.summary_dtype == CHESS_SUMMARY_BF16;
     const size_t lds = (size_t)(g.n_c * g.n_g + g.n_g) * kHeadDim * (bf16 ? sizeof(uint16_t) : sizeof(float));
     const int ppg = g.n_c * g.n_g;
