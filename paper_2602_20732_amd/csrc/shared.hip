@@ -7,7 +7,7 @@
 // select_shared_kernel: a cluster of C workgroups per sequence runs the three levels of select_device.h; only the
 // scoring differs.  A unit's vector is n_layers * H_kv rows of 512 bytes in as many arrays, so all 16 lane
 // groups of a workgroup work on the same few slots: group j takes the rows r = j, j + 16, ... (row r = layer
-// r / H_kv, head r % H_kv), eight slots and two rows at a time (sixteen vectors in flight per group), fp64
+// r / H_kv, head r % H_kv), up to eight slots and two rows or four slots and four rows at a time (sixteen vectors in flight per group), fp64
 // partial sums; the groups' partials are added in group order through LDS.  The order of the additions is fixed, so a
 // unit's score does not depend on the launch shape.
 #include "select_device.h"
@@ -44,12 +44,18 @@ hipError_t launch_anchor(chess_ctx* ctx, const AnchorTable& tab, int n_layers, c
                   window);
 }
 
+// Where the layers' probes and summaries are, in LDS.
+struct SharedRows {
+    uint64_t probes[kMaxLayers], summaries[kMaxLayers];
+};
+
 constexpr int kSharedSlots = 8;                      // slots a workgroup scores together
 
 template <class T>
 struct SharedScorer {
     static constexpr int kTrip = kSharedSlots;
     const SharedTable& tab;
+    const SharedRows* rows;                          // LDS
     int b;
     const Geom& g;
     double* red;                                     // LDS [16 groups][kSharedSlots]
@@ -73,38 +79,57 @@ struct SharedScorer {
             unit[x] = target(s0 + x).unit;
             part[x] = 0.0;
         }
-        // two rows per trip: 2 N vectors in flight per group.  A trip's second row may not exist: it then reads the
-        // first row again with a zero probe (adding exact zeros)
-        for (int r = g16; r < R; r += 2 * kSelGroups) {
-            double pr[2][8];
-            const T* base[2];
+        // kRows rows per trip: kRows N vectors in flight per group.  A trip's last rows may not exist: it then reads the
+        // first row again with a zero probe (adding exact zeros).  The pointers come from LDS: loads from memory return in
+        // order, so a pointer fetched behind vectors is waited for with them (four rows so: 83 us where two took 75).  Four
+        // rows where sixteen vectors allow it; eight are slower (a row is in a page of memory of its own, and a compute unit
+        // gets only so many translations at a time: 256 rows a level, about 40 ns each).  us, 32 layers of 8 KV heads at 1 %:
+        // two rows with pointers from memory / from LDS / four rows / eight up to two slots: 4 sequences of 24-32K 75.8 / 72.1 /
+        // 67.8 / 71.6; one of 32K 61.2 / 52.2 / 51.2 / 53.0; 16 of 8K 78.5 / 71.7 / 68.2 / 74.3
+        constexpr int kRows = N <= 4 ? 4 : 2;
+        const size_t head_bytes = units * (kHeadDim * sizeof(T));
+        const size_t first_head = level_off + (size_t)b * H * head_bytes;
+        const int step_l = kSelGroups / H, step_h = kSelGroups - step_l * H;
+        int l = g16 / H, h = g16 - l * H;
+        for (int r = g16; r < R; r += kRows * kSelGroups) {
+            const float* from[kRows];
+            const char* base[kRows];
 #pragma unroll
-            for (int y = 0; y < 2; ++y) {
-                const bool have = r + y * kSelGroups < R;
-                const int ry = have ? r + y * kSelGroups : r;
-                const int l = ry / H, h = ry - l * H;
-                const size_t row = (size_t)b * H + h;
-                const float* p0 = tab.probes[l] + row * kHeadDim;
-                base[y] = reinterpret_cast<const T*>(tab.summaries[l] + level_off) + row * units * kHeadDim;
-                // the probe in the arrangement the vectors are held in (two runs of four consecutive dims)
-                const float4 pa = *reinterpret_cast<const float4*>(p0 + Vec<T>::lane_dim(ln, 0));
-                const float4 pb = *reinterpret_cast<const float4*>(p0 + Vec<T>::lane_dim(ln, 4));
-                pr[y][0] = have ? (double)pa.x : 0.0; pr[y][1] = have ? (double)pa.y : 0.0;
-                pr[y][2] = have ? (double)pa.z : 0.0; pr[y][3] = have ? (double)pa.w : 0.0;
-                pr[y][4] = have ? (double)pb.x : 0.0; pr[y][5] = have ? (double)pb.y : 0.0;
-                pr[y][6] = have ? (double)pb.z : 0.0; pr[y][7] = have ? (double)pb.w : 0.0;
+            for (int y = 0; y < kRows; ++y) {
+                const bool have = r + y * kSelGroups < R;      // (r itself always is)
+                if (y > 0 && !have) {
+                    from[y] = from[0];
+                    base[y] = base[0];
+                } else {
+                    from[y] = device_pointer<const float>(rows->probes[l]) + ((size_t)b * H + h) * kHeadDim;
+                    base[y] = device_pointer<const char>(rows->summaries[l]) + first_head + (size_t)h * head_bytes;
+                }
+                h += step_h;
+                l += step_l + (h >= H ? 1 : 0);
+                h -= h >= H ? H : 0;
+                l = min(l, tab.n_layers - 1);                  // (past the last row: not read)
             }
-            Vec<T> v[2][N];
+            // the probes in the arrangement the vectors are held in (two runs of four consecutive dims)
+            float4 pa[kRows], pb[kRows];
+            Vec<T> v[kRows][N];
 #pragma unroll
-            for (int y = 0; y < 2; ++y) {
+            for (int y = 0; y < kRows; ++y) {
+                pa[y] = *reinterpret_cast<const float4*>(from[y] + Vec<T>::lane_dim(ln, 0));
+                pb[y] = *reinterpret_cast<const float4*>(from[y] + Vec<T>::lane_dim(ln, 4));
 #pragma unroll
                 for (int x = 0; x < N; ++x)       // always load (unit 0 when the slot has no unit): all stay in flight
-                    v[y][x].load(base[y] + (size_t)max(unit[x], 0) * kHeadDim, ln);
+                    v[y][x].load(reinterpret_cast<const T*>(base[y]) + (size_t)max(unit[x], 0) * kHeadDim, ln);
             }
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int y = 0; y < 2; ++y) {
+            for (int y = 0; y < kRows; ++y) {
+                const bool have = r + y * kSelGroups < R;
+                const float pf[8] = {pa[y].x, pa[y].y, pa[y].z, pa[y].w, pb[y].x, pb[y].y, pb[y].z, pb[y].w};
+                double pr[8];
 #pragma unroll
-                for (int x = 0; x < N; ++x) part[x] = dot8<T>(pr[y], v[y][x], part[x]);
+                for (int i = 0; i < 8; ++i) pr[i] = have ? (double)pf[i] : 0.0;
+#pragma unroll
+                for (int x = 0; x < N; ++x) part[x] = dot8<T>(pr, v[y][x], part[x]);
             }
         }
 #pragma unroll
@@ -162,11 +187,16 @@ __global__ __launch_bounds__(kSelThreads) void select_shared_kernel(SharedTable 
     int32_t* sel_pages = kept_chunks + sp.cap_kc;                             // [max_sel]
     __shared__ Shared sh;
     __shared__ double red[kSelGroups * kSharedSlots];
+    __shared__ SharedRows rows;
 
     const int m = blockIdx.x, C = gridDim.x, b = blockIdx.z, tid = threadIdx.x;
     const int H = g.n_kv_heads, B = g.page_size;
     Prof prof;
     init_shared(sh, sp.poll_limit);
+    if (tid < tab.n_layers) {                        // (read after the barrier below)
+        rows.probes[tid] = reinterpret_cast<uint64_t>(tab.probes[tid]);
+        rows.summaries[tid] = reinterpret_cast<uint64_t>(tab.summaries[tid]);
+    }
     const int L = min(max(seq_lens[b], 0), g.max_pages * B);
     const int k_fixed = fixed_budget(sp, g, b);
     const int P = (L + B - 1) / B;
@@ -187,7 +217,7 @@ __global__ __launch_bounds__(kSelThreads) void select_shared_kernel(SharedTable 
 
     const PubLayout pubs = pub_layout(ws.keys + (size_t)b * ws.key_stride, g);
     CascadeResult res;
-    const SharedScorer<T> scorer{tab, b, g, red};
+    const SharedScorer<T> scorer{tab, &rows, b, g, red};
     const bool ok = cascade_with<kMode, false>(scorer, P, g, sp, pubs, m, C, m == 0, keys, kept_grids, kept_chunks, sel_pages, sh,
                                         &res, prof, nullptr, false, [] {}, [] {}, k_fixed, FirstShare{});
     if (!ok) {
