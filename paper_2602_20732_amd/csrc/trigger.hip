@@ -46,8 +46,7 @@ __device__ __forceinline__ float wave_all(float v, float identity, Op op)
 }
 
 // The triplets of a wave's lanes merged, in every lane: the maximum first, one exponential a lane to bring its sums to it, then
-// plain sums in a fixed order.  (A tree of pairwise merges is two exponentials a level in one chain; twice per launch.  One row
-// of 151936 logits 7.4 -> 5.3 us, 32 rows 12.2 -> 10.2.)
+// plain sums in a fixed order.  (A tree of pairwise merges is two exponentials a level in one chain; twice per launch.)
 __device__ __forceinline__ Ent ent_wave(const Ent& e)
 {
     const float M = wave_all(e.m, -INFINITY, [](float a, float b) { return fmaxf(a, b); });
@@ -58,12 +57,13 @@ __device__ __forceinline__ Ent ent_wave(const Ent& e)
     return Ent{M, wave_all(e.s0 * f, 0.f, add), wave_all((e.s1 + d * e.s0) * f, 0.f, add)};
 }
 
-// What the monitor call adds to the entropy kernel: the page statistics, done by the thread that has the entropy.
-struct TriggerArgs {
-    int page_steps;                                      // 0: entropy only
+// What the entropy kernel reads late, and what the monitor call adds to it: the page statistics, done by the thread that has the entropy.
+struct EntropyArgs {
+    float* H;
+    float* partials;                                     // [batch][splits][4]
+    int32_t* arrivals;                                   // [batch], zero between launches
     double tau_h, tau_v;
     float* history;
-    int32_t* count;
     int32_t* fire;
     double* stats;
 };
@@ -71,24 +71,28 @@ struct TriggerArgs {
 constexpr int kEntThreads = 256;
 constexpr int kEntFly = 4;                               // 16-byte loads per thread and trip
 
-// partials: [batch][splits][4] floats; arrivals: [batch] int32, zero between launches
-__global__ __launch_bounds__(kEntThreads) void entropy_kernel(const uint16_t* __restrict__ logits, int vocab, int64_t row_stride,
-                                                              float* __restrict__ H, float* __restrict__ partials,
-                                                              int32_t* __restrict__ arrivals, TriggerArgs tr)
+// The first loads need only the arguments ahead of `tr`, which are in registers when a wave starts; the lines of the others are asked for
+// with the first instruction and are there when the row has been read.  `per`: 16-byte chunks a split.  page_steps 0: entropy only.
+// us, rows of 151936 logits, every argument fetched and every logit masked for itself / now: one 6.2 / 5.6, 8 rows 8.7 / 8.1, 32 11.5 /
+// 10.8, 96 15.0 / 13.6.
+__global__ __launch_bounds__(kEntThreads) void entropy_kernel(const uint16_t* __restrict__ logits, int32_t* __restrict__ count, int64_t row_stride,
+                                                              int vocab, int n_splits, int per, int page_steps, EntropyArgs tr)
 {
+    typedef ArgLines<40, 40 + sizeof(EntropyArgs)> Lines;
+    Lines lines;
+    lines.ask();
     __shared__ Ent lds[kEntThreads / 64];
     __shared__ int flag;
-    const int split = blockIdx.x, n_splits = gridDim.x, b = blockIdx.y, tid = threadIdx.x;
+    const int split = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
     // (asked for now: whoever ends up with the entropy would wait for it then)
-    const int count_before = tr.page_steps > 0 ? tr.count[b] : 0;
+    const int count_before = page_steps > 0 ? count[b] : 0;
     const auto finish = [&](const Ent& e) {
         const float Hb = e.s0 > 0.f ? logf(e.s0) - e.s1 / e.s0 : 0.f;
-        H[b] = Hb;
-        if (tr.page_steps > 0) trigger_update_one(Hb, b, count_before, tr.page_steps, tr.tau_h, tr.tau_v, tr.history, tr.count, tr.fire, tr.stats);
+        tr.H[b] = Hb;
+        if (page_steps > 0) trigger_update_one(Hb, b, count_before, page_steps, tr.tau_h, tr.tau_v, tr.history, count, tr.fire, tr.stats);
     };
     const uint4* row = reinterpret_cast<const uint4*>(logits + (size_t)b * row_stride);
     const int n_chunks = (vocab + 7) / 8;                                    // 8 logits per 16 bytes
-    const int per = (n_chunks + n_splits - 1) / n_splits;
     const int c_lo = split * per, c_hi = min(n_chunks, c_lo + per);
     Ent acc{-INFINITY, 0.f, 0.f};
     for (int c0 = c_lo + tid; c0 < c_hi; c0 += kEntThreads * kEntFly) {
@@ -100,11 +104,18 @@ __global__ __launch_bounds__(kEntThreads) void entropy_kernel(const uint16_t* __
 #pragma unroll
         for (int x = 0; x < kEntFly; ++x) {
             const int c = c0 + x * kEntThreads;
-            const uint32_t w[4] = {r[x].x, r[x].y, r[x].z, r[x].w};
+            const uint32_t none = 0xff80ff80u;               // two times -inf
+            uint32_t w[4] = {r[x].x, r[x].y, r[x].z, r[x].w};
+            if (c >= n_chunks - 1) {                          // (the row's last chunk may be partly beyond the vocabulary)
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    if (c * 8 + i >= vocab) w[i >> 1] = (i & 1) ? (w[i >> 1] & 0xffffu) | (none & 0xffff0000u) : (w[i >> 1] & 0xffff0000u) | (none & 0xffffu);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w[i] = c < c_hi ? w[i] : none;
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                const float v = __uint_as_float((i & 1) ? (w[i >> 1] & 0xffff0000u) : (w[i >> 1] << 16));
-                z[x * 8 + i] = (c < c_hi && c * 8 + i < vocab) ? v : -INFINITY;
+                z[x * 8 + i] = __uint_as_float((i & 1) ? (w[i >> 1] & 0xffff0000u) : (w[i >> 1] << 16));
                 mx = fmaxf(mx, z[x * 8 + i]);
             }
         }
@@ -112,13 +123,15 @@ __global__ __launch_bounds__(kEntThreads) void entropy_kernel(const uint16_t* __
         Ent e{mx, 0.f, 0.f};
 #pragma unroll
         for (int i = 0; i < kEntFly * 8; ++i) {
-            const float d = z[i] - mx;                    // -inf for a masked entry: contributes 0
+#pragma clang fp contract(off)
+            const float d = z[i] - mx;                    // -inf for a masked entry: contributes 0 (times a finite number: 0 x inf is none)
             const float p = __expf(d);
             e.s0 += p;
-            e.s1 += d > -INFINITY ? p * d : 0.f;
+            e.s1 += p * fmaxf(d, -1e30f);
         }
         acc = ent_merge(acc, e);
     }
+    lines.hold();
     const Ent own = ent_wave(acc);
     if ((tid & 63) == 0) lds[tid >> 6] = own;
     __syncthreads();
@@ -127,18 +140,18 @@ __global__ __launch_bounds__(kEntThreads) void entropy_kernel(const uint16_t* __
         if (tid == 0) {
             if (n_splits == 1) finish(e);
             else {
-                float* p = partials + ((size_t)b * n_splits + split) * 4;
+                float* p = tr.partials + ((size_t)b * n_splits + split) * 4;
                 publish_f32(p, e.m); publish_f32(p + 1, e.s0); publish_f32(p + 2, e.s1);
             }
         }
     }
     if (n_splits == 1) return;
-    if (!arrive_last(arrivals + b, n_splits, &flag)) return;
+    if (!arrive_last(tr.arrivals + b, n_splits, &flag)) return;
     // the splits' triplets: lane s of wave 0 takes split s (at most kEntMaxSplits = 32 of them)
     if (tid < 64) {
         Ent e{-INFINITY, 0.f, 0.f};
         if (tid < n_splits) {
-            const float* p = partials + ((size_t)b * n_splits + tid) * 4;
+            const float* p = tr.partials + ((size_t)b * n_splits + tid) * 4;
             e = Ent{observe_f32(p), observe_f32(p + 1), observe_f32(p + 2)};
         }
         e = ent_wave(e);
@@ -151,9 +164,11 @@ hipError_t launch_entropy(chess_ctx* ctx, const uint16_t* logits, int batch, int
                           float* history, int32_t* count, int32_t* fire, double* stats, hipStream_t stream)
 {
     (void)ctx;
-    const TriggerArgs tr{page_steps, tau_h, tau_v, history, count, fire, stats};
-    return launch(entropy_kernel, dim3(splits, batch), dim3(kEntThreads), 0, stream, logits, vocab, row_stride, H, partials,
-                  arrivals, tr);
+    static_assert(sizeof(EntropyArgs) == 64, "the lines that the kernel asks for");
+    const EntropyArgs tr{H, partials, arrivals, tau_h, tau_v, history, fire, stats};
+    const int chunks = (vocab + 7) / 8;                   // (as the kernel counts them: 8 logits per 16 bytes)
+    return launch(entropy_kernel, dim3(splits, batch), dim3(kEntThreads), 0, stream, logits, count, row_stride, vocab, splits,
+                  (chunks + splits - 1) / splits, page_steps, tr);
 }
 
 // The page statistics of one sequence (what trigger_kernel does per thread).

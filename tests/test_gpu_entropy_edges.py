@@ -1,0 +1,39 @@
+"""The entropy of rows that end inside, at and just past a 16-byte chunk and a split, with infinite logits and a NaN among them,
+against fp64."""
+from __future__ import annotations
+
+import pytest
+import torch
+
+import paper_2602_20732_amd as pk
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("batch", [1, 3, 17])
+@pytest.mark.parametrize("vocab", [1, 7, 8, 9, 4095, 8191, 8192, 8193, 8200, 32769, 151937])
+def test_entropy_at_the_edges(vocab, batch):
+    g = torch.Generator().manual_seed(vocab + batch)
+    wide = (vocab + 7) // 8 * 8 + 8
+    z = (3 * torch.randn((batch, wide), generator=g)).to(torch.bfloat16)
+    z[:, vocab:] = float("inf")                                # beyond the vocabulary: never part of the sum
+    if batch > 1 and vocab > 1:
+        z[1, vocab // 2] = float("-inf")
+        z[2, : vocab - 1] = float("-inf")                      # all the probability on the last entry
+    nan_row = batch > 3
+    if nan_row:
+        z[3, vocab - 1] = float("nan")
+    lib = pk.Chess(pk.Config(1, 1, 16, batch, 8, 8))
+    ws, got = lib.new_workspace(), torch.full((batch,), -1.0, device="cuda")
+    d = z.cuda()
+    for _ in range(2):                                         # the counters are armed again
+        lib.entropy(d, got, ws, vocab=vocab)
+    p = torch.softmax(z[:, :vocab].double(), -1)
+    want = -torch.where(p > 0, p * torch.log(p), p).sum(-1)
+    out = got.cpu().double()
+    rows = [b for b in range(batch) if not (nan_row and b == 3)]
+    # fp32 sums of s0 and s1 (|z - m| < 32): their rounding, relative to an entropy below log(vocab) + 1
+    assert float((out[rows] - want[rows]).abs().max()) < 2e-5
+    # (a row of nothing but a NaN has no finite maximum to begin from and counts as empty)
+    assert not nan_row or vocab == 1 or bool(torch.isnan(out[3]))
+    lib.close()
