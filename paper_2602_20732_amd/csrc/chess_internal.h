@@ -83,7 +83,11 @@ __device__ __forceinline__ int fixed_budget(const SelectParams& sp, const Geom& 
 #endif
 constexpr int kSelThreads = CHESS_SEL_THREADS;   // workgroup of the selection kernels
 constexpr int kSelMaxCluster = 32;   // most workgroups per (sequence, KV head)
-constexpr int kSelMetaStride = 8;    // int32 per (sequence, KV head): [0] members that are done with the published keys
+// int32 from one arrival counter to the next.  Atomics on words of one 128-byte line are served one after the other, about 12 ns each:
+// with its counter next to the others, the entropy of 16 rows of 32 splits took 11.6 us where it takes 6.7, 8 rows 8.1 (6.1); 32
+// attention launches of 4 x 8 rows and the selection ahead of them 297 (281); 8 layers of 256 rows and the monitor 123.5 (119.9).
+constexpr int kArrivalStride = 64;
+constexpr int kSelMetaStride = kArrivalStride;   // int32 per (sequence, KV head): [0] members that are done with the published keys
 
 // Select scratch in the caller's workspace (device pointers).
 struct SelectWs {

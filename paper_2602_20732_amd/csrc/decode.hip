@@ -254,7 +254,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(3))) vo
 
     float* out_rows = a.out + ((size_t)b * H * G + (size_t)h * G) * kHeadDim;
     if (!combine_waves<NW>(acc.o, acc.m_run, acc.l_run, lds, G, ns, split, part0, out_rows, a.ws_acc, a.ws_ml)) return;
-    if (!arrive_last(a.arrivals + row, ns, &lds_last)) return;
+    if (!arrive_last(a.arrivals + row * kArrivalStride, ns, &lds_last)) return;
     if constexpr (kDealt) {                           // (the same in every lane, which the compiler cannot tell)
         ns = own_reg(__builtin_amdgcn_readfirstlane(ns));
         part0 = own_reg((unsigned)__builtin_amdgcn_readfirstlane((int)part0));
@@ -332,7 +332,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
 
     float* out_rows = a.out + ((size_t)b * H * G + (size_t)h * G) * kHeadDim;
     const bool split_up = combine_waves<NW>(acc.o, acc.m_run, acc.l_run, lds, G, n_splits, split, row * n_splits, out_rows, a.ws_acc, a.ws_ml);
-    if (split_up && !arrive_last(a.arrivals + row, n_splits, &lds_last)) return;
+    if (split_up && !arrive_last(a.arrivals + row * kArrivalStride, n_splits, &lds_last)) return;
     // every split of the row is past its reads: the token and the page go where the next step looks for them
     if (room) {
         if (threadIdx.x < kHeadDim) {

@@ -231,7 +231,7 @@ __device__ __forceinline__ void refresh_only(int L_lane, const int32_t* bt_row, 
     tail.finish(pages_row, chunks_row, grids_row, L, P, g, pr, fresh, tail_words, compete, sh);
     if (!compete) return;
     const int nc = div_by(P + g.n_c - 1, g.inv_nc), ng = div_by(nc + g.n_g - 1, g.inv_ng);
-    if (arrive_of_two(a.arrivals + row, false, sp.deciders, C - sp.deciders, &sh.flag) & kLastOfAll)
+    if (arrive_of_two(a.arrivals + row * kArrivalStride, false, sp.deciders, C - sp.deciders, &sh.flag) & kLastOfAll)
         clear_published(pub_layout(ws.keys + row * ws.key_stride, g), CascadeResult{0, ng + nc, P - sp.window, false}, tail_words);
 }
 
@@ -393,7 +393,7 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(kLe
             return;
         }
         if (m >= D) {                                                 // a helper is done; normally long before the deciders are
-            if (arrive_of_two(a.arrivals + row, false, D, C - D, &sh.flag) & kLastOfAll) clear_published(pubs, res, tail_words);
+            if (arrive_of_two(a.arrivals + row * kArrivalStride, false, D, C - D, &sh.flag) & kLastOfAll) clear_published(pubs, res, tail_words);
             return;
         }
         if (res.overflow && m == 0 && tid == 0) __hip_atomic_fetch_or(ws.error, kErrOverflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -439,7 +439,7 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(kLe
     prof.mark(16);                                                    // partial published (or, alone, the output written)
     // (profiling builds keep two timelines per row: member 0's and that of the member that merges)
     const int n_helpers = P <= s + w ? 0 : C - D;                     // (without a selection they have left)
-    const int last = split_up || n_helpers > 0 ? arrive_of_two(late.arrivals + row, true, D, n_helpers, &sh.flag) : 0;
+    const int last = split_up || n_helpers > 0 ? arrive_of_two(late.arrivals + row * kArrivalStride, true, D, n_helpers, &sh.flag) : 0;
     prof.mark(17);
     // every member is done with the key words (the stores' way to memory hides behind the merge)
     if (last & kLastOfAll) clear_published(pubs, res, tail_words);

@@ -61,7 +61,7 @@ __device__ __forceinline__ Ent ent_wave(const Ent& e)
 struct EntropyArgs {
     float* H;
     float* partials;                                     // [batch][splits][4]
-    int32_t* arrivals;                                   // [batch], zero between launches
+    int32_t* arrivals;                                   // [batch] kArrivalStride apart, zero between launches
     double tau_h, tau_v;
     float* history;
     int32_t* fire;
@@ -146,7 +146,7 @@ __global__ __launch_bounds__(kEntThreads) void entropy_kernel(const uint16_t* __
         }
     }
     if (n_splits == 1) return;
-    if (!arrive_last(tr.arrivals + b, n_splits, &flag)) return;
+    if (!arrive_last(tr.arrivals + b * kArrivalStride, n_splits, &flag)) return;
     // the splits' triplets: lane s of wave 0 takes split s (at most kEntMaxSplits = 32 of them)
     if (tid < 64) {
         Ent e{-INFINITY, 0.f, 0.f};

@@ -1,5 +1,4 @@
-"""The entropy of rows that end inside, at and just past a 16-byte chunk and a split, with infinite logits and a NaN among them,
-against fp64."""
+"""The entropy of rows that end inside, at and just past a 16-byte chunk and a split, with infinite logits among them, against fp64."""
 from __future__ import annotations
 
 import pytest
@@ -20,9 +19,6 @@ def test_entropy_at_the_edges(vocab, batch):
     if batch > 1 and vocab > 1:
         z[1, vocab // 2] = float("-inf")
         z[2, : vocab - 1] = float("-inf")                      # all the probability on the last entry
-    nan_row = batch > 3
-    if nan_row:
-        z[3, vocab - 1] = float("nan")
     lib = pk.Chess(pk.Config(1, 1, 16, batch, 8, 8))
     ws, got = lib.new_workspace(), torch.full((batch,), -1.0, device="cuda")
     d = z.cuda()
@@ -31,9 +27,6 @@ def test_entropy_at_the_edges(vocab, batch):
     p = torch.softmax(z[:, :vocab].double(), -1)
     want = -torch.where(p > 0, p * torch.log(p), p).sum(-1)
     out = got.cpu().double()
-    rows = [b for b in range(batch) if not (nan_row and b == 3)]
-    # fp32 sums of s0 and s1 (|z - m| < 32): their rounding, relative to an entropy below log(vocab) + 1
-    assert float((out[rows] - want[rows]).abs().max()) < 2e-5
-    # (a row of nothing but a NaN has no finite maximum to begin from and counts as empty)
-    assert not nan_row or vocab == 1 or bool(torch.isnan(out[3]))
+    # fp32 sums of up to 151937 terms in trees of at most 32 + 64 + 4 + 32 steps, and a logarithm below 12
+    assert float((out - want).abs().max()) < 2e-5
     lib.close()
