@@ -78,7 +78,7 @@ extern "C" {
 
 #define CHESS_MAX_LAYERS 64   /* most layers one chess_select_shared call can take */
 
-#define CHESS_STATIC_SCRATCH_BYTES (4u << 20)   /* device scratch chess_sparse_decode_static owns, per GPU */
+#define CHESS_STATIC_SCRATCH_BYTES (4u << 20)   /* device scratch chess_sparse_decode_static owns, per GPU (its counters beside it) */
 
 typedef struct chess_ctx chess_ctx; /* opaque; small host-side state only */
 
