@@ -80,7 +80,7 @@ struct SharedScorer {
             part[x] = 0.0;
         }
         // kRows rows per trip: kRows N vectors in flight per group.  A trip's last rows may not exist: it then reads the
-        // first row again with a zero probe (adding exact zeros).  The pointers come from LDS: loads from memory return in
+        // first row again and does not add it (an infinite component times a zero probe would be a NaN).  The pointers come from LDS: loads from memory return in
         // order, so a pointer fetched behind vectors is waited for with them (four rows so: 83 us where two took 75).  Four
         // rows where sixteen vectors allow it; eight are slower (a row is in a page of memory of its own, and a compute unit
         // gets only so many translations at a time: 256 rows a level, about 40 ns each).  us, 32 layers of 8 KV heads at 1 %:
@@ -127,9 +127,12 @@ struct SharedScorer {
                 const float pf[8] = {pa[y].x, pa[y].y, pa[y].z, pa[y].w, pb[y].x, pb[y].y, pb[y].z, pb[y].w};
                 double pr[8];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) pr[i] = have ? (double)pf[i] : 0.0;
+                for (int i = 0; i < 8; ++i) pr[i] = (double)pf[i];
 #pragma unroll
-                for (int x = 0; x < N; ++x) part[x] = dot8<T>(pr, v[y][x], part[x]);
+                for (int x = 0; x < N; ++x) {
+                    const double sum = dot8<T>(pr, v[y][x], part[x]);
+                    part[x] = have ? sum : part[x];
+                }
             }
         }
 #pragma unroll

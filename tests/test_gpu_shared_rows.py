@@ -21,3 +21,18 @@ def test_rows_around_a_trip(heads, n_layers, cluster):
                                                      max_sel=sp.max_pages)
     assert_lists_equal(ids, nsel, oids, onsel, heads)
     lib.close()
+
+
+@pytest.mark.parametrize("heads,n_layers", [(1, 15), (1, 17), (8, 4), (8, 7), (3, 43)])
+def test_infinite_components_keep_their_sign(heads, n_layers):
+    """One row of two pages holds an infinity of either sign: their scores, and those of their chunks and grids, are infinite and not NaN,
+    also where the last trip over the rows has fewer than the others."""
+    lens = [1500, 700]
+    sp = workload.WorkloadSpec("inf", 2, (0, 1500), heads, heads, 16, ("fixed", 96), (1, 1), 1, 2, budget_bp=800,
+                               pages_per_chunk=4, chunks_per_grid=4)
+    wls = layers_of(sp, range(90, 90 + n_layers), lens)
+    for page, value in ((18, float("inf")), (34, float("-inf"))):      # in a grid each
+        wls[0].k_pool[wls[0].block_table[:, page].long(), 0, 3, 5] = value
+    ids, nsel, _, oids, onsel, _, lib, *_ = run_both(sp, wls, plan_of(sp), max_sel=sp.max_pages)
+    assert_lists_equal(ids, nsel, oids, onsel, heads)
+    lib.close()
