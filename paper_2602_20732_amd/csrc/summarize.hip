@@ -157,9 +157,10 @@ __global__ __launch_bounds__(256) void summarize_kernel(const uint16_t* __restri
 // (sequence, KV head), a 16-lane group per page and per unchanged page or chunk that a refreshed chunk or grid still averages, so
 // everything is requested in two round trips behind the length (block-table entries, siblings; key rows) and the sums meet in LDS
 // once a level.  The kernel above walks a grid's pages sixteen at a time and asks for an unchanged chunk when it comes to it.
-// Bound: that chain.  us, 8 KV heads, the kernel above / this one, 1 page, 10 and 16: 96 sequences of 4-21K 7.9 / 5.8, 19.9 / 11.9, 24.2 /
-// 14.6; 32 of 16-32K 7.3 / 5.3, 11.5 / 6.1, 14.4 / 7.6; one of 32K 6.1 / 5.3, 5.9 / 5.2, 5.9 / 5.3; pages of 32, 32 of 32K 7.2 / 6.9, 11.2 /
-// 9.1, 13.1 / 12.4.
+// Bound: that chain.  us, 8 KV heads, sixteen draws of lengths of 8-16K, the kernel above / this one, 1 page, 10 and 16: 96 sequences 13.6 /
+// 6.6, 23.9 / 12.4, 29.3 / 15.6; 32 11.0 / 5.3, 12.0 / 6.8, 15.3 / 8.3; one 5.5 / 4.2, 6.2 / 4.7, 7.4 / 5.1; pages of 32, 96 sequences 20.9 / 8.2,
+// 38.6 / 18.8, 49.6 / 24.5 (all rows of a page at once: 12.0, 20.4, 26.8); 32 18.3 / 6.9, 20.5 / 9.3, 26.9 / 11.9; one 7.1 / 5.3, 8.7 / 6.0,
+// 10.2 / 6.8.  With every last page full, where the kernel above is at its best: 96 11.6 / 8.5 (13.6 at once), 24.2 / 19.2, 35.1 / 25.0.
 // shape: recent | n_c << 5 | n_g << 10 | KV heads << 15.  The arguments up to inv_ng are preloaded (see build.py).
 constexpr int kRecentMost = 16;                       // pages, and children of a unit: one per group
 template <int B, class T>
@@ -193,13 +194,17 @@ __global__ __launch_bounds__(256) void summarize_recent_kernel(uint64_t seq_lens
     if (grp < n_new) {                                // (a wave whose groups have no page skips the rows)
         const int n = j == P - 1 ? L - j * B : B;
         const uint4* src = reinterpret_cast<const uint4*>(device_pointer<const uint16_t>(k_pool_at) + ((phys * H + h) * B) * kHeadDim) + ln;
-        uint4 r[B];
-#pragma unroll
-        for (int t = 0; t < B; ++t) r[t] = src[min(t, n - 1) * 16];  // (rows past the last token repeat it and are not added)
         double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0}, mean[8];
+        // (sixteen at a time: 32 rows of a page at once are 172 registers, two workgroups to a compute unit)
 #pragma unroll
-        for (int t = 0; t < B; ++t)
-            if (t < n) add_row(acc, r[t]);
+        for (int t0 = 0; t0 < B; t0 += 16) {
+            uint4 r[16];
+#pragma unroll
+            for (int t = 0; t < 16; ++t) r[t] = src[min(t0 + t, n - 1) * 16];      // (rows past the last token repeat it and are not added)
+#pragma unroll
+            for (int t = 0; t < 16; ++t)
+                if (t0 + t < n) add_row(acc, r[t]);
+        }
         const double dn = (double)n;
 #pragma unroll
         for (int i = 0; i < 8; ++i) mean[i] = acc[i] / dn;

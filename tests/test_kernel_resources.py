@@ -76,6 +76,14 @@ def test_no_kernel_needs_scratch_memory(listings):
     assert len(scratch) > 50 and not any(scratch.values()), {n: b for n, b in scratch.items() if b}
 
 
+def test_three_workgroups_of_the_recent_pages_fit_on_a_compute_unit(listings):
+    """With more than 168 registers a lane two fit, and 96 sequences of 8 KV heads took two rounds of the 256 compute units (a page of 32
+    of each 13.6 us where the kernel for every page takes 11.6, and 8.5 in one round)."""
+    registers = {m.group(1): int(m.group(2)) for _, notes in listings
+                 for m in re.finditer(r"\.name:\s+(\S*summarize_recent\S*)\n(?:(?!\.name:).*\n)*?\s+\.vgpr_count:\s+(\d+)", notes)}
+    assert len(registers) == 4 and max(registers.values()) <= 168, registers
+
+
 def test_the_runtime_sees_no_pointers_in_the_step(listings):
     """A pointer argument is looked up at each launch, and memory seen for the first time cost 20-120 us there: the fused step takes its
     pointers as numbers and inside structs."""
