@@ -270,8 +270,9 @@ hipError_t launch_summarize(chess_ctx* ctx, const uint16_t* k_pool, const int32_
                             void* pages, void* chunks, void* grids, hipStream_t stream)
 {
     const Geom& g = ctx->geom;
-    // (more than ten pages of 32 are a long stream for one workgroup: 16 of one sequence, 4 KV heads, 6.7 us with the kernel above, 7.4)
-    if (recent > 0 && recent <= kRecentMost && recent * g.page_size <= 320 && g.n_c <= kRecentMost && g.n_g <= kRecentMost && g.n_kv_heads < 1 << 16)
+    // (at its least favourable, one sequence whose last page is full, the kernel above and this one, 16 pages: of 32 8.0 / 6.8 us, of 16 6.0 / 5.1;
+    // hierarchies of 4 x 4, where a grid is one trip for it, 5.9 / 7.1 and 4.7 / 5.3, but 8.4 / 7.1 and 5.4 / 5.4 over all lengths)
+    if (recent > 0 && recent <= kRecentMost && g.n_c <= kRecentMost && g.n_g <= kRecentMost && g.n_kv_heads < 1 << 16)
         return launch_recent(ctx, k_pool, block_table, seq_lens, batch, recent, pages, stream);
     const bool bf16 = ctx->cfg.summary_dtype == CHESS_SUMMARY_BF16;
     const size_t lds = (size_t)(g.n_c * g.n_g + g.n_g) * kHeadDim * (bf16 ? sizeof(uint16_t) : sizeof(float));
