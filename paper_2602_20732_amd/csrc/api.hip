@@ -281,7 +281,7 @@ int chess_workspace_init(chess_ctx* ctx, void* workspace, void* stream)
 {
     if (!ctx || !workspace || (reinterpret_cast<uintptr_t>(workspace) & 15)) return CHESS_EINVAL;
     hipError_t e = chess::launch_zero(ctx, reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + ctx->ws_zero_off),
-                                      ctx->ws_zero_bytes / sizeof(int32_t), static_cast<hipStream_t>(stream));
+                                      ctx->ws_zero_bytes / sizeof(int32_t), 1, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? CHESS_OK : CHESS_EHIP;
 }
 
@@ -687,7 +687,8 @@ int chess_sparse_decode_static(chess_ctx* ctx, const void* q, const void* k_pool
     if (hipGetDevice(&dev) != hipSuccess || dev != ctx->device || ctx->static_scratch == nullptr) return CHESS_EHIP;
     const SplitShape sh = choose_splits(ctx, batch, ctx->geom.max_sel, true);
     // layout inside the array: partial rows [rows][splits][G][128] | (m, l) [rows][splits][G], and the arrival counters behind
-    // CHESS_STATIC_SCRATCH_BYTES (a call is held to that size with four bytes for each counter ahead of its partials)
+    // CHESS_STATIC_SCRATCH_BYTES.  (Four bytes a row stay free ahead of the partials: what is accepted and what is refused
+    // follows from the size that the header states, in which a counter is four bytes.)
     const size_t rows = (size_t)batch * ctx->geom.n_kv_heads;
     const size_t part_rows = sh.n_splits > 1 ? rows * sh.n_splits * ctx->geom.group : 0;
     const size_t acc_off = align_up(rows * sizeof(int32_t), 256);
@@ -696,10 +697,12 @@ int chess_sparse_decode_static(chess_ctx* ctx, const void* q, const void* k_pool
     if (need > (size_t)CHESS_STATIC_SCRATCH_BYTES) return CHESS_ESCRATCH;
     char* base = static_cast<char*>(ctx->static_scratch);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // whatever the previous call on this GPU left where the counters are (another context's partials, say) goes
-    // first: a small fill kernel, not a memset node, so that the call can be captured in a graph
+    // A launch leaves its counters at zero.  The array is the process's, though, with no way for a caller to clear it as
+    // chess_workspace_init clears a workspace: were a counter ever left in between (by two calls that overlapped in time, which the
+    // header rules out), every later call would be wrong.  So a call clears those that it counts with: a small fill kernel, not a
+    // memset node, so that the call can be captured in a graph.
     int32_t* arrivals = reinterpret_cast<int32_t*>(base + CHESS_STATIC_SCRATCH_BYTES);
-    if (part_rows > 0 && chess::launch_zero(ctx, arrivals, rows * chess::kArrivalStride, s) != hipSuccess) return CHESS_EHIP;
+    if (part_rows > 0 && chess::launch_zero(ctx, arrivals, rows, chess::kArrivalStride, s) != hipSuccess) return CHESS_EHIP;
     const hipError_t e = chess::launch_decode(ctx, static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k_pool),
                              static_cast<const uint16_t*>(v_pool), block_table, seq_lens, page_ids, n_selected, batch,
                              sh.n_splits, sh.waves, 0, out, reinterpret_cast<float*>(base + acc_off),

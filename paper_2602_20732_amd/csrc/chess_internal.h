@@ -268,7 +268,7 @@ struct StepLaunch {
     float* out;
     float* ws_acc;
     float* ws_ml;
-    int32_t* arrivals;
+    int32_t* arrivals;       // [rows][kArrivalStride], as launch_decode's
     int32_t refresh_tail;
 };
 hipError_t launch_step(chess_ctx* ctx, const StepLaunch& sl, int batch, int cluster, const SelectParams& sp,
@@ -302,6 +302,7 @@ hipError_t dense_occupancy(int page_size, int group, int* blocks_per_cu);
 hipError_t launch_append(chess_ctx* ctx, const uint16_t* k_new, const uint16_t* v_new, uint16_t* k_pool, uint16_t* v_pool,
                          const int32_t* block_table, const int32_t* seq_lens, int batch, int32_t* page_ids,
                          int32_t* n_selected, hipStream_t stream);
+// arrivals: as launch_decode's
 hipError_t launch_reuse(chess_ctx* ctx, const uint16_t* q, const uint16_t* k_new, const uint16_t* v_new, uint16_t* k_pool,
                         uint16_t* v_pool, const int32_t* block_table, const int32_t* seq_lens, int32_t* page_ids,
                         int32_t* n_selected, int batch, int n_splits, int waves, float* out, float* ws_acc, float* ws_ml,
@@ -309,16 +310,19 @@ hipError_t launch_reuse(chess_ctx* ctx, const uint16_t* q, const uint16_t* k_new
 hipError_t launch_extend(chess_ctx* ctx, const int32_t* seq_lens, int batch, int32_t* page_ids, int32_t* n_selected,
                          hipStream_t stream);
 constexpr int kEntMaxSplits = 32;
-// page_steps > 0: the thread that ends up with a sequence's entropy also does that sequence's trigger update
+// page_steps > 0: the thread that ends up with a sequence's entropy also does that sequence's trigger update.
+// partials: [batch][splits][4]; arrivals: int32 [batch][kArrivalStride], as launch_decode's.
 hipError_t launch_entropy(chess_ctx* ctx, const uint16_t* logits, int batch, int vocab, int64_t row_stride, int splits,
                           float* H, float* partials, int32_t* arrivals, int page_steps, double tau_h, double tau_v,
                           float* history, int32_t* count, int32_t* fire, double* stats, hipStream_t stream);
 hipError_t launch_trigger(const float* H, int batch, int page_steps, double tau_h, double tau_v, float* history,
                           int32_t* count, int32_t* fire, double* stats, hipStream_t stream);
-hipError_t launch_zero(chess_ctx* ctx, int32_t* p, size_t n_words, hipStream_t stream);
+// p[0], p[stride], ...: n_words of them
+hipError_t launch_zero(chess_ctx* ctx, int32_t* p, size_t n_words, int stride, hipStream_t stream);
 
 // page_ids == nullptr: every page of the sequence.  n_splits >= 1; the last split of a (sequence,
-// KV head) to finish merges the partials and writes `out`.  `arrivals`: int32 [rows], zero before first use.
+// KV head) to finish merges the partials and writes `out`.  `arrivals`: int32 [rows][kArrivalStride], of which the first word of
+// each row is used, zero before first use and left at zero.
 hipError_t launch_decode(chess_ctx* ctx, const uint16_t* q, const uint16_t* k_pool, const uint16_t* v_pool,
                          const int32_t* block_table, const int32_t* seq_lens, const int32_t* page_ids,
                          const int32_t* n_selected, int batch, int n_splits, int waves, int n_slots, float* out,

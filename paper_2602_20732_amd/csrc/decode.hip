@@ -478,17 +478,16 @@ hipError_t launch_extend(chess_ctx* ctx, const int32_t* seq_lens, int batch, int
     return launch(extend_kernel, dim3((rows + 63) / 64), dim3(64), 0, stream, seq_lens, rows, ctx->geom, page_ids, n_selected);
 }
 
-__global__ void zero_kernel(int32_t* p, size_t n)
+__global__ void zero_kernel(int32_t* p, size_t n, int stride)
 {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0;
+    if (i < n) p[i * stride] = 0;
 }
 
-hipError_t launch_zero(chess_ctx* ctx, int32_t* p, size_t n_words, hipStream_t stream)
+hipError_t launch_zero(chess_ctx* ctx, int32_t* p, size_t n_words, int stride, hipStream_t stream)
 {
     (void)ctx;
-    hipLaunchKernelGGL(zero_kernel, dim3((unsigned)((n_words + 255) / 256)), dim3(256), 0, stream, p, n_words);
-    return hipGetLastError();
+    return launch(zero_kernel, dim3((unsigned)((n_words + 255) / 256)), dim3(256), 0, stream, p, n_words, stride);
 }
 
 }  // namespace chess
