@@ -78,7 +78,7 @@ extern "C" {
 
 #define CHESS_MAX_LAYERS 64   /* most layers one chess_select_shared call can take */
 
-#define CHESS_STATIC_SCRATCH_BYTES (4u << 20)   /* device scratch chess_sparse_decode_static owns, per GPU (its counters beside it) */
+#define CHESS_STATIC_SCRATCH_BYTES (4u << 20)   /* device scratch chess_sparse_decode_static owns, per GPU, beside 1 MiB for its counters */
 
 typedef struct chess_ctx chess_ctx; /* opaque; small host-side state only */
 
@@ -131,7 +131,7 @@ int chess_summary_bytes(const chess_ctx* ctx, size_t* bytes);
 int chess_summary_layout(const chess_ctx* ctx, size_t* page_off, size_t* chunk_off, size_t* grid_off);
 
 /* Size in bytes of the workspace (split partials of decode, published keys and kept-unit lists of
- * select, arrival counters); allocate 256-byte aligned.  chess_workspace_init must run once on a
+ * select, arrival counters: 512 bytes a (sequence, KV head) and 256 a sequence); allocate 256-byte aligned.  chess_workspace_init must run once on a
  * fresh allocation (it clears the arrival counters with a small fill kernel; the kernels re-arm
  * them themselves afterwards).  A workspace carries no results between calls, but two calls that
  * share one must not overlap in time (use one workspace per stream). */
@@ -328,8 +328,8 @@ int chess_workspace_error(chess_ctx* ctx, const void* workspace, int32_t* flag, 
 /*
  * chess_sparse_decode for callers that cannot allocate device memory (code under HIP graph capture that was not
  * handed a workspace, tight serving loops, harnesses that forbid hipMalloc): the same kernels and results, with
- * the split partials and arrival counters in a device array the library owns (CHESS_STATIC_SCRATCH_BYTES per
- * GPU, alive until the process ends) instead of a caller's workspace.  No allocation of any kind happens in the
+ * the split partials and arrival counters in a device array the library owns (CHESS_STATIC_SCRATCH_BYTES and 1 MiB
+ * for the counters per GPU, alive until the process ends) instead of a caller's workspace.  No allocation of any kind happens in the
  * call.  CHESS_ESCRATCH if batch * H_kv * (splits chosen for this shape) needs more than the array holds.
  * Every call on one GPU uses that GPU's one array: calls that overlap in time on the same GPU (two streams, two
  * contexts) race; calls on one stream are safe.
