@@ -1257,22 +1257,24 @@ __device__ __forceinline__ bool cascade_with(const Scorer& scorer, int P, const 
     const bool local_first = solo || (first.asked ? first.local : !merged && sp.local_grids != 0 && n_first <= kSelGroups * 8);
     // ---- the first phase: grids [0, n_g), behind them all chunks (merged), behind those all pages (eager)
     {
-        // (the member that refreshes the tail units has a chain of dependent loads of its own to get through
-        // before the first cut: it takes no share of the first phase if the others can still cover it in one
-        // memory round trip each)
-        const int n_work = eager ? n_first + P - w : n_first;
-        const int without = div_by(n_work + C - 2, sp.inv_others);
-        const bool spare = tail_on && !local_first && without <= Scorer::kTrip;
-        const int mine = spare ? m - 1 : m;           // (member 0 refreshes; the eager kernel's shares are all asked for)
-        const int per = local_first ? n_work : spare ? without : div_by(n_work + C - 1, sp.inv_members);
-        int lo = local_first ? 0 : (spare && m == 0) ? n_work : min(n_work, mine * per), hi = min(n_work, lo + per);
-        if (first.asked) {
-            lo = first.lo;
-            hi = n_first > 0 ? first.hi : lo;
+        int lo = first.lo, hi = n_first > 0 ? first.hi : lo;
+        if constexpr (solo) {
+            lo = 0;
+            hi = first.asked ? hi : n_first;
+        } else if (!eager && !first.asked) {          // (the eager kernel's shares are all asked for)
+            // (member 0, which refreshes the tail units, has a chain of dependent loads of its own to get through
+            // before the first cut: it takes no share of the first phase if the others can still cover it in one
+            // memory round trip each)
+            const int without = div_by(n_first + C - 2, sp.inv_others);
+            const bool spare = tail_on && !local_first && without <= Scorer::kTrip;
+            const int mine = spare ? m - 1 : m;
+            const int per = local_first ? n_first : spare ? without : div_by(n_first + C - 1, sp.inv_members);
+            lo = local_first ? 0 : (spare && m == 0) ? n_first : min(n_first, mine * per);
+            hi = min(n_first, lo + per);
         }
-        const int slots_g = first.asked ? g.max_grids : ng, slots_gc = slots_g + (first.asked ? g.max_chunks : nc);
+        const int slots_g = eager || first.asked ? g.max_grids : ng;
         // (one instance of the scoring loop per phase, each with straight-line slot arithmetic)
-        if constexpr (eager) scorer(lo, hi, AllTarget{slots_g, slots_gc, ng, nc, s, P - w, (int)(pubs.pages - pubs.units), scorer.at}, false, keys, pubs.units, requested, first.asked);
+        if constexpr (eager) scorer(lo, hi, AllTarget{slots_g, slots_g + g.max_chunks, ng, nc, s, P - w, (int)(pubs.pages - pubs.units), scorer.at}, false, keys, pubs.units, requested, true);
         else scorer(lo, hi, GridPhaseTarget{slots_g, ng, nc, scorer.at}, local_first, keys, pubs.units, requested, first.asked);
         if (!local_first) res->n_a = n_first;
         if (eager) res->n_p = P - w;

@@ -195,9 +195,10 @@ struct TailUnits {
 };
 
 // What the first loads need beside pointers, in few registers: KV heads, the group, and how the first phase is shared (see
-// choose_first_share): units a member takes, whether every member takes the same, whether the refreshing member takes none, which it is.
+// choose_first_share): units a member takes, whether every member takes the same, whether the refreshing member (the last one under the
+// eager schedule, else the first) takes none.
 struct FirstLoads {
-    static constexpr int kLocal = 1, kSpare = 2, kLastRefreshes = 4, kQueryProbe = 8, kGrids = 16, kChunks = 32, kFlagBits = 6, kPerBits = 12;
+    static constexpr int kLocal = 1, kSpare = 2, kQueryProbe = 4, kGrids = 8, kChunks = 16, kFlagBits = 5, kPerBits = 11;
     int heads, share;        // n_kv_heads << 8 | group; per << kPerBits | members << kFlagBits | flags
 };
 static_assert(kSelMaxCluster < 1 << (FirstLoads::kPerBits - FirstLoads::kFlagBits), "members fit their bits");
@@ -276,7 +277,7 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(kLe
     const int n_static = (share & FirstLoads::kGrids ? max_grids : 0) + (share & FirstLoads::kChunks ? max_chunks : 0) + (kMode == kEagerCluster ? max_pages : 0);
     FirstShare first{n_static > 0, kMode == kSolo || (share & FirstLoads::kLocal) != 0, 0, n_static};
     {
-        const int per = share >> FirstLoads::kPerBits, who = (share & FirstLoads::kLastRefreshes) ? C - 1 : 0;
+        const int per = share >> FirstLoads::kPerBits, who = kMode == kEagerCluster ? C - 1 : 0;
         const bool spare = (share & FirstLoads::kSpare) != 0;
         if (!first.local) {
             first.lo = spare && m == who ? n_static : min(n_static, (spare && m > who ? m - 1 : m) * per);
@@ -517,7 +518,7 @@ static void choose_first_share(const Geom& g, const SelectParams& sp, int mode, 
     f->share |= cluster << FirstLoads::kFlagBits;
     if (!eager && (sp.cap_kg >= g.max_grids || per > trip || bytes > (8LL << 20))) return;      // (a grid level that keeps every grid is not scored)
     f->share |= per << FirstLoads::kPerBits | FirstLoads::kGrids | (n > g.max_grids ? FirstLoads::kChunks : 0) | (local ? FirstLoads::kLocal : 0) |
-                (spare ? FirstLoads::kSpare : 0) | (eager ? FirstLoads::kLastRefreshes : 0);
+                (spare ? FirstLoads::kSpare : 0);
 }
 
 hipError_t launch_step(chess_ctx* ctx, const StepLaunch& sl, int batch, int cluster, const SelectParams& sp,

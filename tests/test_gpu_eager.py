@@ -1,5 +1,6 @@
-"""The eager schedule (grids, chunks and pages scored in one phase, members that only score) at the sizes where it can go
-wrong: more and fewer members than have work, members that only score and none, the tail page among the candidates,
+"""The eager schedule (grids, chunks and pages scored in one phase, members that do not decide) at the sizes where it can go
+wrong: more and fewer members than have work, one member that does not decide (the last, which scores or renews the tail
+units) and many, the tail page among the candidates,
 sequences that the safety pages cover, levels that keep everything, a page level beyond 1024 slots; against the oracle,
 twice on one workspace (the second launch finds what the first one cleared)."""
 import numpy as np
