@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "../../include/chess.h"
 #include "../../include/chess_debug.h"
 
@@ -103,10 +105,26 @@ struct SelectWs {
 constexpr int kErrWait = 1;          // a wait for published keys was given up
 constexpr int kErrOverflow = 2;      // the threshold rule kept more units than a list has room for (the list was cut short)
 
+// Where in the argument segment of a kernel of this signature the first argument of type Arg lies: in order, each at the next multiple of
+// its alignment.
+template <class Arg, class... Args>
+constexpr size_t kernarg_offset(void (*)(Args...))
+{
+    size_t at = 0, found = ~(size_t)0;
+    const auto place = [&](size_t size, size_t align, bool it) {
+        at = (at + align - 1) / align * align;
+        found = it && found == ~(size_t)0 ? at : found;
+        at += size;
+    };
+    (place(sizeof(Args), alignof(Args), std::is_same_v<Args, Arg>), ...);
+    return found;
+}
+
 // The 64-byte lines of a kernel's arguments that hold bytes [kBegin, kEnd), asked for with the kernel's first instructions, so that the
 // arguments are in the scalar cache when they are read: a first read takes 1.2 us, and the compiler puts it in front of its use.
 template <size_t kBegin, size_t kEnd>
 struct ArgLines {
+    static_assert(kBegin < kEnd, "the kernel has no such parameter");
     static constexpr size_t kFirst = kBegin / 64, kLines = (kEnd - 1) / 64 - kFirst + 1;
     uint32_t w[kLines];
     __device__ __forceinline__ void ask()
@@ -123,6 +141,10 @@ struct ArgLines {
         for (size_t i = 0; i < kLines; ++i) asm volatile("" : : "s"(w[i]) : "memory");
     }
 };
+
+// Those of the argument of type Arg of a kernel of signature Kernel (which whatever launches the kernel holds it to).
+template <class Kernel, class Arg>
+using ArgLinesOf = ArgLines<kernarg_offset<Arg>(Kernel(nullptr)), kernarg_offset<Arg>(Kernel(nullptr)) + sizeof(Arg)>;
 
 // A pointer that travels as a number.
 template <class V>

@@ -186,9 +186,8 @@ struct DecodeArgs {
     const uint16_t* k_new;   // reuse
     const uint16_t* v_new;
 };
-constexpr size_t kDecodeArgsAt = 5 * 8 + 4 * 4;       // (in the kernels' arguments, behind five numbers of 8 and four of 4 bytes)
-static_assert(kDecodeArgsAt % alignof(DecodeArgs) == 0);
-using DecodeLines = ArgLines<kDecodeArgsAt, kDecodeArgsAt + sizeof(DecodeArgs)>;
+using DecodeKernel = void (*)(uint64_t, uint64_t, uint64_t, uint64_t, uint64_t, int, int, int, int, DecodeArgs);   // (the launchers' tables hold the kernels to it)
+using DecodeLines = ArgLinesOf<DecodeKernel, DecodeArgs>;
 // What stands before is requested before what stands behind (the compiler moves a load that only a branch uses into the branch).
 __device__ __forceinline__ void requested_by_here() { asm volatile("" : : : "memory"); }
 
@@ -348,8 +347,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     }
     if (split_up) merge_splits<NW, kMergePlain>(G, n_splits, row * n_splits, out_rows, a.ws_acc, a.ws_ml);
 }
-
-using DecodeKernel = void (*)(uint64_t, uint64_t, uint64_t, uint64_t, uint64_t, int, int, int, int, DecodeArgs);
 
 hipError_t launch_reuse(chess_ctx* ctx, const uint16_t* q, const uint16_t* k_new, const uint16_t* v_new, uint16_t* k_pool,
                         uint16_t* v_pool, const int32_t* block_table, const int32_t* seq_lens, int32_t* page_ids,

@@ -32,21 +32,8 @@ struct StepArgs {
     int32_t refresh_tail;    // recompute the summaries of the tail page, its chunk and its grid first
 };
 
-// The kernel's parameters (the table in step_kernel_of holds every instance to them), and where in the argument segment the first one of
-// type Arg lies: in order, each at the next multiple of its alignment.
+// The kernel's parameters (the table in step_kernel_of holds every instance to them).
 using StepKernel = void (*)(uint64_t, uint64_t, uint64_t, uint64_t, int, int, int, int, int, int, StepArgs, Geom, SelectParams, SelectWs);
-template <class Arg, class... Args>
-constexpr size_t kernarg_offset(void (*)(Args...))
-{
-    size_t at = 0, found = ~(size_t)0;
-    const auto place = [&](size_t size, size_t align, bool it) {
-        at = (at + align - 1) / align * align;
-        found = it && found == ~(size_t)0 ? at : found;
-        at += size;
-    };
-    (place(sizeof(Args), alignof(Args), std::is_same_v<Args, Arg>), ...);
-    return found;
-}
 
 // A struct among the kernel's arguments, read where this stands and not when the kernel starts: what comes before does not wait for it,
 // and what the compiler would keep in scalar registers meanwhile -- or, as there are too few, save and restore -- can be read again.

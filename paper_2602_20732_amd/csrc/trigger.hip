@@ -67,6 +67,7 @@ struct EntropyArgs {
     int32_t* fire;
     double* stats;
 };
+using EntropyKernel = void (*)(const uint16_t*, int32_t*, int64_t, int, int, int, int, EntropyArgs);
 
 constexpr int kEntThreads = 256;
 constexpr int kEntFly = 4;                               // 16-byte loads per thread and trip
@@ -78,8 +79,7 @@ constexpr int kEntFly = 4;                               // 16-byte loads per th
 __global__ __launch_bounds__(kEntThreads) void entropy_kernel(const uint16_t* __restrict__ logits, int32_t* __restrict__ count, int64_t row_stride,
                                                               int vocab, int n_splits, int per, int page_steps, EntropyArgs tr)
 {
-    typedef ArgLines<40, 40 + sizeof(EntropyArgs)> Lines;
-    Lines lines;
+    ArgLinesOf<EntropyKernel, EntropyArgs> lines;
     lines.ask();
     __shared__ Ent lds[kEntThreads / 64];
     __shared__ int flag;
@@ -164,10 +164,10 @@ hipError_t launch_entropy(chess_ctx* ctx, const uint16_t* logits, int batch, int
                           float* history, int32_t* count, int32_t* fire, double* stats, hipStream_t stream)
 {
     (void)ctx;
-    static_assert(sizeof(EntropyArgs) == 64, "the lines that the kernel asks for");
     const EntropyArgs tr{H, partials, arrivals, tau_h, tau_v, history, fire, stats};
     const int chunks = (vocab + 7) / 8;                   // (as the kernel counts them: 8 logits per 16 bytes)
-    return launch(entropy_kernel, dim3(splits, batch), dim3(kEntThreads), 0, stream, logits, count, row_stride, vocab, splits,
+    const EntropyKernel kern = entropy_kernel;            // (the signature that its argument lines follow from)
+    return launch(kern, dim3(splits, batch), dim3(kEntThreads), 0, stream, logits, count, row_stride, vocab, splits,
                   (chunks + splits - 1) / splits, page_steps, tr);
 }
 
