@@ -252,8 +252,9 @@ int chess_reuse_step(chess_ctx* ctx, const void* q, const void* k_new, const voi
 /*
  * The quality monitor of Sec. 3.3, first half: the entropy (nats) of the output distribution of one decode step,
  * H[b] = -sum_v p_v log p_v with p = softmax(logits[b]).  logits: device, bf16 [batch][row_stride], the first
- * `vocab` entries of a row are used (-inf entries count as probability 0); 16-byte aligned, row_stride a multiple
- * of 8.  entropy: device fp32 [batch], written.  fp32 arithmetic (absolute error around 1e-5).  Uses the workspace.
+ * `vocab` entries of a row are used (-inf entries count as probability 0; a row of nothing else, and a row with a
+ * +inf among them, has entropy 0; with a NaN among them the value is 0 or leaves the NaN out); 16-byte aligned,
+ * row_stride a multiple of 8.  entropy: device fp32 [batch], written.  fp32 arithmetic (absolute error around 1e-5).  Uses the workspace.
  * CHESS_EINVAL on null / misaligned pointers, batch outside [1, max_batch], vocab < 1, row_stride < vocab or not
  * a multiple of 8.
  */

@@ -30,3 +30,19 @@ def test_entropy_at_the_edges(vocab, batch):
     # fp32 sums of up to 151937 terms in trees of at most 32 + 64 + 4 + 32 steps, and a logarithm below 12
     assert float((out - want).abs().max()) < 2e-5
     lib.close()
+
+
+@pytest.mark.parametrize("vocab", [1, 7, 8192, 8193, 32769])
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_rows_without_an_entropy(vocab, bad):
+    """A row whose first logit is infinite or a NaN has entropy 0, as does one of nothing but -inf; its neighbours are as they are."""
+    z = torch.randn((4, (vocab + 7) // 8 * 8), generator=torch.Generator().manual_seed(vocab)).to(torch.bfloat16)
+    lib = pk.Chess(pk.Config(1, 1, 16, 4, 8, 8))
+    ws, want, got = lib.new_workspace(), torch.empty(4, device="cuda"), torch.full((4,), -1.0, device="cuda")
+    lib.entropy(z.cuda(), want, ws, vocab=vocab)
+    z[1, 0] = bad
+    z[3] = float("-inf")
+    lib.entropy(z.cuda(), got, ws, vocab=vocab)
+    assert got[1].item() == 0.0 and got[3].item() == 0.0
+    assert torch.equal(got[::2], want[::2])
+    lib.close()
