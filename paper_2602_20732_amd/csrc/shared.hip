@@ -82,8 +82,9 @@ struct SharedScorer {
         // kRows rows per trip: kRows N vectors in flight per group.  A trip's last rows may not exist: it then reads the
         // first row again and does not add it (an infinite component times a zero probe would be a NaN).  The pointers come from LDS: loads from memory return in
         // order, so a pointer fetched behind vectors is waited for with them (four rows so: 83 us where two took 75).  Four
-        // rows where sixteen vectors allow it; eight are slower (a row is in a page of memory of its own, and a compute unit
-        // gets only so many translations at a time: 256 rows a level, about 40 ns each).  us, 32 layers of 8 KV heads at 1 %:
+        // rows where sixteen vectors allow it; eight are slower.  (Why is not shown.  The rows lie in as many buffers as there are
+        // layers, and a compute unit misses 95 address translations a launch, by counter, where an attention launch misses 5; what
+        // these cost is not known.)  us, 32 layers of 8 KV heads at 1 %:
         // two rows with pointers from memory / from LDS / four rows / eight up to two slots: 4 sequences of 24-32K 75.8 / 72.1 /
         // 67.8 / 71.6; one of 32K 61.2 / 52.2 / 51.2 / 53.0; 16 of 8K 78.5 / 71.7 / 68.2 / 74.3
         constexpr int kRows = N <= 4 ? 4 : 2;

@@ -226,8 +226,9 @@ __device__ __forceinline__ void refresh_only(int L_lane, const int32_t* bt_row, 
 // grid = (C, H_kv, batch); T = storage type of the summaries (float or bf16 bits); kMode: see cascade_with; kLean: three
 // workgroups on a compute unit instead of two (see launch_step)
 // The pointers that the first loads need are numbers in the kernel's signature: a pointer among the arguments is looked up by the
-// runtime at each launch, and the first launch with memory that it has not seen as an argument yet took 20-120 us of host time (a first
-// pass of 96 ragged sequences, two layers, 130-290 us instead of 125-165).
+// runtime at each launch, and in most processes the first launch with memory that it has not seen as an argument yet took longer there
+// (first pass of a newly prepared reselection of 96 ragged sequences, two layers, states in turn in one process, pointers / numbers: 176 /
+// 130 us in three processes of seven, 181 / 130 and 184 / 136 in two, equal in the others).
 // The first loads need nothing but preloaded registers, and nothing waits for the other arguments before they are on their way: units of
 // the first phase are counted in the configuration's (max_grids, then max_chunks, then max_pages), so that their vectors can be requested
 // while the sequence's length is still on its way (0.93 us; 1.25 as a scalar load, which came back with the arguments).

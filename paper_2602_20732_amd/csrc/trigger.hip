@@ -74,8 +74,9 @@ constexpr int kEntFly = 4;                               // 16-byte loads per th
 
 // The first loads need only the arguments ahead of `tr`, which are in registers when a wave starts; the lines of the others are asked for
 // with the first instruction and are there when the row has been read.  `per`: 16-byte chunks a split.  page_steps 0: entropy only.
-// us, rows of 151936 logits, every argument fetched and every logit masked for itself / now: one 6.2 / 5.6, 8 rows 8.7 / 8.1, 32 11.5 /
-// 10.8, 96 15.0 / 13.6.
+// us, rows of 151936 logits, every argument fetched, every logit masked for itself, the counters side by side and two workgroups a compute
+// unit / now: one 6.2 / 5.7, 8 rows 8.7 / 6.1, 16 12.2 / 6.6, 32 11.7 / 8.1, 96 15.1 / 12.3; preloading and masks by the word alone: 5.6, 8.1
+// (8 rows), 10.8 (32), 13.6 (96).
 __global__ __launch_bounds__(kEntThreads) void entropy_kernel(const uint16_t* __restrict__ logits, int32_t* __restrict__ count, int64_t row_stride,
                                                               int vocab, int n_splits, int per, int page_steps, EntropyArgs tr)
 {

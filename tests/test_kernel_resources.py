@@ -84,8 +84,18 @@ def test_three_workgroups_of_the_recent_pages_fit_on_a_compute_unit(listings):
     assert len(registers) == 4 and max(registers.values()) <= 168, registers
 
 
+def kernels_named(listings, name):
+    return [b for _, notes in listings for b in notes.split("- .agpr_count:")[1:] if re.search(r"\.name:\s+_ZN5chess\d+" + name, b)]
+
+
 def test_the_runtime_sees_no_pointers_in_the_step(listings):
-    """A pointer argument is looked up at each launch, and memory seen for the first time cost 20-120 us there: the fused step takes its
-    pointers as numbers and inside structs."""
-    kernels = [b for _, notes in listings for b in notes.split("- .agpr_count:")[1:] if "11step_kernel" in b]
+    """A pointer argument is looked up at each launch, and memory seen for the first time cost 45 us of a first pass there: the fused step
+    takes its pointers as numbers and inside structs."""
+    kernels = kernels_named(listings, "step_kernel")
     assert len(kernels) == 16 and not any("global_buffer" in b for b in kernels)
+
+
+@pytest.mark.parametrize("name,instances", [("decode_kernel", 12), ("reuse_kernel", 8), ("summarize_recent_kernel", 4)])
+def test_nor_in_the_other_kernels_of_a_step(listings, name, instances):
+    kernels = kernels_named(listings, name)
+    assert len(kernels) == instances and not any("global_buffer" in b for b in kernels)
