@@ -192,9 +192,12 @@ using DecodeLines = ArgLinesOf<DecodeKernel, DecodeArgs>;
 __device__ __forceinline__ void requested_by_here() { asm volatile("" : : : "memory"); }
 
 // Three workgroups of four waves per compute unit (at most 170 registers a lane): see run_tiles_with, kSingle.
+// One sequence's every page of 32: within the registers of four.  With 136 of them the compiler asks for a tile's value rows ahead of its
+// first product and not behind it, and the few workgroups there are, which wait for their rows tile by tile, take longer: us, one KV head,
+// 131072 tokens, G = 1 / 4 / 7 / 16: 26.2 / 30.3 / 39.9 / 55.7 with 136 registers, 25.3 / 28.7 / 37.0 / 50.7 so.
 // heads: KV heads << 8 | group.
 template <int B, int NW, bool kList, bool kDealt = false>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(3))) void decode_kernel(uint64_t seq_lens_at, uint64_t block_table_at, uint64_t q_at,
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(B == 32 && NW == 4 && !kList && !kDealt ? 4 : 3))) void decode_kernel(uint64_t seq_lens_at, uint64_t block_table_at, uint64_t q_at,
                                                          uint64_t page_ids_at, uint64_t n_selected_at, int heads, int max_sel, int max_pages,
                                                          int n_splits, DecodeArgs a)
 {
