@@ -490,7 +490,9 @@ hipError_t step_occupancy(int page_size, bool bf16, int lds_bytes, int* blocks_p
 // Which of the first phase's vectors are requested before the lengths are known: units counted in the configuration's, dealt as
 // the phase deals them; only where the first trip is all of them and, beside the eager schedule (whose bytes choose_eager bounds), they are
 // few: of sequences much shorter than the configuration's most of them do not exist (8 MB take 1.3 us; us a layer with room for 4 to 32
-// times the length, behind the length / as here: 1 x 4K 16.5 / 16.3 and 18.9 / 18.0, 8 x 8K 25.6 / 23.9, 32 x 4K 19.1 / 18.5).
+// times the length, behind the length / as here: 1 x 4K 16.5 / 16.3 and 18.9 / 18.0, 8 x 8K 25.6 / 23.9,
+// 32 x 4K 19.1 / 18.5; but 96 of 12 pages with room for 512 18.8 / 19.5, and where sink and window cover the sequence, which needs no vector
+// at all, 8 of 5 pages 11.0 / 11.5).
 static void choose_first_share(const Geom& g, const SelectParams& sp, int mode, int64_t rows, int cluster, bool bf16, int refresh_tail, FirstLoads* f)
 {
     const bool solo = mode == kSolo || mode == kSoloLean, eager = mode == kEagerCluster;
