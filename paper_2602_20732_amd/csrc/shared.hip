@@ -79,63 +79,71 @@ struct SharedScorer {
             unit[x] = target(s0 + x).unit;
             part[x] = 0.0;
         }
-        // kRows rows per trip: kRows N vectors in flight per group.  A trip's last rows may not exist: it then reads the
-        // first row again and does not add it (an infinite component times a zero probe would be a NaN).  The pointers come from LDS: loads from memory return in
-        // order, so a pointer fetched behind vectors is waited for with them (four rows so: 83 us where two took 75).  Four
-        // rows where sixteen vectors allow it; eight are slower.  (Why is not shown.  The rows lie in as many buffers as there are
-        // layers, and a compute unit misses 95 address translations a launch, by counter, where an attention launch misses 5; what
-        // these cost is not known.)  us, 32 layers of 8 KV heads at 1 %:
-        // two rows with pointers from memory / from LDS / four rows / eight up to two slots: 4 sequences of 24-32K 75.8 / 72.1 /
-        // 67.8 / 71.6; one of 32K 61.2 / 52.2 / 51.2 / 53.0; 16 of 8K 78.5 / 71.7 / 68.2 / 74.3
-        constexpr int kRows = N <= 4 ? 4 : 2;
+        // Sixteen vectors in flight per group: four rows per trip where there are up to four slots, and two rows for what is left
+        // then (up to 32 rows of all groups: four would be repeats; 16 rows a unit 21.5 us with two, 23.0 with four, 8 x 16K at 1 %).
+        // A trip's last rows may not exist: it then reads the first row again and does not add it (an infinite component times a
+        // zero probe would be a NaN).  The pointers come from LDS: loads from memory return in order, so a pointer fetched behind
+        // vectors is waited for with them (four rows so: 83 us where two took 75).  Eight rows are slower.  (Why is not shown.  The
+        // rows lie in as many buffers as there are layers, and a compute unit misses 95 address translations a launch, by counter,
+        // where an attention launch misses 5; what these cost is not known.)  us, 32 layers of 8 KV heads at 1 %: two rows with
+        // pointers from memory / from LDS / four rows / eight up to two slots: 4 sequences of 24-32K 75.8 / 72.1 / 67.8 / 71.6; one of
+        // 32K 61.2 / 52.2 / 51.2 / 53.0; 16 of 8K 78.5 / 71.7 / 68.2 / 74.3
         const size_t head_bytes = units * (kHeadDim * sizeof(T));
         const size_t first_head = level_off + (size_t)b * H * head_bytes;
         const int step_l = kSelGroups / H, step_h = kSelGroups - step_l * H;
-        int l = g16 / H, h = g16 - l * H;
-        for (int r = g16; r < R; r += kRows * kSelGroups) {
-            const float* from[kRows];
-            const char* base[kRows];
+        int l = g16 / H, h = g16 - l * H, r = g16;
+        const auto trip = [&](auto rows_a_trip) {
+            constexpr int kRows = decltype(rows_a_trip)::value;
+            if (r < R) {
+                const float* from[kRows];
+                const char* base[kRows];
 #pragma unroll
-            for (int y = 0; y < kRows; ++y) {
-                const bool have = r + y * kSelGroups < R;      // (r itself always is)
-                if (y > 0 && !have) {
-                    from[y] = from[0];
-                    base[y] = base[0];
-                } else {
-                    from[y] = device_pointer<const float>(rows->probes[l]) + ((size_t)b * H + h) * kHeadDim;
-                    base[y] = device_pointer<const char>(rows->summaries[l]) + first_head + (size_t)h * head_bytes;
+                for (int y = 0; y < kRows; ++y) {
+                    const bool have = r + y * kSelGroups < R;      // (r itself always is)
+                    if (y > 0 && !have) {
+                        from[y] = from[0];
+                        base[y] = base[0];
+                    } else {
+                        from[y] = device_pointer<const float>(rows->probes[l]) + ((size_t)b * H + h) * kHeadDim;
+                        base[y] = device_pointer<const char>(rows->summaries[l]) + first_head + (size_t)h * head_bytes;
+                    }
+                    h += step_h;
+                    l += step_l + (h >= H ? 1 : 0);
+                    h -= h >= H ? H : 0;
+                    l = min(l, tab.n_layers - 1);                  // (past the last row: not read)
                 }
-                h += step_h;
-                l += step_l + (h >= H ? 1 : 0);
-                h -= h >= H ? H : 0;
-                l = min(l, tab.n_layers - 1);                  // (past the last row: not read)
-            }
-            // the probes in the arrangement the vectors are held in (two runs of four consecutive dims)
-            float4 pa[kRows], pb[kRows];
-            Vec<T> v[kRows][N];
+                // the probes in the arrangement the vectors are held in (two runs of four consecutive dims)
+                float4 pa[kRows], pb[kRows];
+                Vec<T> v[kRows][N];
 #pragma unroll
-            for (int y = 0; y < kRows; ++y) {
-                pa[y] = *reinterpret_cast<const float4*>(from[y] + Vec<T>::lane_dim(ln, 0));
-                pb[y] = *reinterpret_cast<const float4*>(from[y] + Vec<T>::lane_dim(ln, 4));
+                for (int y = 0; y < kRows; ++y) {
+                    pa[y] = *reinterpret_cast<const float4*>(from[y] + Vec<T>::lane_dim(ln, 0));
+                    pb[y] = *reinterpret_cast<const float4*>(from[y] + Vec<T>::lane_dim(ln, 4));
 #pragma unroll
-                for (int x = 0; x < N; ++x)       // always load (unit 0 when the slot has no unit): all stay in flight
-                    v[y][x].load(reinterpret_cast<const T*>(base[y]) + (size_t)max(unit[x], 0) * kHeadDim, ln);
-            }
-            __builtin_amdgcn_sched_barrier(0);
+                    for (int x = 0; x < N; ++x)       // always load (unit 0 when the slot has no unit): all stay in flight
+                        v[y][x].load(reinterpret_cast<const T*>(base[y]) + (size_t)max(unit[x], 0) * kHeadDim, ln);
+                }
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int y = 0; y < kRows; ++y) {
-                const bool have = r + y * kSelGroups < R;
-                const float pf[8] = {pa[y].x, pa[y].y, pa[y].z, pa[y].w, pb[y].x, pb[y].y, pb[y].z, pb[y].w};
-                double pr[8];
+                for (int y = 0; y < kRows; ++y) {
+                    const bool have = r + y * kSelGroups < R;
+                    const float pf[8] = {pa[y].x, pa[y].y, pa[y].z, pa[y].w, pb[y].x, pb[y].y, pb[y].z, pb[y].w};
+                    double pr[8];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) pr[i] = (double)pf[i];
+                    for (int i = 0; i < 8; ++i) pr[i] = (double)pf[i];
 #pragma unroll
-                for (int x = 0; x < N; ++x) {
-                    const double sum = dot8<T>(pr, v[y][x], part[x]);
-                    part[x] = have ? sum : part[x];
+                    for (int x = 0; x < N; ++x) {
+                        const double sum = dot8<T>(pr, v[y][x], part[x]);
+                        part[x] = have ? sum : part[x];
+                    }
                 }
             }
-        }
+            r += kRows * kSelGroups;
+        };
+        int left = R;                                          // rows of all groups
+        if constexpr (N <= 4)
+            for (; left > 2 * kSelGroups; left -= 4 * kSelGroups) trip(std::integral_constant<int, 4>{});
+        for (; left > 0; left -= 2 * kSelGroups) trip(std::integral_constant<int, 2>{});
 #pragma unroll
         for (int x = 0; x < N; ++x) {
             const double d = row16_sum(part[x]);

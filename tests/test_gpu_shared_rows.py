@@ -1,4 +1,4 @@
-"""The model-wide selection where a unit's rows (layers x KV heads) end inside a trip of four rows for each of the 16 lane
+"""The model-wide selection where a unit's rows (layers x KV heads) end inside a trip of four or of two rows for each of the 16 lane
 groups, or leave some groups without a row: page lists against the oracle, bit for bit."""
 from __future__ import annotations
 
@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("cluster", [0, 2])
-@pytest.mark.parametrize("heads,n_layers", [(1, 15), (1, 17), (3, 21), (2, 32), (5, 13), (16, 5), (17, 4), (3, 43)])
+@pytest.mark.parametrize("heads,n_layers", [(1, 15), (1, 17), (3, 11), (3, 21), (2, 32), (5, 13), (16, 5), (17, 4), (8, 12), (7, 14), (3, 43)])
 def test_rows_around_a_trip(heads, n_layers, cluster):
     lens = [1500, 700, 100]
     sp = workload.WorkloadSpec("rows", 3, (0, 1500), heads, heads, 16, ("fixed", 96), (1, 1), 1, 2, budget_bp=800,
@@ -23,7 +23,7 @@ def test_rows_around_a_trip(heads, n_layers, cluster):
     lib.close()
 
 
-@pytest.mark.parametrize("heads,n_layers", [(1, 15), (1, 17), (8, 4), (8, 7), (3, 43)])
+@pytest.mark.parametrize("heads,n_layers", [(1, 15), (1, 17), (8, 4), (8, 7), (7, 14), (3, 43)])
 def test_infinite_components_keep_their_sign(heads, n_layers):
     """One row of two pages holds an infinity of either sign: their scores, and those of their chunks and grids, are infinite and not NaN,
     also where the last trip over the rows has fewer than the others."""
